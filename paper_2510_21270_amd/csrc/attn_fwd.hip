@@ -1,6 +1,7 @@
 // pbs_attn_fwd: Algorithm 1's main loop -- online-softmax attention over the listed key blocks only.
-// This file holds the entry point, the 32-queries-per-wave matrix-core kernel and the vector kernel; the
-// 64-queries-per-wave kernel that serves block = 128 first is in attn_wide.hip.
+// This file holds the entry point and the 32-queries-per-wave matrix-core kernel; the 64-queries-per-wave kernel that
+// serves block = 128 first is in attn_wide.hip, the kernel in fp32 arithmetic, which serves every other supported dtype /
+// d / block, in attn_fp32.hip.
 //
 // Matrix-core kernel (bf16, d = 128; block 64, and the second pass of block 128).  Everything is kept TRANSPOSED so
 // that one lane owns one query for the whole row of work:
@@ -13,10 +14,6 @@
 // lane contributes to one 16-key contraction step are 8 CONSECUTIVE keys, which lets V'^T be read from LDS
 // with plain 16-byte loads.  LDS tile rows are padded by 16 bytes against bank conflicts.
 // A block that is not listed costs nothing: the loop runs over the list.
-//
-// Vector kernel (fp32 arithmetic): every other supported dtype / d / block.
-#include <limits.h>
-
 #include "pbs_host.h"
 
 namespace pbs {
@@ -500,91 +497,6 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
     }
 }
 
-// ---------------------------------------------------------------------------------------------
-// Vector kernel: two threads per query row, each owning half of d.  K' and V'^T tiles are staged in LDS as
-// fp32; every key updates the running (m, l, O) directly.  grid = (T, batch*h_q), 2*block threads.
-// ---------------------------------------------------------------------------------------------
-template <typename E, int D>
-__global__ __launch_bounds__(256) void attn_vector_kernel(
-    const E *__restrict__ Qp, const E *__restrict__ Kp, const E *__restrict__ Vt, const int32_t *__restrict__ qidx,
-    const int32_t *__restrict__ kidx, const int32_t *__restrict__ row_cnt, const int32_t *__restrict__ col_idx,
-    E *__restrict__ Op, float *__restrict__ lse, Geo g)
-{
-    constexpr int HALF = D / 2;
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    float *kt = reinterpret_cast<float *>(smem_raw);             // [block][D]
-    float *vt = kt + g.block * D;                                // the block's Vt image: [block / G][D][G]
-    int *kpos = reinterpret_cast<int *>(vt + D * g.block);       // [block]
-
-    const int i = g.T - 1 - (int)blockIdx.x;
-    const int bhq = blockIdx.y;
-    const int b = bhq / g.h_q, hq = bhq % g.h_q;
-    const size_t bhk = (size_t)b * g.h_kv + hq / g.r;
-    const int row = threadIdx.x >> 1, half = threadIdx.x & 1;
-    const int qs = i * g.block + row;
-    const bool live = qs < g.n;
-    const int qpos = live ? (qidx ? qidx[(size_t)bhq * g.n + qs] : qs) : -1;
-
-    float q[HALF], o[HALF];
-    {
-        const E *src = Qp + ((size_t)bhq * g.n + (live ? qs : g.n - 1)) * D + half * HALF;
-#pragma unroll
-        for (int e = 0; e < HALF; ++e) { q[e] = ElemTraits<E>::to_float(src[e]); o[e] = 0.0f; }
-    }
-    float m = -INFINITY, l = 0.0f;
-    const int ni = allowed_cols(i, g);
-    const int cnt = min(row_cnt[(size_t)bhq * g.T + i], g.T);
-    const int32_t *cols = col_idx + ((size_t)bhq * g.T + i) * g.T;
-    const E *Kh = Kp + bhk * (size_t)g.n * D;
-    const E *Vh = Vt + bhk * (size_t)g.T * D * g.block;
-    const int32_t *kih = kidx + bhk * (size_t)g.n;
-    const int G = vt_group(g.block);
-
-    for (int t = 0; t < cnt; ++t) {
-        const int j = cols[t];
-        if (j < 0 || j >= ni) continue;
-        __syncthreads();
-        for (int c = threadIdx.x; c < g.block * D; c += blockDim.x) {
-            const int kr = c / D, e = c % D;
-            const int slot = j * g.block + kr;
-            kt[c] = slot < g.n ? ElemTraits<E>::to_float(Kh[(size_t)slot * D + e]) : 0.0f;
-            vt[c] = ElemTraits<E>::to_float(Vh[(size_t)j * D * g.block + c]);
-        }
-        for (int c = threadIdx.x; c < g.block; c += blockDim.x) {
-            const int slot = j * g.block + c;
-            kpos[c] = slot < g.n ? kih[slot] : INT_MAX;
-        }
-        __syncthreads();
-        for (int c = 0; c < g.block; ++c) {
-            float part = 0.0f;
-            const float *kr = kt + c * D + half * HALF;
-#pragma unroll
-            for (int e = 0; e < HALF; ++e) part += q[e] * kr[e];
-            const float s = (part + __shfl_xor(part, 1, 64)) * g.scale;
-            if (kpos[c] > qpos) continue;
-            if (s > m) {
-                const float alpha = __expf(m - s);               // exp(-inf) = 0 on the first visible key
-                l *= alpha;
-#pragma unroll
-                for (int e = 0; e < HALF; ++e) o[e] *= alpha;
-                m = s;
-            }
-            const float p = __expf(s - m);
-            l += p;
-            const float *vr = vt + ((c / G) * D + half * HALF) * G + c % G;
-#pragma unroll
-            for (int e = 0; e < HALF; ++e) o[e] += p * vr[e * G];
-        }
-    }
-    if (live) {
-        const float inv = l > 0.0f ? 1.0f / l : 0.0f;
-        E *dst = Op + ((size_t)bhq * g.n + qs) * D + half * HALF;
-#pragma unroll
-        for (int e = 0; e < HALF; ++e) dst[e] = ElemTraits<E>::from_float(o[e] * inv);
-        if (lse && half == 0) lse[(size_t)bhq * g.n + qs] = l > 0.0f ? m + logf(l) : -INFINITY;
-    }
-}
-
 // true when the 64-queries-per-wave kernel (attn_wide.hip) serves the problem
 static bool wide_path(const pbs_problem *p) { return p->dtype == PBS_BF16 && p->d == 128 && p->block == 128; }
 
@@ -600,21 +512,10 @@ pbs_status launch_attn_wide(const Geo &g, const void *Qp, const void *Kp, const 
                             const int32_t *kidx, const int32_t *row_cnt, const int32_t *col_idx, void *Op, float *lse,
                             int32_t *redo, int tok_delta, hipStream_t s);
 
-template <typename E, int D>
-static pbs_status launch_vector(const Geo &g, const void *Qp, const void *Kp, const void *Vt, const int32_t *qidx,
-                                const int32_t *kidx, const int32_t *row_cnt, const int32_t *col_idx, void *Op,
-                                float *lse, hipStream_t s)
-{
-    const size_t lds = (size_t)2 * g.block * D * sizeof(float) + (size_t)g.block * sizeof(int);
-    static std::atomic<unsigned long long> lds_raised{0};
-    if (lds > 32 * 1024) {
-        const pbs_status st = raise_lds_limit(reinterpret_cast<const void *>(&attn_vector_kernel<E, D>),
-                                              160 * 1024 - 2048, lds_raised);
-        if (st != PBS_OK) return st;
-    }
-    return launch((attn_vector_kernel<E, D>), dim3(g.T, g.batch * g.h_q), dim3(2 * g.block), lds, s,
-                       (const E *)Qp, (const E *)Kp, (const E *)Vt, qidx, kidx, row_cnt, col_idx, (E *)Op, lse, g);
-}
+// fp32 arithmetic (attn_fp32.hip)
+pbs_status launch_attn_fp32(const Geo &g, int dtype, const void *Qp, const void *Kp, const void *Vt, const int32_t *qidx,
+                            const int32_t *kidx, const int32_t *row_cnt, const int32_t *col_idx, void *Op, float *lse,
+                            hipStream_t s);
 
 }  // namespace pbs
 
@@ -671,10 +572,5 @@ extern "C" pbs_status pbs_attn_fwd(const pbs_problem *p, const void *Qp, const v
         return st;
     }
     if (p->flags & PBS_FLAG_INDEX_REMAP) return PBS_ERR_UNSUPPORTED;   // only the matrix-core kernels remap
-    if (p->dtype == PBS_BF16)
-        return p->d == 128 ? launch_vector<bf16_t, 128>(g, Qp, Kp, Vt, qidx, kidx, row_cnt, col_idx, Op, lse, s)
-                           : launch_vector<bf16_t, 64>(g, Qp, Kp, Vt, qidx, kidx, row_cnt, col_idx, Op, lse, s);
-    return p->d == 128 ? launch_vector<float, 128>(g, Qp, Kp, Vt, qidx, kidx, row_cnt, col_idx, Op, lse, s)
-                       : launch_vector<float, 64>(g, Qp, Kp, Vt, qidx, kidx, row_cnt, col_idx, Op, lse, s);
+    return launch_attn_fp32(g, p->dtype, Qp, Kp, Vt, qidx, kidx, row_cnt, col_idx, Op, lse, s);
 }
-

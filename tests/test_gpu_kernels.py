@@ -1,0 +1,62 @@
+"""Kernels at the sizes where their tiling can go wrong, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_helpers import check_close, i32_dev, to_dev, to_host, vt_layout
+from paper_2510_21270_amd import binding as pbs
+from paper_2510_21270_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def _qkv(seed, Hq, Hkv, n, d, dtype):
+    rng = np.random.default_rng(seed)
+    x = [rng.standard_normal((1, h, n, d)).astype(np.float32) for h in (Hq, Hkv, Hkv)]
+    return [wl.round_to_bf16(a) for a in x] if dtype == "bf16" else x
+
+
+# n: one query, one query past a 16-query tile, one short of a block, several blocks and a ragged tail.  34 heads and
+# the longer lengths pass the workgroup count from which four waves share a list instead of eight.
+@pytest.mark.parametrize("n", [1, 17, 127, 700])
+@pytest.mark.parametrize("dtype,d,block,Hq,Hkv", [("f32", 64, 16, 2, 1), ("f32", 64, 64, 34, 2), ("f32", 128, 32, 3, 3),
+                                                   ("f32", 128, 128, 34, 34), ("bf16", 64, 32, 2, 2),
+                                                   ("bf16", 128, 16, 34, 2)])
+def test_fp32_attention_over_given_lists(oracle, dtype, d, block, Hq, Hkv, n):
+    Q, K, V = _qkv(n + d, Hq, Hkv, n, d, dtype)
+    T, seg = -(-n // block), 2 * block
+    kidx = wl.random_segment_perm(3, Hkv, n, seg).reshape(1, Hkv, n)
+    Kp, Vp = oracle.gather_rows(K, kidx), oracle.gather_rows(V, kidx)
+    cnt, cols = wl.random_block_lists(5, 1, Hq, T, 0.5)
+    p = pbs.problem(1, Hq, Hkv, n, d, block, seg, dtype)
+    want, want_lse = oracle.attn_fwd(Q, Kp, Vp, None, kidx, cnt, cols, block, want_lse=True)
+    got, lse = pbs.attn_fwd(p, to_dev(Q, dtype), to_dev(Kp, dtype), to_dev(vt_layout(Vp, block), dtype), None,
+                            i32_dev(kidx), i32_dev(cnt), i32_dev(cols), want_lse=True)
+    torch.cuda.synchronize()
+    lse = lse.cpu().numpy()
+    fin = np.isfinite(want_lse)                            # a query that sees no listed key: zeros and -inf
+    assert np.isneginf(lse[~fin]).all()
+    check_close(to_host(got), np.where(fin[..., None], want, 0.0), dtype, "fp32 kernel")
+    np.testing.assert_allclose(lse[fin], want_lse[fin], atol=1e-4, rtol=0)
+
+
+@pytest.mark.parametrize("dtype,d,block", [("f32", 64, 64), ("f32", 128, 16), ("bf16", 64, 32), ("bf16", 64, 64),
+                                           ("bf16", 64, 128)])
+def test_values_that_are_not_finite_reach_only_the_queries_that_see_them(oracle, dtype, d, block):
+    n, at = 3 * block - 5, block + block // 2
+    Q, K, V = _qkv(7, 2, 1, n, d, dtype)
+    kidx = np.arange(n, dtype=np.int32).reshape(1, 1, n)
+    p = pbs.problem(1, 2, 1, n, d, block, block, dtype)
+    cnt, cols = pbs.admitted_lists(p)
+
+    def run(v):
+        return to_host(pbs.attn_fwd(p, to_dev(Q, dtype), to_dev(K, dtype), to_dev(vt_layout(v, block), dtype), None,
+                                    i32_dev(kidx), cnt, cols))
+    clean = run(V)
+    bad = V.copy()
+    bad[0, 0, at, 3], bad[0, 0, at, d - 1], bad[0, 0, n - 1, 5] = np.inf, np.nan, -np.inf
+    got = run(bad)
+    torch.cuda.synchronize()
+    want = clean.copy()
+    want[0, :, at:, 3], want[0, :, at:, d - 1], want[0, :, n - 1, 5] = np.inf, np.nan, -np.inf
+    np.testing.assert_array_equal(got, want)
