@@ -37,9 +37,9 @@
  *     zero-filled.  Vt is produced by pbs_segment_permute and consumed by
  *     pbs_attn_fwd; pbs_vt_bytes gives its size.
  *   - Supported: dtype PBS_BF16 or PBS_F32; d in {64, 128}; block in
- *     {16, 32, 64, 128}; segment <= 4096; T <= 4096; any n >= 1.  The matrix-core
- *     attention kernel serves PBS_BF16 with d = 128 and block in {64, 128};
- *     every other supported combination runs on fp32 vector arithmetic.
+ *     {16, 32, 64, 128}; segment <= 4096; T <= 4096; any n >= 1.  Attention over PBS_BF16 with block in {64, 128} runs
+ *     on the bf16 matrix cores (d = 64 with probabilities kept to fp32 in two terms); every other supported
+ *     combination in fp32 arithmetic.
  *   - Results are deterministic: the same inputs give bit-identical outputs.
  */
 #ifndef PBS_H

@@ -1,7 +1,7 @@
 // pbs_attn_fwd: Algorithm 1's main loop -- online-softmax attention over the listed key blocks only.
 // This file holds the entry point and the 32-queries-per-wave matrix-core kernel; the 64-queries-per-wave kernel that
-// serves block = 128 first is in attn_wide.hip, the kernel in fp32 arithmetic, which serves every other supported dtype /
-// d / block, in attn_fp32.hip.
+// serves block = 128 first is in attn_wide.hip, the kernel for d = 64 with blocks of 64 or 128 in attn_d64.hip, the
+// kernel in fp32 arithmetic, which serves every other supported dtype / d / block, in attn_fp32.hip.
 //
 // Matrix-core kernel (bf16, d = 128; block 64, and the second pass of block 128).  Everything is kept TRANSPOSED so
 // that one lane owns one query for the whole row of work:
@@ -512,6 +512,11 @@ pbs_status launch_attn_wide(const Geo &g, const void *Qp, const void *Kp, const 
                             const int32_t *kidx, const int32_t *row_cnt, const int32_t *col_idx, void *Op, float *lse,
                             int32_t *redo, int tok_delta, hipStream_t s);
 
+// bf16 storage, d = 64, block 64 or 128 (attn_d64.hip)
+pbs_status launch_attn_d64(const Geo &g, const void *Qp, const void *Kp, const void *Vt, const int32_t *qidx,
+                           const int32_t *kidx, const int32_t *row_cnt, const int32_t *col_idx, void *Op, float *lse,
+                           hipStream_t s);
+
 // fp32 arithmetic (attn_fp32.hip)
 pbs_status launch_attn_fp32(const Geo &g, int dtype, const void *Qp, const void *Kp, const void *Vt, const int32_t *qidx,
                             const int32_t *kidx, const int32_t *row_cnt, const int32_t *col_idx, void *Op, float *lse,
@@ -572,5 +577,7 @@ extern "C" pbs_status pbs_attn_fwd(const pbs_problem *p, const void *Qp, const v
         return st;
     }
     if (p->flags & PBS_FLAG_INDEX_REMAP) return PBS_ERR_UNSUPPORTED;   // only the matrix-core kernels remap
+    if (p->dtype == PBS_BF16 && p->d == 64 && p->block >= 64)
+        return launch_attn_d64(g, Qp, Kp, Vt, qidx, kidx, row_cnt, col_idx, Op, lse, s);
     return launch_attn_fp32(g, p->dtype, Qp, Kp, Vt, qidx, kidx, row_cnt, col_idx, Op, lse, s);
 }

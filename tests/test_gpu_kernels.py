@@ -40,6 +40,29 @@ def test_fp32_attention_over_given_lists(oracle, dtype, d, block, Hq, Hkv, n):
     np.testing.assert_allclose(lse[fin], want_lse[fin], atol=1e-4, rtol=0)
 
 
+# ... and the d = 64 kernel, 64 queries to a wave: short of a wave, one past it, ragged blocks, a T of its own
+@pytest.mark.parametrize("n", [1, 65, 190, 900])
+@pytest.mark.parametrize("block,Hq,Hkv", [(64, 4, 2), (128, 3, 1), (64, 7, 7)])
+def test_d64_attention_over_given_lists(oracle, block, Hq, Hkv, n):
+    Q, K, V = _qkv(n + block, Hq, Hkv, n, 64, "bf16")
+    Q[0, :, n // 2:] *= 8.0                                # scores that outgrow the first reference
+    T, seg = -(-n // block), 2 * block
+    kidx = wl.random_segment_perm(3, Hkv, n, seg).reshape(1, Hkv, n)
+    qidx = wl.random_segment_perm(4, Hq, n, seg).reshape(1, Hq, n)
+    Qp, Kp, Vp = oracle.gather_rows(Q, qidx), oracle.gather_rows(K, kidx), oracle.gather_rows(V, kidx)
+    cnt, cols = wl.random_block_lists(5, 1, Hq, T, 0.5)
+    p = pbs.problem(1, Hq, Hkv, n, 64, block, seg, "bf16")
+    want, want_lse = oracle.attn_fwd(Qp, Kp, Vp, qidx, kidx, cnt, cols, block, want_lse=True)
+    got, lse = pbs.attn_fwd(p, to_dev(Qp, "bf16"), to_dev(Kp, "bf16"), to_dev(vt_layout(Vp, block), "bf16"),
+                            i32_dev(qidx), i32_dev(kidx), i32_dev(cnt), i32_dev(cols), want_lse=True)
+    torch.cuda.synchronize()
+    lse = lse.cpu().numpy()
+    fin = np.isfinite(want_lse)
+    assert np.isneginf(lse[~fin]).all()
+    check_close(to_host(got), np.where(fin[..., None], want, 0.0), "bf16", "d = 64 kernel")
+    np.testing.assert_allclose(lse[fin], want_lse[fin], atol=1e-4, rtol=0)
+
+
 @pytest.mark.parametrize("dtype,d,block", [("f32", 64, 64), ("f32", 128, 16), ("bf16", 64, 32), ("bf16", 64, 64),
                                            ("bf16", 64, 128)])
 def test_values_that_are_not_finite_reach_only_the_queries_that_see_them(oracle, dtype, d, block):
@@ -59,4 +82,6 @@ def test_values_that_are_not_finite_reach_only_the_queries_that_see_them(oracle,
     torch.cuda.synchronize()
     want = clean.copy()
     want[0, :, at:, 3], want[0, :, at:, d - 1], want[0, :, n - 1, 5] = np.inf, np.nan, -np.inf
-    np.testing.assert_array_equal(got, want)
+    # (the d = 64 kernel sums such a query tile in another order, with probabilities that are not split: sums that differ
+    # by less than 2^-17 of the weights times |v| < 4, then one bf16 rounding of either side)
+    np.testing.assert_allclose(got, want, rtol=2.0 ** -7, atol=2.0 ** -15, equal_nan=True)
