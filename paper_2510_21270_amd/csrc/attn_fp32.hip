@@ -37,18 +37,6 @@ constexpr float kLead = 6.0f;
 
 typedef int int4u __attribute__((ext_vector_type(4), aligned(4)));
 
-// four consecutive elements as float
-template <typename E>
-__device__ __forceinline__ floatx4 load4(const E *src)
-{
-    if constexpr (sizeof(E) == 4) {
-        return *reinterpret_cast<const floatx4 *>(src);
-    } else {
-        const bf16x4 v = *reinterpret_cast<const bf16x4 *>(src);
-        return floatx4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
-    }
-}
-
 // grid: linear ids (x fastest; y only where x alone would pass 2^32 threads), cohorts of `cohort` workgroups of one kv
 // head per XCD, longest lists first (see the decoding below)
 template <typename E, int D, int KT, int WAVES>

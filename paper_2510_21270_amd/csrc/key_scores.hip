@@ -12,7 +12,7 @@
 // accumulator).  Qhat is an fp32 mean, not a bf16 value, so it is pre-multiplied by scale*log2(e) and split
 // into two bf16 terms hi + lo; each tile takes two MFMAs per fragment.  A wave keeps the fragments of its 32 rows
 // of Qhat in registers and the K tiles go through LDS, shared by the four waves of a workgroup.
-// Everything else (fp32 inputs, d = 64): fp64 vector arithmetic, one thread per key.
+// Everything else (fp32 inputs, d = 64): the same two sweeps on the fp64 matrix instruction.
 #include "pbs_host.h"
 
 namespace pbs {
@@ -291,25 +291,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 }
 
 // ------------------------------------------------------------------ generic path (fp64 accumulation)
+// one thread per element of Qhat; grid = (ceil(bl * d / 256), batch * h_kv)
 template <typename E>
 __global__ __launch_bounds__(256) void qhat_f64_kernel(const E *__restrict__ Q, double *__restrict__ qhat, Geo g,
                                                        int bl, const int32_t *__restrict__ qrows,
                                                        const double *__restrict__ qavg)
 {
-    const int bh = blockIdx.x;
+    const int bh = blockIdx.y;
     const int b = bh / g.h_kv, h = bh % g.h_kv;
-    for (int idx = threadIdx.x; idx < bl * g.d; idx += blockDim.x) {
-        const int row = idx / g.d, e = idx % g.d;
-        if (qavg) {
-            qhat[(size_t)bh * bl * g.d + idx] = qavg[(size_t)bh * 128 + e];
-            continue;
-        }
-        const int pos = query_row_position(qrows, row, bl, g.n);
-        double acc = 0.0;
-        for (int t = 0; t < g.r; ++t)
-            acc += (double)ElemTraits<E>::to_float(Q[(((size_t)b * g.h_q + h * g.r + t) * g.n + pos) * g.d + e]);
-        qhat[(size_t)bh * bl * g.d + idx] = acc / (double)g.r;
+    const int idx = blockIdx.x * 256 + threadIdx.x;
+    if (idx >= bl * g.d) return;
+    const int row = idx / g.d, e = idx % g.d;
+    if (qavg) {
+        qhat[(size_t)bh * bl * g.d + idx] = qavg[(size_t)bh * 128 + e];
+        return;
     }
+    const int pos = query_row_position(qrows, row, bl, g.n);
+    double acc = 0.0;
+    for (int t = 0; t < g.r; ++t)
+        acc += (double)ElemTraits<E>::to_float(Q[(((size_t)b * g.h_q + h * g.r + t) * g.n + pos) * g.d + e]);
+    qhat[(size_t)bh * bl * g.d + idx] = acc / (double)g.r;
 }
 
 // ------------------------------------------------------------------ the average query (one proxy of the ablations)
@@ -351,94 +352,205 @@ __global__ __launch_bounds__(128) void qavg_final_kernel(const double *__restric
     qavg[(size_t)bh * 128 + e] = s / ((double)g.r * (double)g.n);
 }
 
-template <typename E>
-__device__ inline double dot_f64(const double *__restrict__ q, const E *__restrict__ k, int d)
+// Both sweeps form 16 keys x 16 query rows of logits at a time on the fp64 matrix instruction (v_mfma_f64_16x16x4:
+// the arithmetic of fp64 fused multiply-adds).  A operand: lane (key = lane % 16, grp = lane / 16) holds
+// K[key][16 u + 4 grp + c] of step (u, c), a 16-byte load for float; B operand: the same features of query row
+// lane % 16, kept in registers; accumulator: keys grp + 4 x (x = 0..3) of query row lane % 16.  So a lane owns a query row
+// (its statistics are per lane) and what a wave needs of K comes straight from memory, without LDS.
+// The four waves of a workgroup divide the 16-row tiles of Qhat among them (at most two each) and, where there are
+// fewer than three, the key tiles as well.
+// Bound: the exponentials (one fp64 exp per logit and sweep, about 30 fp64 instructions) and the latency of a few short
+// launches.  Measured, stage: float32, 2 heads x 2048 keys 541 -> 28 us; bf16 d = 64, 4 kv heads x 12301 keys 757 -> 52 us
+// against one thread per key (or per key and row) walking its K row alone.
+struct WaveShare {
+    int rw, kg;                        // waves that share the rows, waves that share the keys; rw * kg = 4
+};
+__host__ __device__ inline WaveShare wave_share(int bl)
 {
-    double acc = 0.0;
-    for (int e = 0; e < d; ++e) acc += q[e] * (double)ElemTraits<E>::to_float(k[e]);
-    return acc;
+    const int tiles = ceil_div(bl, 16);
+    return tiles > 2 ? WaveShare{4, 1} : (tiles == 2 ? WaveShare{2, 2} : WaveShare{1, 4});
 }
 
-// grid = (chunks, bl, nbh): partial (max, sumexp) of one logit row over one chunk of keys.
-template <typename E>
+template <typename E, int D>
+struct F64Logits {
+    double q[2][D / 4];                // query rows 16 (wr + rw t) + lane % 16, t = 0, 1
+    int row[2];                        // those rows' indices
+    int tiles;                         // row tiles of this wave
+
+    __device__ __forceinline__ void load_rows(const double *qhat, int bl, int wr, int rw, int lane)
+    {
+        tiles = wr * 16 >= bl ? 0 : ((wr + rw) * 16 >= bl ? 1 : 2);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            row[t] = 16 * (wr + rw * t) + (lane & 15);
+            const double *src = qhat + (size_t)min(row[t], bl - 1) * D + 4 * (lane >> 4);
+            if (t < tiles)
+#pragma unroll
+                for (int e = 0; e < D / 4; ++e) q[t][e] = src[16 * (e >> 2) + (e & 3)];
+        }
+    }
+    // logits of the 16 keys from key0 on (keys past n are clamped: the caller masks them) against row tile t
+    __device__ __forceinline__ void load_keys(floatx4 (&k)[D / 16], const E *Kh, int key0, int n, int lane) const
+    {
+        const E *src = Kh + (size_t)min(key0 + (lane & 15), n - 1) * D + 4 * (lane >> 4);
+#pragma unroll
+        for (int u = 0; u < D / 16; ++u) k[u] = load4(src + 16 * u);
+    }
+    __device__ __forceinline__ doublex4 operator()(const floatx4 (&k)[D / 16], int t) const
+    {
+        doublex4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int e = 0; e < D / 4; ++e)
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)k[e >> 2][e & 3], q[t][e], acc, 0, 0, 0);
+        return acc;
+    }
+};
+
+// Sweep 1.  grid = (chunks, nbh): (max, sum of exp) of every query row over one chunk of keys and one key share;
+// partial[bh][row][part], part = chunk * kg + key share.
+template <typename E, int D>
 __global__ __launch_bounds__(256) void scores_stats_f64_kernel(const E *__restrict__ K,
                                                                const double *__restrict__ qhat,
                                                                double2 *__restrict__ partial, Geo g, int bl,
                                                                int keys_per_chunk)
 {
-    __shared__ double q[128];
-    __shared__ double redm[4], redl[4];
-    const int chunk = blockIdx.x, row = blockIdx.y, bh = blockIdx.z;
-    for (int e = threadIdx.x; e < g.d; e += blockDim.x) q[e] = qhat[((size_t)bh * bl + row) * g.d + e];
-    __syncthreads();
-    const E *Kh = K + (size_t)bh * g.n * g.d;
-    const int j1 = min(g.n, (chunk + 1) * keys_per_chunk);
-    double m = -INFINITY, l = 0.0;
-    for (int j = chunk * keys_per_chunk + threadIdx.x; j < j1; j += blockDim.x) {
-        const double v = dot_f64(q, Kh + (size_t)j * g.d, g.d) * g.scale64;
-        const double mn = fmax(m, v);
-        l = l * exp(m - mn) + exp(v - mn);
-        m = mn;
+    const int chunk = blockIdx.x, bh = blockIdx.y;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const WaveShare ws = wave_share(bl);
+    const int wr = wave % ws.rw, wk = wave / ws.rw;
+    F64Logits<E, D> logits;
+    logits.load_rows(qhat + (size_t)bh * bl * D, bl, wr, ws.rw, lane);
+    const E *Kh = K + (size_t)bh * g.n * D;
+    const int end = min(g.n, (chunk + 1) * keys_per_chunk);
+    double m[2] = {-INFINITY, -INFINITY}, l[2] = {0.0, 0.0};
+    for (int key0 = chunk * keys_per_chunk + 16 * wk; key0 < end; key0 += 16 * ws.kg) {
+        floatx4 k[D / 16];
+        logits.load_keys(k, Kh, key0, g.n, lane);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            if (t >= logits.tiles) break;
+            doublex4 v = logits(k, t);
+            double top = -INFINITY;
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                v[x] = key0 + (lane >> 4) + 4 * x < end ? v[x] * g.scale64 : -INFINITY;
+                top = fmax(top, v[x]);
+            }
+            if (__any(top > m[t])) {                       // rare after the first tiles
+                const double mn = fmax(m[t], top);
+                if (mn != -INFINITY) l[t] *= exp(m[t] - mn);
+                m[t] = mn;
+            }
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+                if (m[t] != -INFINITY) l[t] += exp(v[x] - m[t]);
+        }
     }
-    const double wm = wave_max(m);
-    const double wl = wave_sum(wm == -INFINITY ? 0.0 : l * exp(m - wm));
-    if ((threadIdx.x & 63) == 0) { redm[threadIdx.x >> 6] = wm; redl[threadIdx.x >> 6] = wl; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double mn = fmax(fmax(redm[0], redm[1]), fmax(redm[2], redm[3]));
-        double ln = 0.0;
-        for (int w = 0; w < 4; ++w)
-            if (redm[w] != -INFINITY) ln += redl[w] * exp(redm[w] - mn);
-        partial[((size_t)bh * bl + row) * gridDim.x + chunk] = make_double2(mn, ln);
+    const int parts = gridDim.x * ws.kg;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        if (t >= logits.tiles) break;
+        // the four lane groups hold different keys of the same row
+#pragma unroll
+        for (int o = 16; o < 64; o <<= 1) {
+            const double mo = __shfl_xor(m[t], o, 64), lo = __shfl_xor(l[t], o, 64);
+            const double mn = fmax(m[t], mo);
+            l[t] = mn == -INFINITY ? l[t] + lo : l[t] * exp(m[t] - mn) + lo * exp(mo - mn);
+            m[t] = mn;
+        }
+        if (lane < 16 && logits.row[t] < bl)
+            partial[((size_t)bh * bl + logits.row[t]) * parts + chunk * ws.kg + wk] = make_double2(m[t], l[t]);
     }
 }
 
-__global__ __launch_bounds__(128) void scores_merge_f64_kernel(const double2 *__restrict__ partial,
-                                                               double2 *__restrict__ stats, int bl, int chunks)
+// One wave per row: stats[bh][row] = (max, 1 / sum of exp) over all parts.  grid = (ceil(bl / 4), nbh)
+__global__ __launch_bounds__(256) void scores_merge_f64_kernel(const double2 *__restrict__ partial,
+                                                               double2 *__restrict__ stats, int bl, int parts)
 {
-    const int row = threadIdx.x, bh = blockIdx.x;
+    const int row = blockIdx.x * 4 + (threadIdx.x >> 6), bh = blockIdx.y, lane = threadIdx.x & 63;
     if (row >= bl) return;
-    const double2 *pr = partial + ((size_t)bh * bl + row) * chunks;
-    double mn = -INFINITY;
-    for (int c = 0; c < chunks; ++c) mn = fmax(mn, pr[c].x);
-    double ln = 0.0;
-    for (int c = 0; c < chunks; ++c)
-        if (pr[c].x != -INFINITY) ln += pr[c].y * exp(pr[c].x - mn);
-    stats[(size_t)bh * bl + row] = make_double2(mn, ln);
+    const double2 *pr = partial + ((size_t)bh * bl + row) * parts;
+    double mn = -INFINITY, ln = 0.0;
+    for (int c = lane; c < parts; c += 64) {
+        const double2 v = pr[c];
+        const double m2 = fmax(mn, v.x);
+        if (m2 != -INFINITY) ln = ln * exp(mn - m2) + v.y * exp(v.x - m2);
+        mn = m2;
+    }
+    const double wm = wave_max(mn);
+    const double wl = wave_sum(mn == -INFINITY ? ln : ln * exp(mn - wm));
+    if (lane == 0) stats[(size_t)bh * bl + row] = make_double2(wm, 1.0 / wl);
 }
 
-// one thread per key: scores[j] = (1/bl) * sum_row exp(logit - max_row) / sumexp_row
-template <typename E>
+// Sweep 2.  grid = (ceil(n / keys), nbh), keys <= kF64Keys: scores[key] = (1 / bl) sum_row exp(logit - max_row) / sum_row
+constexpr int kF64Keys = 256;
+
+template <typename E, int D>
 __global__ __launch_bounds__(256) void scores_final_f64_kernel(const E *__restrict__ K,
                                                                const double *__restrict__ qhat,
                                                                const double2 *__restrict__ stats,
-                                                               float *__restrict__ scores, Geo g, int bl)
+                                                               float *__restrict__ scores, Geo g, int bl, int keys)
 {
-    constexpr int kRowsPerPass = 8;
-    __shared__ double q[kRowsPerPass][128];
-    __shared__ double2 st[kRowsPerPass];
+    __shared__ double psum[4][kF64Keys];
     const int bh = blockIdx.y;
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    const E *krow = K + ((size_t)bh * g.n + (j < g.n ? j : g.n - 1)) * g.d;
-    double acc = 0.0;
-    for (int r0 = 0; r0 < bl; r0 += kRowsPerPass) {
-        const int nr = min(kRowsPerPass, bl - r0);
-        __syncthreads();
-        for (int idx = threadIdx.x; idx < nr * g.d; idx += blockDim.x)
-            q[idx / g.d][idx % g.d] = qhat[((size_t)bh * bl + r0 + idx / g.d) * g.d + idx % g.d];
-        if ((int)threadIdx.x < nr) st[threadIdx.x] = stats[(size_t)bh * bl + r0 + threadIdx.x];
-        __syncthreads();
-        for (int rr = 0; rr < nr; ++rr) {
-            const double v = dot_f64(q[rr], krow, g.d) * g.scale64;
-            acc += exp(v - st[rr].x) / st[rr].y;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const WaveShare ws = wave_share(bl);
+    const int wr = wave % ws.rw, wk = wave / ws.rw;
+    F64Logits<E, D> logits;
+    logits.load_rows(qhat + (size_t)bh * bl * D, bl, wr, ws.rw, lane);
+    double mrow[2], inv[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const double2 st = stats[(size_t)bh * bl + min(logits.row[t], bl - 1)];
+        mrow[t] = st.x;
+        inv[t] = st.y;
+    }
+    const E *Kh = K + (size_t)bh * g.n * D;
+    const int begin = blockIdx.x * keys, end = min(g.n, begin + keys);
+    for (int key0 = begin + 16 * wk; key0 < end; key0 += 16 * ws.kg) {
+        floatx4 k[D / 16];
+        logits.load_keys(k, Kh, key0, g.n, lane);
+        double sum[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            if (t >= logits.tiles) break;
+            const doublex4 v = logits(k, t);
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+                if (logits.row[t] < bl) sum[x] += exp(v[x] * g.scale64 - mrow[t]) * inv[t];
+        }
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            sum[x] = row_sum_dpp(sum[x]);                  // over the 16 query rows of the lane group
+            if ((lane & 15) == 0) psum[wr][key0 - begin + (lane >> 4) + 4 * x] = sum[x];
         }
     }
-    if (j < g.n) scores[(size_t)bh * g.n + j] = (float)(acc / (double)bl);
+    __syncthreads();
+    for (int j = threadIdx.x; j < end - begin; j += 256) {
+        double acc = psum[0][j];
+        for (int w = 1; w < ws.rw; ++w) acc += psum[w][j];
+        scores[(size_t)bh * g.n + begin + j] = (float)(acc / (double)bl);
+    }
 }
 
 static bool use_mfma(const pbs_problem *p) { return p->dtype == PBS_BF16 && p->d == 128; }
 
+// The generic path's workspace holds the statistics of one chunk per 4096 keys and the average-query region; the
+// partial sums of that region are dead once Qhat is formed, so sweep 1 may use both.
 constexpr int kGenericKeysPerChunk = 4096;
+constexpr int kMinF64Chunk = 64;       // keys a sweep-1 workgroup takes at least
+
+static size_t ws_avg_query(size_t nbh);
+
+// keys per chunk of sweep 1: as many chunks as the workspace has room for, of at least kMinF64Chunk keys
+static int f64_keys_per_chunk(const Geo &g, int bl)
+{
+    const size_t nbh = (size_t)g.batch * g.h_kv;
+    const size_t room = nbh * kQRows * ceil_div(g.n, kGenericKeysPerChunk) * sizeof(double2) + ws_avg_query(nbh);
+    const size_t parts = room / (nbh * bl * sizeof(double2)) / wave_share(bl).kg;
+    const size_t keys = (g.n + parts - 1) / parts;
+    return (int)(keys < kMinF64Chunk ? kMinF64Chunk : (keys + 15) / 16 * 16);
+}
 
 // Keys per workgroup of the MFMA sweeps: 1024 for long inputs; halved (down to one tile per wave) while the
 // grid would hold fewer than kSweepWgs workgroups, so that short inputs still spread over all compute units.
@@ -481,30 +593,31 @@ static pbs_status run_qavg(const Geo &g, const void *Q, double *partial, double 
 }
 
 // bl query rows: the last bl of the sequence (qrows == NULL), the listed ones, or (avg) the one average query.
-template <typename E>
-static pbs_status run_generic(const pbs_problem *p, const Geo &g, const void *Q, const void *K, float *scores,
+template <typename E, int D>
+static pbs_status run_generic(const Geo &g, const void *Q, const void *K, float *scores,
                               char *ws, int bl, const int32_t *qrows, bool avg, hipStream_t s)
 {
     const int nbh = g.batch * g.h_kv;
-    const int chunks = ceil_div(g.n, kGenericKeysPerChunk);
+    const int kpc = f64_keys_per_chunk(g, bl), chunks = ceil_div(g.n, kpc);
     double *qhat = reinterpret_cast<double *>(ws);
     ws += align_up((size_t)nbh * kQRows * g.d * sizeof(double), kWsAlign);
-    double2 *partial = reinterpret_cast<double2 *>(ws);
-    ws += align_up((size_t)nbh * kQRows * chunks * sizeof(double2), kWsAlign);
     double2 *stats = reinterpret_cast<double2 *>(ws);
     ws += align_up((size_t)nbh * kQRows * sizeof(double2), kWsAlign);
+    double2 *partial = reinterpret_cast<double2 *>(ws);    // runs on into the average-query region behind it
+    ws += align_up((size_t)nbh * kQRows * ceil_div(g.n, kGenericKeysPerChunk) * sizeof(double2), kWsAlign);
     double *avg_partial = reinterpret_cast<double *>(ws), *qavg = avg_partial + (size_t)nbh * kAvgChunks * 128;
     pbs_status st;
     if (avg && (st = run_qavg<E>(g, Q, avg_partial, qavg, s)) != PBS_OK) return st;
-    if ((st = launch(qhat_f64_kernel<E>, dim3(nbh), dim3(256), 0, s, (const E *)Q, qhat, g, bl, qrows,
-                     (const double *)(avg ? qavg : nullptr))) != PBS_OK) return st;
-    if ((st = launch(scores_stats_f64_kernel<E>, dim3(chunks, bl, nbh), dim3(256), 0, s, (const E *)K, qhat, partial,
-                       g, bl, kGenericKeysPerChunk)) != PBS_OK) return st;
-    if ((st = launch(scores_merge_f64_kernel, dim3(nbh), dim3(128), 0, s, partial, stats, bl, chunks)) != PBS_OK) return st;
-    st = launch(scores_final_f64_kernel<E>, dim3(ceil_div(g.n, 256), nbh), dim3(256), 0, s, (const E *)K, qhat,
-                       stats, scores, g, bl);
-    (void)p;
-    return st;
+    if ((st = launch(qhat_f64_kernel<E>, dim3(ceil_div(bl * g.d, 256), nbh), dim3(256), 0, s, (const E *)Q, qhat, g, bl,
+                     qrows, (const double *)(avg ? qavg : nullptr))) != PBS_OK) return st;
+    if ((st = launch((scores_stats_f64_kernel<E, D>), dim3(chunks, nbh), dim3(256), 0, s, (const E *)K, qhat, partial, g,
+                     bl, kpc)) != PBS_OK) return st;
+    if ((st = launch(scores_merge_f64_kernel, dim3(ceil_div(bl, 4), nbh), dim3(256), 0, s, partial, stats, bl,
+                     chunks * wave_share(bl).kg)) != PBS_OK) return st;
+    // short ranges until there are workgroups enough for eight per compute unit
+    const int keys = (long long)g.n * nbh > 256LL * 8 * 64 ? kF64Keys : 64;
+    return launch((scores_final_f64_kernel<E, D>), dim3(ceil_div(g.n, keys), nbh), dim3(256), 0, s, (const E *)K, qhat,
+                  stats, scores, g, bl, keys);
 }
 
 }  // namespace pbs
@@ -523,8 +636,9 @@ static pbs_status enqueue_key_scores(const pbs_problem *p, int proxy, const int3
     const int bl = avg ? 1 : (proxy == PBS_PROXY_QUERY_ROWS ? m : (g.block < g.n ? g.block : g.n));
     if (proxy != PBS_PROXY_QUERY_ROWS) qrows = nullptr;
     if (!use_mfma(p)) {
-        if (p->dtype == PBS_BF16) return run_generic<bf16_t>(p, g, Q, K, scores, w, bl, qrows, avg, s);
-        return run_generic<float>(p, g, Q, K, scores, w, bl, qrows, avg, s);
+        if (p->dtype == PBS_BF16) return run_generic<bf16_t, 64>(g, Q, K, scores, w, bl, qrows, avg, s);
+        return p->d == 128 ? run_generic<float, 128>(g, Q, K, scores, w, bl, qrows, avg, s)
+                           : run_generic<float, 64>(g, Q, K, scores, w, bl, qrows, avg, s);
     }
     const int nbh = g.batch * g.h_kv;
     const int kpw = sweep_keys_per_wg(g);

@@ -13,6 +13,7 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef double doublex4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
 typedef uint32_t uintx2 __attribute__((ext_vector_type(2)));
@@ -70,6 +71,18 @@ template <> struct ElemTraits<bf16_t> {
     __device__ static inline bf16_t from_float(float v) { return (bf16_t)v; }
 };
 
+// four consecutive elements as float
+template <typename E>
+__device__ __forceinline__ floatx4 load4(const E *src)
+{
+    if constexpr (sizeof(E) == 4) {
+        return *reinterpret_cast<const floatx4 *>(src);
+    } else {
+        const bf16x4 v = *reinterpret_cast<const bf16x4 *>(src);
+        return floatx4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
+    }
+}
+
 __device__ inline float wave_max(float v)
 {
 #pragma unroll
@@ -95,9 +108,8 @@ __device__ inline double wave_sum(double v)
     return v;
 }
 
-// Sum over the wave without LDS traffic: butterflies inside each row of 16 lanes by DPP, then the four row totals
-// through scalar registers.  Every lane receives the same value, formed in the same order.
-__device__ inline double wave_sum_dpp(double v)
+// Sum over each row of 16 lanes by DPP butterflies; every lane of the row receives the same value.
+__device__ inline double row_sum_dpp(double v)
 {
 #define PBS_DPP_STEP(ctrl)                                                                      \
     {                                                                                           \
@@ -111,6 +123,14 @@ __device__ inline double wave_sum_dpp(double v)
     PBS_DPP_STEP(0x141)   // row_half_mirror
     PBS_DPP_STEP(0x140)   // row_mirror
 #undef PBS_DPP_STEP
+    return v;
+}
+
+// Sum over the wave without LDS traffic: the rows of 16 lanes by DPP, then the four row totals through scalar
+// registers.  Every lane receives the same value, formed in the same order.
+__device__ inline double wave_sum_dpp(double v)
+{
+    v = row_sum_dpp(v);
     double rows[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {

@@ -85,3 +85,27 @@ def test_values_that_are_not_finite_reach_only_the_queries_that_see_them(oracle,
     # (the d = 64 kernel sums such a query tile in another order, with probabilities that are not split: sums that differ
     # by less than 2^-17 of the weights times |v| < 4, then one bf16 rounding of either side)
     np.testing.assert_allclose(got, want, rtol=2.0 ** -7, atol=2.0 ** -15, equal_nan=True)
+
+
+# key tiles of 16, chunks of at least 64 keys, one to eight row tiles shared by four waves; 140001 keys: long ranges in
+# both sweeps, the statistics running on into the average-query region of the workspace
+@pytest.mark.parametrize("n", [1, 15, 63, 65, 1000, 140001])
+@pytest.mark.parametrize("dtype,d,block", [("f32", 64, 64), ("f32", 128, 128), ("bf16", 64, 64), ("bf16", 64, 128)])
+def test_fp64_key_scores(oracle, dtype, d, block, n):
+    Hq, Hkv = (2, 1) if n > 100000 else (6, 3)
+    Q, K, _ = _qkv(n + d, Hq, Hkv, n, d, dtype)
+    p = pbs.problem(1, Hq, Hkv, n, d, block, block, dtype)
+    got = pbs.key_scores(p, to_dev(Q, dtype), to_dev(K, dtype))
+    # sums in fp64 on both sides, one rounding to float32
+    np.testing.assert_allclose(got.cpu().numpy(), oracle.key_scores(Q, K, block), rtol=2.0 ** -23, atol=1e-37)
+
+
+@pytest.mark.parametrize("m", [1, 16, 17, 33, 48, 128])
+@pytest.mark.parametrize("dtype,d,block", [("f32", 64, 16), ("bf16", 64, 32), ("f32", 128, 16)])
+def test_fp64_key_scores_from_listed_rows(oracle_variants, dtype, d, block, m):
+    Q, K, _ = _qkv(m, 4, 2, 777, d, dtype)
+    rows = wl.random_query_rows(m, 777, m)
+    p = pbs.problem(1, 4, 2, 777, d, block, block, dtype)
+    got = pbs.key_scores_proxy(p, pbs.PROXY_QUERY_ROWS, i32_dev(rows), to_dev(Q, dtype), to_dev(K, dtype))
+    want = oracle_variants.key_scores_proxy(Q, K, rows)
+    np.testing.assert_allclose(got.cpu().numpy(), want, rtol=2.0 ** -23, atol=1e-37)
