@@ -338,13 +338,14 @@ __device__ inline void compute_subtile(AttnState<NT> &st, const unsigned char *k
     }
 }
 
-// REMAP: Kp is the caller's K in token order and the K' sub-tiles are gathered from it through kidx (index remapping).
-template <int BLOCK, int WAVES, int KT, bool REMAP = false>
-__global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_mfma_kernel(
+// One query block i of query head bhq.  REMAP: Kp is the caller's K in token order and the K' sub-tiles are gathered from
+// it through kidx (index remapping).
+template <int BLOCK, int WAVES, int KT, bool REMAP>
+__device__ __forceinline__ void attn_row(
     const bf16_t *__restrict__ Qp, const bf16_t *__restrict__ Kp, const bf16_t *__restrict__ Vt,
     const int32_t *__restrict__ qidx, const int32_t *__restrict__ kidx, const int32_t *__restrict__ row_cnt,
-    const int32_t *__restrict__ col_idx, bf16_t *__restrict__ Op, float *__restrict__ lse,
-    const int32_t *__restrict__ only, Geo g)
+    const int32_t *__restrict__ col_idx, bf16_t *__restrict__ Op, float *__restrict__ lse, const Geo &g, int bhq, int unit,
+    int i, int tid)
 {
     constexpr int D = 128;
     constexpr int NT = BLOCK / WAVES / 32;         // 32-query tiles per wave
@@ -356,27 +357,9 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
     __shared__ __align__(16) int kpos0[64], kpos1[64];
     __shared__ int jl[kListChunk];                                            // validated block list, -1 = skip
 
-    // Workgroup -> (query head, query block).  Workgroups are handed to the 8 XCDs round-robin by linear id and
-    // every XCD has its own L2, so the id is decoded as (xcd, slot): the 64 workgroups that are resident on one XCD
-    // at a time form a cohort of 64 rows of ONE kv head with nearly equal list lengths (16 consecutive query blocks
-    // x the r query heads of the group, longest first).  A cohort walks its ascending lists in near lock-step, so a
-    // K'/V' sub-tile is fetched into that L2 once and hit by the other members.
-    const int nbk = g.batch * g.h_kv;
-    const int rows_per_unit = g.r * g.T;
-    const int coh_per_unit = (rows_per_unit + kCohort - 1) / kCohort;
-    const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
-    const int coh = (slot / kCohort) * kXcds + xcd;
-    if (coh >= nbk * coh_per_unit) return;
-    const int unit = coh % nbk;
-    const int mrow = (coh / nbk) * kCohort + slot % kCohort;
-    if (mrow >= rows_per_unit) return;
-    const int i = g.T - 1 - mrow / g.r;
-    const int b = unit / g.h_kv, hq = (unit % g.h_kv) * g.r + mrow % g.r;
-    const int bhq = b * g.h_q + hq;
-    if (only && only[(size_t)bhq * g.T + i] == 0) return;    // second pass: only the query blocks flagged by the first
     const size_t bhk = unit;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ln = lane & 31, lh = lane >> 5;
     const int q0 = i * BLOCK + wave * (BLOCK / WAVES);
     const float c2 = g.scale * kLog2eF;
@@ -417,7 +400,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
     for (int base = 0; base < cnt; base += kListChunk) {
         const int len = min(kListChunk, cnt - base);
         __syncthreads();                   // previous chunk fully consumed
-        for (int t = threadIdx.x; t < len; t += WAVES * 64) {
+        for (int t = tid; t < len; t += WAVES * 64) {
             const int j = cols[base + t];
             jl[t] = (j >= 0 && j < ni) ? j : -1;
         }
@@ -497,20 +480,73 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
     }
 }
 
+template <int BLOCK, int WAVES, int KT, bool REMAP = false>
+__global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_mfma_kernel(
+    const bf16_t *__restrict__ Qp, const bf16_t *__restrict__ Kp, const bf16_t *__restrict__ Vt,
+    const int32_t *__restrict__ qidx, const int32_t *__restrict__ kidx, const int32_t *__restrict__ row_cnt,
+    const int32_t *__restrict__ col_idx, bf16_t *__restrict__ Op, float *__restrict__ lse, Geo g)
+{
+    // Workgroup -> (query head, query block).  Workgroups are handed to the 8 XCDs round-robin by linear id and
+    // every XCD has its own L2, so the id is decoded as (xcd, slot): the 64 workgroups that are resident on one XCD
+    // at a time form a cohort of 64 rows of ONE kv head with nearly equal list lengths (16 consecutive query blocks
+    // x the r query heads of the group, longest first).  A cohort walks its ascending lists in near lock-step, so a
+    // K'/V' sub-tile is fetched into that L2 once and hit by the other members.
+    const int nbk = g.batch * g.h_kv;
+    const int rows_per_unit = g.r * g.T;
+    const int coh_per_unit = (rows_per_unit + kCohort - 1) / kCohort;
+    const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
+    const int coh = (slot / kCohort) * kXcds + xcd;
+    if (coh >= nbk * coh_per_unit) return;
+    const int unit = coh % nbk;
+    const int mrow = (coh / nbk) * kCohort + slot % kCohort;
+    if (mrow >= rows_per_unit) return;
+    const int i = g.T - 1 - mrow / g.r;
+    const int b = unit / g.h_kv, hq = (unit % g.h_kv) * g.r + mrow % g.r;
+    attn_row<BLOCK, WAVES, KT, REMAP>(Qp, Kp, Vt, qidx, kidx, row_cnt, col_idx, Op, lse, g, b * g.h_q + hq, unit, i, threadIdx.x);
+}
+
+// Second pass of block 128: the query blocks that the first pass flagged, none on ordinary inputs.  A workgroup looks
+// at the rows blockIdx.x + k gridDim.x, 64 flags at a time, so that finding none costs a launch and one load: with a
+// workgroup per row the 32 768 of them that leave at once took 66 us at 128K tokens, the 8 192 at 32K 27 us.
+constexpr int kRedoWgs = 1024;
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_redo_kernel(
+    const bf16_t *__restrict__ Qp, const bf16_t *__restrict__ Kp, const bf16_t *__restrict__ Vt,
+    const int32_t *__restrict__ qidx, const int32_t *__restrict__ kidx, const int32_t *__restrict__ row_cnt,
+    const int32_t *__restrict__ col_idx, bf16_t *__restrict__ Op, float *__restrict__ lse,
+    const int32_t *__restrict__ flags, Geo g)
+{
+    const int rows = g.batch * g.h_q * g.T, step = (int)gridDim.x;
+    for (int base = blockIdx.x; base < rows; base += 64 * step) {
+        const int mine = base + (int)(threadIdx.x & 63) * step;
+        uint64_t todo = __ballot(mine < rows && mine >= 0 && flags[mine] != 0);
+        while (todo) {
+            const int row = base + __builtin_ctzll(todo) * step;
+            todo &= todo - 1;
+            const int bhq = row / g.T, i = row % g.T;
+            const int unit = bhq / g.h_q * g.h_kv + bhq % g.h_q / g.r;
+            int tid = threadIdx.x;
+            asm volatile("" : "+v"(tid));                  // per-lane offsets are formed per row, not kept across rows
+            attn_row<128, 4, 64, false>(Qp, Kp, Vt, qidx, kidx, row_cnt, col_idx, Op, lse, g, bhq, unit, i, tid);
+        }
+    }
+}
+
 // true when the 64-queries-per-wave kernel (attn_wide.hip) serves the problem
 static bool wide_path(const pbs_problem *p) { return p->dtype == PBS_BF16 && p->d == 128 && p->block == 128; }
 
-// The wide kernel leaves one flag per query block: blocks it could not finish with a fixed softmax reference.
+// The wide kernel leaves one flag per query block: blocks it could not finish with a fixed softmax reference.  Behind
+// the flags lie the heads of its row queues.
+static size_t ws_redo_flags(const Geo &g) { return align_up((size_t)g.batch * g.h_q * g.T * sizeof(int32_t), kWsAlign); }
 size_t ws_attn_fwd(const pbs_problem *p)
 {
     if (!wide_path(p)) return 0;
-    const Geo g = make_geo(p);
-    return align_up((size_t)g.batch * g.h_q * g.T * sizeof(int32_t), kWsAlign);
+    return ws_redo_flags(make_geo(p)) + 1024;               // 8 queue heads, 128 bytes apart
 }
 
 pbs_status launch_attn_wide(const Geo &g, const void *Qp, const void *Kp, const void *Vt, const int32_t *qidx,
                             const int32_t *kidx, const int32_t *row_cnt, const int32_t *col_idx, void *Op, float *lse,
-                            int32_t *redo, int tok_delta, hipStream_t s);
+                            int32_t *redo, int32_t *tickets, int tok_delta, hipStream_t s);
 
 // bf16 storage, d = 64, block 64 or 128 (attn_d64.hip)
 pbs_status launch_attn_d64(const Geo &g, const void *Qp, const void *Kp, const void *Vt, const int32_t *qidx,
@@ -546,33 +582,36 @@ extern "C" pbs_status pbs_attn_fwd(const pbs_problem *p, const void *Qp, const v
         if (remap) {
             if (p->block == 128)
                 return launch((attn_mfma_kernel<128, 4, 64, true>), mgrid, dim3(256), 0, s, (const bf16_t *)Qp,
-                              (const bf16_t *)Kp, (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse,
-                              (const int32_t *)nullptr, g);
+                              (const bf16_t *)Kp, (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse, g);
             return launch((attn_mfma_kernel<64, 2, 32, true>), mgrid, dim3(128), 0, s, (const bf16_t *)Qp,
-                          (const bf16_t *)Kp, (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse,
-                          (const int32_t *)nullptr, g);
+                          (const bf16_t *)Kp, (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse, g);
         }
         if (p->block == 128) {
             // first pass: every query block with a fixed softmax reference; second pass: the flagged blocks (none
             // on ordinary inputs, then each workgroup of the second launch leaves at once) with the rescaling kernel
             int32_t *redo = narrow_only ? nullptr : reinterpret_cast<int32_t *>(ws);
             if (redo) {
+                int32_t *tickets = reinterpret_cast<int32_t *>(reinterpret_cast<char *>(ws) + ws_redo_flags(g));
                 // own segments from the token-order copies: identity sigma, and every byte of both copies of a head
                 // within reach of 32-bit buffer offsets
                 const long long tok_blocks = (long long)g.batch * g.h_kv * g.T;
                 const bool own_tok = (p->flags & PBS_FLAG_TOKEN_ORDER_COPY) && !qidx &&
                                      (tok_blocks + g.T) * 128 * 256 < 0x7fffffffLL;
                 const int tok_delta = own_tok ? (int)tok_blocks : 0;
-                st = launch_attn_wide(g, Qp, Kp, Vt, qidx, kidx, row_cnt, col_idx, Op, lse, redo, tok_delta, s);
+                st = launch_attn_wide(g, Qp, Kp, Vt, qidx, kidx, row_cnt, col_idx, Op, lse, redo, tickets, tok_delta, s);
                 if (st != PBS_OK) return st;
             }
-            st = launch((attn_mfma_kernel<128, 4, 64>), mgrid, dim3(256), 0, s, (const bf16_t *)Qp,
-                               (const bf16_t *)Kp, (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse,
-                               (const int32_t *)redo, g);
+            const long long rows = (long long)g.batch * g.h_q * g.T;
+            if (redo)
+                st = launch(attn_redo_kernel, dim3((unsigned)(rows < kRedoWgs ? rows : kRedoWgs)), dim3(256), 0, s,
+                            (const bf16_t *)Qp, (const bf16_t *)Kp, (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx,
+                            (bf16_t *)Op, lse, (const int32_t *)redo, g);
+            else
+                st = launch((attn_mfma_kernel<128, 4, 64>), mgrid, dim3(256), 0, s, (const bf16_t *)Qp,
+                            (const bf16_t *)Kp, (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse, g);
         } else {
             st = launch((attn_mfma_kernel<64, 2, 32>), mgrid, dim3(128), 0, s, (const bf16_t *)Qp,
-                               (const bf16_t *)Kp, (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse,
-                               (const int32_t *)nullptr, g);
+                               (const bf16_t *)Kp, (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse, g);
         }
         return st;
     }

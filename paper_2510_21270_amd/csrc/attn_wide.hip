@@ -26,6 +26,12 @@
 // bit).  When K', Vt and kidx carry a token-order copy behind the permuted tensors (tok_delta > 0), the R own-segment
 // blocks at the end of a list are replaced, while staged, by the token-order blocks up to the diagonal; the loop
 // itself does not know the difference (a token-order block is just a block index beyond the permuted ones).
+// Large problems run on as many workgroups as the chip holds, which take query blocks from queues and prepare the next
+// one under the current one.  Measured against one workgroup per query block, whole call: 32 / 8 heads, lists of a tenth
+// of the causal blocks, 65536 tokens 3.57 -> 3.48 ms; masks of an eighth, 131072 tokens 14.1 -> 13.7 ms (layer); dense
+// masks, where the chip's power and not its idle time is what runs out, 102.0 -> 100.1 ms (layer, 131072 tokens).
+#include <limits.h>
+
 #include "pbs_host.h"
 
 namespace pbs {
@@ -37,6 +43,9 @@ constexpr int kStageB = 8192;                              // K' sub-tile: 32 ro
 constexpr int kLoadsPerWave = 8;                           // 16-byte-per-lane loads a wave issues per stage
 constexpr int kList = 1024;                                // listed blocks staged in LDS at a time
 constexpr int kXcds = 8, kCohort = 64;
+constexpr int kResident = 512;                             // workgroups the chip holds: two on each of 256 compute units
+constexpr int kTicketStride = 32;                          // queue heads lie 128 bytes apart
+constexpr int kQueueRows = 8 * kResident;                  // rows from which on workgroups take them from queues
 constexpr float kLog2eF = 1.4426950408889634f;
 constexpr float kLn2F = 0.6931471805599453f;
 // The softmax reference of a query is the row maximum of the sub-tile that holds its first visible key and is never
@@ -62,8 +71,9 @@ struct __align__(16) Stage {
 
 __device__ __forceinline__ int swap23(int m) { return (m & ~12) | ((m & 4) << 1) | ((m & 8) >> 1); }
 
+// Descriptors of one kv head: what this wave loads (wave 0: K', wave 1: V'^T) and the key positions.
 struct TileBuffers {
-    __amdgpu_buffer_rsrc_t k, v, pos;
+    __amdgpu_buffer_rsrc_t tile, pos;
 };
 
 // A stage is 16 chunks of 1 KiB, one load instruction each (64 lanes x 16 bytes, consecutive in LDS).  Both waves
@@ -106,7 +116,7 @@ __device__ __forceinline__ LaneOffsets lane_offsets(int wave, int lane)
 struct StageLoad {
     __amdgpu_buffer_rsrc_t rsrc;
     int soff;                          // scalar byte offset of the sub-tile in the tensor
-    unsigned char *dst;                // LDS destination of load 0
+    __attribute__((address_space(3))) unsigned char *dst;    // LDS destination of load 0
 };
 
 // Stage P receives the K' part P of block jk and the V'^T part (P + 3) % 4 of block jv.
@@ -114,9 +124,12 @@ template <int P>
 __device__ __forceinline__ StageLoad stage_load(Stage &sg, const TileBuffers &buf, int jk, int jv, int wave)
 {
     StageLoad a;
-    a.rsrc = wave == 0 ? buf.k : buf.v;
-    a.soff = wave == 0 ? (jk * BLOCK + P * KS) * 256 : jv * (D * BLOCK * 2) + ((P + 3) & 3) * (D * KS * 2);
-    a.dst = wave == 0 ? sg.k : sg.v;
+    static_assert(BLOCK * 256 == D * BLOCK * 2 && KS * 256 == D * KS * 2, "blocks and sub-tiles of K' and Vt are equally large");
+    a.rsrc = buf.tile;
+    a.soff = (wave == 0 ? jk : jv) * (BLOCK * 256) + (wave == 0 ? P : (P + 3) & 3) * (KS * 256);
+    int half = wave * kStageB;                             // sg.k for wave 0, sg.v behind it for wave 1
+    asm volatile("" : "+s"(half));     // formed here: 32 loop-invariant addresses would not fit the scalar registers
+    a.dst = (__attribute__((address_space(3))) unsigned char *)sg.k + half;
     return a;
 }
 
@@ -419,121 +432,248 @@ __device__ __forceinline__ void drain(State &st, const bf16x8 (&pf)[2][2], const
 }
 #undef PBS_MQ
 
+// A row (query block of one head), in LDS; list entries as (block to load | keys that exist << 20 | mask bit).
+struct RowInfo {
+    int unit, bhq, i;       // kv head (batch * h_kv + head; -1: there is no such row), query head, query block
+    int cnt;                // listed blocks
+    int first;              // own segment in token order from this entry on
+    int len;                // entries to process (at least one); 0: not known yet
+};
+constexpr int kEntryBlock = (1 << 18) - 1, kEntryRoomShift = 20, kEntryMask = 1 << 28;
+constexpr int kEntryAhead = 1 << 29;                       // behind the last entry: the next row's first block
+
+// Rows are handed out in cohorts of `cohort` rows of one kv head with near-equal list lengths, longest lists first; XCD x
+// starts with the cohorts x, x + 8, ... (its L2 then holds the tiles its workgroups share).  Ticket t of XCD x -> row
+// index unit * rows_per_unit + mrow, -1 past the last cohort, -2 for the unused end of a unit's last cohort.
+__device__ __forceinline__ int ticket_row(const Geo &g, int cohort, int x, int t)
+{
+    const int nbk = g.batch * g.h_kv, rows_per_unit = g.r * g.T;
+    const int coh_per_unit = (rows_per_unit + cohort - 1) / cohort;
+    const int coh = (t / cohort) * kXcds + x;
+    if (coh >= nbk * coh_per_unit) return -1;
+    const int mrow = (coh / nbk) * cohort + t % cohort;
+    return mrow < rows_per_unit ? (coh % nbk) * rows_per_unit + mrow : -2;
+}
+
+// The next row for a workgroup of XCD `home` (one lane) that has drawn `ticket` from its own queue: the row of that
+// ticket, else one of the other XCDs' queues (the XCDs run at clocks that differ by up to 8 %).  -1: every queue is empty.
+__device__ __forceinline__ int claim_row(const Geo &g, int cohort, int32_t *tickets, int home, int ticket)
+{
+    int row = ticket_row(g, cohort, home, ticket);
+#pragma unroll 1
+    for (int k = 0; row < 0 && k < kXcds; ++k) {
+        const int x = (home + k) % kXcds;
+        do row = ticket_row(g, cohort, x, atomicAdd(tickets + x * kTicketStride, 1));
+        while (row == -2);
+    }
+    return row;
+}
+
+// One lane per queue: the workgroups' first tickets are their ids.
+__global__ __launch_bounds__(64) void init_tickets_kernel(int32_t *tickets, int first)
+{
+    if (threadIdx.x < kXcds) tickets[threadIdx.x * kTicketStride] = first;
+}
+
+// tickets == NULL: one workgroup per row, which it finds from its id.  Otherwise the grid is what the chip holds at a
+// time and every workgroup takes rows until none is left (tickets: 8 queue heads, set to gridDim.x / 8 beforehand).
+//
+// Between two rows a wave that has its SIMD to itself has nothing to overlap with, so the next row is prepared under
+// the current one: near the end of the current row wave 0 loads its list into LDS (asynchronously) and, a block later,
+// brings it into the form the loop reads and draws the ticket of the row after it.  The loads that the last
+// block would issue past its end are then those of the next row's first block, and the next Q' fragments travel under
+// the epilogue.  (A workgroup per row spent 9-10 us outside its loop and 1-6 us between two workgroups, against 3.3 us per
+// block; and the XCDs, which run at clocks up to 8 % apart, waited for the slowest.)
 __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) void attn_wide_kernel(
     const bf16_t *__restrict__ Qp, const bf16_t *__restrict__ Kp, const bf16_t *__restrict__ Vt,
     const int32_t *__restrict__ qidx, const int32_t *__restrict__ kidx, const int32_t *__restrict__ row_cnt,
     const int32_t *__restrict__ col_idx, bf16_t *__restrict__ Op, float *__restrict__ lse,
-    int32_t *__restrict__ redo, Geo g, int tok_delta)
+    int16_t *__restrict__ redo, Geo g, int tok_delta, int32_t *tickets, int cohort)
 {
     __shared__ Stage sg0, sg1, sg2, sg3;                   // 4 x 16 KiB
-    __shared__ int jl[kList];                              // current chunk of the list: block index to load
-    __shared__ int jm[kList];                              // ... keys of that block that exist, bit 30: token-level mask
-    __shared__ int bad_any;
-    __shared__ int own_tail_ok;                            // the chunk ends with the whole own segment, ascending
+    __shared__ int lists[2][kList];                        // block lists (a chunk of each) of this row and the next
+    __shared__ int tails[64];                              // the end of a list that is longer than a chunk
+    __shared__ int next_cnt[64], sink[64];
+    __shared__ RowInfo info[2];
 
-    // Workgroup -> (query head, query block): cohorts of 64 rows of one kv head per XCD, longest lists first
-    // (same decoding as the 32-queries-per-wave kernel).
-    const int nbk = g.batch * g.h_kv;
-    const int rows_per_unit = g.r * g.T;
-    const int coh_per_unit = (rows_per_unit + kCohort - 1) / kCohort;
-    const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
-    const int coh = (slot / kCohort) * kXcds + xcd;
-    if (coh >= nbk * coh_per_unit) return;
-    const int unit = coh % nbk;
-    const int mrow = (coh / nbk) * kCohort + slot % kCohort;
-    if (mrow >= rows_per_unit) return;
-    const int i = g.T - 1 - mrow / g.r;
-    const int b = unit / g.h_kv, hq = (unit % g.h_kv) * g.r + mrow % g.r;
-    const int bhq = b * g.h_q + hq;
-    const size_t bhk = unit;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ln = lane & 31, lh = lane >> 5;
-    const int q0 = i * BLOCK + wave * 64;
     const float c2 = g.scale * kLog2eF;
-
-    // Q' fragments: lane (n, h) holds Q'[q0 + 32 nt + n][16 ks + 8 h .. +8]
-    bf16x8 qf[2][8];
-    int qpos[2];
-    State st;
-    st.bad = false;
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-        const int qs = q0 + 32 * nt + ln;
-        const int qc = qs < g.n ? qs : g.n - 1;
-        const bf16_t *src = Qp + ((size_t)bhq * g.n + qc) * D + 8 * lh;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) qf[nt][k] = *reinterpret_cast<const bf16x8 *>(src + 16 * k);
-        qpos[nt] = qs < g.n ? (qidx ? qidx[(size_t)bhq * g.n + qs] : qs) : -1;
-        st.mref[nt] = 0.0f;
-        st.l[nt] = 0.0f;
-        st.seen[nt] = qs >= g.n;                  // padding rows never hold the wave on the careful path
-#pragma unroll
-        for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-            for (int x = 0; x < 16; ++x) st.acc_o[dt][nt][x] = 0.0f;
-    }
-
-    const int ni = allowed_cols(i, g);
-    const int jmask = first_masked_col(i, g);
-    const int cnt = min(row_cnt[(size_t)bhq * g.T + i], g.T);
-    const int32_t *cols = col_idx + ((size_t)bhq * g.T + i) * g.T;
-    constexpr int kRawDword = 0x00020000;                  // gfx9 descriptor word 3: raw 32-bit data format
-    TileBuffers buf;
-    // tok_delta > 0: a token-order copy of K', Vt and kidx lies tok_delta = batch * h_kv * T blocks behind the
-    // permuted one, so block j of this head in token order is block tok_delta + j of the same descriptors
-    const int reach = tok_delta * BLOCK + g.n;             // rows within reach of this head's descriptors
-    buf.k = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(Kp + bhk * (size_t)g.n * D), 0, reach * 256, kRawDword);
-    buf.v = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(Vt + bhk * (size_t)g.T * D * BLOCK), 0,
-                                              (tok_delta + g.T) * (D * BLOCK * 2), kRawDword);
-    buf.pos = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(kidx + bhk * (size_t)g.n), 0, reach * 4, kRawDword);
     const LaneOffsets off = lane_offsets(wave, lane);
+    constexpr int kRawDword = 0x00020000;                  // gfx9 descriptor word 3: raw 32-bit data format
 
-    // The list is staged as (block to load, keys that exist | mask bit).  An entry that the causal structure does not
-    // admit is staged as block 0 with no existing key and the mask bit: a sub-tile that contributes nothing.
-    constexpr int kMaskBit = 1 << 30;
-    auto entry = [&](int e) -> int { return __builtin_amdgcn_readfirstlane(jl[e]); };
-    auto entry_meta = [&](int e) -> int { return __builtin_amdgcn_readfirstlane(jm[e]); };
-
-    for (int base = 0; base < cnt; base += kList) {
-        int len = min(kList, cnt - base);
-        __syncthreads();                                   // previous chunk fully consumed
-        if (threadIdx.x == 0) own_tail_ok = 1;
-        for (int t = threadIdx.x; t < len; t += 128) {
-            const int j = cols[base + t];
-            const bool ok = j >= 0 && j < ni;
-            jl[t] = ok ? j : 0;
-            jm[t] = ok ? (g.n - j * BLOCK) | (j >= jmask ? kMaskBit : 0) : kMaskBit;
-        }
-        __syncthreads();
-        // Own segment in token order: when the list ends with all blocks jmask .. ni - 1 of the query block's own
-        // (full) segment, ascending, they are replaced by the blocks jmask .. i of the token-order copies.
-        // Keys of a segment are the same set in either order, so the visible keys are the same; in token order
-        // the blocks before the diagonal need no mask and those after it hold no visible key.
-        if (tok_delta > 0 && i / g.R < g.G && base + len == cnt && len >= ni - jmask) {
-            const int own = ni - jmask, first = len - own;
-            const int t = threadIdx.x;
-            if (t < own && (jl[first + t] != jmask + t || jm[first + t] != ((g.n - (jmask + t) * BLOCK) | kMaskBit)))
-                own_tail_ok = 0;
-            __syncthreads();
-            if (own_tail_ok) {
-                if (t <= i - jmask) {
-                    jl[first + t] = tok_delta + jmask + t;
-                    jm[first + t] = (g.n - (jmask + t) * BLOCK) | (jmask + t == i ? kMaskBit : 0);
-                }
+    auto decode = [&](int row, int &unit, int &bhq, int &i) {
+        const int rows_per_unit = g.r * g.T;
+        unit = row / rows_per_unit;
+        const int mrow = row % rows_per_unit;
+        i = g.T - 1 - mrow / g.r;
+        bhq = (unit / g.h_kv) * g.h_q + (unit % g.h_kv) * g.r + mrow % g.r;
+    };
+    auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+    // the raw list entries [base, base + kList) of a row, up to T (wave 0)
+    auto load_list = [&](int bhq, int i, int *list, int base) {
+        const int m = max(0, min(g.T - base, kList));
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<int32_t *>(col_idx + ((size_t)bhq * g.T + i) * g.T + base), 0, m * 4, kRawDword);
+        for (int k = 0; k < m; k += 64)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)(list + k), 4, lane * 4, k * 4, 0, 0);
+    };
+    // blocks of a row's own segment that token order may replace, 0: none
+    auto own_blocks = [&](int i) { return tok_delta > 0 && i / g.R < g.G ? allowed_cols(i, g) - first_masked_col(i, g) : 0; };
+    // Raw entries [base, base + kList) -> the form the loop reads (wave 0).  An entry that the causal structure does not
+    // admit becomes block 0 with no existing key under the mask: a sub-tile that contributes nothing.
+    // Behind the last entry stands a copy of it: the loop reads one entry ahead.
+    auto pack_list = [&](int i, int first, int len, int *list, int base) {
+        const int ni = allowed_cols(i, g), jmask = first_masked_col(i, g);
+        auto packed = [&](int e, int raw) {
+            int j = raw, to = raw;
+            if (e >= first) {                              // token order: keys of the diagonal block need the mask
+                j = jmask + e - first;
+                to = tok_delta + j;
+            } else if (j < 0 || j >= ni) {
+                return (int)kEntryMask;
+            }
+            const bool masked = e >= first ? j == i : j >= jmask;
+            return to | min(BLOCK, g.n - j * BLOCK) << kEntryRoomShift | (masked ? kEntryMask : 0);
+        };
+        for (int t = lane; t < min(len - base, kList); t += 64) list[t] = packed(base + t, list[t]);
+        if (lane == 0 && len - base < kList) list[len - base] = 0;
+    };
+    // With a list's first chunk (and, where it is longer, its end in tails) in LDS: its length in blocks to process, and
+    // the packed entries (wave 0).
+    // Own segment in token order: when a list ends with all blocks jmask .. ni - 1 of the query block's own (full)
+    // segment, ascending, these entries stand for the blocks jmask .. i of the token-order copies.  Keys of a segment are
+    // the same set in either order, so the visible keys are the same; in token order the blocks before the diagonal
+    // need no mask and those after it hold no visible key.
+    auto close_list = [&](RowInfo &w, int i, int cnt, int *list) {
+        const int own = own_blocks(i), jmask = first_masked_col(i, g);
+        int first = INT_MAX, len = cnt;
+        if (own > 0 && cnt >= own) {
+            const int t = cnt <= kList ? list[min(cnt - own + lane, kList - 1)] : tails[lane];
+            if (__all(lane >= own || t == jmask + lane)) {
+                first = cnt - own;
                 len = first + i - jmask + 1;
             }
-            __syncthreads();
         }
+        if (len == 0) {                                    // an empty list: one entry that contributes nothing
+            len = 1;
+            if (lane == 0) list[0] = -1;
+        }
+        pack_list(i, first, len, list, 0);
+        if (lane == 0) {
+            w.cnt = cnt;
+            w.first = first;
+            w.len = len;
+        }
+    };
+    auto load_tail = [&](int bhq, int i, int cnt) {
+        const int own = own_blocks(i);
+        if (own > 0 && cnt > kList) {
+            const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<int32_t *>(col_idx + ((size_t)bhq * g.T + i) * g.T + cnt - own), 0, own * 4, kRawDword);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)tails, 4, lane * 4, 0, 0, 0);
+        }
+    };
+    TileBuffers buf;
+    auto open_buffers = [&](int unit) {
+        // tok_delta > 0: a token-order copy of K', Vt and kidx lies tok_delta = batch * h_kv * T blocks behind the
+        // permuted one, so block j of this head in token order is block tok_delta + j of the same descriptors
+        const size_t bhk = unit;
+        const int reach = tok_delta * BLOCK + g.n;         // rows within reach of this head's descriptors
+        buf.tile = wave == 0 ? __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(Kp + bhk * (size_t)g.n * D), 0, reach * 256, kRawDword)
+                             : __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(Vt + bhk * (size_t)g.T * D * BLOCK), 0,
+                                                                 (tok_delta + g.T) * (D * BLOCK * 2), kRawDword);
+        buf.pos = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(kidx + bhk * (size_t)g.n), 0, reach * 4, kRawDword);
+    };
+    auto issue_block = [&](int j) {
+        issue_stage<0>(sg0, buf, off, j, wave, lane);
+        issue_stage<1>(sg1, buf, off, j, wave, lane);
+        issue_stage<2>(sg2, buf, off, j, wave, lane);
+        issue_stage<3>(sg3, buf, off, j, wave, lane);
+    };
+    auto query_buffer = [&](int bhq) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(Qp + (size_t)bhq * g.n * D), 0, g.n * 256, kRawDword);
+    };
+    // Q' fragments: lane (n, h) holds Q'[q0 + 32 nt + n][16 ks + 8 h .. +8]
+    // (buffer loads: the compiler moves plain loads of read-only memory down to their use, behind the waits; rows past
+    // the end of the head read as zeros)
+    bf16x8 qf[2][8];
+    int qpos[2];
+    auto load_queries = [&](int bhq, int i) {
+        const __amdgpu_buffer_rsrc_t r = query_buffer(bhq);
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) {
+            const int qs = i * BLOCK + wave * 64 + 32 * nt + ln;
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                qf[nt][k] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, qs * 256 + 16 * lh, 32 * k, 0));
+            qpos[nt] = qs < g.n ? (qidx ? qidx[(size_t)bhq * g.n + qs] : qs) : -1;
+        }
+    };
 
-        // prologue: the four parts of the first block, its first scores, the K' fragments of part 1
-        int jc = entry(0);
-        int meta = entry_meta(0);
-        issue_stage<0>(sg0, buf, off, jc, wave, lane);
-        issue_stage<1>(sg1, buf, off, jc, wave, lane);
-        issue_stage<2>(sg2, buf, off, jc, wave, lane);
-        issue_stage<3>(sg3, buf, off, jc, wave, lane);
+    const int home = blockIdx.x % kXcds;
+    // the row of a ticket as the next one (one lane); ticket < 0: there is none
+    auto open_next = [&](RowInfo &w, int ticket) {
+        const int row = ticket < 0 ? -1 : claim_row(g, cohort, tickets, home, ticket);
+        w.unit = -1;
+        w.len = 0;
+        if (row >= 0) decode(row, w.unit, w.bhq, w.i);
+    };
+    int unit, bhq, i;                                      // of the current row
+    {
+        int row = ticket_row(g, cohort, home, blockIdx.x / kXcds);
+        if (row < 0) {
+            if (!tickets) return;
+            if (threadIdx.x == 0) next_cnt[0] = claim_row(g, cohort, tickets, home, blockIdx.x / kXcds);
+            __syncthreads();
+            row = uniform(next_cnt[0]);
+            if (row < 0) return;
+        }
+        decode(row, unit, bhq, i);
+        const size_t at = (size_t)bhq * g.T + i;
+        if (wave == 0) load_list(bhq, i, lists[0], 0);
+        load_queries(bhq, i);
+        open_buffers(unit);
+        const int raw0 = uniform(col_idx[at * g.T]);       // read beside the count
+        const int cnt = max(0, min(uniform(row_cnt[at]), g.T));
+        if (wave == 0) load_tail(bhq, i, cnt);
+        const bool early = cnt > own_blocks(i);            // the first entry cannot be one that token order replaces
+        int j0 = raw0 >= 0 && raw0 < allowed_cols(i, g) ? raw0 : 0;
+        if (!early) {
+            sync_stages();
+            if (wave == 0) close_list(info[0], i, cnt, lists[0]);
+            __syncthreads();
+            j0 = uniform(lists[0][0]) & kEntryBlock;
+        }
+        issue_block(j0);
+        if (early && wave == 0) {
+            __builtin_amdgcn_s_waitcnt(0x8F74);            // vmcnt(36): what was issued before the tiles has landed
+            asm volatile("" ::: "memory");
+            close_list(info[0], i, cnt, lists[0]);
+        }
+        if (threadIdx.x == 0) open_next(info[1], tickets ? atomicAdd(tickets + home * kTicketStride, 1) : -1);
         sync_stages();
+    }
+
+    for (int cur = 0;; cur ^= 1) {
+        // here: the first block's tiles (its four K' parts and V'^T parts) are in the ring, Q' in registers, the row's
+        // info and list (first chunk) in info[cur], lists[cur]
+        const int len = uniform(info[cur].len);
+        const int *list = lists[cur];
+        State st;
+        st.bad = false;
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) {
+            st.mref[nt] = 0.0f;
+            st.l[nt] = 0.0f;
+            st.seen[nt] = qpos[nt] < 0;                    // padding rows never hold the wave on the careful path
+#pragma unroll
+            for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+                for (int x = 0; x < 16; ++x) st.acc_o[dt][nt][x] = 0.0f;
+        }
+        // first scores, the K' fragments of part 1
         floatx16 sa[2], sb[2];
         bf16x8 kf[8];
         load_kf(kf, sg0, off);
@@ -547,69 +687,204 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             for (int x = 0; x < 8; ++x) pa[u >> 1][u & 1][x] = (bf16_t)0.0f;
         __builtin_amdgcn_sched_barrier(0);
 
+        // The next row's preparation (wave 0), in steps 0 .. 2 at the ends of blocks; 3: done, info[cur ^ 1] and
+        // lists[cur ^ 1] are complete.  The last step also puts the row's first entry behind this row's last one, where
+        // the block before the last one picks it up: both waves, so that a block's barriers have to lie in between.
+        constexpr int kPrepare = 5;
+        int step_no = 0, ticket = -1;
+        auto prepare = [&]() {
+            asm volatile("" ::: "memory");                 // no read of LDS moves up across the blocks' barriers
+            RowInfo &w = info[cur ^ 1];
+            if (uniform(w.unit) < 0) {
+                step_no = 3;
+                return;
+            }
+            const int nb = uniform(w.bhq), nq = uniform(w.i);
+            if (step_no == 0) {
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                    __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(row_cnt + (size_t)nb * g.T + nq), 0, 4, kRawDword),
+                    (lptr_t)next_cnt, 4, lane * 4, 0, 0, 0);
+                load_list(nb, nq, lists[cur ^ 1], 0);
+                // one word of every line of the row's Q' block, so that its fragments come from the cache
+                const __amdgpu_buffer_rsrc_t r = query_buffer(nb);
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)sink, 4, lane * 128, nq * (BLOCK * 256) + k * 8192, 0, 0);
+                step_no = 1;
+                return;
+            }
+            const int cnt = max(0, min(uniform(next_cnt[0]), g.T));
+            if (step_no == 1 && cnt > kList) {
+                load_tail(nb, nq, cnt);
+                step_no = 2;
+                return;
+            }
+            close_list(w, nq, cnt, lists[cur ^ 1]);
+            if (lane == 0 && w.unit == unit) lists[cur][len & (kList - 1)] = lists[cur ^ 1][0] | kEntryAhead;
+            if (lane == 0) ticket = atomicAdd(tickets + home * kTicketStride, 1);        // of the row after that, used in the epilogue
+            step_no = 3;
+        };
+        // rare work at the end of block e: the next chunk of a list of more than kList entries, preparation steps
+        const int chunk_end = len >= kList ? kList - 3 : INT_MAX;
+        int event = wave == 0 ? min(chunk_end, max(0, len - kPrepare)) : chunk_end;
+        auto at_event = [&](int e) {
+            asm volatile("" ::: "memory");
+            if (((e + 3) & (kList - 1)) == 0 && e + 3 <= len) {
+                __syncthreads();
+                if (wave == 0) {
+                    load_list(bhq, i, lists[cur], e + 3);
+                    __builtin_amdgcn_s_waitcnt(0x0F70);
+                    asm volatile("" ::: "memory");
+                    pack_list(i, uniform(info[cur].first), len, lists[cur], e + 3);
+                }
+                sync_stages();
+            }
+            if (wave == 0 && e >= len - kPrepare && e <= len - 4 && step_no < 3) prepare();
+            const int chunk = e + 3 + kList <= len ? ((e + 3) & -kList) + kList - 3 : INT_MAX;
+            event = wave == 0 ? min(chunk, e < len - kPrepare ? len - kPrepare : e + 1) : chunk;
+        };
+
+        int pk = uniform(list[0]);
+        int later = list[1];                               // the entry after the next one, read a block ahead
+        int jc = pk & kEntryBlock;
         for (int e = 0; e < len; ++e) {
-            const int enext = min(e + 1, len - 1);         // past the end: the last block again (results unused)
-            const int jn = entry(enext);
-            const int meta_next = entry_meta(enext);
-            const bool masked = (meta & kMaskBit) != 0;
-            const int room0 = meta & (kMaskBit - 1);       // keys of the block that exist
+            const int pn = uniform(later);                 // past the end: the next row's first block or any (unused)
+            later = list[(e + 2) & (kList - 1)];
+            const int jn = pn & kEntryBlock;
+            const bool masked = (pk & kEntryMask) != 0;
+            const int room0 = (pk >> kEntryRoomShift) & 255;             // keys of the block that exist
             // part p: probabilities of part p; scores of part p + 1; O^T update with part p - 1; K' fragments of
             // part p + 2 (parts outside 0..3 are those of the neighbouring listed blocks).  Stage p is refilled with
             // K' part p of the next block and V'^T part p - 1 of the next block (part 3 of this block when p = 0).
-            // The first iteration of a chunk updates O^T with zero probabilities.
+            // The first iteration of a row updates O^T with zero probabilities.
             step<0>(st, sa, sb, kf, qf, pa, pb, sg0, sg2, qpos, room0, masked, c2, lh, buf, off, jn, jc, wave, lane);
             step<1>(st, sb, sa, kf, qf, pb, pa, sg1, sg3, qpos, room0 - KS, masked, c2, lh, buf, off, jn, jn, wave, lane);
             step<2>(st, sa, sb, kf, qf, pa, pb, sg2, sg0, qpos, room0 - 2 * KS, masked, c2, lh, buf, off, jn, jn, wave, lane);
             step<3>(st, sb, sa, kf, qf, pb, pa, sg3, sg1, qpos, room0 - 3 * KS, masked, c2, lh, buf, off, jn, jn, wave, lane);
             jc = jn;
-            meta = meta_next;
+            pk = pn;
+            if (e == event) at_event(e);
         }
+        const bool ahead = (pk & kEntryAhead) != 0;        // the ring holds the next row's first block
         drain(st, pa, sg0, off);
-        __builtin_amdgcn_s_waitcnt(0x0F70);                // the loads issued past the end have landed too
-    }
 
-    // redo[query block] = 1 when some probability outgrew its fixed reference (the caller recomputes the block)
-    if (threadIdx.x == 0) bad_any = 0;
-    __syncthreads();
-    if (st.bad) bad_any = 1;
-    __syncthreads();
-    if (threadIdx.x == 0) redo[(size_t)bhq * g.T + i] = bad_any;
-
-    // ---- O' = diag(l)^-1 O; acc_o[dt][nt][x]: d = 32 dt + 8 (x / 4) + 4 h + (x % 4), query = q0 + 32 nt + n
+        // ---- O' = diag(l)^-1 O; acc_o[dt][nt][x]: d = 32 dt + 8 (x / 4) + 4 h + (x % 4), query = q0 + 32 nt + n.
+        // The two lanes of a query exchange pieces so that each stores 8 consecutive features.
+        uintx4 out[2][4][2];
+        float lt[2];
+        auto finish = [&]() {
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-        const float lt = st.l[nt] + __shfl_xor(st.l[nt], 32, 64);
-        const float inv = lt > 0.0f ? 1.0f / lt : 0.0f;
-        const int qs = q0 + 32 * nt + ln;
-        if (qs < g.n) {
-            bf16_t *dst = Op + ((size_t)bhq * g.n + qs) * D;
+            for (int nt = 0; nt < 2; ++nt) {
+                lt[nt] = st.l[nt] + __shfl_xor(st.l[nt], 32, 64);
+                const float inv = lt[nt] > 0.0f ? 1.0f / lt[nt] : 0.0f;
 #pragma unroll
-            for (int dt = 0; dt < 4; ++dt)
+                for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-                for (int gq = 0; gq < 4; ++gq) {
-                    floatx2 a = {st.acc_o[dt][nt][4 * gq] * inv, st.acc_o[dt][nt][4 * gq + 1] * inv};
-                    floatx2 bb = {st.acc_o[dt][nt][4 * gq + 2] * inv, st.acc_o[dt][nt][4 * gq + 3] * inv};
-                    const bf16x2 pa = __builtin_convertvector(a, bf16x2), pb = __builtin_convertvector(bb, bf16x2);
-                    bf16x4 o4 = {pa[0], pa[1], pb[0], pb[1]};
-                    *reinterpret_cast<bf16x4 *>(dst + 32 * dt + 8 * gq + 4 * lh) = o4;
+                    for (int a = 0; a < 2; ++a) {
+                        uint32_t piece[2][2];              // [features 8 (2 a + y)][pair]
+#pragma unroll
+                        for (int y = 0; y < 2; ++y)
+#pragma unroll
+                            for (int z = 0; z < 2; ++z) {
+                                const int x = 4 * (2 * a + y) + 2 * z;
+                                const floatx2 o = {st.acc_o[dt][nt][x] * inv, st.acc_o[dt][nt][x + 1] * inv};
+                                piece[y][z] = __builtin_bit_cast(uint32_t, __builtin_convertvector(o, bf16x2));
+                            }
+#pragma unroll
+                        for (int z = 0; z < 2; ++z) {
+                            // lower half: (own, other's) of piece 0; upper half: (other's, own) of piece 1
+                            const auto sw = __builtin_amdgcn_permlane32_swap(piece[0][z], piece[1][z], false, false);
+                            out[nt][dt][a][z] = sw[0];
+                            out[nt][dt][a][2 + z] = sw[1];
+                        }
+                    }
+            }
+        };
+        auto store = [&]() {
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt) {
+                const int qs = i * BLOCK + wave * 64 + 32 * nt + ln;
+                if (qs < g.n) {
+                    bf16_t *dst = Op + ((size_t)bhq * g.n + qs) * D + 8 * lh;
+#pragma unroll
+                    for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+                        for (int a = 0; a < 2; ++a) *reinterpret_cast<uintx4 *>(dst + 32 * dt + 16 * a) = out[nt][dt][a];
+                    if (lse && lh == 0)
+                        lse[(size_t)bhq * g.n + qs] = lt[nt] > 0.0f ? (st.mref[nt] + log2f(lt[nt])) * kLn2F : -INFINITY;
                 }
-            if (lse && lh == 0)
-                lse[(size_t)bhq * g.n + qs] = lt > 0.0f ? (st.mref[nt] + log2f(lt)) * kLn2F : -INFINITY;
+            }
+            // each wave's half of the row's flag: some probability outgrew its fixed reference (the caller redoes the row)
+            const bool bad = __any(st.bad);
+            if (lane == 0) redo[((size_t)bhq * g.T + i) * 2 + wave] = bad ? 1 : 0;
+        };
+        if (!ahead) {
+            if (wave == 0)
+                while (step_no < 3) {                      // a list too short to prepare the next row under it
+                    __builtin_amdgcn_s_waitcnt(0x0F70);
+                    prepare();
+                }
+            sync_stages();                                 // info, list; the loads issued past the end have landed
         }
+        const int unit1 = uniform(info[cur ^ 1].unit);
+        if (unit1 < 0) {                                   // no further row
+            finish();
+            store();
+            break;
+        }
+        const int bhq1 = uniform(info[cur ^ 1].bhq), i1 = uniform(info[cur ^ 1].i);
+        const int j1 = uniform(lists[cur ^ 1][0]) & kEntryBlock;
+        load_queries(bhq1, i1);
+        if (ahead) {                                       // V'^T part 3 of the first block is all that is missing
+            __builtin_amdgcn_s_waitcnt(0xC07F);            // lgkmcnt(0): this wave has read sg0.v ...
+            __builtin_amdgcn_s_barrier();                  // ... and so has the other
+            __builtin_amdgcn_sched_barrier(0);
+            if (wave == 1) {
+                const StageLoad ld = stage_load<0>(sg0, buf, j1, j1, 1);
+                issue_load<0>(ld, off); issue_load<1>(ld, off); issue_load<2>(ld, off); issue_load<3>(ld, off);
+                issue_load<4>(ld, off); issue_load<5>(ld, off); issue_load<6>(ld, off); issue_load<7>(ld, off);
+            }
+        } else {
+            open_buffers(unit1);
+            issue_block(j1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        finish();
+        __builtin_amdgcn_sched_barrier(0);
+        if (threadIdx.x == 0) open_next(info[cur], ticket);              // in the place of this row's
+        sync_stages();                                     // Q' and the first block are here
+        store();
+        unit = unit1;
+        bhq = bhq1;
+        i = i1;
     }
+    __builtin_amdgcn_s_waitcnt(0x0F70);                    // the loads issued past the end have landed
 }
 
 }  // namespace wide
 
-// redo: [batch * h_q * T] flags, written for every query block.
+// redo: [batch * h_q * T] flags, written for every query block, then (aligned to 64 bytes) the 8 queue heads.
 pbs_status launch_attn_wide(const Geo &g, const void *Qp, const void *Kp, const void *Vt, const int32_t *qidx,
                             const int32_t *kidx, const int32_t *row_cnt, const int32_t *col_idx, void *Op, float *lse,
-                            int32_t *redo, int tok_delta, hipStream_t s)
+                            int32_t *redo, int32_t *tickets, int tok_delta, hipStream_t s)
 {
-    const int ncoh = g.batch * g.h_kv * ((g.r * g.T + wide::kCohort - 1) / wide::kCohort);
-    const dim3 grid((unsigned)(((ncoh + wide::kXcds - 1) / wide::kXcds) * wide::kCohort * wide::kXcds));
-    return launch(wide::attn_wide_kernel, grid, dim3(128), 0, s, (const bf16_t *)Qp, (const bf16_t *)Kp,
-                       (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse, redo, g, tok_delta);
+    const long long units = (long long)g.batch * g.h_kv, rows = (long long)g.r * g.T;
+    int cohort = wide::kCohort;
+    unsigned wgs = wide::kResident;
+    if (units * rows >= wide::kQueueRows) {
+        const pbs_status st = launch(wide::init_tickets_kernel, dim3(1), dim3(64), 0, s, tickets, wide::kResident / wide::kXcds);
+        if (st != PBS_OK) return st;
+    } else {
+        // every row has a workgroup of its own (a queue's lookahead of one row costs more balance than the gaps between
+        // workgroups while each takes only a few rows); cohorts narrower while some XCD would get none
+        tickets = nullptr;
+        while (cohort > 8 && units * ((rows + cohort - 1) / cohort) < wide::kXcds) cohort >>= 1;
+        const long long ncoh = units * ((rows + cohort - 1) / cohort);
+        wgs = (unsigned)((ncoh + wide::kXcds - 1) / wide::kXcds * wide::kXcds * cohort);
+    }
+    return launch(wide::attn_wide_kernel, dim3(wgs), dim3(128), 0, s, (const bf16_t *)Qp, (const bf16_t *)Kp,
+                  (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse, (int16_t *)redo, g, tok_delta,
+                  tickets, cohort);
 }
 
 }  // namespace pbs

@@ -109,3 +109,46 @@ def test_fp64_key_scores_from_listed_rows(oracle_variants, dtype, d, block, m):
     got = pbs.key_scores_proxy(p, pbs.PROXY_QUERY_ROWS, i32_dev(rows), to_dev(Q, dtype), to_dev(K, dtype))
     want = oracle_variants.key_scores_proxy(Q, K, rows)
     np.testing.assert_allclose(got.cpu().numpy(), want, rtol=2.0 ** -23, atol=1e-37)
+
+
+def test_rows_from_queues_and_lists_of_every_length(oracle):
+    # 4400 rows: workgroups take rows from queues and prepare the next one under the current one.  Lists too short for
+    # that, empty ones, and ones that end around the 1024 entries that are staged at a time, with and without the own
+    # segment that token order replaces at their end.
+    block, d, T, Hq, Hkv, seg = 128, 128, 1100, 4, 2, 1024
+    n, R = T * block - 77, seg // block
+    g = torch.Generator(device="cuda")
+    g.manual_seed(11)
+    Q, K, V = (torch.randn((1, h, n, d), generator=g, device="cuda").to(torch.bfloat16) for h in (Hq, Hkv, Hkv))
+    p = pbs.problem(1, Hq, Hkv, n, d, block, seg, "bf16", flags=pbs.FLAG_TOKEN_ORDER_COPY)
+    kidx, Kp, Vt = pbs.segment_permute(p, None, K, V)
+    rng = np.random.default_rng(12)
+    lens = [0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 12, 40, 1015, 1016, 1020, 1021, 1022, 1023, 1024, 1025, 1026, 1027, 1040]
+    cnt = np.zeros((1, Hq, T), dtype=np.int32)
+    cols = np.full((1, Hq, T, T), -1, dtype=np.int32)
+    rows = []
+    for h in range(Hq):
+        for i in range(T):
+            seg_lo, full = i // R * R, (i // R + 1) * seg <= n
+            want = lens[(i * Hq + h) % len(lens)]
+            own = list(range(seg_lo, seg_lo + R)) if full and i % 3 else [i]
+            below = seg_lo if full else i
+            take = min(max(0, want - len(own)), below)
+            lst = ([] if want == 0 else sorted(rng.choice(below, take, replace=False).tolist()) + own)
+            cnt[0, h, i] = len(lst)
+            cols[0, h, i, :len(lst)] = lst
+            if i >= T - 60 and (h + i) % 3 == 0 or i < 40 and h == 1:
+                rows.append([0, h, i])
+    rows = np.asarray(rows, dtype=np.int32)
+    got, lse = pbs.attn_fwd(p, Q, Kp, Vt, None, kidx, i32_dev(cnt), i32_dev(cols), want_lse=True)
+    torch.cuda.synchronize()
+    host = [x.float().cpu().numpy() for x in (Q, K, V)]
+    kh = np.tile(np.arange(n, dtype=np.int32), (1, Hkv, 1))
+    want = oracle.attn_rows(*host, None, kh, cnt, cols, block, rows)
+    got = to_host(got)
+    for k, (_, h, i) in enumerate(rows):
+        lo, hi = i * block, min(n, (i + 1) * block)
+        if cnt[0, h, i] == 0:
+            assert (got[0, h, lo:hi] == 0).all() and torch.isneginf(lse[0, h, lo:hi]).all()
+        else:
+            check_close(got[0, h, lo:hi], want[k][:hi - lo], "bf16", "row %d of head %d" % (i, h))
