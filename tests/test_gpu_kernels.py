@@ -152,3 +152,19 @@ def test_rows_from_queues_and_lists_of_every_length(oracle):
             assert (got[0, h, lo:hi] == 0).all() and torch.isneginf(lse[0, h, lo:hi]).all()
         else:
             check_close(got[0, h, lo:hi], want[k][:hi - lo], "bf16", "row %d of head %d" % (i, h))
+
+
+# four keys to a lane, 64 lanes to a wave: segments inside a lane row, a wave, two waves, sixteen; sizes
+# that are no power of two; ties, both zeros, infinities
+@pytest.mark.parametrize("block,segment", [(16, 16), (16, 48), (32, 256), (16, 272), (128, 512), (128, 1024), (64, 1088),
+                                           (128, 2048), (128, 3968), (128, 4096)])
+def test_segment_argsort_of_ragged_lengths_with_ties(oracle, block, segment):
+    n = 3 * segment + segment // 2 + 3
+    rng = np.random.default_rng(segment)
+    s = rng.standard_normal((1, 3, n)).astype(np.float32)
+    s[0, 1] = np.round(s[0, 1])                            # mostly ties, -0.0 among them
+    s[0, 2, ::7], s[0, 2, ::11] = np.inf, -np.inf
+    p = pbs.problem(1, 3, 3, n, 64, block, segment, "f32", flags=pbs.FLAG_TOKEN_ORDER_COPY)
+    kidx, _, _ = pbs.segment_permute(p, torch.from_numpy(s).cuda(), None, None, indices_only=True)
+    np.testing.assert_array_equal(kidx.cpu().numpy(), oracle.segment_argsort(s, segment))
+    assert (pbs.token_copy(p, kidx, 1).cpu().numpy() == np.arange(n)).all()
