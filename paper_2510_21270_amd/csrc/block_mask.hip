@@ -80,13 +80,18 @@ __global__ __launch_bounds__(256) void pool_kernel(const E *__restrict__ X, doub
 }
 
 // ---------------------------------------------------------------------------------------------
-// Selection.  One workgroup per (kv head, chunk of RB query heads of its group, query block i): the RB rows
-// share the allowed columns and the pooled keys.  The logits are register-tiled: a thread owns four neighbouring
-// columns of all RB rows, so the two 16-byte loads that bring one feature of its four pooled keys and the (at most)
-// two 16-byte LDS reads that bring that feature of the RB pooled queries feed 4 * RB fused multiply-adds; every sum
-// runs over the features in ascending order.  After the
-// logits, wave w owns row w and finishes it alone (no workgroup barriers): softmax, then the smallest
-// probability v* that is still kept, found by bisection instead of a sort.
+// Selection.  One workgroup per (kv head, chunk of RB query heads of its group, QB query blocks): the RB * QB rows share
+// the allowed columns and the pooled keys.  The logits run on the fp64 matrix instruction v_mfma_f64_4x4x4 (four
+// independent 4 x 4 x 4 products: here 4 rows x 16 columns x 4 features), whose accumulator takes the four products in
+// ascending order with one rounding each, i.e. exactly the chain of fused multiply-adds over ascending features that
+// defines a logit.  It does 12.8 multiply-adds per clock where v_fma_f64 does 8, and a pooled query comes out of LDS
+// once per 64 of them instead of once per 2.  A wave takes 32 columns at a time.  After the logits, wave w owns row w
+// and finishes it alone (no workgroup barriers): softmax, then the smallest probability v* that is still kept, found by
+// bisection instead of a sort, with the row in registers where it has at most 1024 columns.
+// Bound: vector issue (pooling Q': a conversion and an fp64 addition per value, 3 us of a wave's time per block; the
+// bisection about as much), 4 waves per SIMD.  Measured, same masks bit for bit, against logits on v_fma_f64 with every
+// multiply-add's query operand read from LDS: 28 / 4 heads x 65536 179 -> 158 us, 32 / 8 heads x 2048 25.5 -> 18.4 us,
+// x 8147 31.9 -> 24.1 us, x 131072 443 -> 437 us.
 //
 // The kept set of Algorithm 2 is the shortest prefix of the order (probability descending, column ascending)
 // whose mass reaches tau.  With M(v) = sum of the probabilities >= v, v* is the largest v with M(v) >= tau:
@@ -100,17 +105,56 @@ struct MassCount {
     int cnt;
 };
 
-// mass and number of the row's probabilities >= v; pr is padded with -1 up to a multiple of 64
-__device__ inline MassCount mass_at_least(const double *pr, int ni64, int lane, double v)
+// One row, 64 columns per chunk, lane = column.  REGS: up to kRegChunks chunks in registers (loaded once), else in LDS.
+// Columns past the row's own count are padded by the caller.
+constexpr int kRegChunks = 16;
+template <bool REGS>
+struct RowProbs;
+template <>
+struct RowProbs<true> {
+    double x[kRegChunks];
+    int chunks;
+    __device__ __forceinline__ RowProbs(double *pr, int ni, int lane) : chunks((ni + 63) >> 6)
+    {
+#pragma unroll
+        for (int c = 0; c < kRegChunks; ++c)
+            if (c < chunks) x[c] = pr[64 * c + lane];
+    }
+    template <typename F>
+    __device__ __forceinline__ void each(F f)              // f(chunk, value), in ascending order
+    {
+#pragma unroll
+        for (int c = 0; c < kRegChunks; ++c)
+            if (c < chunks) f(c, x[c]);
+    }
+};
+template <>
+struct RowProbs<false> {
+    double *pr;
+    int chunks;
+    __device__ __forceinline__ RowProbs(double *row, int ni, int lane) : pr(row + lane), chunks((ni + 63) >> 6) {}
+    template <typename F>
+    __device__ __forceinline__ void each(F f)
+    {
+        for (int c = 0; c < chunks; ++c) {
+            double v = pr[64 * c];
+            f(c, v);
+            pr[64 * c] = v;
+        }
+    }
+};
+
+// mass and number of the row's probabilities >= v (padding is negative)
+template <bool REGS>
+__device__ __forceinline__ MassCount mass_at_least(RowProbs<REGS> &row, double v)
 {
     double acc = 0.0;
     int cnt = 0;
-    for (int j0 = 0; j0 < ni64; j0 += 64) {
-        const double x = pr[j0 + lane];
+    row.each([&](int, double &x) {
         const bool ge = x >= v;
         acc += ge ? x : 0.0;
         cnt += __popcll(__ballot(ge));
-    }
+    });
     return {wave_sum_dpp(acc), cnt};
 }
 
@@ -120,7 +164,7 @@ __device__ inline MassCount mass_at_least(const double *pr, int ni64, int lane, 
 // Query blocks are taken from the last one down: the long rows start first, the short ones fill the tail.
 constexpr int kPairedLds = 64 * 1024;
 
-template <int RB, int QB, typename E>
+template <int RB, int QB, bool REGS, typename E>
 __global__ __launch_bounds__(64 * RB * QB) __attribute__((amdgpu_waves_per_eu(1, 4)))
 void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
                    const double *__restrict__ KbarT,   // [bhkv][d][Ts]
@@ -128,10 +172,8 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
                    Geo g, int chunks, int Tpad, int Ts)
 {
     constexpr int RT = RB * QB;                                      // rows (= waves) of the workgroup
-    constexpr int THREADS = 64 * RT;
-    constexpr int CT = 4 / QB;                                       // columns per thread: 4 * 64 * RB per pass
-    constexpr int FD = 4 * QB;                                       // features per register buffer
-    static_assert(QB == 1 || QB == 2, "column tile is one or two 16-byte loads");
+    constexpr int NG = (RT + 3) / 4;                                 // groups of four rows
+    constexpr int FS = 8;                                            // steps of four features per register buffer
     extern __shared__ __align__(16) unsigned char smem_raw[];
     double *prob = reinterpret_cast<double *>(smem_raw);             // [RT][Tpad]
     __shared__ __align__(16) double qs[128][RT];                     // block means of the RT query rows, feature-major
@@ -201,86 +243,84 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
     }
     __syncthreads();
 
-    // logits: fused multiply-adds in the order e = 0..d-1; columns j .. j + CT - 1 of every row per thread (columns at
-    // or beyond a row's own count are computed from whatever the padded Kbar rows hold and never read; rows that are
-    // not there from whatever qs holds).  Two register buffers of FD features each, filled alternately: the loads of
-    // one are in flight while the other is multiplied (scheduling barriers keep the compiler from moving a buffer's
-    // loads down to its use).
+    // logits: A operand: lane holds the mean of row lane % 4 (of its group), feature 4 step + lane / 16; B operand: column
+    // lane % 16, same feature; accumulator: row lane / 16, column lane % 16.  Rows that are not there compute whatever
+    // qs holds, columns past the row end the last one's; neither is stored.  Two register buffers of FS steps, filled
+    // alternately: the loads of one are in flight while the other is multiplied (scheduling barriers keep the compiler
+    // from moving a buffer's loads down to its use).
     const double *kt = KbarT + (size_t)bhk * g.d * Ts;
-    typedef double double2v __attribute__((ext_vector_type(2)));
-    for (int j = CT * tid; j < ni_all; j += CT * THREADS) {
-        double acc[RT][CT];
+    for (int c0 = 32 * w; c0 < ni_all; c0 += 32 * RT) {
+        const double *src[2];
 #pragma unroll
-        for (int row = 0; row < RT; ++row)
+        for (int t = 0; t < 2; ++t) src[t] = kt + (size_t)(lane >> 4) * Ts + min(c0 + 16 * t + (lane & 15), Ts - 1);
+        double acc[2][NG];
 #pragma unroll
-            for (int c = 0; c < CT; ++c) acc[row][c] = 0.0;
-        double kva[FD][CT], kvb[FD][CT];
-        auto fetch = [&](double (&kv)[FD][CT], int e) {
-            const int ec = e < g.d ? e : g.d - FD;             // past the end: re-read the last features (unused)
+        for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int u = 0; u < FD; ++u) {
-                const double *src = kt + (size_t)(ec + u) * Ts + j;
-                const double2v lo2 = *reinterpret_cast<const double2v *>(src);
-                kv[u][0] = lo2[0];
-                kv[u][1] = lo2[1];
-                if constexpr (CT == 4) {
-                    const double2v hi2 = *reinterpret_cast<const double2v *>(src + 2);
-                    kv[u][2] = hi2[0];
-                    kv[u][3] = hi2[1];
-                }
-            }
+            for (int y = 0; y < NG; ++y) acc[t][y] = 0.0;
+        double ka[FS][2], kb[FS][2];
+        const int steps = g.d / 4;                                   // 16 or 32
+        auto fetch = [&](double (&k)[FS][2], int s0) {
+            const int sc = s0 < steps ? s0 : 0;                      // past the end: the first features again (unused)
+#pragma unroll
+            for (int u = 0; u < FS; ++u)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) k[u][t] = src[t][(size_t)(4 * (sc + u)) * Ts];
         };
-        auto multiply = [&](const double (&kv)[FD][CT], int e) {
+        auto multiply = [&](const double (&k)[FS][2], int s0) {
 #pragma unroll
-            for (int u = 0; u < FD; ++u)
+            for (int u = 0; u < FS; ++u)
 #pragma unroll
-                for (int row = 0; row < RT; ++row) {
-                    const double q = qs[e + u][row];
+                for (int y = 0; y < NG; ++y) {
+                    const double q = qs[4 * (s0 + u) + (lane >> 4)][min(4 * y + (lane & 3), RT - 1)];
 #pragma unroll
-                    for (int c = 0; c < CT; ++c) acc[row][c] = __builtin_fma(q, kv[u][c], acc[row][c]);
+                    for (int t = 0; t < 2; ++t) acc[t][y] = __builtin_amdgcn_mfma_f64_4x4x4f64(q, k[u][t], acc[t][y], 0, 0, 0);
                 }
         };
-        fetch(kva, 0);
-        for (int e = 0; e < g.d; e += 2 * FD) {                // d is 64 or 128
-            fetch(kvb, e + FD);
+        fetch(ka, 0);
+        for (int s0 = 0; s0 < steps; s0 += 2 * FS) {
+            fetch(kb, s0 + FS);
             __builtin_amdgcn_sched_barrier(0);
-            multiply(kva, e);
+            multiply(ka, s0);
             __builtin_amdgcn_sched_barrier(0);
-            fetch(kva, e + 2 * FD);
+            fetch(ka, s0 + 2 * FS);
             __builtin_amdgcn_sched_barrier(0);
-            multiply(kvb, e + FD);
+            multiply(kb, s0 + FS);
             __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
-        for (int row = 0; row < RT; ++row)
+        for (int y = 0; y < NG; ++y) {
+            const int row = 4 * y + (lane >> 4);
 #pragma unroll
-            for (int c = 0; c < CT; ++c)
-                if (j + c < ni_all) prob[row * Tpad + j + c] = __dmul_rn(acc[row][c], g.scale64);
+            for (int t = 0; t < 2; ++t) {
+                const int col = c0 + 16 * t + (lane & 15);
+                if (row < RT && col < ni_all) prob[row * Tpad + col] = __dmul_rn(acc[t][y], g.scale64);
+            }
+        }
     }
     __syncthreads();
 
     // from here on wave w works alone on its row
     if (!active) return;
-    const int row = w;
     const int ni = allowed_cols(i, g);
-    double *pr = prob + row * Tpad;
-    const int ni64 = (ni + 63) & ~63;
+    RowProbs<REGS> row(prob + w * Tpad, ni, lane);
     double lmax = -INFINITY;
-    for (int j = lane; j < ni; j += 64) lmax = fmax(lmax, pr[j]);
+    row.each([&](int c, double &x) {
+        if (64 * c + lane >= ni) x = -INFINITY;
+        lmax = fmax(lmax, x);
+    });
     lmax = wave_max(lmax);
     double lsum = 0.0, emin = INFINITY;
-    for (int j = lane; j < ni; j += 64) {
-        const double ev = exp(pr[j] - lmax);
-        pr[j] = ev;
-        lsum += ev;
-        emin = fmin(emin, ev);
-    }
+    row.each([&](int c, double &x) {
+        if (64 * c + lane < ni) {
+            x = exp(x - lmax);
+            lsum += x;
+            emin = fmin(emin, x);
+        }
+    });
     lsum = wave_sum_dpp(lsum);
     emin = -wave_max(-emin);
-    for (int j0 = 0; j0 < ni64; j0 += 64) {
-        const int j = j0 + lane;
-        pr[j] = j < ni ? pr[j] / lsum : -1.0;                // padding never counts
-    }
+    row.each([&](int c, double &x) { x = 64 * c + lane < ni ? x / lsum : -1.0; });      // padding never counts
     const double pmax = 1.0 / lsum, pmin = emin / lsum;      // exp(0) = 1 is the largest numerator
 
     // vstar: smallest kept probability; above: mass and count of the probabilities > vstar; ties: columns at vstar
@@ -289,10 +329,10 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
     int m;                                                   // ties kept, lowest columns first
     if (!(g.tau > 0.0)) {                                    // the first cumulative sum already reaches tau
         vstar = pmax;
-        n_tie = mass_at_least(pr, ni64, lane, pmax).cnt;
+        n_tie = mass_at_least(row, pmax).cnt;
         m = 1;
     } else {
-        const MassCount all = mass_at_least(pr, ni64, lane, pmin);
+        const MassCount all = mass_at_least(row, pmin);
         if (all.mass < g.tau) {                              // never reached: everything is kept
             vstar = -0.5;
             n_above = ni;
@@ -304,7 +344,7 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
             int cnt_lo = all.cnt;
             while (hi - lo > 1 && cnt_lo - n_above > 1) {
                 const long long mid = lo + ((hi - lo) >> 1);
-                const MassCount mc = mass_at_least(pr, ni64, lane, __longlong_as_double(mid));
+                const MassCount mc = mass_at_least(row, __longlong_as_double(mid));
                 if (mc.mass >= g.tau) { lo = mid; cnt_lo = mc.cnt; }
                 else { hi = mid; n_above = mc.cnt; above = mc.mass; }
             }
@@ -312,10 +352,7 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
             if (hi - lo > 1) {                               // one element left in [lo, hi): it is vstar
                 const double hid = __longlong_as_double(hi);
                 double best = -1.0;
-                for (int j0 = 0; j0 < ni64; j0 += 64) {
-                    const double x = pr[j0 + lane];
-                    best = fmax(best, x < hid ? x : -1.0);
-                }
+                row.each([&](int, double &x) { best = fmax(best, x < hid ? x : -1.0); });
                 vstar = wave_max(best);
             } else {
                 vstar = __longlong_as_double(lo);
@@ -335,9 +372,8 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
     int32_t *crow = col_idx + orow * g.T;
     const uint64_t below = (1ull << lane) - 1ull;
     int base = 0, ties_seen = 0;
-    for (int w = 0; w < W; ++w) {
-        const int j = w * 64 + lane;
-        const double x = j < ni ? pr[j] : -1.0;
+    row.each([&](int c, double &x) {
+        const int j = 64 * c + lane;
         const uint64_t tie_word = __ballot(x == vstar);
         const int tie_rank = ties_seen + __popcll(tie_word & below);
         ties_seen += __popcll(tie_word);
@@ -346,14 +382,15 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
             on = x > vstar || (x == vstar && tie_rank < m) || j >= flo ||
                  (j == 0 && (g.flags & PBS_FLAG_FORCE_FIRST_BLOCK));
         const uint64_t word = __ballot(on);
-        if (lane == 0) mrow[w] = word;
+        if (lane == 0) mrow[c] = word;
         if (on) crow[base + __popcll(word & below)] = j;
         base += __popcll(word);
-    }
+    });
+    for (int c = row.chunks + lane; c < W; c += 64) mrow[c] = 0;     // columns past the allowed ones
     if (lane == 0) row_cnt[orow] = base;
 }
 
-template <int RB, int QB, typename E>
+template <int RB, int QB, bool REGS, typename E>
 static pbs_status launch_select_qb(const E *Qp, const double *KbarT, uint64_t *mask_bits, int32_t *row_cnt,
                                    int32_t *col_idx, const Geo &g, hipStream_t s)
 {
@@ -363,23 +400,25 @@ static pbs_status launch_select_qb(const E *Qp, const double *KbarT, uint64_t *m
     const size_t lds = (size_t)RB * QB * Tpad * sizeof(double);
     static std::atomic<unsigned long long> lds_raised{0};
     if (lds > 32 * 1024) {
-        const pbs_status st = raise_lds_limit(reinterpret_cast<const void *>(&select_kernel<RB, QB, E>),
+        const pbs_status st = raise_lds_limit(reinterpret_cast<const void *>(&select_kernel<RB, QB, REGS, E>),
                                               QB == 1 ? RB * kMaxT * (int)sizeof(double) : kPairedLds, lds_raised);
         if (st != PBS_OK) return st;
     }
-    return launch((select_kernel<RB, QB, E>), dim3((g.T + QB - 1) / QB, g.batch * g.h_kv * chunks), dim3(64 * RB * QB),
+    return launch((select_kernel<RB, QB, REGS, E>), dim3((g.T + QB - 1) / QB, g.batch * g.h_kv * chunks), dim3(64 * RB * QB),
                   lds, s, Qp, KbarT, mask_bits, row_cnt, col_idx, g, chunks, Tpad, Ts);
 }
 
-// two query blocks per workgroup while their logits fit 64 KiB of LDS (two such workgroups per compute unit)
+// two query blocks per workgroup while their logits fit 64 KiB of LDS (two such workgroups per compute unit); rows of at
+// most 1024 columns, which then always fit, in registers
 template <int RB, typename E>
 static pbs_status launch_select(const E *Qp, const double *KbarT, uint64_t *mask_bits, int32_t *row_cnt,
                                 int32_t *col_idx, const Geo &g, hipStream_t s)
 {
     const int Tpad = (g.T + 63) & ~63;
+    if (Tpad <= 64 * kRegChunks) return launch_select_qb<RB, 2, true>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
     if ((size_t)RB * 2 * Tpad * sizeof(double) <= (size_t)kPairedLds)
-        return launch_select_qb<RB, 2>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
-    return launch_select_qb<RB, 1>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
+        return launch_select_qb<RB, 2, false>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
+    return launch_select_qb<RB, 1, false>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
 }
 
 // Block means of K' into KbarT ([kv head][feature][kbar_stride(T)] fp64); also called by pbs_segment_permute for the
