@@ -17,6 +17,26 @@
 
 namespace pbs {
 
+// Sum of `rows` values `stride` apart, added in ascending order (fp32 storage); sixteen loads are in flight ahead of their
+// additions, so that a block costs a few memory latencies and not one per row.
+template <typename E>
+__device__ __forceinline__ double ordered_column_sum(const E *x, int rows, int stride)
+{
+    constexpr int U = 16;
+    double s = 0.0;
+    int r0 = 0;
+    for (; r0 + U <= rows; r0 += U) {
+        float v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = ElemTraits<E>::to_float(x[(r0 + u) * stride]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < U; ++u) s += (double)v[u];
+    }
+    for (; r0 < rows; ++r0) s += (double)ElemTraits<E>::to_float(x[r0 * stride]);
+    return s;
+}
+
 // ---------------------------------------------------------------------------------------------
 // grid = (T, heads); E = input element type.  TRANSPOSED: write out[head][e][Ts] (row stride Ts >= T) instead of
 // out[head][i][e].
@@ -39,9 +59,7 @@ __global__ __launch_bounds__(256) void pool_kernel(const E *__restrict__ X, doub
         // fp32 storage: thread e owns column e and adds its rows in ascending order
         if ((int)threadIdx.x < d) {
             const int e = threadIdx.x;
-            double s = 0.0;
-            for (int row = lo; row < hi; ++row) s += (double)ElemTraits<E>::to_float(X[(head * n + row) * (size_t)d + e]);
-            const double mean = s / (double)(hi - lo);
+            const double mean = ordered_column_sum(X + (head * n + lo) * (size_t)d + e, hi - lo, d) / (double)(hi - lo);
             if (TRANSPOSED) out[(head * d + e) * (size_t)Ts + i] = mean;
             else out[(head * T + i) * (size_t)d + e] = mean;
         }
@@ -200,9 +218,7 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
         if (active) {
             const E *X = Qp + (size_t)(bhq0 + wh) * g.n * g.d;
             for (int e = lane; e < g.d; e += 64) {
-                double s = 0.0;
-                for (int row = lo; row < hi; ++row) s += (double)ElemTraits<E>::to_float(X[(size_t)row * g.d + e]);
-                qs[e][w] = s / (double)(hi - lo);
+                qs[e][w] = ordered_column_sum(X + (size_t)lo * g.d + e, hi - lo, g.d) / (double)(hi - lo);
             }
         }
     } else {
