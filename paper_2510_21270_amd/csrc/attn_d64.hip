@@ -6,11 +6,12 @@
 // instructions per fragment (what is left out is 1/256 of the rounding of the bf16 result; measured against 64 bits the
 // error is the same 1.6e-3 as with fp32 fused multiply-adds).
 //
-// A workgroup is ONE wave with 64 queries (all of a block of 64, half a block of 128): every fragment read from LDS
-// feeds two (K') or four (V'^T) matrix instructions, and a wave that shares nothing meets no barrier.  Its K' / V'^T
-// sub-tiles of 32 keys come through a ring of two 8 KiB stages filled by asynchronous buffer->LDS loads, two sub-tiles
-// ahead; 16 KiB per wave lets eight waves, two per SIMD, share a compute unit, which is what overlaps one wave's
-// softmax with the other's products.  Bound: vector issue, 36 clocks per score (multiply-add, exp2, sum, split and
+// A workgroup owns 64 queries (all of a block of 64, half a block of 128) and every wave of it works on all 64: each
+// fragment read from LDS feeds two (K') or four (V'^T) matrix instructions.  The waves divide the key list among them in
+// pieces of 64 keys, each with a softmax and an O^T of its own, meet no barrier on the way and add up in LDS at the end.
+// A wave's K' / V'^T sub-tiles of 32 keys come through a ring of its own of two 8 KiB stages filled by asynchronous
+// buffer->LDS loads, two sub-tiles ahead; 16 KiB per wave lets eight waves, two per SIMD, share a compute unit, which is
+// what overlaps one wave's softmax with the other's products.  Bound: vector issue, 36 clocks per score (multiply-add, exp2, sum, split and
 // packs) against 24 of matrix work.  Measured, 16 / 4 heads x 12301 tokens, block 64, nine tenths of the causal blocks:
 // 609 us = 460 TFLOP/s; fp32 matrix instructions (attn_fp32.hip) take 3.71 ms for it, fp32 vector arithmetic took 22.8 ms.
 #include "pbs_host.h"
@@ -135,12 +136,15 @@ __device__ __attribute__((noinline)) void plain_rows(Row w, bf16_t *out, int qpo
 
 // grid: linear ids (x fastest, y for more than 2^20 workgroups), decoded as cohorts of `cohort` query tiles of one kv
 // head per XCD, longest lists first, as in the other attention kernels
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_d64_kernel(
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_d64_kernel(
     const bf16_t *__restrict__ Qp, const bf16_t *__restrict__ Kp, const bf16_t *__restrict__ Vt,
     const int32_t *__restrict__ qidx, const int32_t *__restrict__ kidx, const int32_t *__restrict__ row_cnt,
     const int32_t *__restrict__ col_idx, bf16_t *__restrict__ Op, float *__restrict__ lse, Geo g, int cohort)
 {
-    __shared__ Stage sg0, sg1;                             // separate variables: the compiler can tell them apart
+    __shared__ Stage ring0[WAVES], ring1[WAVES];           // separate variables: the compiler can tell them apart
+    __shared__ float sm[WAVES][kQ], sl[WAVES][kQ];
+    __shared__ int odd[WAVES];
 
     const int tiles = ceil_div(g.n, kQ);
     const int rows_per_unit = g.r * tiles;
@@ -158,8 +162,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     const int i = w.q0 / g.block;
     const int b = unit / g.h_kv, hq = (unit % g.h_kv) * g.r + mrow % g.r;
     const size_t bhq = (size_t)b * g.h_q + hq, bhk = unit;
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    const int wave = WAVES == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ln = lane & 31, lh = lane >> 5;
+    Stage &sg0 = ring0[wave], &sg1 = ring1[wave];
     const float c2 = g.scale * kLog2eF;
     w.n = g.n;
     w.block = g.block;
@@ -219,14 +225,15 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (lptr_t)(sg.v + c * 1024), 16, voff, slot0 * (D * 2) + c * 1024, 0, 0);
     };
 
-    // the list as pairs of sub-tiles: the first slot of the next admitted 64 keys, -1 past the end
+    // the list as pairs of sub-tiles, this wave's are every WAVES-th: the first slot of its next admitted 64 keys, -1 past
+    // the end
     const int halves = g.block / 64, total = w.cnt * halves;
-    int u_next = 0;
+    int u_next = wave;
     auto next_slot = [&]() -> int {
         while (u_next < total) {
             const int j = __builtin_amdgcn_readfirstlane(w.cols[u_next / halves]);
             const int part = u_next % halves;
-            ++u_next;
+            u_next += WAVES;
             if (j >= 0 && j < w.ni) return j * g.block + 64 * part;
         }
         return -1;
@@ -332,27 +339,85 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 
     float lt[2];
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-        lt[nt] = st.l[nt] + __shfl_xor(st.l[nt], 32, 64);
-        const float inv = lt[nt] > 0.0f ? 1.0f / lt[nt] : 0.0f;
-        const int qs = w.q0 + 32 * nt + ln;
-        if (qs < g.n) {
-            bf16_t *dst = Op + (bhq * g.n + qs) * D;
+    for (int nt = 0; nt < 2; ++nt) lt[nt] = st.l[nt] + __shfl_xor(st.l[nt], 32, 64);
+    if constexpr (WAVES == 1) {
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) {
+            const float inv = lt[nt] > 0.0f ? 1.0f / lt[nt] : 0.0f;
+            const int qs = w.q0 + 32 * nt + ln;
+            if (qs < g.n) {
+                bf16_t *dst = Op + (bhq * g.n + qs) * D;
+#pragma unroll
+                for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) {
+                        const floatx2 a = {st.acc[dt][nt][4 * x] * inv, st.acc[dt][nt][4 * x + 1] * inv};
+                        const floatx2 c = {st.acc[dt][nt][4 * x + 2] * inv, st.acc[dt][nt][4 * x + 3] * inv};
+                        const bf16x2 pa = __builtin_convertvector(a, bf16x2), pc = __builtin_convertvector(c, bf16x2);
+                        *reinterpret_cast<bf16x4 *>(dst + 32 * dt + 8 * x + 4 * lh) = bf16x4{pa[0], pa[1], pc[0], pc[1]};
+                    }
+                if (lse && lh == 0)
+                    lse[bhq * g.n + qs] = lt[nt] > 0.0f ? (st.mref[nt] + log2f(lt[nt])) * kLn2F : -INFINITY;
+            }
+        }
+        if (__any(odd_values))                             // lane = query from here on
+            plain_rows(w, Op + bhq * g.n * D, lh ? qpos[1] : qpos[0], lh ? st.mref[1] : st.mref[0], lh ? lt[1] : lt[0], c2);
+    } else {
+        // every wave leaves its O^T in its own ring, [feature][query], and its (m, l)
+        float *part[2] = {reinterpret_cast<float *>(&sg0), reinterpret_cast<float *>(&sg1)};
+        static_assert(sizeof(Stage) == 32 * kQ * sizeof(float), "half of the features of 64 queries");
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) {
+            if (lh == 0) {
+                sm[wave][32 * nt + ln] = st.seen[nt] && qpos[nt] >= 0 ? st.mref[nt] : -INFINITY;
+                sl[wave][32 * nt + ln] = lt[nt];
+            }
 #pragma unroll
             for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-                for (int x = 0; x < 4; ++x) {
-                    const floatx2 a = {st.acc[dt][nt][4 * x] * inv, st.acc[dt][nt][4 * x + 1] * inv};
-                    const floatx2 c = {st.acc[dt][nt][4 * x + 2] * inv, st.acc[dt][nt][4 * x + 3] * inv};
-                    const bf16x2 pa = __builtin_convertvector(a, bf16x2), pc = __builtin_convertvector(c, bf16x2);
-                    *reinterpret_cast<bf16x4 *>(dst + 32 * dt + 8 * x + 4 * lh) = bf16x4{pa[0], pa[1], pc[0], pc[1]};
-                }
-            if (lse && lh == 0)
-                lse[bhq * g.n + qs] = lt[nt] > 0.0f ? (st.mref[nt] + log2f(lt[nt])) * kLn2F : -INFINITY;
+                for (int x = 0; x < 16; ++x)
+                    part[dt][(8 * (x >> 2) + 4 * lh + (x & 3)) * kQ + 32 * nt + ln] = st.acc[dt][nt][x];
+        }
+        const bool odd_here = __any(odd_values);
+        if (lane == 0) odd[wave] = odd_here;
+        __syncthreads();
+        // thread (query, part of the features)
+        constexpr int F = D / WAVES;
+        const int q = lane, qs = w.q0 + q, f0 = wave * F;
+        float m = -INFINITY, l = 0.0f, scale[WAVES];
+#pragma unroll
+        for (int v = 0; v < WAVES; ++v) m = fmaxf(m, sm[v][q]);
+#pragma unroll
+        for (int v = 0; v < WAVES; ++v) {
+            scale[v] = sm[v][q] == m ? 1.0f : __builtin_amdgcn_exp2f(sm[v][q] - m);
+            l += sl[v][q] * scale[v];
+        }
+        const float inv = l > 0.0f ? 1.0f / l : 0.0f;
+        const Stage *ring = f0 < 32 ? ring0 : ring1;
+        bf16x8 out[F / 8];
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+            float o = 0.0f;
+#pragma unroll
+            for (int v = 0; v < WAVES; ++v)
+                o += reinterpret_cast<const float *>(&ring[v])[((f0 & 31) + f) * kQ + q] * scale[v];
+            out[f >> 3][f & 7] = (bf16_t)(o * inv);
+        }
+        if (qs < g.n) {
+#pragma unroll
+            for (int f = 0; f < F / 8; ++f) *reinterpret_cast<bf16x8 *>(Op + (bhq * g.n + qs) * D + f0 + 8 * f) = out[f];
+            if (lse && wave == 0) lse[bhq * g.n + qs] = l > 0.0f ? (m + log2f(l)) * kLn2F : -INFINITY;
+        }
+        int odd_any = 0;
+#pragma unroll
+        for (int v = 0; v < WAVES; ++v) odd_any |= odd[v];
+        if (odd_any) {
+            __syncthreads();                               // behind the stores of the other waves
+            if (wave == 0)
+                plain_rows(w, Op + bhq * g.n * D, qs < g.n ? (qidx ? qidx[bhq * g.n + qs] : qs) : -1,
+                           m == -INFINITY ? 0.0f : m, l, c2);
         }
     }
-    if (__any(odd_values))                                 // lane = query from here on
-        plain_rows(w, Op + bhq * g.n * D, lh ? qpos[1] : qpos[0], lh ? st.mref[1] : st.mref[0], lh ? lt[1] : lt[0], c2);
 }
 
 }  // namespace d64
@@ -368,8 +433,14 @@ pbs_status launch_attn_d64(const Geo &g, const void *Qp, const void *Kp, const v
     const long long wgs = (ncoh + d64::kXcds - 1) / d64::kXcds * d64::kXcds * cohort;
     constexpr long long kMaxX = 1 << 20;
     const dim3 grid((unsigned)(wgs < kMaxX ? wgs : kMaxX), (unsigned)((wgs + kMaxX - 1) / kMaxX));
-    return launch(d64::attn_d64_kernel, grid, dim3(64), 0, s, (const bf16_t *)Qp, (const bf16_t *)Kp, (const bf16_t *)Vt,
-                  qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse, g, cohort);
+    // The chip holds 2048 of these waves, and under the causal mask the last query tile has twice the average list: with
+    // few tiles per wave slot that one list is what everything waits for, so its tiles are shared by four waves until
+    // there are about eight tiles per slot.
+    if (units * rows < 8 * 2048)
+        return launch(d64::attn_d64_kernel<4>, grid, dim3(256), 0, s, (const bf16_t *)Qp, (const bf16_t *)Kp,
+                      (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse, g, cohort);
+    return launch(d64::attn_d64_kernel<1>, grid, dim3(64), 0, s, (const bf16_t *)Qp, (const bf16_t *)Kp,
+                  (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse, g, cohort);
 }
 
 }  // namespace pbs

@@ -40,17 +40,18 @@ def test_fp32_attention_over_given_lists(oracle, dtype, d, block, Hq, Hkv, n):
     np.testing.assert_allclose(lse[fin], want_lse[fin], atol=1e-4, rtol=0)
 
 
-# ... and the d = 64 kernel, 64 queries to a wave: short of a wave, one past it, ragged blocks, a T of its own
-@pytest.mark.parametrize("n", [1, 65, 190, 900])
-@pytest.mark.parametrize("block,Hq,Hkv", [(64, 4, 2), (128, 3, 1), (64, 7, 7)])
-def test_d64_attention_over_given_lists(oracle, block, Hq, Hkv, n):
+# ... and the d = 64 kernel, 64 queries to a tile: short of one, one past it, ragged blocks, a T of its own; four waves
+# share a list (all of them, or fewer entries than waves) up to 16384 tiles, one wave has it to itself from there on
+@pytest.mark.parametrize("block,Hq,Hkv,n,rho", [(b, hq, hkv, n, 0.5) for b, hq, hkv in [(64, 4, 2), (128, 3, 1), (64, 7, 7)]
+                                                for n in (1, 65, 190, 900)] + [(64, 64, 2, 16410, 0.02)])
+def test_d64_attention_over_given_lists(oracle, block, Hq, Hkv, n, rho):
     Q, K, V = _qkv(n + block, Hq, Hkv, n, 64, "bf16")
     Q[0, :, n // 2:] *= 8.0                                # scores that outgrow the first reference
     T, seg = -(-n // block), 2 * block
     kidx = wl.random_segment_perm(3, Hkv, n, seg).reshape(1, Hkv, n)
     qidx = wl.random_segment_perm(4, Hq, n, seg).reshape(1, Hq, n)
     Qp, Kp, Vp = oracle.gather_rows(Q, qidx), oracle.gather_rows(K, kidx), oracle.gather_rows(V, kidx)
-    cnt, cols = wl.random_block_lists(5, 1, Hq, T, 0.5)
+    cnt, cols = wl.random_block_lists(5, 1, Hq, T, rho)
     p = pbs.problem(1, Hq, Hkv, n, 64, block, seg, "bf16")
     want, want_lse = oracle.attn_fwd(Qp, Kp, Vp, qidx, kidx, cnt, cols, block, want_lse=True)
     got, lse = pbs.attn_fwd(p, to_dev(Qp, "bf16"), to_dev(Kp, "bf16"), to_dev(vt_layout(Vp, block), "bf16"),
