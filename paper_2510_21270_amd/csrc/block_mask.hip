@@ -123,31 +123,28 @@ struct MassCount {
     int cnt;
 };
 
-// One row, 64 columns per chunk, lane = column.  REGS: up to kRegChunks chunks in registers (loaded once), else in LDS.
+// One row, 64 columns per chunk, lane = column.  NC > 0: up to NC chunks in registers (loaded once), 0: in LDS.
 // Columns past the row's own count are padded by the caller.
-constexpr int kRegChunks = 16;
-template <bool REGS>
-struct RowProbs;
-template <>
-struct RowProbs<true> {
-    double x[kRegChunks];
+template <int NC>
+struct RowProbs {
+    double x[NC];
     int chunks;
     __device__ __forceinline__ RowProbs(double *pr, int ni, int lane) : chunks((ni + 63) >> 6)
     {
 #pragma unroll
-        for (int c = 0; c < kRegChunks; ++c)
+        for (int c = 0; c < NC; ++c)
             if (c < chunks) x[c] = pr[64 * c + lane];
     }
     template <typename F>
     __device__ __forceinline__ void each(F f)              // f(chunk, value), in ascending order
     {
 #pragma unroll
-        for (int c = 0; c < kRegChunks; ++c)
+        for (int c = 0; c < NC; ++c)
             if (c < chunks) f(c, x[c]);
     }
 };
 template <>
-struct RowProbs<false> {
+struct RowProbs<0> {
     double *pr;
     int chunks;
     __device__ __forceinline__ RowProbs(double *row, int ni, int lane) : pr(row + lane), chunks((ni + 63) >> 6) {}
@@ -163,8 +160,8 @@ struct RowProbs<false> {
 };
 
 // mass and number of the row's probabilities >= v (padding is negative)
-template <bool REGS>
-__device__ __forceinline__ MassCount mass_at_least(RowProbs<REGS> &row, double v)
+template <int NC>
+__device__ __forceinline__ MassCount mass_at_least(RowProbs<NC> &row, double v)
 {
     double acc = 0.0;
     int cnt = 0;
@@ -182,8 +179,9 @@ __device__ __forceinline__ MassCount mass_at_least(RowProbs<REGS> &row, double v
 // Query blocks are taken from the last one down: the long rows start first, the short ones fill the tail.
 constexpr int kPairedLds = 64 * 1024;
 
-template <int RB, int QB, bool REGS, typename E>
-__global__ __launch_bounds__(64 * RB * QB) __attribute__((amdgpu_waves_per_eu(1, 4)))
+// Rows of at most 512 columns (NC = 8) leave room for eight waves per SIMD, which hide more of each other's phases.
+template <int RB, int QB, int NC, typename E>
+__global__ __launch_bounds__(64 * RB * QB) __attribute__((amdgpu_waves_per_eu(NC == 8 ? 8 : 4, NC == 8 ? 8 : 4)))
 void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
                    const double *__restrict__ KbarT,   // [bhkv][d][Ts]
                    uint64_t *__restrict__ mask_bits, int32_t *__restrict__ row_cnt, int32_t *__restrict__ col_idx,
@@ -191,7 +189,7 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
 {
     constexpr int RT = RB * QB;                                      // rows (= waves) of the workgroup
     constexpr int NG = (RT + 3) / 4;                                 // groups of four rows
-    constexpr int FS = 8;                                            // steps of four features per register buffer
+    constexpr int FS = NC == 8 ? 4 : 8;                              // steps of four features per register buffer
     extern __shared__ __align__(16) unsigned char smem_raw[];
     double *prob = reinterpret_cast<double *>(smem_raw);             // [RT][Tpad]
     __shared__ __align__(16) double qs[128][RT];                     // block means of the RT query rows, feature-major
@@ -201,8 +199,8 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
     const int b = bhk / g.h_kv, hk = bhk % g.h_kv;
     const int rows = min(RB, g.r - chunk * RB);                      // query heads handled here
     const int bhq0 = b * g.h_q + hk * g.r + chunk * RB;
-    const int tid = threadIdx.x;
-    const int w = tid >> 6, lane = tid & 63;
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wq = w / RB, wh = w % RB;                              // this wave's query block (i0 + wq) and head
     const int i = i0 + wq;
     const bool active = i < g.T && wh < rows;
@@ -210,7 +208,7 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
     const int ni_all = allowed_cols(i0 + nblk - 1, g);               // the last one sees the most columns
 
     // Block mean of query block i of head wh, by wave w (sums of storage values in fp64; 16-byte column groups,
-    // sixteen loads in flight per lane, then the row groups of the wave are added up).  Pooling Q' here instead of in
+    // U loads in flight per lane, then the row groups of the wave are added up).  Pooling Q' here instead of in
     // a kernel of its own lets the 1 GiB read of Q' overlap with the arithmetic of other workgroups.
     // fp32 storage: every lane owns columns and adds their rows in ascending order (see the note at the top).
     if constexpr (sizeof(E) == 4) {
@@ -232,23 +230,30 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
 #pragma unroll
         for (int u = 0; u < VEC; ++u) acc[u] = 0.0;
         if (active) {
-            // (a block of 128 rows of 256 bytes is two rounds): the read of Q' is the one large HBM stream of this
-            // kernel and a workgroup does nothing else while it waits for it
-            constexpr int U = 16;
-            const E *X = Qp + (size_t)(bhq0 + wh) * g.n * g.d + cg * VEC;
-            for (int r0 = lo + rg; r0 < hi; r0 += U * RG) {
-                vec_t v[U];
+            // A register is requested again as soon as it is added up, so that the additions (a conversion and an fp64
+            // addition per value) run under the loads of the others.  Buffer loads: rows past the block lie past
+            // the descriptor's end and read as zeros, without a branch per load.
+            constexpr int U = NC == 8 ? 4 : 8, kNonTemporal = 2;
+            const int row_bytes = g.d * (int)sizeof(E);
+            const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<E *>(Qp + ((size_t)(bhq0 + wh) * g.n + lo) * g.d), 0, (hi - lo) * row_bytes, 0x00020000);
+            const int voff = lane * 16;                              // row rg, column group cg of a piece of 1 KiB = RG rows
+            static_assert(VEC * sizeof(E) == 16, "one load of 16 bytes per lane");
+            const int pieces = (g.block + RG - 1) / RG;
+            vec_t v[U];
+#pragma unroll
+            for (int q = 0; q < U; ++q)
+                v[q] = __builtin_bit_cast(vec_t, __builtin_amdgcn_raw_buffer_load_b128(r, voff, q * 1024, kNonTemporal));
+            __builtin_amdgcn_sched_barrier(0);
+            for (int q0 = 0; q0 < pieces; q0 += U)
 #pragma unroll
                 for (int q = 0; q < U; ++q) {
-                    v[q] = vec_t{};
-                    if (r0 + q * RG < hi) v[q] = __builtin_nontemporal_load(reinterpret_cast<const vec_t *>(X + (size_t)(r0 + q * RG) * g.d));
+#pragma unroll
+                    for (int u = 0; u < VEC; ++u) acc[u] += (double)ElemTraits<E>::to_float(v[q][u]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    v[q] = __builtin_bit_cast(vec_t, __builtin_amdgcn_raw_buffer_load_b128(r, voff, (q0 + U + q) * 1024, kNonTemporal));
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-#pragma unroll
-                for (int q = 0; q < U; ++q)
-                    if (r0 + q * RG < hi)
-#pragma unroll
-                        for (int u = 0; u < VEC; ++u) acc[u] += (double)ElemTraits<E>::to_float(v[q][u]);
-            }
         }
         for (int o = cpr; o < 64; o <<= 1)
 #pragma unroll
@@ -319,7 +324,7 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
     // from here on wave w works alone on its row
     if (!active) return;
     const int ni = allowed_cols(i, g);
-    RowProbs<REGS> row(prob + w * Tpad, ni, lane);
+    RowProbs<NC> row(prob + w * Tpad, ni, lane);
     double lmax = -INFINITY;
     row.each([&](int c, double &x) {
         if (64 * c + lane >= ni) x = -INFINITY;
@@ -406,7 +411,7 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
     if (lane == 0) row_cnt[orow] = base;
 }
 
-template <int RB, int QB, bool REGS, typename E>
+template <int RB, int QB, int NC, typename E>
 static pbs_status launch_select_qb(const E *Qp, const double *KbarT, uint64_t *mask_bits, int32_t *row_cnt,
                                    int32_t *col_idx, const Geo &g, hipStream_t s)
 {
@@ -416,11 +421,11 @@ static pbs_status launch_select_qb(const E *Qp, const double *KbarT, uint64_t *m
     const size_t lds = (size_t)RB * QB * Tpad * sizeof(double);
     static std::atomic<unsigned long long> lds_raised{0};
     if (lds > 32 * 1024) {
-        const pbs_status st = raise_lds_limit(reinterpret_cast<const void *>(&select_kernel<RB, QB, REGS, E>),
+        const pbs_status st = raise_lds_limit(reinterpret_cast<const void *>(&select_kernel<RB, QB, NC, E>),
                                               QB == 1 ? RB * kMaxT * (int)sizeof(double) : kPairedLds, lds_raised);
         if (st != PBS_OK) return st;
     }
-    return launch((select_kernel<RB, QB, REGS, E>), dim3((g.T + QB - 1) / QB, g.batch * g.h_kv * chunks), dim3(64 * RB * QB),
+    return launch((select_kernel<RB, QB, NC, E>), dim3((g.T + QB - 1) / QB, g.batch * g.h_kv * chunks), dim3(64 * RB * QB),
                   lds, s, Qp, KbarT, mask_bits, row_cnt, col_idx, g, chunks, Tpad, Ts);
 }
 
@@ -431,10 +436,11 @@ static pbs_status launch_select(const E *Qp, const double *KbarT, uint64_t *mask
                                 int32_t *col_idx, const Geo &g, hipStream_t s)
 {
     const int Tpad = (g.T + 63) & ~63;
-    if (Tpad <= 64 * kRegChunks) return launch_select_qb<RB, 2, true>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
+    if (Tpad <= 512) return launch_select_qb<RB, 2, 8>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
+    if (Tpad <= 1024) return launch_select_qb<RB, 2, 16>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
     if ((size_t)RB * 2 * Tpad * sizeof(double) <= (size_t)kPairedLds)
-        return launch_select_qb<RB, 2, false>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
-    return launch_select_qb<RB, 1, false>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
+        return launch_select_qb<RB, 2, 0>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
+    return launch_select_qb<RB, 1, 0>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
 }
 
 // Block means of K' into KbarT ([kv head][feature][kbar_stride(T)] fp64); also called by pbs_segment_permute for the
