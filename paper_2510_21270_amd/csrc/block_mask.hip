@@ -13,6 +13,8 @@
 //   2. select_kernel   block means of its own Q' blocks, then logits of up to four query heads of one group against
 //                      the allowed columns, softmax, the mass threshold by bisection (one wave per row), forced
 //                      blocks, then bit-mask words by wave ballot and the ascending column list by prefix popcount.
+#include <type_traits>
+
 #include "pbs_host.h"
 
 namespace pbs {
@@ -107,9 +109,10 @@ __global__ __launch_bounds__(256) void pool_kernel(const E *__restrict__ X, doub
 // and finishes it alone (no workgroup barriers): softmax, then the smallest probability v* that is still kept, found by
 // bisection instead of a sort, with the row in registers where it has at most 1024 columns.
 // Bound: vector issue (pooling Q': a conversion and an fp64 addition per value, 3 us of a wave's time per block; the
-// bisection about as much), 4 waves per SIMD.  Measured, same masks bit for bit, against logits on v_fma_f64 with every
-// multiply-add's query operand read from LDS: 28 / 4 heads x 65536 179 -> 158 us, 32 / 8 heads x 2048 25.5 -> 18.4 us,
-// x 8147 31.9 -> 24.1 us, x 131072 443 -> 437 us.
+// bisection about as much) and the phases' latencies, which only other waves of the SIMD hide.  Measured, same masks bit
+// for bit, against logits on v_fma_f64 with every multiply-add's query operand read from LDS and two workgroups to a
+// compute unit: 28 / 4 heads x 65536 179 -> 134 us, 32 / 8 heads x 2048 25.5 -> 15.9 us, x 8147 31.9 -> 22.4 us,
+// x 131072 443 -> 386 us.
 //
 // The kept set of Algorithm 2 is the shortest prefix of the order (probability descending, column ascending)
 // whose mass reaches tau.  With M(v) = sum of the probabilities >= v, v* is the largest v with M(v) >= tau:
@@ -125,15 +128,19 @@ struct MassCount {
 
 // One row, 64 columns per chunk, lane = column.  NC > 0: up to NC chunks in registers (loaded once), 0: in LDS.
 // Columns past the row's own count are padded by the caller.
+constexpr int kPanel = 512;                                // columns whose logits go through LDS at a time where NC > 0
 template <int NC>
 struct RowProbs {
     double x[NC];
     int chunks;
-    __device__ __forceinline__ RowProbs(double *pr, int ni, int lane) : chunks((ni + 63) >> 6)
+    __device__ __forceinline__ RowProbs(double *, int ni, int) : chunks((ni + 63) >> 6) {}
+    // the chunks of panel p (kPanel columns, compile-time p) from the panel's row in LDS
+    template <int P>
+    __device__ __forceinline__ void take(const double *pr, int lane)
     {
 #pragma unroll
-        for (int c = 0; c < NC; ++c)
-            if (c < chunks) x[c] = pr[64 * c + lane];
+        for (int c = 0; c < kPanel / 64; ++c)
+            if (P * (kPanel / 64) + c < chunks) x[P * (kPanel / 64) + c] = pr[64 * c + lane];
     }
     template <typename F>
     __device__ __forceinline__ void each(F f)              // f(chunk, value), in ascending order
@@ -179,9 +186,10 @@ __device__ __forceinline__ MassCount mass_at_least(RowProbs<NC> &row, double v)
 // Query blocks are taken from the last one down: the long rows start first, the short ones fill the tail.
 constexpr int kPairedLds = 64 * 1024;
 
-// Rows of at most 512 columns (NC = 8) leave room for eight waves per SIMD, which hide more of each other's phases.
+// Rows of at most 512 columns (NC = 8) leave room for eight waves per SIMD, rows of at most 1024 for six; they hide more
+// of each other's phases.
 template <int RB, int QB, int NC, typename E>
-__global__ __launch_bounds__(64 * RB * QB) __attribute__((amdgpu_waves_per_eu(NC == 8 ? 8 : 4, NC == 8 ? 8 : 4)))
+__global__ __launch_bounds__(64 * RB * QB) __attribute__((amdgpu_waves_per_eu(NC == 8 ? 8 : NC == 16 ? 6 : 4, NC == 8 ? 8 : NC == 16 ? 6 : 4)))
 void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
                    const double *__restrict__ KbarT,   // [bhkv][d][Ts]
                    uint64_t *__restrict__ mask_bits, int32_t *__restrict__ row_cnt, int32_t *__restrict__ col_idx,
@@ -189,7 +197,7 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
 {
     constexpr int RT = RB * QB;                                      // rows (= waves) of the workgroup
     constexpr int NG = (RT + 3) / 4;                                 // groups of four rows
-    constexpr int FS = NC == 8 ? 4 : 8;                              // steps of four features per register buffer
+    constexpr int FS = NC > 0 ? 4 : 8;                               // steps of four features per register buffer
     extern __shared__ __align__(16) unsigned char smem_raw[];
     double *prob = reinterpret_cast<double *>(smem_raw);             // [RT][Tpad]
     __shared__ __align__(16) double qs[128][RT];                     // block means of the RT query rows, feature-major
@@ -233,7 +241,7 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
             // A register is requested again as soon as it is added up, so that the additions (a conversion and an fp64
             // addition per value) run under the loads of the others.  Buffer loads: rows past the block lie past
             // the descriptor's end and read as zeros, without a branch per load.
-            constexpr int U = NC == 8 ? 4 : 8, kNonTemporal = 2;
+            constexpr int U = NC > 0 ? 4 : 8, kNonTemporal = 2;
             const int row_bytes = g.d * (int)sizeof(E);
             const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
                 const_cast<E *>(Qp + ((size_t)(bhq0 + wh) * g.n + lo) * g.d), 0, (hi - lo) * row_bytes, 0x00020000);
@@ -270,7 +278,8 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
     // alternately: the loads of one are in flight while the other is multiplied (scheduling barriers keep the compiler
     // from moving a buffer's loads down to its use).
     const double *kt = KbarT + (size_t)bhk * g.d * Ts;
-    for (int c0 = 32 * w; c0 < ni_all; c0 += 32 * RT) {
+    auto logits = [&](int first, int end, int stride) {              // columns first .. end - 1 into prob rows of `stride`
+      for (int c0 = first + 32 * w; c0 < end; c0 += 32 * RT) {
         const double *src[2];
 #pragma unroll
         for (int t = 0; t < 2; ++t) src[t] = kt + (size_t)(lane >> 4) * Ts + min(c0 + 16 * t + (lane & 15), Ts - 1);
@@ -315,16 +324,34 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
                 const int col = c0 + 16 * t + (lane & 15);
-                if (row < RT && col < ni_all) prob[row * Tpad + col] = __dmul_rn(acc[t][y], g.scale64);
+                if (row < RT && col < end) prob[row * stride + col - first] = __dmul_rn(acc[t][y], g.scale64);
             }
         }
+      }
+    };
+    // Where the row is to sit in registers, it gets there in panels of kPanel columns, so that LDS holds one panel.
+    const int ni = allowed_cols(active ? i : i0, g);
+    RowProbs<NC> row(prob + w * Tpad, ni, lane);
+    if constexpr (NC == 0) {
+        logits(0, ni_all, Tpad);
+        __syncthreads();
+    } else {
+        const int stride = min(Tpad, kPanel);
+        auto panel = [&](auto p_) {
+            constexpr int P = decltype(p_)::value;
+            if (P * kPanel >= ni_all) return;                        // uniform over the workgroup
+            if (P > 0) __syncthreads();                              // the panel before is in registers everywhere
+            logits(P * kPanel, min(ni_all, (P + 1) * kPanel), stride);
+            __syncthreads();
+            row.template take<P>(prob + w * stride, lane);
+        };
+        panel(std::integral_constant<int, 0>{});
+        if constexpr (NC * 64 > kPanel) panel(std::integral_constant<int, 1>{});
+        static_assert(NC * 64 <= 2 * kPanel, "two panels");
     }
-    __syncthreads();
 
     // from here on wave w works alone on its row
     if (!active) return;
-    const int ni = allowed_cols(i, g);
-    RowProbs<NC> row(prob + w * Tpad, ni, lane);
     double lmax = -INFINITY;
     row.each([&](int c, double &x) {
         if (64 * c + lane >= ni) x = -INFINITY;
@@ -418,7 +445,7 @@ static pbs_status launch_select_qb(const E *Qp, const double *KbarT, uint64_t *m
     const int chunks = (g.r + RB - 1) / RB;
     const int Tpad = (g.T + 63) & ~63;
     const int Ts = kbar_stride(g.T);
-    const size_t lds = (size_t)RB * QB * Tpad * sizeof(double);
+    const size_t lds = (size_t)RB * QB * (NC > 0 && Tpad > kPanel ? kPanel : Tpad) * sizeof(double);
     static std::atomic<unsigned long long> lds_raised{0};
     if (lds > 32 * 1024) {
         const pbs_status st = raise_lds_limit(reinterpret_cast<const void *>(&select_kernel<RB, QB, NC, E>),
