@@ -251,18 +251,17 @@ __global__ __launch_bounds__(256) void move_rows_kernel(const uintx4 *__restrict
 // remapping: the attention kernel gathers the rows itself and no K' is written).
 // ---------------------------------------------------------------------------------------------
 template <bool TWICE>
-__global__ __launch_bounds__(256) void gather_pool_kernel(const uintx4 *__restrict__ src,
-                                                          const int32_t *__restrict__ idx, uintx4 *__restrict__ dst,
-                                                          int n, int cpr_log2, size_t copy_stride,
-                                                          double *__restrict__ kbarT, int block, int Ts)
+__device__ __forceinline__ void gather_pool(const uintx4 *__restrict__ src, const int32_t *__restrict__ idx,
+                                            uintx4 *__restrict__ dst, int n, int cpr_log2, size_t copy_stride,
+                                            double *__restrict__ kbarT, int block, int Ts, uint32_t bx, uint32_t gx,
+                                            double *red /* 256 * 8, LDS */)
 {
     constexpr int U = 4;
-    __shared__ double red[256 * 8];
     const size_t head = (size_t)blockIdx.y * n;
     const uint32_t chunks = (uint32_t)n << cpr_log2;
     const uint32_t cpr = 1u << cpr_log2, cmask = cpr - 1u;
-    const bool plain = copy_stride != 0 && (blockIdx.x & 1);
-    const uint32_t wg = copy_stride ? blockIdx.x >> 1 : blockIdx.x, nwg = copy_stride ? gridDim.x >> 1 : gridDim.x;
+    const bool plain = copy_stride != 0 && (bx & 1);
+    const uint32_t wg = copy_stride ? bx >> 1 : bx, nwg = copy_stride ? gx >> 1 : gx;
     const uintx4 *hsrc = src + (head << cpr_log2);
     uintx4 *hdst = dst + (head << cpr_log2) + (plain ? copy_stride : 0);
     const int32_t *hidx = (idx && !plain) ? idx + head : nullptr;
@@ -337,16 +336,14 @@ __global__ __launch_bounds__(256) void gather_pool_kernel(const uintx4 *__restri
 // copy_stride > 0: the grid is twice as wide; odd workgroups transpose the same key block without the permutation
 // into the copy copy_stride elements behind Vt (see move_rows_kernel).
 template <typename E, bool TWICE>
-__global__ __launch_bounds__(256) void gather_vt_kernel(const E *__restrict__ V, const int32_t *__restrict__ kidx,
-                                                        E *__restrict__ Vt, int n, int d, int block, int T,
-                                                        size_t copy_stride)
+__device__ __forceinline__ void gather_vt(const E *__restrict__ V, const int32_t *__restrict__ kidx, E *__restrict__ Vt,
+                                          int n, int d, int block, int T, size_t copy_stride, uint32_t bx,
+                                          uint32_t *tile /* LDS */)
 {
     constexpr int VEC = 16 / sizeof(E);
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    uint32_t *tile = reinterpret_cast<uint32_t *>(smem_raw);
     const int roww = d * (int)sizeof(E) / 4;               // 4-byte words per row
-    const bool plain = copy_stride != 0 && (blockIdx.x & 1);
-    const int j = copy_stride ? blockIdx.x >> 1 : blockIdx.x;
+    const bool plain = copy_stride != 0 && (bx & 1);
+    const int j = copy_stride ? bx >> 1 : bx;
     const size_t bh = blockIdx.y;
     if (plain) kidx = nullptr;
     const int cpr = d / VEC;
@@ -405,6 +402,34 @@ __global__ __launch_bounds__(256) void gather_vt_kernel(const E *__restrict__ V,
             __builtin_nontemporal_store(hi, reinterpret_cast<uintx4 *>(og + (size_t)(2 * w + 1) * G));
         }
     }
+}
+
+template <typename E, bool TWICE>
+__global__ __launch_bounds__(256) void gather_vt_kernel(const E *__restrict__ V, const int32_t *__restrict__ kidx,
+                                                        E *__restrict__ Vt, int n, int d, int block, int T,
+                                                        size_t copy_stride)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    gather_vt<E, TWICE>(V, kidx, Vt, n, d, block, T, copy_stride, blockIdx.x, reinterpret_cast<uint32_t *>(smem_raw));
+}
+
+// Both gathers of a head in one launch: workgroups 0 .. kwgs - 1 move K rows, the rest key blocks of V.  They do not
+// depend on each other, and a launch of its own costs each of them its ramp and its tail.
+// LDS (dynamic): what either of the two needs.
+template <bool TWICE>
+__global__ __launch_bounds__(256) void gather_both_kernel(const uintx4 *__restrict__ K, const uint16_t *__restrict__ V,
+                                                          const int32_t *__restrict__ kidx, uintx4 *__restrict__ Kp,
+                                                          uint16_t *__restrict__ Vt, int n, int d, int cpr_log2,
+                                                          size_t kcopy, size_t vcopy, double *__restrict__ kbarT,
+                                                          int block, int T, int Ts, uint32_t kwgs)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    if (blockIdx.x < kwgs)
+        gather_pool<TWICE>(K, kidx, Kp, n, cpr_log2, kcopy, kbarT, block, Ts, blockIdx.x, kwgs,
+                           reinterpret_cast<double *>(smem_raw));
+    else
+        gather_vt<uint16_t, TWICE>(V, kidx, Vt, n, d, block, T, vcopy, blockIdx.x - kwgs,
+                                   reinterpret_cast<uint32_t *>(smem_raw));
 }
 
 static int ilog2(int v) { int l = 0; while ((1 << l) < v) ++l; return l; }
@@ -489,33 +514,38 @@ extern "C" pbs_status pbs_segment_permute(const pbs_problem *p, const float *sco
     if (remap && kbarT && !pool_on_the_way) return PBS_ERR_UNSUPPORTED;   // means without K' only from the gather kernel
     const size_t kcopy = token_copy ? tok_rows * cpr : (size_t)0;
     const int Tsk = kbar_stride(g.T), cl = ilog2(cpr);
-    if (pool_on_the_way)
-        st = token_copy ? launch(gather_pool_kernel<true>, mg, dim3(256), 0, s, (const uintx4 *)K, (const int32_t *)kidx,
-                                 (uintx4 *)kdst, g.n, cl, kcopy, kbarT, g.block, Tsk)
-                        : launch(gather_pool_kernel<false>, mg, dim3(256), 0, s, (const uintx4 *)K, (const int32_t *)kidx,
-                                 (uintx4 *)kdst, g.n, cl, kcopy, kbarT, g.block, Tsk);
-    else if (kdst)
+    const dim3 vg(token_copy ? 2 * g.T : g.T, nbh);
+    const size_t vcopy = token_copy ? vt_half : (size_t)0;
+    const size_t vlds = p->dtype == PBS_BF16                              // tile + skew
+                            ? (size_t)g.block * g.d * 2 + (size_t)(g.block / 8) * (64 / (vt_group(g.block) / 8)) * 4
+                            : (size_t)g.block * g.d * 4 + (size_t)(g.block / 4) * (64 / (vt_group(g.block) / 4)) * 4;
+    if (pool_on_the_way) {
+        const size_t pool_lds = 256 * 8 * sizeof(double), lds = vlds > pool_lds ? vlds : pool_lds;
+        const dim3 both(mg.x + vg.x, nbh);
+        return token_copy ? launch(gather_both_kernel<true>, both, dim3(256), lds, s, (const uintx4 *)K, (const uint16_t *)V,
+                                   (const int32_t *)kidx, (uintx4 *)kdst, (uint16_t *)Vt, g.n, g.d, cl, kcopy, vcopy, kbarT,
+                                   g.block, g.T, Tsk, mg.x)
+                          : launch(gather_both_kernel<false>, both, dim3(256), lds, s, (const uintx4 *)K, (const uint16_t *)V,
+                                   (const int32_t *)kidx, (uintx4 *)kdst, (uint16_t *)Vt, g.n, g.d, cl, kcopy, vcopy, kbarT,
+                                   g.block, g.T, Tsk, mg.x);
+    }
+    if (kdst)
         st = token_copy ? launch((move_rows_kernel<false, true>), mg, dim3(256), 0, s, (const uintx4 *)K,
                                  (const int32_t *)kidx, (uintx4 *)kdst, g.n, cl, kcopy)
                         : launch((move_rows_kernel<false, false>), mg, dim3(256), 0, s, (const uintx4 *)K,
                                  (const int32_t *)kidx, (uintx4 *)kdst, g.n, cl, kcopy);
     if (st != PBS_OK) return st;
-    if (kbarT && !pool_on_the_way && (st = launch_pool_keys(p, g, Kp, kbarT, s)) != PBS_OK) return st;
-    const dim3 vg(token_copy ? 2 * g.T : g.T, nbh);
-    const size_t vcopy = token_copy ? vt_half : (size_t)0;
-    if (p->dtype == PBS_BF16) {
-        const size_t lds = (size_t)g.block * g.d * 2 + (size_t)(g.block / 8) * (64 / (vt_group(g.block) / 8)) * 4;   // tile + skew
-        st = token_copy ? launch((gather_vt_kernel<uint16_t, true>), vg, dim3(256), lds, s, (const uint16_t *)V,
+    if (kbarT && (st = launch_pool_keys(p, g, Kp, kbarT, s)) != PBS_OK) return st;
+    if (p->dtype == PBS_BF16)
+        st = token_copy ? launch((gather_vt_kernel<uint16_t, true>), vg, dim3(256), vlds, s, (const uint16_t *)V,
                                  (const int32_t *)kidx, (uint16_t *)Vt, g.n, g.d, g.block, g.T, vcopy)
-                        : launch((gather_vt_kernel<uint16_t, false>), vg, dim3(256), lds, s, (const uint16_t *)V,
+                        : launch((gather_vt_kernel<uint16_t, false>), vg, dim3(256), vlds, s, (const uint16_t *)V,
                                  (const int32_t *)kidx, (uint16_t *)Vt, g.n, g.d, g.block, g.T, vcopy);
-    } else {
-        const size_t lds = (size_t)g.block * g.d * 4 + (size_t)(g.block / 4) * (64 / (vt_group(g.block) / 4)) * 4;
-        st = token_copy ? launch((gather_vt_kernel<uint32_t, true>), vg, dim3(256), lds, s, (const uint32_t *)V,
+    else
+        st = token_copy ? launch((gather_vt_kernel<uint32_t, true>), vg, dim3(256), vlds, s, (const uint32_t *)V,
                                  (const int32_t *)kidx, (uint32_t *)Vt, g.n, g.d, g.block, g.T, vcopy)
-                        : launch((gather_vt_kernel<uint32_t, false>), vg, dim3(256), lds, s, (const uint32_t *)V,
+                        : launch((gather_vt_kernel<uint32_t, false>), vg, dim3(256), vlds, s, (const uint32_t *)V,
                                  (const int32_t *)kidx, (uint32_t *)Vt, g.n, g.d, g.block, g.T, vcopy);
-    }
     return st;
 }
 
