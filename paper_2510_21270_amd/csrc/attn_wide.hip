@@ -42,7 +42,7 @@ constexpr int KS = 32;                                     // keys per sub-tile
 constexpr int kStageB = 8192;                              // K' sub-tile: 32 rows x 256 B; V'^T sub-tile: 128 rows x 64 B
 constexpr int kLoadsPerWave = 8;                           // 16-byte-per-lane loads a wave issues per stage
 constexpr int kList = 1024;                                // listed blocks staged in LDS at a time
-constexpr int kXcds = 8, kCohort = 64;
+constexpr int kXcds = 8, kCohortLog2 = 6;
 constexpr int kResident = 512;                             // workgroups the chip holds: two on each of 256 compute units
 constexpr int kTicketStride = 32;                          // queue heads lie 128 bytes apart
 constexpr int kQueueRows = 8 * kResident;                  // rows from which on workgroups take them from queues
@@ -442,31 +442,33 @@ struct RowInfo {
 constexpr int kEntryBlock = (1 << 18) - 1, kEntryRoomShift = 20, kEntryMask = 1 << 28;
 constexpr int kEntryAhead = 1 << 29;                       // behind the last entry: the next row's first block
 
-// Rows are handed out in cohorts of `cohort` rows of one kv head with near-equal list lengths, longest lists first; XCD x
-// starts with the cohorts x, x + 8, ... (its L2 then holds the tiles its workgroups share).  Ticket t of XCD x -> row
-// index unit * rows_per_unit + mrow, -1 past the last cohort, -2 for the unused end of a unit's last cohort.
-__device__ __forceinline__ int ticket_row(const Geo &g, int cohort, int x, int t)
+// Rows are handed out in cohorts of 2^cohort_log2 rows of one kv head with near-equal list lengths, longest lists first;
+// XCD x starts with the cohorts x, x + 8, ... (its L2 then holds the tiles its workgroups share).  Ticket t of XCD x ->
+// kv head and row of it (0 = the longest list); false past the last cohort, unit = -1 for the unused end of a unit's last
+// cohort.
+__device__ __forceinline__ bool ticket_row(const Geo &g, int cohort_log2, int x, int t, int &unit, int &mrow)
 {
     const int nbk = g.batch * g.h_kv, rows_per_unit = g.r * g.T;
-    const int coh_per_unit = (rows_per_unit + cohort - 1) / cohort;
-    const int coh = (t / cohort) * kXcds + x;
-    if (coh >= nbk * coh_per_unit) return -1;
-    const int mrow = (coh / nbk) * cohort + t % cohort;
-    return mrow < rows_per_unit ? (coh % nbk) * rows_per_unit + mrow : -2;
+    const int coh = (t >> cohort_log2) * kXcds + x, index = coh / nbk;
+    mrow = (index << cohort_log2) + (t & ((1 << cohort_log2) - 1));
+    unit = mrow < rows_per_unit ? coh - index * nbk : -1;
+    return (index << cohort_log2) < rows_per_unit;
 }
 
 // The next row for a workgroup of XCD `home` (one lane) that has drawn `ticket` from its own queue: the row of that
-// ticket, else one of the other XCDs' queues (the XCDs run at clocks that differ by up to 8 %).  -1: every queue is empty.
-__device__ __forceinline__ int claim_row(const Geo &g, int cohort, int32_t *tickets, int home, int ticket)
+// ticket, else one of the other XCDs' queues (the XCDs run at clocks that differ by up to 8 %).  unit = -1: every queue
+// is empty.
+__device__ __forceinline__ void claim_row(const Geo &g, int cohort_log2, int32_t *tickets, int home, int ticket, int &unit,
+                                          int &mrow)
 {
-    int row = ticket_row(g, cohort, home, ticket);
+    if (ticket_row(g, cohort_log2, home, ticket, unit, mrow) && unit >= 0) return;
 #pragma unroll 1
-    for (int k = 0; row < 0 && k < kXcds; ++k) {
+    for (int k = 0; k < kXcds; ++k) {
         const int x = (home + k) % kXcds;
-        do row = ticket_row(g, cohort, x, atomicAdd(tickets + x * kTicketStride, 1));
-        while (row == -2);
+        while (ticket_row(g, cohort_log2, x, atomicAdd(tickets + x * kTicketStride, 1), unit, mrow))
+            if (unit >= 0) return;
     }
-    return row;
+    unit = -1;
 }
 
 // One lane per queue: the workgroups' first tickets are their ids.
@@ -488,7 +490,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const bf16_t *__restrict__ Qp, const bf16_t *__restrict__ Kp, const bf16_t *__restrict__ Vt,
     const int32_t *__restrict__ qidx, const int32_t *__restrict__ kidx, const int32_t *__restrict__ row_cnt,
     const int32_t *__restrict__ col_idx, bf16_t *__restrict__ Op, float *__restrict__ lse,
-    int16_t *__restrict__ redo, Geo g, int tok_delta, int32_t *tickets, int cohort)
+    int16_t *__restrict__ redo, Geo g, int tok_delta, int32_t *tickets, int cohort_log2)
 {
     __shared__ Stage sg0, sg1, sg2, sg3;                   // 4 x 16 KiB
     __shared__ int lists[2][kList];                        // block lists (a chunk of each) of this row and the next
@@ -503,12 +505,10 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const LaneOffsets off = lane_offsets(wave, lane);
     constexpr int kRawDword = 0x00020000;                  // gfx9 descriptor word 3: raw 32-bit data format
 
-    auto decode = [&](int row, int &unit, int &bhq, int &i) {
-        const int rows_per_unit = g.r * g.T;
-        unit = row / rows_per_unit;
-        const int mrow = row % rows_per_unit;
-        i = g.T - 1 - mrow / g.r;
-        bhq = (unit / g.h_kv) * g.h_q + (unit % g.h_kv) * g.r + mrow % g.r;
+    auto decode = [&](int unit, int mrow, int &bhq, int &i) {
+        const int later = mrow / g.r, kv = unit / g.h_kv;
+        i = g.T - 1 - later;
+        bhq = kv * g.h_q + (unit - kv * g.h_kv) * g.r + mrow - later * g.r;
     };
     auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
     // the raw list entries [base, base + kList) of a row, up to T (wave 0)
@@ -615,22 +615,26 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const int home = blockIdx.x % kXcds;
     // the row of a ticket as the next one (one lane); ticket < 0: there is none
     auto open_next = [&](RowInfo &w, int ticket) {
-        const int row = ticket < 0 ? -1 : claim_row(g, cohort, tickets, home, ticket);
-        w.unit = -1;
+        int unit = -1, mrow = 0;
+        if (ticket >= 0) claim_row(g, cohort_log2, tickets, home, ticket, unit, mrow);
+        w.unit = unit;
         w.len = 0;
-        if (row >= 0) decode(row, w.unit, w.bhq, w.i);
+        if (unit >= 0) decode(unit, mrow, w.bhq, w.i);
     };
     int unit, bhq, i;                                      // of the current row
     {
-        int row = ticket_row(g, cohort, home, blockIdx.x / kXcds);
-        if (row < 0) {
+        int mrow;
+        const bool inside = ticket_row(g, cohort_log2, home, blockIdx.x / kXcds, unit, mrow);
+        if (!inside || unit < 0) {
             if (!tickets) return;
-            if (threadIdx.x == 0) next_cnt[0] = claim_row(g, cohort, tickets, home, blockIdx.x / kXcds);
+            if (threadIdx.x == 0) claim_row(g, cohort_log2, tickets, home, blockIdx.x / kXcds, next_cnt[0], next_cnt[1]);
             __syncthreads();
-            row = uniform(next_cnt[0]);
-            if (row < 0) return;
+            unit = uniform(next_cnt[0]);
+            mrow = uniform(next_cnt[1]);
+            if (unit < 0) return;
+            __syncthreads();                               // (next_cnt is loaded into later)
         }
-        decode(row, unit, bhq, i);
+        decode(unit, mrow, bhq, i);
         const size_t at = (size_t)bhq * g.T + i;
         if (wave == 0) load_list(bhq, i, lists[0], 0);
         load_queries(bhq, i);
@@ -869,7 +873,7 @@ pbs_status launch_attn_wide(const Geo &g, const void *Qp, const void *Kp, const 
                             int32_t *redo, int32_t *tickets, int tok_delta, hipStream_t s)
 {
     const long long units = (long long)g.batch * g.h_kv, rows = (long long)g.r * g.T;
-    int cohort = wide::kCohort;
+    int cohort_log2 = wide::kCohortLog2;
     unsigned wgs = wide::kResident;
     if (units * rows >= wide::kQueueRows) {
         const pbs_status st = launch(wide::init_tickets_kernel, dim3(1), dim3(64), 0, s, tickets, wide::kResident / wide::kXcds);
@@ -878,13 +882,13 @@ pbs_status launch_attn_wide(const Geo &g, const void *Qp, const void *Kp, const 
         // every row has a workgroup of its own (a queue's lookahead of one row costs more balance than the gaps between
         // workgroups while each takes only a few rows); cohorts narrower while some XCD would get none
         tickets = nullptr;
-        while (cohort > 8 && units * ((rows + cohort - 1) / cohort) < wide::kXcds) cohort >>= 1;
-        const long long ncoh = units * ((rows + cohort - 1) / cohort);
-        wgs = (unsigned)((ncoh + wide::kXcds - 1) / wide::kXcds * wide::kXcds * cohort);
+        auto cohorts = [&]() { return units * ((rows + (1 << cohort_log2) - 1) >> cohort_log2); };
+        while (cohort_log2 > 3 && cohorts() < wide::kXcds) --cohort_log2;
+        wgs = (unsigned)(((cohorts() + wide::kXcds - 1) / wide::kXcds * wide::kXcds) << cohort_log2);
     }
     return launch(wide::attn_wide_kernel, dim3(wgs), dim3(128), 0, s, (const bf16_t *)Qp, (const bf16_t *)Kp,
                   (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse, (int16_t *)redo, g, tok_delta,
-                  tickets, cohort);
+                  tickets, cohort_log2);
 }
 
 }  // namespace pbs
