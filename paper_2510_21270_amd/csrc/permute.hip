@@ -63,6 +63,15 @@ __device__ __forceinline__ void exchange_in_lane(u64 &a, u64 &b, bool asc)
     b = swap ? t : b;
 }
 
+// the bits of a score (INT_KEYS: an int32 key) as an unsigned number in the order of the sort
+template <bool INT_KEYS>
+__device__ __forceinline__ uint32_t sort_key(int raw)
+{
+    if (INT_KEYS) return (uint32_t)raw ^ 0x80000000u;        // signed order
+    const uint32_t u = __float_as_uint(__int_as_float(raw) + 0.0f);
+    return ~((u & 0x80000000u) ? ~u : (u | 0x80000000u));    // descending in u == ascending in the score
+}
+
 // identity != NULL: the positions 0 .. n-1 are written there as well (the kidx of a token-order copy).
 // INT_KEYS: `scores` holds int32 keys instead, sorted ascending (equal keys in ascending position).
 // p2: the segment padded to a power of two of at least 256; blockDim.x = p2 / kSortPer.
@@ -90,14 +99,7 @@ __global__ __launch_bounds__(1024) void segment_argsort_kernel(const float *__re
         const int4u raw = *reinterpret_cast<const int4u *>(s + t0);
 #pragma unroll
         for (int e = 0; e < kSortPer; ++e) {
-            uint32_t u;
-            if (INT_KEYS) {
-                u = (uint32_t)raw[e] ^ 0x80000000u;          // signed order
-            } else {
-                u = __float_as_uint(__int_as_float(raw[e]) + 0.0f);
-                u = ~((u & 0x80000000u) ? ~u : (u | 0x80000000u));   // descending in u == ascending in the score
-            }
-            key[e] = ((u64)u << 32) | (uint32_t)(t0 + e);
+            key[e] = ((u64)sort_key<INT_KEYS>(raw[e]) << 32) | (uint32_t)(t0 + e);
         }
     } else {
 #pragma unroll
@@ -142,6 +144,76 @@ __global__ __launch_bounds__(1024) void segment_argsort_kernel(const float *__re
     }
 }
 
+// ---------------------------------------------------------------------------------------------
+// The same order by counting, for calls whose segments are too few to fill the chip: a key's place is the number of keys
+// in front of it, so 64 keys of a segment (one per lane) are placed by a workgroup of their own.  The segment's keys lie
+// in LDS and are read as broadcasts, 64-key chunk by chunk, the chunks dealt out to the waves; equal keys count
+// where they come from an earlier position.  Bound by launch and load latency where it is used: no chain of exchanges.
+// grid = (G * chunks + 1, heads), the last workgroup for the tail; scores and kidx must not overlap.
+// ---------------------------------------------------------------------------------------------
+constexpr int kRankWaves = 8;
+
+template <bool INT_KEYS>
+__global__ __launch_bounds__(64 * kRankWaves) void segment_rank_kernel(const float *__restrict__ scores, int32_t *__restrict__ kidx,
+                                                           int32_t *__restrict__ identity, int n, int segment, int G,
+                                                           int chunks)
+{
+    extern __shared__ __align__(16) uint32_t rank_lds[];     // chunks * 64 keys, then kRankWaves * 64 counts
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const size_t base = (size_t)blockIdx.y * n;
+    const int g = blockIdx.x / chunks, own = blockIdx.x - g * chunks;
+    if (g >= G) {
+        for (int p = G * segment + tid; p < n; p += 64 * kRankWaves) {
+            kidx[base + p] = p;
+            if (identity) identity[base + p] = p;
+        }
+        return;
+    }
+    const float *s = scores + base + (size_t)g * segment;
+    for (int t0 = tid * 4; t0 < chunks * 64; t0 += 256 * kRankWaves) {   // a segment is a multiple of 16 keys
+        uintx4 u = {~0u, ~0u, ~0u, ~0u};                     // behind the segment: in front of nothing
+        if (t0 < segment) {
+            const int4u raw = *reinterpret_cast<const int4u *>(s + t0);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) u[e] = sort_key<INT_KEYS>(raw[e]);
+        }
+        *reinterpret_cast<uintx4 *>(rank_lds + t0) = u;
+    }
+    __syncthreads();
+    const uint32_t mine = rank_lds[own * 64 + lane];
+    uint32_t before = 0;
+    for (int c = wave; c < chunks; c += kRankWaves) {
+        const uintx4 *k = reinterpret_cast<const uintx4 *>(rank_lds + c * 64);
+        if (c < own) {
+#pragma unroll
+            for (int q = 0; q < 16; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) before += k[q][e] <= mine;
+        } else if (c > own) {
+#pragma unroll
+            for (int q = 0; q < 16; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) before += k[q][e] < mine;
+        } else {
+#pragma unroll 2
+            for (int q = 0; q < 16; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) before += k[q][e] < mine || (k[q][e] == mine && q * 4 + e < lane);
+        }
+    }
+    uint32_t *counts = rank_lds + chunks * 64;
+    counts[tid] = before;
+    __syncthreads();
+    const int i = own * 64 + lane;
+    if (wave != 0 || i >= segment) return;
+    int at = 0;
+#pragma unroll
+    for (int w = 0; w < kRankWaves; ++w) at += (int)counts[w * 64 + lane];
+    kidx[base + (size_t)g * segment + at] = g * segment + i;
+    if (identity) identity[base + (size_t)g * segment + i] = g * segment + i;
+}
+
 // launch shape of the sort: padded segment, threads, dynamic LDS
 struct SortShape {
     int p2, threads;
@@ -154,9 +226,21 @@ static SortShape sort_shape(int segment)
     return {p2, p2 / kSortPer, p2 > 64 * kSortPer ? 2 * (size_t)p2 * sizeof(u64) : 0};
 }
 
+// Counting costs a segment's square, the network hardly more than its own depth until it fills the chip: up to 32768 keys
+// in all counting is ahead (us, counting / network: 64 segments of 512 keys 6.1 / 6.8, 32 of 1024 7.2 / 9.0, 16 of 2048
+// 10.5 / 11.4, 8 of 4096 16.8 / 20.6; 16 of 1024 6.5 / 8.8), past it no longer (64 of 1024 9.0 / 9.0, 128 of 1024
+// 14.1 / 9.0); below 256 keys a segment is one wave's network.
+constexpr int kRankKeys = 32768, kRankMinSegment = 256;
+
 template <bool INT_KEYS>
 static pbs_status launch_sort(const Geo &g, int heads, const float *scores, int32_t *idx, int32_t *identity, hipStream_t s)
 {
+    const int chunks = (g.segment + 63) / 64;
+    const uintptr_t in = reinterpret_cast<uintptr_t>(scores), out = reinterpret_cast<uintptr_t>(idx),
+                    bytes = (uintptr_t)heads * g.n * sizeof(float);
+    if (g.segment >= kRankMinSegment && (long long)heads * g.G * g.segment <= kRankKeys && (in + bytes <= out || out + bytes <= in))
+        return launch(segment_rank_kernel<INT_KEYS>, dim3(g.G * chunks + 1, heads), dim3(64 * kRankWaves),
+                      ((size_t)chunks + kRankWaves) * 64 * sizeof(uint32_t), s, scores, idx, identity, g.n, g.segment, g.G, chunks);
     const SortShape sh = sort_shape(g.segment);
     static std::atomic<unsigned long long> lds_raised{0};
     if (sh.lds > 32 * 1024) {
@@ -414,7 +498,8 @@ __global__ __launch_bounds__(256) void gather_vt_kernel(const E *__restrict__ V,
 }
 
 // Both gathers of a head in one launch: workgroups 0 .. kwgs - 1 move K rows, the rest key blocks of V.  They do not
-// depend on each other, and a launch of its own costs each of them its ramp and its tail.
+// depend on each other, and a launch of its own costs each of them its ramp and its tail: 159 + 164 -> 311 us at
+// 8 x 131072 keys with the token-order copies (7 TB/s), 6.4 + 5.9 -> 7.9 us at 8 x 2048.
 // LDS (dynamic): what either of the two needs.
 template <bool TWICE>
 __global__ __launch_bounds__(256) void gather_both_kernel(const uintx4 *__restrict__ K, const uint16_t *__restrict__ V,

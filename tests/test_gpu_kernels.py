@@ -169,3 +169,23 @@ def test_segment_argsort_of_ragged_lengths_with_ties(oracle, block, segment):
     kidx, _, _ = pbs.segment_permute(p, torch.from_numpy(s).cuda(), None, None, indices_only=True)
     np.testing.assert_array_equal(kidx.cpu().numpy(), oracle.segment_argsort(s, segment))
     assert (pbs.token_copy(p, kidx, 1).cpu().numpy() == np.arange(n)).all()
+
+
+# up to 32768 keys in segments of 256 and more are placed by counting: both sides of that line, a buffer shared by scores
+# and indices (never by counting)
+@pytest.mark.parametrize("heads,segment,segments", [(8, 1024, 4), (8, 1024, 5), (1, 256, 128), (1, 256, 129), (2, 240, 3),
+                                                    (1, 4096, 8), (3, 1040, 2), (1, 4096, 0)])
+def test_segment_argsort_by_counting(oracle, heads, segment, segments):
+    n = max(segments * segment + 37, 300)
+    rng = np.random.default_rng(heads * segment + segments)
+    s = np.round(rng.standard_normal((1, heads, n)) * 8).astype(np.float32) / 8
+    s[0, 0, ::5] = -0.0
+    p = pbs.problem(1, heads, heads, n, 64, 16, segment, "f32", flags=pbs.FLAG_TOKEN_ORDER_COPY)
+    want = oracle.segment_argsort(s, segment)
+    kidx, _, _ = pbs.segment_permute(p, torch.from_numpy(s).cuda(), None, None, indices_only=True)
+    np.testing.assert_array_equal(kidx.cpu().numpy(), want)
+    assert (pbs.token_copy(p, kidx, 1).cpu().numpy() == np.arange(n)).all()
+    p = pbs.problem(1, heads, heads, n, 64, 16, segment, "f32")
+    both = torch.from_numpy(s).cuda()
+    kidx, _, _ = pbs.segment_permute(p, both, None, None, kidx=both.view(torch.int32), indices_only=True)
+    np.testing.assert_array_equal(kidx.cpu().numpy(), want)
