@@ -514,12 +514,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const bf16_t *__restrict__ Qp, const bf16_t *__restrict__ Kp, const bf16_t *__restrict__ Vt,
     const int32_t *__restrict__ qidx, const int32_t *__restrict__ kidx, const int32_t *__restrict__ row_cnt,
     const int32_t *__restrict__ col_idx, bf16_t *__restrict__ Op, float *__restrict__ lse,
-    const int32_t *__restrict__ flags, Geo g)
+    const void *__restrict__ flags, int narrow, Geo g)     // narrow: int16 flags, else int32
 {
+    auto flagged = [&](int row) {
+        return (narrow ? static_cast<const int16_t *>(flags)[row] : static_cast<const int32_t *>(flags)[row]) != 0;
+    };
     const int rows = g.batch * g.h_q * g.T, step = (int)gridDim.x;
     for (int base = blockIdx.x; base < rows; base += 64 * step) {
         const int mine = base + (int)(threadIdx.x & 63) * step;
-        uint64_t todo = __ballot(mine < rows && mine >= 0 && flags[mine] != 0);
+        uint64_t todo = __ballot(mine < rows && mine >= 0 && flagged(mine));
         while (todo) {
             const int row = base + __builtin_ctzll(todo) * step;
             todo &= todo - 1;
@@ -535,18 +538,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // true when the 64-queries-per-wave kernel (attn_wide.hip) serves the problem
 static bool wide_path(const pbs_problem *p) { return p->dtype == PBS_BF16 && p->d == 128 && p->block == 128; }
 
-// The wide kernel leaves one flag per query block: blocks it could not finish with a fixed softmax reference.  Behind
-// the flags lie the heads of its row queues.
-static size_t ws_redo_flags(const Geo &g) { return align_up((size_t)g.batch * g.h_q * g.T * sizeof(int32_t), kWsAlign); }
+bool wide_rows_from_queues(const Geo &g);
+size_t wide_queue_bytes();
+
+// The wide kernel leaves one flag per query block: blocks it could not finish with a fixed softmax reference.  Four bytes
+// each; where its rows come from queues (4096 query blocks and more) two bytes each, and the queue heads lie behind them
+// in the other half.
+static size_t ws_narrow_flags(const Geo &g) { return align_up((size_t)g.batch * g.h_q * g.T * sizeof(int16_t), kWsAlign); }
 size_t ws_attn_fwd(const pbs_problem *p)
 {
     if (!wide_path(p)) return 0;
-    return ws_redo_flags(make_geo(p)) + 1024;               // 8 queue heads, 128 bytes apart
+    const Geo g = make_geo(p);
+    return align_up((size_t)g.batch * g.h_q * g.T * sizeof(int32_t), kWsAlign);
 }
 
 pbs_status launch_attn_wide(const Geo &g, const void *Qp, const void *Kp, const void *Vt, const int32_t *qidx,
                             const int32_t *kidx, const int32_t *row_cnt, const int32_t *col_idx, void *Op, float *lse,
-                            int32_t *redo, int32_t *tickets, int tok_delta, hipStream_t s);
+                            void *redo, int32_t *tickets, int tok_delta, hipStream_t s);
 
 // bf16 storage, d = 64, block 64 or 128 (attn_d64.hip)
 pbs_status launch_attn_d64(const Geo &g, const void *Qp, const void *Kp, const void *Vt, const int32_t *qidx,
@@ -589,9 +597,13 @@ extern "C" pbs_status pbs_attn_fwd(const pbs_problem *p, const void *Qp, const v
         if (p->block == 128) {
             // first pass: every query block with a fixed softmax reference; second pass: the flagged blocks (none
             // on ordinary inputs, then each workgroup of the second launch leaves at once) with the rescaling kernel
-            int32_t *redo = narrow_only ? nullptr : reinterpret_cast<int32_t *>(ws);
+            void *redo = narrow_only ? nullptr : ws;
+            int32_t *tickets = nullptr;
             if (redo) {
-                int32_t *tickets = reinterpret_cast<int32_t *>(reinterpret_cast<char *>(ws) + ws_redo_flags(g));
+                if (wide_rows_from_queues(g)) {
+                    if (ws_narrow_flags(g) + wide_queue_bytes() > ws_attn_fwd(p)) return PBS_ERR_WORKSPACE;
+                    tickets = reinterpret_cast<int32_t *>(static_cast<char *>(ws) + ws_narrow_flags(g));
+                }
                 // own segments from the token-order copies: identity sigma, and every byte of both copies of a head
                 // within reach of 32-bit buffer offsets
                 const long long tok_blocks = (long long)g.batch * g.h_kv * g.T;
@@ -605,7 +617,7 @@ extern "C" pbs_status pbs_attn_fwd(const pbs_problem *p, const void *Qp, const v
             if (redo)
                 st = launch(attn_redo_kernel, dim3((unsigned)(rows < kRedoWgs ? rows : kRedoWgs)), dim3(256), 0, s,
                             (const bf16_t *)Qp, (const bf16_t *)Kp, (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx,
-                            (bf16_t *)Op, lse, (const int32_t *)redo, g);
+                            (bf16_t *)Op, lse, (const void *)redo, tickets ? 1 : 0, g);
             else
                 st = launch((attn_mfma_kernel<128, 4, 64>), mgrid, dim3(256), 0, s, (const bf16_t *)Qp,
                             (const bf16_t *)Kp, (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse, g);

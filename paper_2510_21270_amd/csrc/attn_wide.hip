@@ -490,7 +490,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const bf16_t *__restrict__ Qp, const bf16_t *__restrict__ Kp, const bf16_t *__restrict__ Vt,
     const int32_t *__restrict__ qidx, const int32_t *__restrict__ kidx, const int32_t *__restrict__ row_cnt,
     const int32_t *__restrict__ col_idx, bf16_t *__restrict__ Op, float *__restrict__ lse,
-    int16_t *__restrict__ redo, Geo g, int tok_delta, int32_t *tickets, int cohort_log2)
+    int8_t *__restrict__ redo, Geo g, int tok_delta, int32_t *tickets, int cohort_log2)
 {
     __shared__ Stage sg0, sg1, sg2, sg3;                   // 4 x 16 KiB
     __shared__ int lists[2][kList];                        // block lists (a chunk of each) of this row and the next
@@ -820,7 +820,11 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             }
             // each wave's half of the row's flag: some probability outgrew its fixed reference (the caller redoes the row)
             const bool bad = __any(st.bad);
-            if (lane == 0) redo[((size_t)bhq * g.T + i) * 2 + wave] = bad ? 1 : 0;
+            if (lane == 0) {
+                const size_t f = ((size_t)bhq * g.T + i) * 2 + wave;
+                if (tickets) redo[f] = bad ? 1 : 0;
+                else reinterpret_cast<int16_t *>(redo)[f] = bad ? 1 : 0;
+            }
         };
         if (!ahead) {
             if (wave == 0)
@@ -867,27 +871,32 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 
 }  // namespace wide
 
-// redo: [batch * h_q * T] flags, written for every query block, then (aligned to 64 bytes) the 8 queue heads.
+// Whether workgroups take their rows from queues: with a few rows per workgroup a queue's lookahead of one row costs more
+// balance than the gaps between workgroups.
+bool wide_rows_from_queues(const Geo &g) { return (long long)g.batch * g.h_q * g.T >= wide::kQueueRows; }
+// bytes of the queue heads
+size_t wide_queue_bytes() { return wide::kXcds * wide::kTicketStride * sizeof(int32_t); }
+
+// redo: [batch * h_q * T] flags, written for every query block: int32, or int16 where rows come from queues.
+// tickets: the queue heads, not NULL exactly where rows come from queues.
 pbs_status launch_attn_wide(const Geo &g, const void *Qp, const void *Kp, const void *Vt, const int32_t *qidx,
                             const int32_t *kidx, const int32_t *row_cnt, const int32_t *col_idx, void *Op, float *lse,
-                            int32_t *redo, int32_t *tickets, int tok_delta, hipStream_t s)
+                            void *redo, int32_t *tickets, int tok_delta, hipStream_t s)
 {
     const long long units = (long long)g.batch * g.h_kv, rows = (long long)g.r * g.T;
     int cohort_log2 = wide::kCohortLog2;
     unsigned wgs = wide::kResident;
-    if (units * rows >= wide::kQueueRows) {
+    if (tickets) {
         const pbs_status st = launch(wide::init_tickets_kernel, dim3(1), dim3(64), 0, s, tickets, wide::kResident / wide::kXcds);
         if (st != PBS_OK) return st;
     } else {
-        // every row has a workgroup of its own (a queue's lookahead of one row costs more balance than the gaps between
-        // workgroups while each takes only a few rows); cohorts narrower while some XCD would get none
-        tickets = nullptr;
+        // every row has a workgroup of its own; cohorts narrower while some XCD would get none
         auto cohorts = [&]() { return units * ((rows + (1 << cohort_log2) - 1) >> cohort_log2); };
         while (cohort_log2 > 3 && cohorts() < wide::kXcds) --cohort_log2;
         wgs = (unsigned)(((cohorts() + wide::kXcds - 1) / wide::kXcds * wide::kXcds) << cohort_log2);
     }
     return launch(wide::attn_wide_kernel, dim3(wgs), dim3(128), 0, s, (const bf16_t *)Qp, (const bf16_t *)Kp,
-                  (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse, (int16_t *)redo, g, tok_delta,
+                  (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse, (int8_t *)redo, g, tok_delta,
                   tickets, cohort_log2);
 }
 

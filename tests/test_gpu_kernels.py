@@ -155,6 +155,39 @@ def test_rows_from_queues_and_lists_of_every_length(oracle):
             check_close(got[0, h, lo:hi], want[k][:hi - lo], "bf16", "row %d of head %d" % (i, h))
 
 
+def test_flagged_rows_from_queues_go_to_the_second_pass(oracle):
+    # 4096 rows, the fewest that come from queues: their flags share the workspace with the queue heads.  Logits rise by
+    # 60 nats along a sequence in the first head of each group only, so that it alone is flagged.
+    block, d, T, Hq, Hkv = 128, 128, 512, 8, 4
+    n = T * block
+    rng = np.random.default_rng(31)
+    Q = 0.05 * rng.standard_normal((1, Hq, n, d)).astype(np.float32)
+    K = 0.05 * rng.standard_normal((1, Hkv, n, d)).astype(np.float32)
+    Q[0, ::2, :, 0] += 16.0
+    K[0, :, :, 0] += np.linspace(0.0, 60.0 * np.sqrt(d) / 16.0, n, dtype=np.float32)
+    Q, K = wl.round_to_bf16(Q), wl.round_to_bf16(K)
+    V = wl.round_to_bf16(rng.standard_normal((1, Hkv, n, d)).astype(np.float32))
+    p = pbs.problem(1, Hq, Hkv, n, d, block, block, "bf16")
+    Qd, Kd, Vd = (to_dev(x, "bf16") for x in (Q, K, V))
+    kidx, Kp, Vt = pbs.segment_permute(p, None, Kd, Vd)
+    cnt = np.tile(np.minimum(np.arange(T) + 1, 6).astype(np.int32), (1, Hq, 1))
+    cols = np.zeros((1, Hq, T, T), dtype=np.int32)
+    for i in range(T):
+        cols[0, :, i, :cnt[0, 0, i]] = np.unique(np.linspace(0, i, 6).astype(np.int32)) if i > 5 else np.arange(i + 1)
+    ws = pbs.alloc_workspace(p, pbs.STAGE_ATTN_FWD)
+    ws.fill_(0x55)
+    got, lse = pbs.attn_fwd(p, Qd, Kp, Vt, None, kidx, i32_dev(cnt), i32_dev(cols), want_lse=True, ws=ws)
+    torch.cuda.synchronize()
+    flags = ws[:Hq * T * 2].view(torch.int16).view(Hq, T).cpu().numpy() != 0
+    assert flags[::2, T - 60:].all() and not flags[1::2].any()
+    rows = np.asarray([[0, h, i] for h in range(Hq) for i in (0, 5, 6, 300, T - 2, T - 1)], dtype=np.int32)
+    kh = np.tile(np.arange(n, dtype=np.int32), (1, Hkv, 1))
+    want = oracle.attn_rows(Q, K, V, None, kh, cnt, cols, block, rows)
+    got = to_host(got)
+    for k, (_, h, i) in enumerate(rows):
+        check_close(got[0, h, i * block:(i + 1) * block], want[k], "bf16", "row %d of head %d" % (i, h))
+
+
 # four keys to a lane, 64 lanes to a wave: segments inside a lane row, a wave, two waves, sixteen; sizes
 # that are no power of two; ties, both zeros, infinities
 @pytest.mark.parametrize("block,segment", [(16, 16), (16, 48), (32, 256), (16, 272), (128, 512), (128, 1024), (64, 1088),
