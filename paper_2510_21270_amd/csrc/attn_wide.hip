@@ -471,14 +471,14 @@ __device__ __forceinline__ void claim_row(const Geo &g, int cohort_log2, int32_t
     unit = -1;
 }
 
-// One lane per queue: the workgroups' first tickets are their ids.
-__global__ __launch_bounds__(64) void init_tickets_kernel(int32_t *tickets, int first)
+// One lane per queue.
+__global__ __launch_bounds__(64) void init_tickets_kernel(int32_t *tickets)
 {
-    if (threadIdx.x < kXcds) tickets[threadIdx.x * kTicketStride] = first;
+    if (threadIdx.x < kXcds) tickets[threadIdx.x * kTicketStride] = 0;
 }
 
 // tickets == NULL: one workgroup per row, which it finds from its id.  Otherwise the grid is what the chip holds at a
-// time and every workgroup takes rows until none is left (tickets: 8 queue heads, set to gridDim.x / 8 beforehand).
+// time and every workgroup takes rows until none is left (tickets: 8 queue heads, set to 0 beforehand).
 //
 // Between two rows a wave that has its SIMD to itself has nothing to overlap with, so the next row is prepared under
 // the current one: near the end of the current row wave 0 loads its list into LDS (asynchronously) and, a block later,
@@ -624,10 +624,13 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     int unit, bhq, i;                                      // of the current row
     {
         int mrow;
-        const bool inside = ticket_row(g, cohort_log2, home, blockIdx.x / kXcds, unit, mrow);
-        if (!inside || unit < 0) {
-            if (!tickets) return;
-            if (threadIdx.x == 0) claim_row(g, cohort_log2, tickets, home, blockIdx.x / kXcds, next_cnt[0], next_cnt[1]);
+        if (!tickets) {
+            if (!ticket_row(g, cohort_log2, home, blockIdx.x / kXcds, unit, mrow) || unit < 0) return;
+        } else {
+            // the first row is drawn too, not tied to the workgroup's id: a workgroup that another kernel's work keeps off
+            // the chip then holds no row back
+            if (threadIdx.x == 0)
+                claim_row(g, cohort_log2, tickets, home, atomicAdd(tickets + home * kTicketStride, 1), next_cnt[0], next_cnt[1]);
             __syncthreads();
             unit = uniform(next_cnt[0]);
             mrow = uniform(next_cnt[1]);
@@ -887,7 +890,7 @@ pbs_status launch_attn_wide(const Geo &g, const void *Qp, const void *Kp, const 
     int cohort_log2 = wide::kCohortLog2;
     unsigned wgs = wide::kResident;
     if (tickets) {
-        const pbs_status st = launch(wide::init_tickets_kernel, dim3(1), dim3(64), 0, s, tickets, wide::kResident / wide::kXcds);
+        const pbs_status st = launch(wide::init_tickets_kernel, dim3(1), dim3(64), 0, s, tickets);
         if (st != PBS_OK) return st;
     } else {
         // every row has a workgroup of its own; cohorts narrower while some XCD would get none
