@@ -389,8 +389,8 @@ def main():
                 "traffic": traffic, "traffic_source": traffic_src or "not measured for this workload",
                 "avg_launch_ms": stage_ms["attn_fwd"]}
     if not (w.dtype == "bf16" and w.d == 128 and w.block in (64, 128)):
-        # every other shape runs on fp32 vector arithmetic (attn_vector_kernel): rated against the chip's fp32 vector
-        # peak (256 compute units x 128 FMA lanes x 2 x 2.4 GHz = 157.3 TFLOP/s)
+        # every other shape is rated against the chip's fp32 vector peak (256 compute units x 128 FMA lanes x 2 x 2.4 GHz
+        # = 157.3 TFLOP/s), which is the rate of the fp32 matrix instructions that fp32 storage runs on as well
         roofline.update(bound="alu", peak=FP32_VECTOR_PEAK_TFLOPS, frac=attn_tflops / FP32_VECTOR_PEAK_TFLOPS,
                         frac_from_visited_blocks=visited_tflops / FP32_VECTOR_PEAK_TFLOPS)
     if given:

@@ -528,7 +528,7 @@ static int grid_for(size_t items, int per_block)
     return (int)b;
 }
 
-// grid for move_rows_kernel and gather_pool_kernel: one batch of 4 x 256 chunks (16 KiB) per workgroup -- or `unit`
+// grid for move_rows_kernel and the K half of gather_both_kernel: one batch of 4 x 256 chunks (16 KiB) per workgroup -- or `unit`
 // chunks where a workgroup has to own whole key blocks --, so that the workgroups in flight at any time sweep one
 // narrow window of addresses (measured on a plain 1 GiB copy: 5.3 TB/s read + write with 1024 long ranges, 6.3 with
 // 65536 short ones and non-temporal accesses)
