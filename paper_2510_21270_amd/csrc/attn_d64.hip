@@ -105,35 +105,6 @@ struct Row {
     int n, block, cnt, ni, jmask, q0;
 };
 
-// The plain definition, one query per lane, for a query tile in whose masked sub-tiles some value is not finite: a key
-// that a query does not see must not touch its result, and in a matrix product 0 * inf would.  ref, l: as found.
-__device__ __attribute__((noinline)) void plain_rows(Row w, bf16_t *out, int qpos, float ref, float l, float c2)
-{
-    const int lane = threadIdx.x & 63;
-    const int qs = min(w.q0 + lane, w.n - 1);
-    const bf16_t *q = w.q + (size_t)qs * D;
-    const float inv = l > 0.0f ? 1.0f / l : 0.0f;
-    for (int e0 = 0; e0 < D; e0 += 8) {
-        float o[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-        for (int e = 0; e < w.cnt; ++e) {
-            const int j = __builtin_amdgcn_readfirstlane(w.cols[e]);
-            if (j < 0 || j >= w.ni) continue;
-            const int last = min(w.block, w.n - j * w.block);
-            for (int c = 0; c < last; ++c) {
-                const int slot = j * w.block + c;
-                float s = 0.0f;
-                for (int f = 0; f < D; ++f) s = __builtin_fmaf((float)q[f], (float)w.k[(size_t)slot * D + f], s);
-                if (j >= w.jmask && w.kidx[slot] > qpos) continue;
-                const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s, c2, -ref));
-                const bf16_t *v = w.vt + (size_t)(slot & ~31) * D + (slot & 31);
-                for (int f = 0; f < 8; ++f) o[f] += p * (float)v[(e0 + f) * 32];
-            }
-        }
-        if (w.q0 + lane < w.n)
-            for (int f = 0; f < 8; ++f) out[(size_t)qs * D + e0 + f] = (bf16_t)(o[f] * inv);
-    }
-}
-
 // grid: linear ids (x fastest, y for more than 2^20 workgroups), decoded as cohorts of `cohort` query tiles of one kv
 // head per XCD, longest lists first, as in the other attention kernels
 template <int WAVES>
@@ -144,7 +115,6 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
 {
     __shared__ Stage ring0[WAVES], ring1[WAVES];           // separate variables: the compiler can tell them apart
     __shared__ float sm[WAVES][kQ], sl[WAVES][kQ];
-    __shared__ int odd[WAVES];
 
     const int tiles = ceil_div(g.n, kQ);
     const int rows_per_unit = g.r * tiles;
@@ -239,7 +209,51 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
         return -1;
     };
 
-    bool odd_values = false;                               // a value that is not finite under the token-level mask
+    auto scores = [&](const bf16x8 (&kf)[4], floatx16 (&s)[2]) {
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) s[nt] = floatx16{0};
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt) s[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[x], qf[nt][x], s[nt], 0, 0, 0);
+    };
+    auto add_values = [&](const bf16x8 (&vf)[2][2], const bf16x8 (&hi)[2][2], const bf16x8 (&lo)[2][2]) {
+#pragma unroll
+        for (int k2 = 0; k2 < 2; ++k2)
+#pragma unroll
+            for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+                for (int nt = 0; nt < 2; ++nt)
+                    st.acc[dt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[dt][k2], hi[nt][k2], st.acc[dt][nt], 0, 0, 0);
+#pragma unroll
+        for (int k2 = 0; k2 < 2; ++k2)
+#pragma unroll
+            for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+                for (int nt = 0; nt < 2; ++nt)
+                    st.acc[dt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[dt][k2], lo[nt][k2], st.acc[dt][nt], 0, 0, 0);
+    };
+    // the token-level mask on the scores of a sub-tile; s[nt][x]: key 16 (x / 8) + 8 h + x % 8, query 32 nt + n
+    auto hide = [&](floatx16 (&s)[2], int slot0) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int k8 = slot0 + 16 * u + 8 * lh;
+            int kp[8];
+            if (slot0 + KS <= w.n) {
+                const int4u a = *reinterpret_cast<const int4u *>(w.kidx + k8), c = *reinterpret_cast<const int4u *>(w.kidx + k8 + 4);
+#pragma unroll
+                for (int x = 0; x < 4; ++x) { kp[x] = a[x]; kp[4 + x] = c[x]; }
+            } else {
+#pragma unroll
+                for (int x = 0; x < 8; ++x) kp[x] = k8 + x < w.n ? w.kidx[k8 + x] : 0x7fffffff;
+            }
+#pragma unroll
+            for (int x = 0; x < 8; ++x)
+#pragma unroll
+                for (int nt = 0; nt < 2; ++nt)
+                    if (kp[x] > qpos[nt]) s[nt][8 * u + x] = -INFINITY;
+        }
+    };
     auto subtile = [&](Stage &sg, int slot0, bool masked, int refill) {
         // this stage's 8 loads have landed, the other stage's may still be in flight
         __builtin_amdgcn_s_waitcnt(0x0F78);                // vmcnt(8), gfx9 encoding
@@ -256,70 +270,21 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
         issue(sg, refill);
         __builtin_amdgcn_sched_barrier(0);
         floatx16 s[2];
-        auto scores = [&]() {
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt) s[nt] = floatx16{0};
-#pragma unroll
-            for (int x = 0; x < 4; ++x)
-#pragma unroll
-                for (int nt = 0; nt < 2; ++nt) s[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[x], qf[nt][x], s[nt], 0, 0, 0);
-        };
-        scores();
-        // s[nt][x]: key 16 (x / 8) + 8 h + x % 8, query 32 nt + n
-        if (masked) {
-            float z = 0.0f;
-#pragma unroll
-            for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-                for (int k2 = 0; k2 < 2; ++k2)
-#pragma unroll
-                    for (int x = 0; x < 8; ++x) z = __builtin_fmaf((float)vf[dt][k2][x], 0.0f, z);
-            odd_values = odd_values || !(z == 0.0f);
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int k8 = slot0 + 16 * u + 8 * lh;
-                int kp[8];
-                if (slot0 + KS <= w.n) {
-                    const int4u a = *reinterpret_cast<const int4u *>(w.kidx + k8), c = *reinterpret_cast<const int4u *>(w.kidx + k8 + 4);
-#pragma unroll
-                    for (int x = 0; x < 4; ++x) { kp[x] = a[x]; kp[4 + x] = c[x]; }
-                } else {
-#pragma unroll
-                    for (int x = 0; x < 8; ++x) kp[x] = k8 + x < w.n ? w.kidx[k8 + x] : 0x7fffffff;
-                }
-#pragma unroll
-                for (int x = 0; x < 8; ++x)
-#pragma unroll
-                    for (int nt = 0; nt < 2; ++nt)
-                        if (kp[x] > qpos[nt]) s[nt][8 * u + x] = -INFINITY;
-            }
-        }
+        scores(kf, s);
+        if (masked) hide(s, slot0);
         const bool first = masked || !__all(st.seen[0] && st.seen[1]);
         if (first) move_reference(st, s, c2);              // at least the row maximum: no sum below can be large
         bf16x8 hi[2][2], lo[2][2];
         float rsum[2];
         probabilities(st, s, c2, hi, lo, rsum);
         if (!first && __any(!(rsum[0] <= kBigRowSum) || !(rsum[1] <= kBigRowSum))) {
-            scores();                                      // formed again rather than kept: 16 registers fewer
+            scores(kf, s);                                 // formed again rather than kept: 16 registers fewer
             move_reference(st, s, c2);
             probabilities(st, s, c2, hi, lo, rsum);
         }
         st.l[0] += rsum[0];
         st.l[1] += rsum[1];
-#pragma unroll
-        for (int k2 = 0; k2 < 2; ++k2)
-#pragma unroll
-            for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-                for (int nt = 0; nt < 2; ++nt)
-                    st.acc[dt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[dt][k2], hi[nt][k2], st.acc[dt][nt], 0, 0, 0);
-#pragma unroll
-        for (int k2 = 0; k2 < 2; ++k2)
-#pragma unroll
-            for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-                for (int nt = 0; nt < 2; ++nt)
-                    st.acc[dt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[dt][k2], lo[nt][k2], st.acc[dt][nt], 0, 0, 0);
+        add_values(vf, hi, lo);
     };
 
     int s0 = next_slot();
@@ -335,6 +300,85 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
             s0 = s1;
         }
         __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0): the loads issued past the end have landed too
+    }
+
+    // A value that is not finite does not come through these products: 0 * inf of a hidden key is NaN, and so is
+    // hi * inf + lo * inf of a visible one whenever lo is zero or negative.  A wave that finds NaN in its O^T forms it again,
+    // relative to the references it has ended with: such values leave the products and are added one key at a time, with the
+    // undivided probability, for the queries that see the key.  Nothing is prefetched here; with one infinite value that every
+    // query of the call sees, 16 / 4 heads x 12301 tokens take 1.26 ms instead of 0.62.
+    bool odd = false;
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+            for (int x = 0; x < 16; ++x) odd = odd || st.acc[dt][nt][x] != st.acc[dt][nt][x];
+    if (__any(odd)) {
+        float *weight = reinterpret_cast<float *>(&sg0);   // [key of the sub-tile][query], -1: not seen
+        static_assert(sizeof(Stage) == KS * kQ * sizeof(float), "the probabilities of a sub-tile");
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+            for (int dt = 0; dt < 2; ++dt) st.acc[dt][nt] = floatx16{0};
+        u_next = wave;
+        int slot0 = next_slot();
+        for (int part = 0; slot0 >= 0; ) {
+            bf16x8 kf[4], vf[2][2];
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+                kf[x] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rk, swap23(ln) * (D * 2) + (2 * x + lh) * 16, slot0 * (D * 2), 0));
+#pragma unroll
+            for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+                for (int k2 = 0; k2 < 2; ++k2)
+                    vf[dt][k2] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rv, (32 * dt + ln) * (KS * 2) + (2 * k2 + lh) * 16, slot0 * (D * 2), 0));
+            floatx16 s[2];
+            scores(kf, s);
+            if (slot0 >= w.jmask * g.block) hide(s, slot0);
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+                for (int x = 0; x < 16; ++x)
+                    weight[(16 * (x >> 3) + 8 * lh + (x & 7)) * kQ + 32 * nt + ln] =
+                        s[nt][x] == -INFINITY ? -1.0f : __builtin_amdgcn_exp2f(__builtin_fmaf(s[nt][x], c2, -st.mref[nt]));
+            uint32_t keys = 0;                             // with some value that is not finite
+#pragma unroll
+            for (int k2 = 0; k2 < 2; ++k2)
+#pragma unroll
+                for (int x = 0; x < 8; ++x) {
+                    bool any = false;
+#pragma unroll
+                    for (int dt = 0; dt < 2; ++dt) {
+                        const bool here = !(fabsf((float)vf[dt][k2][x]) < INFINITY);
+                        if (here) vf[dt][k2][x] = (bf16_t)0.0f;
+                        any = any || here;
+                    }
+                    const uint64_t lanes = __ballot(any);
+                    keys |= ((uint32_t)lanes ? 1u : 0u) << (16 * k2 + x) | ((uint32_t)(lanes >> 32) ? 1u : 0u) << (16 * k2 + 8 + x);
+                }
+            bf16x8 hi[2][2], lo[2][2];
+            float unused[2];
+            probabilities(st, s, c2, hi, lo, unused);
+            add_values(vf, hi, lo);
+            for (; keys; keys &= keys - 1) {
+                const int key = __builtin_ctz(keys);
+                const float p[2] = {weight[key * kQ + ln], weight[key * kQ + 32 + ln]};
+                const bf16_t *vk = w.vt + (size_t)slot0 * D + key;
+#pragma unroll
+                for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+                    for (int x = 0; x < 16; ++x) {
+                        const float v = (float)vk[(32 * dt + 8 * (x >> 2) + 4 * lh + (x & 3)) * KS];
+                        if (!(fabsf(v) < INFINITY))
+#pragma unroll
+                            for (int nt = 0; nt < 2; ++nt)
+                                if (!(p[nt] < 0.0f)) st.acc[dt][nt][x] += p[nt] * v;
+                    }
+            }
+            slot0 = part == 0 ? slot0 + KS : next_slot();
+            part ^= 1;
+        }
     }
 
     float lt[2];
@@ -360,8 +404,6 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
                     lse[bhq * g.n + qs] = lt[nt] > 0.0f ? (st.mref[nt] + log2f(lt[nt])) * kLn2F : -INFINITY;
             }
         }
-        if (__any(odd_values))                             // lane = query from here on
-            plain_rows(w, Op + bhq * g.n * D, lh ? qpos[1] : qpos[0], lh ? st.mref[1] : st.mref[0], lh ? lt[1] : lt[0], c2);
     } else {
         // every wave leaves its O^T in its own ring, [feature][query], and its (m, l)
         float *part[2] = {reinterpret_cast<float *>(&sg0), reinterpret_cast<float *>(&sg1)};
@@ -378,8 +420,6 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
                 for (int x = 0; x < 16; ++x)
                     part[dt][(8 * (x >> 2) + 4 * lh + (x & 3)) * kQ + 32 * nt + ln] = st.acc[dt][nt][x];
         }
-        const bool odd_here = __any(odd_values);
-        if (lane == 0) odd[wave] = odd_here;
         __syncthreads();
         // thread (query, part of the features)
         constexpr int F = D / WAVES;
@@ -407,15 +447,6 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
 #pragma unroll
             for (int f = 0; f < F / 8; ++f) *reinterpret_cast<bf16x8 *>(Op + (bhq * g.n + qs) * D + f0 + 8 * f) = out[f];
             if (lse && wave == 0) lse[bhq * g.n + qs] = l > 0.0f ? (m + log2f(l)) * kLn2F : -INFINITY;
-        }
-        int odd_any = 0;
-#pragma unroll
-        for (int v = 0; v < WAVES; ++v) odd_any |= odd[v];
-        if (odd_any) {
-            __syncthreads();                               // behind the stores of the other waves
-            if (wave == 0)
-                plain_rows(w, Op + bhq * g.n * D, qs < g.n ? (qidx ? qidx[bhq * g.n + qs] : qs) : -1,
-                           m == -INFINITY ? 0.0f : m, l, c2);
         }
     }
 }

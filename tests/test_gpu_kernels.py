@@ -222,3 +222,36 @@ def test_segment_argsort_by_counting(oracle, heads, segment, segments):
     both = torch.from_numpy(s).cuda()
     kidx, _, _ = pbs.segment_permute(p, both, None, None, kidx=both.view(torch.int32), indices_only=True)
     np.testing.assert_array_equal(kidx.cpu().numpy(), want)
+
+
+# A value that is not finite in a block that every later query sees in full, the later blocks' own values finite: what
+# p * v gives must come out, also where p enters the product as two terms of either sign.  The long case has more than 16384
+# query tiles: there a wave has its list to itself.
+@pytest.mark.parametrize("dtype,d,block,Hq,Hkv,n", [("bf16", 64, 64, 4, 2, 500), ("bf16", 64, 128, 2, 1, 700),
+                                                    ("bf16", 64, 64, 64, 2, 16410), ("bf16", 64, 32, 2, 1, 300),
+                                                    ("f32", 64, 64, 2, 1, 300)])
+def test_values_of_an_earlier_segment_that_are_not_finite(dtype, d, block, Hq, Hkv, n):
+    Q, K, V = (to_dev(x, dtype) for x in _qkv(9, Hq, Hkv, n, d, dtype))
+    T, at = -(-n // block), block // 2
+    p = pbs.problem(1, Hq, Hkv, n, d, block, block, dtype)
+    i = torch.arange(T, dtype=torch.int32, device="cuda")
+    cnt = torch.clamp(i + 1, max=2).repeat(1, Hq, 1).contiguous()
+    cols = torch.zeros((T, T), dtype=torch.int32, device="cuda")
+    cols[1:, 1] = i[1:]                                    # every query block sees block 0 and itself
+    cols = cols.repeat(1, Hq, 1, 1).contiguous()
+
+    def run(v):
+        kidx, kp, vt = pbs.segment_permute(p, None, K, v)
+        return pbs.attn_fwd(p, Q, kp, vt, None, kidx, cnt, cols, want_lse=True)
+    want, want_lse = run(V)
+    bad = V.clone()
+    bad[0, :, at, 3], bad[0, :, at, 5], bad[0, :, at, d - 1] = np.inf, -np.inf, np.nan
+    bad[0, :, at, 7], bad[0, :, at + 1, 7] = np.inf, -np.inf
+    got, lse = run(bad)
+    torch.cuda.synchronize()
+    want = want.clone()
+    want[0, :, at:, 3], want[0, :, at:, 5], want[0, :, at:, d - 1] = np.inf, -np.inf, np.nan
+    want[0, :, at, 7], want[0, :, at + 1:, 7] = np.inf, np.nan
+    # two bf16 roundings of sums of which one may be formed relative to another reference: as above
+    torch.testing.assert_close(got.float(), want.float(), rtol=2.0 ** -7, atol=2.0 ** -15, equal_nan=True)
+    assert torch.equal(lse, want_lse)
