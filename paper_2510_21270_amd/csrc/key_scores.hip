@@ -442,8 +442,8 @@ __global__ __launch_bounds__(256) void scores_stats_f64_kernel(const E *__restri
                 m[t] = mn;
             }
 #pragma unroll
-            for (int x = 0; x < 4; ++x)
-                if (m[t] != -INFINITY) l[t] += exp(v[x] - m[t]);
+            for (int x = 0; x < 4; ++x)                    // (a logit that is not a number counts, whatever m is)
+                if (v[x] != -INFINITY) l[t] += exp(v[x] - m[t]);
         }
     }
     const int parts = gridDim.x * ws.kg;
@@ -474,7 +474,7 @@ __global__ __launch_bounds__(256) void scores_merge_f64_kernel(const double2 *__
     for (int c = lane; c < parts; c += 64) {
         const double2 v = pr[c];
         const double m2 = fmax(mn, v.x);
-        if (m2 != -INFINITY) ln = ln * exp(mn - m2) + v.y * exp(v.x - m2);
+        ln = m2 == -INFINITY ? ln + v.y : ln * exp(mn - m2) + v.y * exp(v.x - m2);
         mn = m2;
     }
     const double wm = wave_max(mn);

@@ -255,3 +255,16 @@ def test_values_of_an_earlier_segment_that_are_not_finite(dtype, d, block, Hq, H
     # two bf16 roundings of sums of which one may be formed relative to another reference: as above
     torch.testing.assert_close(got.float(), want.float(), rtol=2.0 ** -7, atol=2.0 ** -15, equal_nan=True)
     assert torch.equal(lse, want_lse)
+
+
+# a key that is not a number makes every score of its head one, wherever it stands: alone in its chunk, in its key share,
+# in its lane's part of a tile
+@pytest.mark.parametrize("dtype,d,block,n", [("f32", 64, 16, 17), ("f32", 128, 128, 65), ("bf16", 64, 32, 33),
+                                             ("bf16", 64, 128, 257), ("f32", 64, 64, 1)])
+def test_fp64_key_scores_of_a_key_that_is_not_a_number(oracle, dtype, d, block, n):
+    Q, K, _ = _qkv(n, 4, 2, n, d, dtype)
+    K[0, 1, n - 1] = np.nan
+    p = pbs.problem(1, 4, 2, n, d, block, block, dtype)
+    got = pbs.key_scores(p, to_dev(Q, dtype), to_dev(K, dtype)).cpu().numpy()
+    assert np.isnan(got[0, 1]).all()
+    np.testing.assert_allclose(got[0, 0], oracle.key_scores(Q, K, block)[0, 0], rtol=2.0 ** -23, atol=1e-37)
