@@ -245,10 +245,11 @@ pbs_status pbs_block_mask(const pbs_problem *p, const void *Qp, const void *Kp, 
  *   listed logits of every query row.
  *   ws: pbs_workspace_bytes(p, PBS_STAGE_ATTN_FWD) bytes, 256-byte aligned device memory (0 bytes, and ws may be NULL,
  *   unless dtype is bf16 with d = 128 and block = 128).  For that shape the call launches up to three kernels on the
- *   stream: one that sets the heads of the row queues in ws (problems of 4096 query blocks and more), one that keeps a
- *   fixed softmax reference per query and writes one flag per query block into ws (not 0 = some probability outgrew
- *   the reference by more than 2^64), and one that recomputes the flagged query blocks with the running-maximum
- *   recurrence of Algorithm 1.  The contents of ws need not be initialised and mean nothing afterwards.
+ *   stream: one that takes a set of row queues from the library's pool (problems of 4096 query blocks and more; the next
+ *   kernel gives it back), one that keeps a fixed softmax reference per query and writes one flag per query block into
+ *   ws (not 0 = some probability outgrew the reference by more than 2^64), and one that recomputes the flagged query
+ *   blocks with the running-maximum recurrence of Algorithm 1.  The contents of ws need not be initialised and mean
+ *   nothing afterwards.
  *   With PBS_FLAG_RUNNING_MAX_ONLY every query block of that shape goes through the second kernel alone.
  *   With PBS_FLAG_TOKEN_ORDER_COPY (Kp, Vt, kidx carry their token-order copies), qidx == NULL and that same shape, a
  *   query block inside a full segment whose list ends with all R blocks of its own segment, ascending (as

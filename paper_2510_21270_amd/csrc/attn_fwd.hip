@@ -539,12 +539,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 static bool wide_path(const pbs_problem *p) { return p->dtype == PBS_BF16 && p->d == 128 && p->block == 128; }
 
 bool wide_rows_from_queues(const Geo &g);
-size_t wide_queue_bytes();
 
 // The wide kernel leaves one flag per query block: blocks it could not finish with a fixed softmax reference.  Four bytes
-// each; where its rows come from queues (4096 query blocks and more) two bytes each, and the queue heads lie behind them
-// in the other half.
-static size_t ws_narrow_flags(const Geo &g) { return align_up((size_t)g.batch * g.h_q * g.T * sizeof(int16_t), kWsAlign); }
+// are set aside for each; where its rows come from queues (4096 query blocks and more) a flag takes two of them, one from each
+// wave, which halves what the second pass reads of them.
 size_t ws_attn_fwd(const pbs_problem *p)
 {
     if (!wide_path(p)) return 0;
@@ -554,7 +552,7 @@ size_t ws_attn_fwd(const pbs_problem *p)
 
 pbs_status launch_attn_wide(const Geo &g, const void *Qp, const void *Kp, const void *Vt, const int32_t *qidx,
                             const int32_t *kidx, const int32_t *row_cnt, const int32_t *col_idx, void *Op, float *lse,
-                            void *redo, int32_t *tickets, int tok_delta, hipStream_t s);
+                            void *redo, int tok_delta, hipStream_t s);
 
 // bf16 storage, d = 64, block 64 or 128 (attn_d64.hip)
 pbs_status launch_attn_d64(const Geo &g, const void *Qp, const void *Kp, const void *Vt, const int32_t *qidx,
@@ -598,26 +596,21 @@ extern "C" pbs_status pbs_attn_fwd(const pbs_problem *p, const void *Qp, const v
             // first pass: every query block with a fixed softmax reference; second pass: the flagged blocks (none
             // on ordinary inputs, then each workgroup of the second launch leaves at once) with the rescaling kernel
             void *redo = narrow_only ? nullptr : ws;
-            int32_t *tickets = nullptr;
             if (redo) {
-                if (wide_rows_from_queues(g)) {
-                    if (ws_narrow_flags(g) + wide_queue_bytes() > ws_attn_fwd(p)) return PBS_ERR_WORKSPACE;
-                    tickets = reinterpret_cast<int32_t *>(static_cast<char *>(ws) + ws_narrow_flags(g));
-                }
                 // own segments from the token-order copies: identity sigma, and every byte of both copies of a head
                 // within reach of 32-bit buffer offsets
                 const long long tok_blocks = (long long)g.batch * g.h_kv * g.T;
                 const bool own_tok = (p->flags & PBS_FLAG_TOKEN_ORDER_COPY) && !qidx &&
                                      (tok_blocks + g.T) * 128 * 256 < 0x7fffffffLL;
                 const int tok_delta = own_tok ? (int)tok_blocks : 0;
-                st = launch_attn_wide(g, Qp, Kp, Vt, qidx, kidx, row_cnt, col_idx, Op, lse, redo, tickets, tok_delta, s);
+                st = launch_attn_wide(g, Qp, Kp, Vt, qidx, kidx, row_cnt, col_idx, Op, lse, redo, tok_delta, s);
                 if (st != PBS_OK) return st;
             }
             const long long rows = (long long)g.batch * g.h_q * g.T;
             if (redo)
                 st = launch(attn_redo_kernel, dim3((unsigned)(rows < kRedoWgs ? rows : kRedoWgs)), dim3(256), 0, s,
                             (const bf16_t *)Qp, (const bf16_t *)Kp, (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx,
-                            (bf16_t *)Op, lse, (const void *)redo, tickets ? 1 : 0, g);
+                            (bf16_t *)Op, lse, (const void *)redo, wide_rows_from_queues(g) ? 1 : 0, g);
             else
                 st = launch((attn_mfma_kernel<128, 4, 64>), mgrid, dim3(256), 0, s, (const bf16_t *)Qp,
                             (const bf16_t *)Kp, (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse, g);

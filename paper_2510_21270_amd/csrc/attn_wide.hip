@@ -471,14 +471,33 @@ __device__ __forceinline__ void claim_row(const Geo &g, int cohort_log2, int32_t
     unit = -1;
 }
 
-// One lane per queue.
-__global__ __launch_bounds__(64) void init_tickets_kernel(int32_t *tickets)
+// Queue heads belong to one call: they come from a pool in device memory that is part of the library image (a copy on
+// every GPU), never from the caller's workspace, which calls on several streams may share.  The kernel in front of the
+// attention kernel takes a set under a key that no other call has (its number; the replays of a graph, which follow
+// one another, use theirs again), every workgroup looks its call's set up by the key, and the last one to leave gives it
+// back.  More calls than sets at one time: the last ones have none and leave all their rows to the second pass.
+constexpr int kQueueSets = 64;                             // one per lane of the wave that looks for its own
+constexpr int kLeft = kTicketStride / 2;                   // in a set: workgroups that have left
+static __device__ unsigned long long queue_owner[kQueueSets];          // key, 0: free
+static __device__ int32_t queue_heads[kQueueSets][kXcds * kTicketStride];
+
+__global__ __launch_bounds__(64) void take_queues_kernel(unsigned long long key)
 {
-    if (threadIdx.x < kXcds) tickets[threadIdx.x * kTicketStride] = 0;
+    const int lane = threadIdx.x;
+    int set = -1;
+    if (lane == 0) {
+        for (int k = 0; k < kQueueSets && set < 0; ++k) {
+            const int at = (int)((key + k) % kQueueSets);
+            if (atomicCAS(&queue_owner[at], 0ull, key) == 0ull) set = at;
+        }
+    }
+    set = __builtin_amdgcn_readfirstlane(set);
+    if (set >= 0 && lane < kXcds) queue_heads[set][lane * kTicketStride] = 0;
+    if (set >= 0 && lane == kXcds) queue_heads[set][kLeft] = 0;
 }
 
-// tickets == NULL: one workgroup per row, which it finds from its id.  Otherwise the grid is what the chip holds at a
-// time and every workgroup takes rows until none is left (tickets: 8 queue heads, set to 0 beforehand).
+// key == 0: one workgroup per row, which it finds from its id.  Otherwise the grid is what the chip holds at a time and
+// every workgroup takes rows from the queues of that key until none is left.
 //
 // Between two rows a wave that has its SIMD to itself has nothing to overlap with, so the next row is prepared under
 // the current one: near the end of the current row wave 0 loads its list into LDS (asynchronously) and, a block later,
@@ -490,7 +509,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const bf16_t *__restrict__ Qp, const bf16_t *__restrict__ Kp, const bf16_t *__restrict__ Vt,
     const int32_t *__restrict__ qidx, const int32_t *__restrict__ kidx, const int32_t *__restrict__ row_cnt,
     const int32_t *__restrict__ col_idx, bf16_t *__restrict__ Op, float *__restrict__ lse,
-    int8_t *__restrict__ redo, Geo g, int tok_delta, int32_t *tickets, int cohort_log2)
+    int8_t *__restrict__ redo, Geo g, int tok_delta, unsigned long long key, int cohort_log2)
 {
     __shared__ Stage sg0, sg1, sg2, sg3;                   // 4 x 16 KiB
     __shared__ int lists[2][kList];                        // block lists (a chunk of each) of this row and the next
@@ -613,6 +632,19 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     };
 
     const int home = blockIdx.x % kXcds;
+    int32_t *tickets = nullptr;
+    if (key) {
+        const uint64_t mine = __ballot(__hip_atomic_load(&queue_owner[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == key);
+        if (!mine) {                                       // no set was free: every row is flagged
+            for (long long f = 128LL * blockIdx.x + threadIdx.x; f < 2LL * g.batch * g.h_q * g.T; f += 128LL * gridDim.x) redo[f] = 1;
+            return;
+        }
+        tickets = queue_heads[__builtin_ctzll(mine)];
+    }
+    auto leave = [&]() {                                   // no ticket is drawn after this (one lane)
+        if (tickets && atomicAdd(tickets + kLeft, 1) == (int)gridDim.x - 1)
+            atomicExch(&queue_owner[(tickets - queue_heads[0]) / (kXcds * kTicketStride)], 0ull);
+    };
     // the row of a ticket as the next one (one lane); ticket < 0: there is none
     auto open_next = [&](RowInfo &w, int ticket) {
         int unit = -1, mrow = 0;
@@ -634,7 +666,10 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             __syncthreads();
             unit = uniform(next_cnt[0]);
             mrow = uniform(next_cnt[1]);
-            if (unit < 0) return;
+            if (unit < 0) {
+                if (threadIdx.x == 0) leave();
+                return;
+            }
             __syncthreads();                               // (next_cnt is loaded into later)
         }
         decode(unit, mrow, bhq, i);
@@ -841,6 +876,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         if (unit1 < 0) {                                   // no further row
             finish();
             store();
+            if (threadIdx.x == 0) leave();
             break;
         }
         const int bhq1 = uniform(info[cur ^ 1].bhq), i1 = uniform(info[cur ^ 1].i);
@@ -877,20 +913,20 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // Whether workgroups take their rows from queues: with a few rows per workgroup a queue's lookahead of one row costs more
 // balance than the gaps between workgroups.
 bool wide_rows_from_queues(const Geo &g) { return (long long)g.batch * g.h_q * g.T >= wide::kQueueRows; }
-// bytes of the queue heads
-size_t wide_queue_bytes() { return wide::kXcds * wide::kTicketStride * sizeof(int32_t); }
 
 // redo: [batch * h_q * T] flags, written for every query block: int32, or int16 where rows come from queues.
-// tickets: the queue heads, not NULL exactly where rows come from queues.
 pbs_status launch_attn_wide(const Geo &g, const void *Qp, const void *Kp, const void *Vt, const int32_t *qidx,
                             const int32_t *kidx, const int32_t *row_cnt, const int32_t *col_idx, void *Op, float *lse,
-                            void *redo, int32_t *tickets, int tok_delta, hipStream_t s)
+                            void *redo, int tok_delta, hipStream_t s)
 {
     const long long units = (long long)g.batch * g.h_kv, rows = (long long)g.r * g.T;
     int cohort_log2 = wide::kCohortLog2;
     unsigned wgs = wide::kResident;
-    if (tickets) {
-        const pbs_status st = launch(wide::init_tickets_kernel, dim3(1), dim3(64), 0, s, tickets);
+    unsigned long long key = 0;
+    if (wide_rows_from_queues(g)) {
+        static std::atomic<unsigned long long> calls{0};
+        key = calls.fetch_add(1, std::memory_order_relaxed) + 1;
+        const pbs_status st = launch(wide::take_queues_kernel, dim3(1), dim3(64), 0, s, key);
         if (st != PBS_OK) return st;
     } else {
         // every row has a workgroup of its own; cohorts narrower while some XCD would get none
@@ -900,7 +936,7 @@ pbs_status launch_attn_wide(const Geo &g, const void *Qp, const void *Kp, const 
     }
     return launch(wide::attn_wide_kernel, dim3(wgs), dim3(128), 0, s, (const bf16_t *)Qp, (const bf16_t *)Kp,
                   (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse, (int8_t *)redo, g, tok_delta,
-                  tickets, cohort_log2);
+                  key, cohort_log2);
 }
 
 }  // namespace pbs

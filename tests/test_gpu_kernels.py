@@ -268,3 +268,35 @@ def test_fp64_key_scores_of_a_key_that_is_not_a_number(oracle, dtype, d, block, 
     got = pbs.key_scores(p, to_dev(Q, dtype), to_dev(K, dtype)).cpu().numpy()
     assert np.isnan(got[0, 1]).all()
     np.testing.assert_allclose(got[0, 0], oracle.key_scores(Q, K, block)[0, 0], rtol=2.0 ** -23, atol=1e-37)
+
+
+def test_calls_on_two_streams_may_share_a_workspace():
+    # 4096 rows each, so that both calls hand their rows out from queues at the same time.  On ordinary inputs the flags that
+    # either call leaves in the workspace are all zero, so nothing else in it can disturb the other.
+    block, d, T, Hq, Hkv = 128, 128, 512, 8, 4
+    n = T * block
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    K, V = (torch.randn((1, Hkv, n, d), generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
+    Q = [torch.randn((1, Hq, n, d), generator=g, device="cuda").to(torch.bfloat16) for _ in range(2)]
+    p = pbs.problem(1, Hq, Hkv, n, d, block, block, "bf16")
+    kidx, Kp, Vt = pbs.segment_permute(p, None, K, V)
+    i = torch.arange(T, dtype=torch.int32, device="cuda")
+    cnt = torch.clamp(i + 1, max=8).repeat(1, Hq, 1).contiguous()
+    cols = torch.zeros((T, T), dtype=torch.int32, device="cuda")
+    for k in range(8):                                     # the last eight blocks, ascending
+        cols[:, k] = torch.clamp(i - 7, min=0) + k
+    cols = cols.repeat(1, Hq, 1, 1).contiguous()
+    want = [pbs.attn_fwd(p, q, Kp, Vt, None, kidx, cnt, cols) for q in Q]
+    ws, streams = pbs.alloc_workspace(p, pbs.STAGE_ATTN_FWD), [torch.cuda.Stream() for _ in range(2)]
+    got = [torch.empty_like(q) for q in Q]
+    for _ in range(4):
+        for o in got:
+            o.fill_(float("nan"))
+        torch.cuda.synchronize()
+        for _ in range(3):
+            for q, o, s in zip(Q, got, streams):
+                with torch.cuda.stream(s):
+                    pbs.attn_fwd(p, q, Kp, Vt, None, kidx, cnt, cols, o, ws=ws)
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
