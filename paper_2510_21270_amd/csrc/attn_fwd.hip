@@ -480,35 +480,48 @@ __device__ __forceinline__ void attn_row(
     }
 }
 
+// Workgroup id -> kv head, query head, query block.  Workgroups are handed to the 8 XCDs round-robin by linear id and
+// every XCD has its own L2, so the id is decoded as (xcd, slot): the 64 workgroups that are resident on one XCD
+// at a time form a cohort of 64 rows of ONE kv head with nearly equal list lengths (16 consecutive query blocks
+// x the r query heads of the group, longest first).  A cohort walks its ascending lists in near lock-step, so a
+// K'/V' sub-tile is fetched into that L2 once and hit by the other members.  false: there is no such row.
+struct Place {
+    int unit, bhq, i;
+};
+__host__ __device__ inline int place_cohorts(const Geo &g) { return g.batch * g.h_kv * ceil_div(g.r * g.T, kCohort); }
+__device__ __forceinline__ bool place_of(const Geo &g, int id, Place &at)
+{
+    const int nbk = g.batch * g.h_kv, rows_per_unit = g.r * g.T;
+    const int xcd = id % kXcds, slot = id / kXcds;
+    const int coh = (slot / kCohort) * kXcds + xcd;
+    const int round = coh / nbk, mrow = round * kCohort + slot % kCohort;
+    at.unit = coh - round * nbk;
+    const int later = mrow / g.r, b = at.unit / g.h_kv;
+    at.i = g.T - 1 - later;
+    at.bhq = b * g.h_q + (at.unit - b * g.h_kv) * g.r + mrow - later * g.r;
+    return coh < place_cohorts(g) && mrow < rows_per_unit;
+}
+
 template <int BLOCK, int WAVES, int KT, bool REMAP = false>
 __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_mfma_kernel(
     const bf16_t *__restrict__ Qp, const bf16_t *__restrict__ Kp, const bf16_t *__restrict__ Vt,
     const int32_t *__restrict__ qidx, const int32_t *__restrict__ kidx, const int32_t *__restrict__ row_cnt,
     const int32_t *__restrict__ col_idx, bf16_t *__restrict__ Op, float *__restrict__ lse, Geo g)
 {
-    // Workgroup -> (query head, query block).  Workgroups are handed to the 8 XCDs round-robin by linear id and
-    // every XCD has its own L2, so the id is decoded as (xcd, slot): the 64 workgroups that are resident on one XCD
-    // at a time form a cohort of 64 rows of ONE kv head with nearly equal list lengths (16 consecutive query blocks
-    // x the r query heads of the group, longest first).  A cohort walks its ascending lists in near lock-step, so a
-    // K'/V' sub-tile is fetched into that L2 once and hit by the other members.
-    const int nbk = g.batch * g.h_kv;
-    const int rows_per_unit = g.r * g.T;
-    const int coh_per_unit = (rows_per_unit + kCohort - 1) / kCohort;
-    const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
-    const int coh = (slot / kCohort) * kXcds + xcd;
-    if (coh >= nbk * coh_per_unit) return;
-    const int unit = coh % nbk;
-    const int mrow = (coh / nbk) * kCohort + slot % kCohort;
-    if (mrow >= rows_per_unit) return;
-    const int i = g.T - 1 - mrow / g.r;
-    const int b = unit / g.h_kv, hq = (unit % g.h_kv) * g.r + mrow % g.r;
-    attn_row<BLOCK, WAVES, KT, REMAP>(Qp, Kp, Vt, qidx, kidx, row_cnt, col_idx, Op, lse, g, b * g.h_q + hq, unit, i, threadIdx.x);
+    Place at;
+    if (!place_of(g, blockIdx.x, at)) return;
+    attn_row<BLOCK, WAVES, KT, REMAP>(Qp, Kp, Vt, qidx, kidx, row_cnt, col_idx, Op, lse, g, at.bhq, at.unit, at.i, threadIdx.x);
 }
 
-// Second pass of block 128: the query blocks that the first pass flagged, none on ordinary inputs.  A workgroup looks
-// at the rows blockIdx.x + k gridDim.x, 64 flags at a time, so that finding none costs a launch and one load: with a
-// workgroup per row the 32 768 of them that leave at once took 66 us at 128K tokens, the 8 192 at 32K 27 us.
-constexpr int kRedoWgs = 1024;
+// Second pass of block 128: the query blocks that the first pass flagged, none on ordinary inputs.  Every workgroup reads
+// all flags: finding none costs a launch and a few loads, 4.2 us at 32 / 8 heads x 32768 tokens and 5.3 us x 131072 (12.6 and
+// 48.1 us with a workgroup per row, most of which leave at once).  The flagged rows, in the order of the ids of place_of,
+// go to the workgroups in turn: wherever they lie they are spread over the chip, longest first, and where all are flagged
+// the cohorts are those of a workgroup per row.  Measured, 32 / 8 heads x 131072 tokens, lists of 64 blocks, both passes: last
+// quarter of the rows flagged 18.4 ms, every other row 22.8, one head 14.4 (a workgroup per row 18.4, 22.7 and 22.4;
+// rows dealt out by their number 20.6, 23.5 and 14.4).  512 workgroups drift apart more (23.0), 2048 read the flags longer (8.4 us).
+constexpr int kRedoWgs = 1024;                             // twice what the chip holds
+constexpr int kRedoIds = 64 * 64;                          // ids looked at together: one 64-bit mask per lane
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_redo_kernel(
     const bf16_t *__restrict__ Qp, const bf16_t *__restrict__ Kp, const bf16_t *__restrict__ Vt,
@@ -519,19 +532,51 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     auto flagged = [&](int row) {
         return (narrow ? static_cast<const int16_t *>(flags)[row] : static_cast<const int32_t *>(flags)[row]) != 0;
     };
-    const int rows = g.batch * g.h_q * g.T, step = (int)gridDim.x;
-    for (int base = blockIdx.x; base < rows; base += 64 * step) {
-        const int mine = base + (int)(threadIdx.x & 63) * step;
-        uint64_t todo = __ballot(mine < rows && mine >= 0 && flagged(mine));
-        while (todo) {
-            const int row = base + __builtin_ctzll(todo) * step;
-            todo &= todo - 1;
-            const int bhq = row / g.T, i = row % g.T;
-            const int unit = bhq / g.h_q * g.h_kv + bhq % g.h_q / g.r;
+    {
+        const int rows = g.batch * g.h_q * g.T, per = narrow ? 8 : 4;          // flags to 16 bytes
+        const uintx4 *v = static_cast<const uintx4 *>(flags);
+        uintx4 any = {0u, 0u, 0u, 0u};
+#pragma unroll 4
+        for (int k = threadIdx.x; k < rows / per; k += 256) any |= v[k];
+        const int row = rows / per * per + (int)threadIdx.x;
+        const bool last = row < rows && flagged(row);
+        if (!__syncthreads_or(last || (any[0] | any[1] | any[2] | any[3]) != 0)) return;
+    }
+    __shared__ uint64_t masks[kRedoIds / 64];
+    const int ids = (place_cohorts(g) + kXcds - 1) / kXcds * kXcds * kCohort;
+    int turn = blockIdx.x;                                 // flagged rows from here on until it is this workgroup's turn
+    for (int base = 0; base < ids; base += kRedoIds) {
+#pragma unroll 4
+        for (int k = threadIdx.x; k < kRedoIds; k += 256) {
+            Place at;
+            const uint64_t m = __ballot(base + k < ids && place_of(g, base + k, at) && flagged(at.bhq * g.T + at.i));
+            if ((threadIdx.x & 63) == 0) masks[k >> 6] = m;
+        }
+        __syncthreads();
+        for (;;) {
+            const int lane = threadIdx.x & 63;
+            int upto = __popcll(masks[lane]);              // flagged rows up to and including this lane's mask
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int below = __shfl_up(upto, o, 64);
+                upto += lane >= o ? below : 0;
+            }
+            const int total = __builtin_amdgcn_readlane(upto, 63);
+            if (turn >= total) {
+                turn -= total;
+                break;
+            }
+            const int word = __builtin_ctzll(__ballot(upto > turn));
+            uint64_t m = masks[word];
+            for (int skip = turn - (__builtin_amdgcn_readlane(upto, word) - __popcll(m)); skip > 0; --skip) m &= m - 1;
+            Place at;
+            place_of(g, __builtin_amdgcn_readfirstlane(base + 64 * word + __builtin_ctzll(m)), at);
             int tid = threadIdx.x;
             asm volatile("" : "+v"(tid));                  // per-lane offsets are formed per row, not kept across rows
-            attn_row<128, 4, 64, false>(Qp, Kp, Vt, qidx, kidx, row_cnt, col_idx, Op, lse, g, bhq, unit, i, tid);
+            attn_row<128, 4, 64, false>(Qp, Kp, Vt, qidx, kidx, row_cnt, col_idx, Op, lse, g, at.bhq, at.unit, at.i, tid);
+            turn += (int)gridDim.x;
         }
+        __syncthreads();                                   // before the masks are written again
     }
 }
 
@@ -581,8 +626,7 @@ extern "C" pbs_status pbs_attn_fwd(const pbs_problem *p, const void *Qp, const v
     const Geo g = make_geo(p);
     hipStream_t s = (hipStream_t)stream;
     if (p->dtype == PBS_BF16 && p->d == 128 && (p->block == 128 || p->block == 64)) {
-        const int ncoh = g.batch * g.h_kv * ((g.r * g.T + kCohort - 1) / kCohort);
-        const dim3 mgrid((unsigned)(((ncoh + kXcds - 1) / kXcds) * kCohort * kXcds));
+        const dim3 mgrid((unsigned)((place_cohorts(g) + kXcds - 1) / kXcds * kCohort * kXcds));
         const bool remap = (p->flags & PBS_FLAG_INDEX_REMAP) != 0;     // Kp is the caller's K
         const bool narrow_only = (p->flags & PBS_FLAG_RUNNING_MAX_ONLY) != 0 || remap;
         if (remap) {

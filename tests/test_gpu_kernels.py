@@ -300,3 +300,68 @@ def test_calls_on_two_streams_may_share_a_workspace():
                     pbs.attn_fwd(p, q, Kp, Vt, None, kidx, cnt, cols, o, ws=ws)
         torch.cuda.synchronize()
         assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
+def _rows_that_outgrow_their_reference(seed, Hq, Hkv, T, last):
+    """Inputs, lists of up to 64 blocks each and a workspace: keys from block T - last on stand 80 nats above the others for
+    the query heads that the caller gives a first feature of 16."""
+    block = d = 128
+    n = T * block
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    Q = 0.05 * torch.randn((1, Hq, n, d), generator=g, device="cuda")
+    K = 0.05 * torch.randn((1, Hkv, n, d), generator=g, device="cuda")
+    K[0, :, (T - last) * block:, 0] += 80.0 * d ** 0.5 / 16.0
+    V = torch.randn((1, Hkv, n, d), generator=g, device="cuda")
+    p = pbs.problem(1, Hq, Hkv, n, d, block, block, "bf16")
+    kidx, Kp, Vt = pbs.segment_permute(p, None, K.to(torch.bfloat16), V.to(torch.bfloat16))
+    i = torch.arange(T, device="cuda")
+    cnt = torch.clamp(i + 1, max=64)
+    k = torch.arange(T, device="cuda")
+    cols = torch.where(k[None] < cnt[:, None], (k[None] * i[:, None]) // torch.clamp(cnt[:, None] - 1, min=1), 0).to(torch.int32)
+    return p, Q, Kp, Vt, kidx, cnt.to(torch.int32).repeat(1, Hq, 1).contiguous(), cols.repeat(1, Hq, 1, 1).contiguous()
+
+
+# 4400 rows (more than the 4096 ids that are looked at together), 840 and 21: all of the late rows flagged, those of one
+# head, of some heads, none
+@pytest.mark.parametrize("Hq,Hkv,T,last", [(44, 4, 100, 40), (44, 4, 100, 1), (28, 4, 30, 12), (3, 3, 7, 3)])
+@pytest.mark.parametrize("heads", ["all", "one", "some", "none"])
+def test_second_pass_takes_exactly_the_flagged_rows(Hq, Hkv, T, last, heads):
+    p, Q, Kp, Vt, kidx, cnt, cols = _rows_that_outgrow_their_reference(Hq + T, Hq, Hkv, T, last)
+    on = {"all": list(range(Hq)), "one": [Hq // 2], "some": [h for h in range(Hq) if h % 5 in (1, 2)], "none": []}[heads]
+    Q[0, on, :, 0] += 16.0
+    Q = Q.to(torch.bfloat16)
+    got, lse = pbs.attn_fwd(p, Q, Kp, Vt, None, kidx, cnt, cols, want_lse=True)
+    plain = pbs.problem(1, Hq, Hkv, p.n, 128, 128, 128, "bf16", flags=pbs.FLAG_RUNNING_MAX_ONLY)
+    want, want_lse = pbs.attn_fwd(plain, Q, Kp, Vt, None, kidx, cnt, cols, want_lse=True)
+    # flagged rows went through the kernel that the plain call uses for all of them: the same bits
+    late = torch.zeros((Hq, T), dtype=torch.bool, device="cuda")
+    late[on, T - last:] = True
+    rows = late.repeat_interleave(128, 1)[None]
+    assert torch.equal(got[rows], want[rows]) and torch.equal(lse[rows], want_lse[rows])
+    err = (got.float() - want.float()).abs()
+    assert err.max() < 4e-2 and err.mean() < 2e-3          # twice the bound against the oracle: each side has its own
+
+
+def test_second_pass_of_some_rows_takes_its_share_of_the_time():
+    # 8192 rows of equally long lists (but for the first 64 blocks), the last quarter of each head flagged: as long as a quarter
+    # of the same kernel over all rows, give or take the end of the launch.  Dealt out by row number it took twice that.
+    p, Q, Kp, Vt, kidx, cnt, cols = _rows_that_outgrow_their_reference(3, 32, 8, 256, 64)
+    flat, steep = Q.to(torch.bfloat16), Q.clone()
+    steep[0, :, :, 0] += 16.0
+    steep = steep.to(torch.bfloat16)
+    plain = pbs.problem(1, 32, 8, p.n, 128, 128, 128, "bf16", flags=pbs.FLAG_RUNNING_MAX_ONLY)
+    ws, out = pbs.alloc_workspace(p, pbs.STAGE_ATTN_FWD), torch.empty_like(flat)
+
+    def best(problem, q):
+        times = []
+        for _ in range(8):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            pbs.attn_fwd(problem, q, Kp, Vt, None, kidx, cnt, cols, out, ws=ws)
+            e1.record()
+            e1.synchronize()
+            times.append(e0.elapsed_time(e1))
+        return min(times[2:])
+    first, both, alone = best(p, flat), best(p, steep), best(plain, steep)
+    assert both - first < 1.5 * alone * 2048 / 8192, (first, both, alone)
