@@ -606,13 +606,22 @@ extern "C" pbs_status pbs_segment_permute(const pbs_problem *p, const float *sco
                             : (size_t)g.block * g.d * 4 + (size_t)(g.block / 4) * (64 / (vt_group(g.block) / 4)) * 4;
     if (pool_on_the_way) {
         const size_t pool_lds = 256 * 8 * sizeof(double), lds = vlds > pool_lds ? vlds : pool_lds;
-        const dim3 both(mg.x + vg.x, nbh);
-        return token_copy ? launch(gather_both_kernel<true>, both, dim3(256), lds, s, (const uintx4 *)K, (const uint16_t *)V,
-                                   (const int32_t *)kidx, (uintx4 *)kdst, (uint16_t *)Vt, g.n, g.d, cl, kcopy, vcopy, kbarT,
-                                   g.block, g.T, Tsk, mg.x)
-                          : launch(gather_both_kernel<false>, both, dim3(256), lds, s, (const uintx4 *)K, (const uint16_t *)V,
-                                   (const int32_t *)kidx, (uintx4 *)kdst, (uint16_t *)Vt, g.n, g.d, cl, kcopy, vcopy, kbarT,
-                                   g.block, g.T, Tsk, mg.x);
+        auto gather = [&](unsigned kwgs, unsigned vwgs) {
+            const dim3 grid(kwgs + vwgs, nbh);
+            return token_copy ? launch(gather_both_kernel<true>, grid, dim3(256), lds, s, (const uintx4 *)K, (const uint16_t *)V,
+                                       (const int32_t *)kidx, (uintx4 *)kdst, (uint16_t *)Vt, g.n, g.d, cl, kcopy, vcopy, kbarT,
+                                       g.block, g.T, Tsk, kwgs)
+                              : launch(gather_both_kernel<false>, grid, dim3(256), lds, s, (const uintx4 *)K, (const uint16_t *)V,
+                                       (const int32_t *)kidx, (uintx4 *)kdst, (uint16_t *)Vt, g.n, g.d, cl, kcopy, vcopy, kbarT,
+                                       g.block, g.T, Tsk, kwgs);
+        };
+        // V' may take the place of K, which nothing needs once K' is gathered: then one after the other
+        const uintptr_t k0 = reinterpret_cast<uintptr_t>(K), v0 = reinterpret_cast<uintptr_t>(Vt);
+        if (v0 < k0 + (size_t)nbh * g.n * g.d * es && k0 < v0 + pbs_vt_bytes(p)) {
+            st = gather(mg.x, 0);
+            return st == PBS_OK ? gather(0, vg.x) : st;
+        }
+        return gather(mg.x, vg.x);
     }
     if (kdst)
         st = token_copy ? launch((move_rows_kernel<false, true>), mg, dim3(256), 0, s, (const uintx4 *)K,

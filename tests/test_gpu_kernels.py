@@ -365,3 +365,27 @@ def test_second_pass_of_some_rows_takes_its_share_of_the_time():
         return min(times[2:])
     first, both, alone = best(p, flat), best(p, steep), best(plain, steep)
     assert both - first < 1.5 * alone * 2048 / 8192, (first, both, alone)
+
+
+@pytest.mark.parametrize("d,block,flags", [(128, 128, 0), (128, 128, pbs.FLAG_TOKEN_ORDER_COPY), (64, 128, 0)])
+def test_v_prime_may_take_the_place_of_k(d, block, flags):
+    # K is not needed once K' and the block means are there, and 16 heads x 8192 rows are far more than the chip moves at a time
+    Hkv, n, seg = 16, 8192, 1024
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    K, V = (torch.randn((1, Hkv, n, d), generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
+    scores = torch.rand((1, Hkv, n), generator=g, device="cuda")
+    p = pbs.problem(1, Hkv, Hkv, n, d, block, seg, "bf16", flags=flags)
+    ws = pbs.alloc_workspace(p, pbs.STAGE_BLOCK_MASK).zero_()
+    want = pbs.segment_permute(p, scores, K, V, ws=ws)
+    Vt, ws2 = pbs.alloc_vt(p), torch.zeros_like(ws)
+    place = torch.as_strided(Vt, K.shape, K.stride(), Vt.storage_offset())       # K lies where V' goes
+    place.copy_(K)
+    got = pbs.segment_permute(p, scores, place, V, Vt=Vt, ws=ws2)
+    torch.cuda.synchronize()
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
+    assert torch.equal(ws, ws2)
+    if flags:
+        assert torch.equal(pbs.token_copy(p, got[1], d), K)
+        assert torch.equal(pbs.token_copy(p, got[2], d), pbs.token_copy(p, want[2], d))
