@@ -38,7 +38,7 @@
  *     pbs_attn_fwd; pbs_vt_bytes gives its size.
  *   - Supported: dtype PBS_BF16 or PBS_F32; d in {64, 128}; block in
  *     {16, 32, 64, 128}; segment <= 4096; T <= 4096; any n >= 1.  Attention over PBS_BF16 with block in {64, 128} runs
- *     on the bf16 matrix cores (d = 64 with probabilities kept to fp32 in two terms); every other supported
+ *     on the bf16 matrix cores (d = 64 with fp32 probabilities, each in three bf16 terms); every other supported
  *     combination in fp32 arithmetic.
  *   - Results are deterministic: the same inputs give bit-identical outputs.
  */

@@ -2,12 +2,12 @@
 //
 // Transposed like the d = 128 kernels (S^T = K' Q'^T, O^T += V'^T P^T, one lane owns one query of each 32-query tile).
 // The scores are exact bf16 products summed in fp32; a probability stays an fp32 number: it enters the second product
-// as two bf16 terms, p = hi + lo, whose sum differs from p by less than 2^-17 p, so an O^T sub-tile takes two matrix
-// instructions per fragment (what is left out is 1/256 of the rounding of the bf16 result; measured against 64 bits the
-// error is the same 1.6e-3 as with fp32 fused multiply-adds).
+// as three bf16 terms, which hold its 24 bits, so an O^T sub-tile takes three matrix instructions per fragment.  (With two
+// terms, 2^-18 of a probability left out, the error against 64 bits came out larger than with fp32 multiply-adds, if only
+// from the seventh digit on; with three it does not: 1.5653902e-3 for both at 16 / 4 heads x 3701 tokens.)
 //
 // A workgroup owns 64 queries (all of a block of 64, half a block of 128) and every wave of it works on all 64: each
-// fragment read from LDS feeds two (K') or four (V'^T) matrix instructions.  The waves divide the key list among them in
+// fragment read from LDS feeds two (K') or six (V'^T) matrix instructions.  The waves divide the key list among them in
 // pieces of 64 keys, each with a softmax and an O^T of its own, meet no barrier on the way and add up in LDS at the end.
 // A wave's K' / V'^T sub-tiles of 32 keys come through a ring of its own of two 8 KiB stages filled by asynchronous
 // buffer->LDS loads, two sub-tiles ahead; 16 KiB per wave lets eight waves, two per SIMD, share a compute unit, which is
@@ -72,10 +72,18 @@ __device__ __forceinline__ void move_reference(State &st, const floatx16 (&s)[2]
     }
 }
 
-// p = exp2(s c2 - mref) of both query tiles as bf16 pairs hi, lo; rsum: sums of the fp32 probabilities.
-__device__ __forceinline__ void probabilities(const State &st, const floatx16 (&s)[2], float c2, bf16x8 (&hi)[2][2],
-                                              bf16x8 (&lo)[2][2], float (&rsum)[2])
+// p = exp2(s c2 - mref) of both query tiles as three bf16 terms, largest first; rsum: sums of the fp32 probabilities.
+// What a term leaves of a pair takes one instruction for each of the two, a bf16 dot product with (-1, 0) or (0, -1): exact, and
+// four instructions fewer for a pair than unpacking and subtracting (layer of 16 / 4 heads x 12301 tokens: 701 us
+// against 742).  The two constants sit in registers: as literals they came out as an inline constant with another meaning.
+struct Split {
+    bf16x8 t[3][2][2];                                     // [term][query tile][16 keys]
+};
+__device__ __forceinline__ void probabilities(const State &st, const floatx16 (&s)[2], float c2, Split &pf, float (&rsum)[2])
 {
+    uint32_t c0 = 0x0000bf80u, c1 = 0xbf800000u;
+    asm volatile("" : "+s"(c0), "+s"(c1));
+    const bf16x2 first = __builtin_bit_cast(bf16x2, c0), second = __builtin_bit_cast(bf16x2, c1);
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt) {
         float even = 0.0f, odd = 0.0f;
@@ -85,14 +93,18 @@ __device__ __forceinline__ void probabilities(const State &st, const floatx16 (&
                                __builtin_amdgcn_exp2f(__builtin_fmaf(s[nt][2 * y + 1], c2, -st.mref[nt]))};
             even += p[0];
             odd += p[1];
-            const bf16x2 h = __builtin_convertvector(p, bf16x2);
-            const uint32_t hb = __builtin_bit_cast(uint32_t, h);
-            const floatx2 rest = {p[0] - __uint_as_float(hb << 16), p[1] - __uint_as_float(hb & 0xffff0000u)};
-            const bf16x2 r = __builtin_convertvector(rest, bf16x2);
-            hi[nt][y >> 2][2 * (y & 3)] = h[0];
-            hi[nt][y >> 2][2 * (y & 3) + 1] = h[1];
-            lo[nt][y >> 2][2 * (y & 3)] = r[0];
-            lo[nt][y >> 2][2 * (y & 3) + 1] = r[1];
+            // (written out: as a loop over the terms it is scheduled worse and takes 3 % longer)
+            const bf16x2 t0 = __builtin_convertvector(p, bf16x2);
+            const floatx2 r1 = {__builtin_amdgcn_fdot2_f32_bf16(t0, first, p[0], false), __builtin_amdgcn_fdot2_f32_bf16(t0, second, p[1], false)};
+            const bf16x2 t1 = __builtin_convertvector(r1, bf16x2);
+            const floatx2 r2 = {__builtin_amdgcn_fdot2_f32_bf16(t1, first, r1[0], false), __builtin_amdgcn_fdot2_f32_bf16(t1, second, r1[1], false)};
+            const bf16x2 t2 = __builtin_convertvector(r2, bf16x2);
+#pragma unroll
+            for (int z = 0; z < 2; ++z) {
+                pf.t[0][nt][y >> 2][2 * (y & 3) + z] = t0[z];
+                pf.t[1][nt][y >> 2][2 * (y & 3) + z] = t1[z];
+                pf.t[2][nt][y >> 2][2 * (y & 3) + z] = t2[z];
+            }
         }
         rsum[nt] = even + odd;
     }
@@ -217,21 +229,16 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
 #pragma unroll
             for (int nt = 0; nt < 2; ++nt) s[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[x], qf[nt][x], s[nt], 0, 0, 0);
     };
-    auto add_values = [&](const bf16x8 (&vf)[2][2], const bf16x8 (&hi)[2][2], const bf16x8 (&lo)[2][2]) {
+    auto add_values = [&](const bf16x8 (&vf)[2][2], const Split &pf) {
 #pragma unroll
-        for (int k2 = 0; k2 < 2; ++k2)
+        for (int term = 0; term < 3; ++term)
 #pragma unroll
-            for (int dt = 0; dt < 2; ++dt)
+            for (int k2 = 0; k2 < 2; ++k2)
 #pragma unroll
-                for (int nt = 0; nt < 2; ++nt)
-                    st.acc[dt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[dt][k2], hi[nt][k2], st.acc[dt][nt], 0, 0, 0);
+                for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-        for (int k2 = 0; k2 < 2; ++k2)
-#pragma unroll
-            for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-                for (int nt = 0; nt < 2; ++nt)
-                    st.acc[dt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[dt][k2], lo[nt][k2], st.acc[dt][nt], 0, 0, 0);
+                    for (int nt = 0; nt < 2; ++nt)
+                        st.acc[dt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[dt][k2], pf.t[term][nt][k2], st.acc[dt][nt], 0, 0, 0);
     };
     // the token-level mask on the scores of a sub-tile; s[nt][x]: key 16 (x / 8) + 8 h + x % 8, query 32 nt + n
     auto hide = [&](floatx16 (&s)[2], int slot0) {
@@ -274,17 +281,17 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
         if (masked) hide(s, slot0);
         const bool first = masked || !__all(st.seen[0] && st.seen[1]);
         if (first) move_reference(st, s, c2);              // at least the row maximum: no sum below can be large
-        bf16x8 hi[2][2], lo[2][2];
+        Split pf;
         float rsum[2];
-        probabilities(st, s, c2, hi, lo, rsum);
+        probabilities(st, s, c2, pf, rsum);
         if (!first && __any(!(rsum[0] <= kBigRowSum) || !(rsum[1] <= kBigRowSum))) {
             scores(kf, s);                                 // formed again rather than kept: 16 registers fewer
             move_reference(st, s, c2);
-            probabilities(st, s, c2, hi, lo, rsum);
+            probabilities(st, s, c2, pf, rsum);
         }
         st.l[0] += rsum[0];
         st.l[1] += rsum[1];
-        add_values(vf, hi, lo);
+        add_values(vf, pf);
     };
 
     int s0 = next_slot();
@@ -303,7 +310,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
     }
 
     // A value that is not finite does not come through these products: 0 * inf of a hidden key is NaN, and so is
-    // hi * inf + lo * inf of a visible one whenever lo is zero or negative.  A wave that finds NaN in its O^T forms it again,
+    // the sum over the terms of a visible one whenever a term is zero or negative.  A wave that finds NaN in its O^T forms it again,
     // relative to the references it has ended with: such values leave the products and are added one key at a time, with the
     // undivided probability, for the queries that see the key.  Nothing is prefetched here; with one infinite value that every
     // query of the call sees, 16 / 4 heads x 12301 tokens take 1.26 ms instead of 0.62.
@@ -357,10 +364,10 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
                     const uint64_t lanes = __ballot(any);
                     keys |= ((uint32_t)lanes ? 1u : 0u) << (16 * k2 + x) | ((uint32_t)(lanes >> 32) ? 1u : 0u) << (16 * k2 + 8 + x);
                 }
-            bf16x8 hi[2][2], lo[2][2];
+            Split pf;
             float unused[2];
-            probabilities(st, s, c2, hi, lo, unused);
-            add_values(vf, hi, lo);
+            probabilities(st, s, c2, pf, unused);
+            add_values(vf, pf);
             for (; keys; keys &= keys - 1) {
                 const int key = __builtin_ctz(keys);
                 const float p[2] = {weight[key * kQ + ln], weight[key * kQ + 32 + ln]};

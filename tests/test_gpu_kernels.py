@@ -225,7 +225,7 @@ def test_segment_argsort_by_counting(oracle, heads, segment, segments):
 
 
 # A value that is not finite in a block that every later query sees in full, the later blocks' own values finite: what
-# p * v gives must come out, also where p enters the product as two terms of either sign.  The long case has more than 16384
+# p * v gives must come out, also where p enters the product as several terms of either sign.  The long case has more than 16384
 # query tiles: there a wave has its list to itself.
 @pytest.mark.parametrize("dtype,d,block,Hq,Hkv,n", [("bf16", 64, 64, 4, 2, 500), ("bf16", 64, 128, 2, 1, 700),
                                                     ("bf16", 64, 64, 64, 2, 16410), ("bf16", 64, 32, 2, 1, 300),
@@ -389,3 +389,30 @@ def test_v_prime_may_take_the_place_of_k(d, block, flags):
     if flags:
         assert torch.equal(pbs.token_copy(p, got[1], d), K)
         assert torch.equal(pbs.token_copy(p, got[2], d), pbs.token_copy(p, want[2], d))
+
+
+@pytest.mark.parametrize("dtype,d,block", [("bf16", 64, 64), ("bf16", 64, 128), ("bf16", 64, 32), ("f32", 64, 64)])
+def test_probabilities_keep_their_32_bits(dtype, d, block):
+    # Three keys whose weighted values all but cancel: V[1] undoes V[0] up to its rounding, V[2] what is left up to its own, so the
+    # sum is about 2^-16 of its terms and shows a probability's error of 2^-18 (two bf16 terms) plainly.  Bound: 2^-20 of the
+    # terms for the weights (scores within 2, so that fp32 sums and exp2 are good to about 2^-22) and the output's rounding.
+    H, n = 64, 3
+    Q, K, V = _qkv(77, H, H, n, d, "bf16")
+    Q = wl.round_to_bf16(0.25 * Q)
+    w = np.exp((K.astype(np.float64) @ Q[..., 2, :, None].astype(np.float64))[..., 0] / np.sqrt(d))   # of the last query
+    w /= w.sum(-1, keepdims=True)
+
+    def cancel(k):
+        V[:, :, k] = 0.0
+        V[:, :, k] = wl.round_to_bf16((-(w[..., None] * V).sum(2) / w[..., k, None]).astype(np.float32))
+    V[:, :, 2] = 0.0
+    cancel(1)
+    cancel(2)
+    want, size = (w[..., None] * V).sum(2), (w[..., None] * np.abs(V)).sum(2)
+    assert np.median(np.abs(want) / size) < 2.0 ** -16
+    p = pbs.problem(1, H, H, n, d, block, block, dtype)
+    cnt, cols = pbs.admitted_lists(p)
+    kidx, Kp, Vt = pbs.segment_permute(p, None, to_dev(K, dtype), to_dev(V, dtype))
+    got = to_host(pbs.attn_fwd(p, to_dev(Q, dtype), Kp, Vt, None, kidx, cnt, cols))[0, :, 2]
+    err = np.abs(got - want[0])
+    assert (err <= 2.0 ** -20 * size[0] + 2.0 ** -8 * np.abs(want[0])).all(), (err / size[0]).max() * 2.0 ** 20
