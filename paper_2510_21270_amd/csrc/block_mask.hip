@@ -14,6 +14,7 @@
 //                      the allowed columns, softmax, the mass threshold by bisection (one wave per row), forced
 //                      blocks, then bit-mask words by wave ballot and the ascending column list by prefix popcount.
 #include <type_traits>
+#include <utility>
 
 #include "pbs_host.h"
 
@@ -107,7 +108,7 @@ __global__ __launch_bounds__(256) void pool_kernel(const E *__restrict__ X, doub
 // defines a logit.  It does 12.8 multiply-adds per clock where v_fma_f64 does 8, and a pooled query comes out of LDS
 // once per 64 of them instead of once per 2.  A wave takes 32 columns at a time.  After the logits, wave w owns row w
 // and finishes it alone (no workgroup barriers): softmax, then the smallest probability v* that is still kept, found by
-// bisection instead of a sort, with the row in registers where it has at most 1024 columns.
+// bisection instead of a sort, with the row in registers.
 // Bound: vector issue (pooling Q': a conversion and an fp64 addition per value, 3 us of a wave's time per block; the
 // bisection about as much) and the phases' latencies, which only other waves of the SIMD hide.  Measured, same masks bit
 // for bit, against logits on v_fma_f64 with every multiply-add's query operand read from LDS and two workgroups to a
@@ -126,14 +127,21 @@ struct MassCount {
     int cnt;
 };
 
-// One row, 64 columns per chunk, lane = column.  NC > 0: up to NC chunks in registers (loaded once), 0: in LDS.
-// Columns past the row's own count are padded by the caller.
-constexpr int kPanel = 512;                                // columns whose logits go through LDS at a time where NC > 0
+constexpr int kPanel = 512;                                // columns whose logits go through LDS at a time
+
+template <int... I, typename F>
+__device__ __forceinline__ void for_each_index(std::integer_sequence<int, I...>, F f)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+
+// One row in registers, 64 columns per chunk, lane = column, up to NC chunks.  Columns past the row's own count are padded
+// by the caller.
 template <int NC>
 struct RowProbs {
     double x[NC];
     int chunks;
-    __device__ __forceinline__ RowProbs(double *, int ni, int) : chunks((ni + 63) >> 6) {}
+    __device__ __forceinline__ explicit RowProbs(int ni) : chunks((ni + 63) >> 6) {}
     // the chunks of panel p (kPanel columns, compile-time p) from the panel's row in LDS
     template <int P>
     __device__ __forceinline__ void take(const double *pr, int lane)
@@ -148,21 +156,6 @@ struct RowProbs {
 #pragma unroll
         for (int c = 0; c < NC; ++c)
             if (c < chunks) f(c, x[c]);
-    }
-};
-template <>
-struct RowProbs<0> {
-    double *pr;
-    int chunks;
-    __device__ __forceinline__ RowProbs(double *row, int ni, int lane) : pr(row + lane), chunks((ni + 63) >> 6) {}
-    template <typename F>
-    __device__ __forceinline__ void each(F f)
-    {
-        for (int c = 0; c < chunks; ++c) {
-            double v = pr[64 * c];
-            f(c, v);
-            pr[64 * c] = v;
-        }
     }
 };
 
@@ -180,16 +173,17 @@ __device__ __forceinline__ MassCount mass_at_least(RowProbs<NC> &row, double v)
     return {wave_sum_dpp(acc), cnt};
 }
 
-// QB query blocks (i0 = QB * blockIdx.x and the next ones) of RB query heads per workgroup: RT = RB * QB rows, one wave
-// each.  Neighbouring query blocks see the same pooled keys (the later one a few more columns), so with QB = 2 a
-// 16-byte load of pooled keys feeds twice the multiply-adds and the logits need half the round trips to L2.
+// QB query blocks (i0 = QB * blockIdx.x and the next one) of RB query heads per workgroup: RT = RB * QB rows, one wave
+// each.  Neighbouring query blocks see the same pooled keys (the later one a few more columns), so that
+// pooled keys once loaded feed twice the multiply-adds and the logits need half the round trips to L2.
 // Query blocks are taken from the last one down: the long rows start first, the short ones fill the tail.
-constexpr int kPairedLds = 64 * 1024;
+// The registers of a row of at most 512 columns (NC = 8) leave room for eight waves per SIMD, of 1024 for six, of 2048 for
+// four, of 4096 for two; the more there are, the more they hide of each other's phases.
+constexpr int QB = 2;
+constexpr int select_waves(int nc) { return nc == 8 ? 8 : nc == 16 ? 6 : nc == 32 ? 4 : 2; }
 
-// Rows of at most 512 columns (NC = 8) leave room for eight waves per SIMD, rows of at most 1024 for six; they hide more
-// of each other's phases.
-template <int RB, int QB, int NC, typename E>
-__global__ __launch_bounds__(64 * RB * QB) __attribute__((amdgpu_waves_per_eu(NC == 8 ? 8 : NC == 16 ? 6 : 4, NC == 8 ? 8 : NC == 16 ? 6 : 4)))
+template <int RB, int NC, typename E>
+__global__ __launch_bounds__(64 * RB * QB) __attribute__((amdgpu_waves_per_eu(select_waves(NC), select_waves(NC))))
 void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
                    const double *__restrict__ KbarT,   // [bhkv][d][Ts]
                    uint64_t *__restrict__ mask_bits, int32_t *__restrict__ row_cnt, int32_t *__restrict__ col_idx,
@@ -197,9 +191,9 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
 {
     constexpr int RT = RB * QB;                                      // rows (= waves) of the workgroup
     constexpr int NG = (RT + 3) / 4;                                 // groups of four rows
-    constexpr int FS = NC > 0 ? 4 : 8;                               // steps of four features per register buffer
+    constexpr int FS = 4;                                            // steps of four features per register buffer
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    double *prob = reinterpret_cast<double *>(smem_raw);             // [RT][Tpad]
+    double *prob = reinterpret_cast<double *>(smem_raw);             // [RT][kPanel, or Tpad if less]
     __shared__ __align__(16) double qs[128][RT];                     // block means of the RT query rows, feature-major
 
     const int i0 = (g.T - 1) / QB * QB - QB * (int)blockIdx.x;       // first query block of this workgroup
@@ -241,7 +235,7 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
             // A register is requested again as soon as it is added up, so that the additions (a conversion and an fp64
             // addition per value) run under the loads of the others.  Buffer loads: rows past the block lie past
             // the descriptor's end and read as zeros, without a branch per load.
-            constexpr int U = NC > 0 ? 4 : 8, kNonTemporal = 2;
+            constexpr int U = 4, kNonTemporal = 2;
             const int row_bytes = g.d * (int)sizeof(E);
             const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
                 const_cast<E *>(Qp + ((size_t)(bhq0 + wh) * g.n + lo) * g.d), 0, (hi - lo) * row_bytes, 0x00020000);
@@ -329,26 +323,19 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
         }
       }
     };
-    // Where the row is to sit in registers, it gets there in panels of kPanel columns, so that LDS holds one panel.
+    // A row gets into its wave's registers in panels of kPanel columns, so that LDS holds one panel of every row.
     const int ni = allowed_cols(active ? i : i0, g);
-    RowProbs<NC> row(prob + w * Tpad, ni, lane);
-    if constexpr (NC == 0) {
-        logits(0, ni_all, Tpad);
+    RowProbs<NC> row(ni);
+    const int stride = min(Tpad, kPanel);
+    auto panel = [&](auto p_) {
+        constexpr int P = decltype(p_)::value;
+        if (P * kPanel >= ni_all) return;                            // uniform over the workgroup
+        if (P > 0) __syncthreads();                                  // the panel before is in registers everywhere
+        logits(P * kPanel, min(ni_all, (P + 1) * kPanel), stride);
         __syncthreads();
-    } else {
-        const int stride = min(Tpad, kPanel);
-        auto panel = [&](auto p_) {
-            constexpr int P = decltype(p_)::value;
-            if (P * kPanel >= ni_all) return;                        // uniform over the workgroup
-            if (P > 0) __syncthreads();                              // the panel before is in registers everywhere
-            logits(P * kPanel, min(ni_all, (P + 1) * kPanel), stride);
-            __syncthreads();
-            row.template take<P>(prob + w * stride, lane);
-        };
-        panel(std::integral_constant<int, 0>{});
-        if constexpr (NC * 64 > kPanel) panel(std::integral_constant<int, 1>{});
-        static_assert(NC * 64 <= 2 * kPanel, "two panels");
-    }
+        row.template take<P>(prob + w * stride, lane);
+    };
+    for_each_index(std::make_integer_sequence<int, NC * 64 / kPanel>{}, panel);
 
     // from here on wave w works alone on its row
     if (!active) return;
@@ -438,36 +425,30 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
     if (lane == 0) row_cnt[orow] = base;
 }
 
-template <int RB, int QB, int NC, typename E>
-static pbs_status launch_select_qb(const E *Qp, const double *KbarT, uint64_t *mask_bits, int32_t *row_cnt,
+template <int RB, int NC, typename E>
+static pbs_status launch_select_nc(const E *Qp, const double *KbarT, uint64_t *mask_bits, int32_t *row_cnt,
                                    int32_t *col_idx, const Geo &g, hipStream_t s)
 {
     const int chunks = (g.r + RB - 1) / RB;
     const int Tpad = (g.T + 63) & ~63;
-    const int Ts = kbar_stride(g.T);
-    const size_t lds = (size_t)RB * QB * (NC > 0 && Tpad > kPanel ? kPanel : Tpad) * sizeof(double);
-    static std::atomic<unsigned long long> lds_raised{0};
-    if (lds > 32 * 1024) {
-        const pbs_status st = raise_lds_limit(reinterpret_cast<const void *>(&select_kernel<RB, QB, NC, E>),
-                                              QB == 1 ? RB * kMaxT * (int)sizeof(double) : kPairedLds, lds_raised);
-        if (st != PBS_OK) return st;
-    }
-    return launch((select_kernel<RB, QB, NC, E>), dim3((g.T + QB - 1) / QB, g.batch * g.h_kv * chunks), dim3(64 * RB * QB),
-                  lds, s, Qp, KbarT, mask_bits, row_cnt, col_idx, g, chunks, Tpad, Ts);
+    const size_t lds = (size_t)RB * QB * (Tpad > kPanel ? kPanel : Tpad) * sizeof(double);           // at most 32 KiB
+    return launch((select_kernel<RB, NC, E>), dim3((g.T + QB - 1) / QB, g.batch * g.h_kv * chunks), dim3(64 * RB * QB),
+                  lds, s, Qp, KbarT, mask_bits, row_cnt, col_idx, g, chunks, Tpad, kbar_stride(g.T));
 }
 
-// two query blocks per workgroup while their logits fit 64 KiB of LDS (two such workgroups per compute unit); rows of at
-// most 1024 columns, which then always fit, in registers
+// Rows stay in registers up to the largest T: more than 1024 columns, heads x tokens, block 32: 8 / 2 x 65536 294 us,
+// 8 / 4 x 131072 1.57 ms, block 128: 32 / 8 x 139264 499 us.  With the rows in LDS, one query block to a workgroup and
+// the logits on v_fma_f64 that took 433 us, 2.73 ms and 513 us; with the rows in LDS and the logits on the matrix instruction
+// 504 us, 3.82 ms and 562 us.
 template <int RB, typename E>
 static pbs_status launch_select(const E *Qp, const double *KbarT, uint64_t *mask_bits, int32_t *row_cnt,
                                 int32_t *col_idx, const Geo &g, hipStream_t s)
 {
-    const int Tpad = (g.T + 63) & ~63;
-    if (Tpad <= 512) return launch_select_qb<RB, 2, 8>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
-    if (Tpad <= 1024) return launch_select_qb<RB, 2, 16>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
-    if ((size_t)RB * 2 * Tpad * sizeof(double) <= (size_t)kPairedLds)
-        return launch_select_qb<RB, 2, 0>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
-    return launch_select_qb<RB, 1, 0>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
+    static_assert(kMaxT <= 4096, "columns of a row");
+    if (g.T <= 512) return launch_select_nc<RB, 8>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
+    if (g.T <= 1024) return launch_select_nc<RB, 16>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
+    if (g.T <= 2048) return launch_select_nc<RB, 32>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
+    return launch_select_nc<RB, 64>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
 }
 
 // Block means of K' into KbarT ([kv head][feature][kbar_stride(T)] fp64); also called by pbs_segment_permute for the

@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_helpers import check_close, i32_dev, to_dev, to_host, vt_layout
+from gpu_helpers import check_close, i32_dev, mask_from_bits, to_dev, to_host, vt_layout
 from paper_2510_21270_amd import binding as pbs
 from paper_2510_21270_amd import workloads as wl
 
@@ -416,3 +416,38 @@ def test_probabilities_keep_their_32_bits(dtype, d, block):
     got = to_host(pbs.attn_fwd(p, to_dev(Q, dtype), Kp, Vt, None, kidx, cnt, cols))[0, :, 2]
     err = np.abs(got - want[0])
     assert (err <= 2.0 ** -20 * size[0] + 2.0 ** -8 * np.abs(want[0])).all(), (err / size[0]).max() * 2.0 ** 20
+
+
+def test_selection_time_follows_the_number_of_columns():
+    # 4096 query blocks against 1024: sixteen times the probabilities (and four times the pooling).  With the long rows in LDS
+    # it took 34 times as long.
+    def best(n):
+        Q, K = (torch.randn((1, h, n, 128), device="cuda").to(torch.bfloat16) for h in (8, 4))
+        p = pbs.problem(1, 8, 4, n, 128, 32, 1024, "bf16")
+        out = pbs.block_mask(p, Q, K)
+        kbar = pbs.alloc_workspace(p, pbs.STAGE_BLOCK_MASK)
+        times = []
+        for _ in range(6):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            pbs.block_mask(p, Q, K, *out, ws=kbar)
+            e1.record()
+            e1.synchronize()
+            times.append(e0.elapsed_time(e1))
+        return min(times)
+    short, long = best(32768), best(131072)
+    assert long < 22.0 * short, (short, long)
+
+
+# rows of 2048 and 4096 columns and one more or less, with query heads in groups of one, two, three and five
+@pytest.mark.parametrize("n,block,Hq,Hkv,dtype", [(32767, 16, 1, 1, "f32"), (32785, 16, 4, 2, "bf16"), (65519, 16, 3, 1, "bf16"),
+                                                  (65536, 16, 5, 1, "f32")])
+def test_selection_of_long_rows(oracle, n, block, Hq, Hkv, dtype):
+    Q, K, _ = _qkv(n, Hq, Hkv, n, 64, dtype)
+    p = pbs.problem(1, Hq, Hkv, n, 64, block, 64 * block, dtype, tau=0.9, flags=pbs.FLAG_FORCE_FIRST_BLOCK)
+    mask, cnt, cols = pbs.block_mask(p, to_dev(Q, dtype), to_dev(K, dtype))
+    want, want_cnt, want_cols = oracle.block_mask(Q, K, block, 64 * block, float(np.float32(0.9)), flags=pbs.FLAG_FORCE_FIRST_BLOCK)
+    np.testing.assert_array_equal(mask_from_bits(mask, pbs.T_of(p)), want)
+    np.testing.assert_array_equal(cnt.cpu().numpy(), want_cnt)
+    listed = np.arange(pbs.T_of(p)) < want_cnt[..., None]
+    np.testing.assert_array_equal(cols.cpu().numpy()[listed], want_cols[listed])
