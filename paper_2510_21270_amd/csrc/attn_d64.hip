@@ -472,9 +472,11 @@ pbs_status launch_attn_d64(const Geo &g, const void *Qp, const void *Kp, const v
     constexpr long long kMaxX = 1 << 20;
     const dim3 grid((unsigned)(wgs < kMaxX ? wgs : kMaxX), (unsigned)((wgs + kMaxX - 1) / kMaxX));
     // The chip holds 2048 of these waves, and under the causal mask the last query tile has twice the average list: with
-    // few tiles per wave slot that one list is what everything waits for, so its tiles are shared by four waves until
-    // there are about eight tiles per slot.
-    if (units * rows < 8 * 2048)
+    // few tiles per wave slot that one list is what everything waits for, so a tile's list is shared by four waves until
+    // there are two tiles per slot.  Measured, four waves / one, us: every admitted block listed, 768 tiles 250 / 461, 1536
+    // 324 / 490, 2048 356 / 395, 3088 765 / 801, 4096 612 / 584 and 1374 / 1321, 8192 1200 / 1150, 24576 37640 / 37200; a tenth of the
+    // blocks, 1536 tiles 61 / 76, 2048 65 / 62, 3088 118 / 109, 4096 120 / 91 and 177 / 154, 16384 619 / 488.
+    if (units * rows < 2 * 2048)
         return launch(d64::attn_d64_kernel<4>, grid, dim3(256), 0, s, (const bf16_t *)Qp, (const bf16_t *)Kp,
                       (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse, g, cohort);
     return launch(d64::attn_d64_kernel<1>, grid, dim3(64), 0, s, (const bf16_t *)Qp, (const bf16_t *)Kp,

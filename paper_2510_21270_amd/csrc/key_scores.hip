@@ -614,8 +614,10 @@ static pbs_status run_generic(const Geo &g, const void *Q, const void *K, float 
                      bl, kpc)) != PBS_OK) return st;
     if ((st = launch(scores_merge_f64_kernel, dim3(ceil_div(bl, 4), nbh), dim3(256), 0, s, partial, stats, bl,
                      chunks * wave_share(bl).kg)) != PBS_OK) return st;
-    // short ranges until there are workgroups enough for eight per compute unit
-    const int keys = (long long)g.n * nbh > 256LL * 8 * 64 ? kF64Keys : 64;
+    // Short ranges until there are workgroups enough for eight per compute unit.  Measured, 256 keys / 64, us: d = 64, 4096 keys in
+    // all 23.2 / 7.7, 49204 23.5 / 19.3, 98304 37.9 / 31.4, 131072 40.3 / 41.8, 196608 55.0 / 60.2; d = 128, 32768 keys 38.0 / 19.9,
+    // 98304 58.8 / 57.9, 131072 61.2 / 74.9, 262144 116 / 147 (a workgroup reads Qhat, 128 KiB, before its first key).
+    const int keys = (long long)g.n * nbh >= 256LL * 8 * 64 ? kF64Keys : 64;
     return launch((scores_final_f64_kernel<E, D>), dim3(ceil_div(g.n, keys), nbh), dim3(256), 0, s, (const E *)K, qhat,
                   stats, scores, g, bl, keys);
 }

@@ -16,8 +16,8 @@ def _qkv(seed, Hq, Hkv, n, d, dtype):
     return [wl.round_to_bf16(a) for a in x] if dtype == "bf16" else x
 
 
-# n: one query, one query past a 16-query tile, one short of a block, several blocks and a ragged tail.  34 heads and
-# the longer lengths pass the workgroup count from which four waves share a list instead of eight.
+# n: one query, one query past a 16-query tile, one short of a block, several blocks and a ragged tail; few workgroups and
+# (34 heads) several to a compute unit
 @pytest.mark.parametrize("n", [1, 17, 127, 700])
 @pytest.mark.parametrize("dtype,d,block,Hq,Hkv", [("f32", 64, 16, 2, 1), ("f32", 64, 64, 34, 2), ("f32", 128, 32, 3, 3),
                                                    ("f32", 128, 128, 34, 34), ("bf16", 64, 32, 2, 2),
@@ -41,7 +41,7 @@ def test_fp32_attention_over_given_lists(oracle, dtype, d, block, Hq, Hkv, n):
 
 
 # ... and the d = 64 kernel, 64 queries to a tile: short of one, one past it, ragged blocks, a T of its own; four waves
-# share a list (all of them, or fewer entries than waves) up to 16384 tiles, one wave has it to itself from there on
+# share a list (all of them, or fewer entries than waves) up to 4096 tiles, one wave has it to itself from there on
 @pytest.mark.parametrize("block,Hq,Hkv,n,rho", [(b, hq, hkv, n, 0.5) for b, hq, hkv in [(64, 4, 2), (128, 3, 1), (64, 7, 7)]
                                                 for n in (1, 65, 190, 900)] + [(64, 64, 2, 16410, 0.02)])
 def test_d64_attention_over_given_lists(oracle, block, Hq, Hkv, n, rho):
@@ -225,7 +225,7 @@ def test_segment_argsort_by_counting(oracle, heads, segment, segments):
 
 
 # A value that is not finite in a block that every later query sees in full, the later blocks' own values finite: what
-# p * v gives must come out, also where p enters the product as several terms of either sign.  The long case has more than 16384
+# p * v gives must come out, also where p enters the product as several terms of either sign.  The long case has more than 4096
 # query tiles: there a wave has its list to itself.
 @pytest.mark.parametrize("dtype,d,block,Hq,Hkv,n", [("bf16", 64, 64, 4, 2, 500), ("bf16", 64, 128, 2, 1, 700),
                                                     ("bf16", 64, 64, 64, 2, 16410), ("bf16", 64, 32, 2, 1, 300),
