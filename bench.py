@@ -21,7 +21,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 MFMA_BF16_PEAK_TFLOPS = 2500.0       # MI355X dense bf16 matrix peak
-FP32_VECTOR_PEAK_TFLOPS = 157.3       # published fp32 vector rate (the shapes outside the matrix-core path)
+FP32_VECTOR_PEAK_TFLOPS = 157.3       # published fp32 vector rate (the shapes in fp32 arithmetic)
 HBM_PEAK_GBS = 8000.0                # MI355X HBM3E
 
 
@@ -356,14 +356,14 @@ def main():
     visited = int(cnt.sum())                           # blocks the masks list
     T = w.T
     # blocks that are multiplied: with the token-order copy, a query block i of a full segment whose list ends with
-    # its R own-segment blocks inside one staged chunk of 1024 entries takes i % R + 1 blocks for them instead of R
+    # its R own-segment blocks takes i % R + 1 blocks for them instead of R
     computed = visited
     own_in_token_order = (token_copy and w.dtype == "bf16" and w.d == 128 and w.block == 128 and
                           (w.batch * w.h_kv + 1) * T * 128 * 256 < 2 ** 31 - 1)   # what pbs_attn_fwd requires for it
     if own_in_token_order:
         R, G = w.segment // w.block, w.n // w.segment
         i = np.arange(T, dtype=np.int64)[None, None, :]
-        applies = (i // R < G) & (cnt >= R) & (((cnt - 1) % 1024) + 1 >= R)
+        applies = (i // R < G) & (cnt >= R)
         computed = int(visited - np.where(applies, R - (i % R + 1), 0).sum())
     causal_total = w.batch * w.h_q * T * (T + 1) // 2
     flop = computed * 4.0 * w.block * w.block * w.d     # effective TFLOP/s counts computed blocks only
@@ -388,9 +388,9 @@ def main():
                 "frac_from_visited_blocks": visited_tflops / MFMA_BF16_PEAK_TFLOPS,
                 "traffic": traffic, "traffic_source": traffic_src or "not measured for this workload",
                 "avg_launch_ms": stage_ms["attn_fwd"]}
-    if not (w.dtype == "bf16" and w.d == 128 and w.block in (64, 128)):
-        # every other shape is rated against the chip's fp32 vector peak (256 compute units x 128 FMA lanes x 2 x 2.4 GHz
-        # = 157.3 TFLOP/s), which is the rate of the fp32 matrix instructions that fp32 storage runs on as well
+    if not (w.dtype == "bf16" and w.block in (64, 128)):
+        # float32 storage and bf16 blocks of 16 or 32 run on fp32 matrix instructions, whose rate is the chip's fp32 vector
+        # peak (256 compute units x 128 FMA lanes x 2 x 2.4 GHz = 157.3 TFLOP/s)
         roofline.update(bound="alu", peak=FP32_VECTOR_PEAK_TFLOPS, frac=attn_tflops / FP32_VECTOR_PEAK_TFLOPS,
                         frac_from_visited_blocks=visited_tflops / FP32_VECTOR_PEAK_TFLOPS)
     if given:

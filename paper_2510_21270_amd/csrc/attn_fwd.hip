@@ -491,15 +491,17 @@ struct Place {
 __host__ __device__ inline int place_cohorts(const Geo &g) { return g.batch * g.h_kv * ceil_div(g.r * g.T, kCohort); }
 __device__ __forceinline__ bool place_of(const Geo &g, int id, Place &at)
 {
-    const int nbk = g.batch * g.h_kv, rows_per_unit = g.r * g.T;
+    const int nbk = g.batch * g.h_kv;
+    const int rows_per_unit = g.r * g.T;
     const int xcd = id % kXcds, slot = id / kXcds;
     const int coh = (slot / kCohort) * kXcds + xcd;
-    const int round = coh / nbk, mrow = round * kCohort + slot % kCohort;
-    at.unit = coh - round * nbk;
-    const int later = mrow / g.r, b = at.unit / g.h_kv;
-    at.i = g.T - 1 - later;
-    at.bhq = b * g.h_q + (at.unit - b * g.h_kv) * g.r + mrow - later * g.r;
-    return coh < place_cohorts(g) && mrow < rows_per_unit;
+    if (coh >= place_cohorts(g)) return false;
+    at.unit = coh % nbk;
+    const int mrow = (coh / nbk) * kCohort + slot % kCohort;
+    if (mrow >= rows_per_unit) return false;
+    at.i = g.T - 1 - mrow / g.r;
+    at.bhq = at.unit / g.h_kv * g.h_q + (at.unit % g.h_kv) * g.r + mrow % g.r;
+    return true;
 }
 
 template <int BLOCK, int WAVES, int KT, bool REMAP = false>
