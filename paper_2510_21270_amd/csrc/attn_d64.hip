@@ -11,9 +11,10 @@
 // pieces of 64 keys, each with a softmax and an O^T of its own, meet no barrier on the way and add up in LDS at the end.
 // A wave's K' / V'^T sub-tiles of 32 keys come through a ring of its own of two 8 KiB stages filled by asynchronous
 // buffer->LDS loads, two sub-tiles ahead; 16 KiB per wave lets eight waves, two per SIMD, share a compute unit, which is
-// what overlaps one wave's softmax with the other's products.  Bound: vector issue, 36 clocks per score (multiply-add, exp2, sum, split and
-// packs) against 24 of matrix work.  Measured, 16 / 4 heads x 12301 tokens, block 64, nine tenths of the causal blocks:
-// 609 us = 460 TFLOP/s; fp32 matrix instructions (attn_fp32.hip) take 3.71 ms for it, fp32 vector arithmetic took 22.8 ms.
+// what overlaps one wave's softmax with the other's products.  Bound: vector issue, 41 clocks per score (multiply-add, exp2, sum, three
+// packs and two remainders) against 32 of matrix work; the matrix pipe is busy 42 % of the time.  Measured, 16 / 4 heads x
+// 12301 tokens, block 64: every admitted block 765 us = 410 TFLOP/s; a layer of nine tenths of the blocks 0.70 ms, with this stage on
+// fp32 matrix instructions (attn_fp32.hip) 4.35 ms, on fp32 vector arithmetic 24 ms.
 #include "pbs_host.h"
 
 namespace pbs {
