@@ -6,7 +6,7 @@
 namespace pbs {
 
 // ---------------------------------------------------------------------------------------------
-// One workgroup sorts one segment.  Key = (~orderable(score)) << 32 | position-in-segment, so an ascending 64-bit
+// One workgroup sorts one segment (or several short ones).  Key = (~orderable(score)) << 32 | position-in-segment, so an ascending 64-bit
 // bitonic sort yields descending score with ties in ascending position.  -0.0 is folded onto +0.0 first so that the bit
 // order agrees with the arithmetic order.
 // The keys stay in registers, kSortPer = 4 neighbouring ones per lane (a padded segment of 4096 keys is 1024 threads):
@@ -16,7 +16,9 @@ namespace pbs {
 // Bound: instruction issue, ~10 vector instructions per key and stage.  Measured at 1024 keys a segment: 16 segments
 // 15.0 -> 9.8 us, 1024 segments 26.5 -> 16.6 us against the same network with the keys in LDS (two LDS round trips and
 // the index arithmetic of a generic loop per stage).
-// grid = (G + 1, batch*h_kv); workgroup G writes the identity for the unpermuted tail.
+// Segments of at most 128 keys lie side by side in a wave, 256 keys (padded) of them: 8 x 65536 keys in segments of 16 take
+// 4.2 us, of 64 5.5, of 128 7.3 (a wave to a segment padded to 256: 40.5, 13.3 and 9.4; keys in LDS 18.0, 10.9 and 10.3).
+// grid = (ceil(G / segments of a workgroup) + 1, batch*h_kv); the last workgroup writes the identity for the unpermuted tail.
 // ---------------------------------------------------------------------------------------------
 constexpr int kSortPer = 4;
 typedef int int4u __attribute__((ext_vector_type(4), aligned(4)));
@@ -74,7 +76,7 @@ __device__ __forceinline__ uint32_t sort_key(int raw)
 
 // identity != NULL: the positions 0 .. n-1 are written there as well (the kidx of a token-order copy).
 // INT_KEYS: `scores` holds int32 keys instead, sorted ascending (equal keys in ascending position).
-// p2: the segment padded to a power of two of at least 256; blockDim.x = p2 / kSortPer.
+// p2: the segment padded to a power of two; blockDim.x = max(p2, 256) / kSortPer.
 template <bool INT_KEYS>
 __global__ __launch_bounds__(1024) void segment_argsort_kernel(const float *__restrict__ scores,
                                                                int32_t *__restrict__ kidx,
@@ -82,20 +84,24 @@ __global__ __launch_bounds__(1024) void segment_argsort_kernel(const float *__re
                                                                int G, int p2)
 {
     extern __shared__ __align__(16) u64 keys[];              // two buffers of p2 keys (segments of more than one wave)
-    const int g = blockIdx.x, tid = threadIdx.x;
+    const int tid = threadIdx.x, p2_log2 = 31 - __builtin_clz(p2);
+    const int per = (int)(blockDim.x * kSortPer) >> p2_log2;  // segments of this workgroup
+    const int g0 = blockIdx.x * per;
     const size_t base = (size_t)blockIdx.y * n;
     if (identity) {
-        const int lo = g * segment, hi = g >= G ? n : lo + segment;
+        const int lo = min(g0, G) * segment, hi = blockIdx.x == gridDim.x - 1 ? n : min(g0 + per, G) * segment;
         for (int p = lo + tid; p < hi; p += blockDim.x) identity[base + p] = p;
     }
-    if (g >= G) {
+    if (blockIdx.x == gridDim.x - 1) {
         for (int p = G * segment + tid; p < n; p += blockDim.x) kidx[base + p] = p;
         return;
     }
-    const float *s = scores + base + (size_t)g * segment;
-    const int t0 = tid * kSortPer;                           // a segment is a multiple of 16 keys
+    // this lane's segment and place in it; a segment is a multiple of 16 keys
+    const int g = g0 + (tid * kSortPer >> p2_log2), t0 = tid * kSortPer & (p2 - 1);
+    const bool mine = g < G && t0 < segment;
+    const float *s = scores + base + (size_t)min(g, G - 1) * segment;
     u64 key[kSortPer];
-    if (t0 < segment) {
+    if (mine) {
         const int4u raw = *reinterpret_cast<const int4u *>(s + t0);
 #pragma unroll
         for (int e = 0; e < kSortPer; ++e) {
@@ -136,7 +142,7 @@ __global__ __launch_bounds__(1024) void segment_argsort_kernel(const float *__re
             exchange_in_lane(key[2], key[3], false);
         }
     }
-    if (t0 < segment) {
+    if (mine) {
         int4u out;
 #pragma unroll
         for (int e = 0; e < kSortPer; ++e) out[e] = g * segment + (int32_t)(key[e] & 0xffffffffu);
@@ -221,15 +227,16 @@ struct SortShape {
 };
 static SortShape sort_shape(int segment)
 {
-    int p2 = 64 * kSortPer;
+    int p2 = 16;
     while (p2 < segment) p2 <<= 1;
-    return {p2, p2 / kSortPer, p2 > 64 * kSortPer ? 2 * (size_t)p2 * sizeof(u64) : 0};
+    const int keys = p2 > 64 * kSortPer ? p2 : 64 * kSortPer;
+    return {p2, keys / kSortPer, p2 > 64 * kSortPer ? 2 * (size_t)p2 * sizeof(u64) : 0};
 }
 
 // Counting costs a segment's square, the network hardly more than its own depth until it fills the chip: up to 32768 keys
 // in all counting is ahead (us, counting / network: 64 segments of 512 keys 6.1 / 6.8, 32 of 1024 7.2 / 9.0, 16 of 2048
 // 10.5 / 11.4, 8 of 4096 16.8 / 20.6; 16 of 1024 6.5 / 8.8), past it no longer (64 of 1024 9.0 / 9.0, 128 of 1024
-// 14.1 / 9.0); below 256 keys a segment is one wave's network.
+// 14.1 / 9.0); below 256 keys a segment is one wave's network, or part of one.
 constexpr int kRankKeys = 32768, kRankMinSegment = 256;
 
 template <bool INT_KEYS>
@@ -247,8 +254,9 @@ static pbs_status launch_sort(const Geo &g, int heads, const float *scores, int3
         const pbs_status st = raise_lds_limit(reinterpret_cast<const void *>(&segment_argsort_kernel<INT_KEYS>), 64 * 1024, lds_raised);
         if (st != PBS_OK) return st;
     }
-    return launch(segment_argsort_kernel<INT_KEYS>, dim3(g.G + 1, heads), dim3(sh.threads), sh.lds, s, scores, idx, identity,
-                  g.n, g.segment, g.G, sh.p2);
+    const int per = sh.threads * kSortPer / sh.p2;
+    return launch(segment_argsort_kernel<INT_KEYS>, dim3(ceil_div(g.G, per) + 1, heads), dim3(sh.threads), sh.lds, s, scores, idx,
+                  identity, g.n, g.segment, g.G, sh.p2);
 }
 
 __global__ __launch_bounds__(256) void iota_kernel(int32_t *__restrict__ idx, int32_t *__restrict__ idx2, int n,

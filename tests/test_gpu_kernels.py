@@ -451,3 +451,40 @@ def test_selection_of_long_rows(oracle, n, block, Hq, Hkv, dtype):
     np.testing.assert_array_equal(cnt.cpu().numpy(), want_cnt)
     listed = np.arange(pbs.T_of(p)) < want_cnt[..., None]
     np.testing.assert_array_equal(cols.cpu().numpy()[listed], want_cols[listed])
+
+
+# segments of at most 128 keys lie side by side in a wave: numbers that fill it and that do not, one segment, none
+@pytest.mark.parametrize("block,segment", [(16, 16), (32, 32), (16, 48), (64, 64), (16, 80), (32, 128), (16, 144)])
+@pytest.mark.parametrize("segments", [0, 1, 2, 15, 16, 17, 53])
+def test_segment_argsort_of_short_segments(oracle, block, segment, segments):
+    n = segments * segment + segment - 5
+    s = np.round(np.random.default_rng(n).standard_normal((1, 3, n)) * 8).astype(np.float32) / 8
+    s[0, 1, ::3], s[0, 2, ::5], s[0, 2, 1::5] = -0.0, np.inf, -np.inf
+    p = pbs.problem(1, 3, 3, n, 64, block, segment, "f32", flags=pbs.FLAG_TOKEN_ORDER_COPY)
+    want = oracle.segment_argsort(s, segment)
+    kidx, _, _ = pbs.segment_permute(p, torch.from_numpy(s).cuda(), None, None, indices_only=True)
+    np.testing.assert_array_equal(kidx.cpu().numpy(), want)
+    assert (pbs.token_copy(p, kidx, 1).cpu().numpy() == np.arange(n)).all()
+    p = pbs.problem(1, 3, 3, n, 64, block, segment, "f32")
+    both = torch.from_numpy(s).cuda()
+    kidx, _, _ = pbs.segment_permute(p, both, None, None, kidx=both.view(torch.int32), indices_only=True)
+    np.testing.assert_array_equal(kidx.cpu().numpy(), want)
+
+
+def test_short_segments_sort_as_fast_as_long_ones():
+    # the same 524288 keys in segments of 16 and of 256: with a wave to a segment of 16 it took more than five times as long
+    def best(block, segment):
+        p = pbs.problem(1, 8, 8, 65536, 64, block, segment, "f32")
+        s, kidx = torch.rand((1, 8, 65536), device="cuda"), pbs.alloc_kidx(p)
+        times = []
+        for _ in range(6):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for _ in range(20):
+                pbs.segment_permute(p, s, None, None, kidx=kidx, indices_only=True)
+            e1.record()
+            e1.synchronize()
+            times.append(e0.elapsed_time(e1))
+        return min(times)
+    short, long = best(16, 16), best(64, 256)
+    assert short < 2.5 * long, (short, long)
