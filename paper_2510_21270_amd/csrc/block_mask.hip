@@ -173,16 +173,15 @@ __device__ __forceinline__ MassCount mass_at_least(RowProbs<NC> &row, double v)
     return {wave_sum_dpp(acc), cnt};
 }
 
-// QB query blocks (i0 = QB * blockIdx.x and the next one) of RB query heads per workgroup: RT = RB * QB rows, one wave
-// each.  Neighbouring query blocks see the same pooled keys (the later one a few more columns), so that
-// pooled keys once loaded feed twice the multiply-adds and the logits need half the round trips to L2.
+// QB query blocks (i0 = QB * blockIdx.x and the next ones) of RB query heads per workgroup: RT = RB * QB rows, one wave
+// each.  Neighbouring query blocks see the same pooled keys (the later ones a few more columns), so that pooled keys once
+// loaded feed QB times the multiply-adds and the logits need that much fewer round trips to L2.
 // Query blocks are taken from the last one down: the long rows start first, the short ones fill the tail.
 // The registers of a row of at most 512 columns (NC = 8) leave room for eight waves per SIMD, of 1024 for six, of 2048 for
 // four, of 4096 for two; the more there are, the more they hide of each other's phases.
-constexpr int QB = 2;
 constexpr int select_waves(int nc) { return nc == 8 ? 8 : nc == 16 ? 6 : nc == 32 ? 4 : 2; }
 
-template <int RB, int NC, typename E>
+template <int RB, int QB, int NC, typename E>
 __global__ __launch_bounds__(64 * RB * QB) __attribute__((amdgpu_waves_per_eu(select_waves(NC), select_waves(NC))))
 void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
                    const double *__restrict__ KbarT,   // [bhkv][d][Ts]
@@ -425,14 +424,14 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
     if (lane == 0) row_cnt[orow] = base;
 }
 
-template <int RB, int NC, typename E>
+template <int RB, int QB, int NC, typename E>
 static pbs_status launch_select_nc(const E *Qp, const double *KbarT, uint64_t *mask_bits, int32_t *row_cnt,
                                    int32_t *col_idx, const Geo &g, hipStream_t s)
 {
     const int chunks = (g.r + RB - 1) / RB;
     const int Tpad = (g.T + 63) & ~63;
     const size_t lds = (size_t)RB * QB * (Tpad > kPanel ? kPanel : Tpad) * sizeof(double);           // at most 32 KiB
-    return launch((select_kernel<RB, NC, E>), dim3((g.T + QB - 1) / QB, g.batch * g.h_kv * chunks), dim3(64 * RB * QB),
+    return launch((select_kernel<RB, QB, NC, E>), dim3((g.T + QB - 1) / QB, g.batch * g.h_kv * chunks), dim3(64 * RB * QB),
                   lds, s, Qp, KbarT, mask_bits, row_cnt, col_idx, g, chunks, Tpad, kbar_stride(g.T));
 }
 
@@ -440,15 +439,31 @@ static pbs_status launch_select_nc(const E *Qp, const double *KbarT, uint64_t *m
 // 8 / 4 x 131072 1.57 ms, block 128: 32 / 8 x 139264 499 us.  With the rows in LDS, one query block to a workgroup and
 // the logits on v_fma_f64 that took 433 us, 2.73 ms and 513 us; with the rows in LDS and the logits on the matrix instruction
 // 504 us, 3.82 ms and 562 us.
-template <int RB, typename E>
+template <int RB, int QB, typename E>
+static pbs_status launch_select_qb(const E *Qp, const double *KbarT, uint64_t *mask_bits, int32_t *row_cnt,
+                                   int32_t *col_idx, const Geo &g, hipStream_t s)
+{
+    static_assert(kMaxT <= 4096, "columns of a row");
+    if (g.T <= 512) return launch_select_nc<RB, QB, 8>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
+    if (g.T <= 1024) return launch_select_nc<RB, QB, 16>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
+    if (g.T <= 2048) return launch_select_nc<RB, QB, 32>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
+    return launch_select_nc<RB, QB, 64>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
+}
+
+// A matrix instruction takes four rows, so one or two query heads to a kv head come with four query blocks to a workgroup as long
+// as that leaves a workgroup for every compute unit.  Measured, four query blocks / two, us: 8 / 8 heads x 65536 67 / 102, x 131072
+// 155 / 222, 32 / 32 x 32768 81 / 113, x 131072 493 / 766, 8 / 4 x 65536 54 / 66; fewer workgroups, 2 / 2 x 4096 10.7 / 10.2, 8 / 8 x
+// 8192 14.5 / 14.1.  (Logits on v_fma_f64, two query blocks: 77, 175, 88, 581, 62; 22 and 16.)
+template <typename E>
 static pbs_status launch_select(const E *Qp, const double *KbarT, uint64_t *mask_bits, int32_t *row_cnt,
                                 int32_t *col_idx, const Geo &g, hipStream_t s)
 {
-    static_assert(kMaxT <= 4096, "columns of a row");
-    if (g.T <= 512) return launch_select_nc<RB, 8>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
-    if (g.T <= 1024) return launch_select_nc<RB, 16>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
-    if (g.T <= 2048) return launch_select_nc<RB, 32>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
-    return launch_select_nc<RB, 64>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
+    const bool many = (long long)g.batch * g.h_kv * ((g.T + 3) / 4) >= 256;
+    if (g.r >= 3) return launch_select_qb<4, 2>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
+    if (g.r == 2) return many ? launch_select_qb<2, 4>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s)
+                              : launch_select_qb<2, 2>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
+    return many ? launch_select_qb<1, 4>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s)
+                : launch_select_qb<1, 2>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
 }
 
 // Block means of K' into KbarT ([kv head][feature][kbar_stride(T)] fp64); also called by pbs_segment_permute for the
@@ -497,14 +512,6 @@ extern "C" pbs_status pbs_block_mask(const pbs_problem *p, const void *Qp, const
     hipStream_t s = (hipStream_t)stream;
     double *KbarT = reinterpret_cast<double *>(ws);
     if (!(p->flags & PBS_FLAG_KBAR_IN_WS) && (st = launch_pool_keys(p, g, Kp, KbarT, s)) != PBS_OK) return st;
-    if (p->dtype == PBS_BF16) {
-        const bf16_t *Q = (const bf16_t *)Qp;
-        if (g.r >= 3) return launch_select<4>(Q, KbarT, mask_bits, row_cnt, col_idx, g, s);
-        if (g.r == 2) return launch_select<2>(Q, KbarT, mask_bits, row_cnt, col_idx, g, s);
-        return launch_select<1>(Q, KbarT, mask_bits, row_cnt, col_idx, g, s);
-    }
-    const float *Q = (const float *)Qp;
-    if (g.r >= 3) return launch_select<4>(Q, KbarT, mask_bits, row_cnt, col_idx, g, s);
-    if (g.r == 2) return launch_select<2>(Q, KbarT, mask_bits, row_cnt, col_idx, g, s);
-    return launch_select<1>(Q, KbarT, mask_bits, row_cnt, col_idx, g, s);
+    return p->dtype == PBS_BF16 ? launch_select((const bf16_t *)Qp, KbarT, mask_bits, row_cnt, col_idx, g, s)
+                                : launch_select((const float *)Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
 }
