@@ -450,20 +450,22 @@ static pbs_status launch_select_qb(const E *Qp, const double *KbarT, uint64_t *m
     return launch_select_nc<RB, QB, 64>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
 }
 
-// A matrix instruction takes four rows, so one or two query heads to a kv head come with four query blocks to a workgroup as long
-// as that leaves a workgroup for every compute unit.  Measured, four query blocks / two, us: 8 / 8 heads x 65536 67 / 102, x 131072
-// 155 / 222, 32 / 32 x 32768 81 / 113, x 131072 493 / 766, 8 / 4 x 65536 54 / 66; fewer workgroups, 2 / 2 x 4096 10.7 / 10.2, 8 / 8 x
-// 8192 14.5 / 14.1.  (Logits on v_fma_f64, two query blocks: 77, 175, 88, 581, 62; 22 and 16.)
+// A matrix instruction takes four rows: with one query head to a kv head two query blocks leave half of it empty, so four come to
+// a workgroup except in the shortest rows; with two heads two blocks fill it and four only halve the reads of pooled keys, which
+// pays once every compute unit has a workgroup.  Measured, four query blocks / two, us: one head, T = 64 12.1 / 10.9 and 11.2 / 11.0,
+// 100 13.3 / 16.2, 128 11.1 / 12.9, 256 15.7 / 19.0, 1024 43 / 56, 8 / 8 heads x 131072 155 / 222, 32 / 32 x 131072 493 / 766; two heads, 32
+// workgroups of four blocks 14.7 / 11.7, 89 22.5 / 20.3, 128 16.2 / 12.6, 200 19.1 / 19.7, 256 48 / 51, 512 54 / 66.  (Logits on
+// v_fma_f64, two query blocks: 8 / 8 x 131072 175, 32 / 32 x 131072 581, two heads at 512 workgroups 62.)
 template <typename E>
 static pbs_status launch_select(const E *Qp, const double *KbarT, uint64_t *mask_bits, int32_t *row_cnt,
                                 int32_t *col_idx, const Geo &g, hipStream_t s)
 {
-    const bool many = (long long)g.batch * g.h_kv * ((g.T + 3) / 4) >= 256;
     if (g.r >= 3) return launch_select_qb<4, 2>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
-    if (g.r == 2) return many ? launch_select_qb<2, 4>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s)
-                              : launch_select_qb<2, 2>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
-    return many ? launch_select_qb<1, 4>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s)
-                : launch_select_qb<1, 2>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
+    if (g.r == 2)
+        return (long long)g.batch * g.h_kv * ceil_div(g.T, 4) >= 256 ? launch_select_qb<2, 4>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s)
+                                                                     : launch_select_qb<2, 2>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
+    return g.T > 64 ? launch_select_qb<1, 4>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s)
+                    : launch_select_qb<1, 2>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
 }
 
 // Block means of K' into KbarT ([kv head][feature][kbar_stride(T)] fp64); also called by pbs_segment_permute for the

@@ -490,9 +490,9 @@ def test_short_segments_sort_as_fast_as_long_ones():
     assert short < 2.5 * long, (short, long)
 
 
-# one and two query heads to a kv head: four query blocks to a workgroup from 256 workgroups on, two below; the last
-# workgroup with one to four of them
-@pytest.mark.parametrize("T", [62, 124, 125, 126, 127])
+# one and two query heads to a kv head: four query blocks to a workgroup in rows of more than 64 columns, or from 256
+# workgroups on, two otherwise; the last workgroup with one to four of them
+@pytest.mark.parametrize("T", [62, 64, 65, 124, 125, 126, 127])
 @pytest.mark.parametrize("Hq,Hkv,d,dtype", [(8, 8, 64, "bf16"), (16, 8, 128, "bf16"), (8, 8, 128, "f32"), (16, 8, 64, "f32")])
 def test_selection_with_few_query_heads_to_a_kv_head(oracle, Hq, Hkv, d, dtype, T):
     n, block, seg = T * 16 - 5, 16, 128
