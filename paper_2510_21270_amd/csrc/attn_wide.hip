@@ -16,8 +16,13 @@
 //     all along:     P^T(t) = softmax arithmetic on S(t), one score pair per two MFMAs
 //     LDS traffic:   V'^T(t - 1) fragment reads under MFMAs 0..7; after MFMA 11 the waves meet (every load issued
 //                    two or more iterations ago has landed, the V'^T part just read is free); the loads of K'(t + 4),
-//                    V'^T(t + 3) and the key positions of sub-tile t + 4 go out under MFMAs 12..20; K'(t + 2)
-//                    fragment reads under MFMAs 16..23
+//                    V'^T(t + 3) and the key positions of sub-tile t + 4 go out under MFMAs 13, 15 .. 29; K'(t + 2)
+//                    fragment reads under MFMAs 16, 18 .. 30
+// A wave issues in order and has its SIMD to itself, so whatever stands between two iterations is paid in full: whether
+// all queries have their reference is one scalar, the check of the row sums waits for the end of the row, the block for
+// sub-tiles that are not plain lies outside the loop, and the operands of the loads are formed ahead of the barrier.  That
+// is 1447 -> 1219 clocks per iteration (dense lists, 32768 tokens; the MFMAs alone take 1024); the clock granted under
+// the chip's power limit falls with it, 1686 -> 1519 MHz, so that layers gain 3 .. 5 %.
 // LDS holds a 4-deep ring of stages filled by asynchronous buffer->LDS loads; stage p holds the K' part p and the
 // V'^T part (p + 3) % 4 of their blocks, which is what iteration t = p (mod 4) frees and refills.
 // A sub-tile that is not plain (token-level mask, queries without a visible key so far) first rewrites its scores
@@ -31,6 +36,8 @@
 // of the causal blocks, 65536 tokens 3.57 -> 3.48 ms; masks of an eighth, 131072 tokens 14.1 -> 13.7 ms (layer); dense
 // masks, where the chip's power and not its idle time is what runs out, 102.0 -> 100.1 ms (layer, 131072 tokens).
 #include <limits.h>
+
+#include <utility>
 
 #include "pbs_host.h"
 
@@ -121,7 +128,7 @@ struct StageLoad {
 
 // Stage P receives the K' part P of block jk and the V'^T part (P + 3) % 4 of block jv.
 template <int P>
-__device__ __forceinline__ StageLoad stage_load(Stage &sg, const TileBuffers &buf, int jk, int jv, int wave)
+__device__ __forceinline__ StageLoad stage_load(__attribute__((address_space(3))) unsigned char *dst, const TileBuffers &buf, int jk, int jv, int wave)
 {
     StageLoad a;
     static_assert(BLOCK * 256 == D * BLOCK * 2 && KS * 256 == D * KS * 2, "blocks and sub-tiles of K' and Vt are equally large");
@@ -129,7 +136,7 @@ __device__ __forceinline__ StageLoad stage_load(Stage &sg, const TileBuffers &bu
     a.soff = (wave == 0 ? jk : jv) * (BLOCK * 256) + (wave == 0 ? P : (P + 3) & 3) * (KS * 256);
     int half = wave * kStageB;                             // sg.k for wave 0, sg.v behind it for wave 1
     asm volatile("" : "+s"(half));     // formed here: 32 loop-invariant addresses would not fit the scalar registers
-    a.dst = (__attribute__((address_space(3))) unsigned char *)sg.k + half;
+    a.dst = dst + half;
     return a;
 }
 
@@ -144,19 +151,19 @@ __device__ __forceinline__ void issue_load(const StageLoad &a, const LaneOffsets
 // token-level mask read them, but the load is issued for every sub-tile, by all lanes of both waves (four bytes per
 // lane, the same 256 bytes from each wave): one more instruction in the stream costs less than a branch around it.
 template <int P>
-__device__ __forceinline__ void issue_positions(Stage &sg, const TileBuffers &buf, int j, int lane)
+__device__ __forceinline__ void issue_positions(lptr_t dst, const TileBuffers &buf, int j, int lane)
 {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(buf.pos, (lptr_t)sg.pos, 4, lane * 4, (j * BLOCK + P * KS) * 4, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(buf.pos, dst, 4, lane * 4, (j * BLOCK + P * KS) * 4, 0, 0);
 }
 
 template <int P>
 __device__ __forceinline__ void issue_stage(Stage &sg, const TileBuffers &buf, const LaneOffsets &off, int j, int wave,
                                             int lane)
 {
-    const StageLoad a = stage_load<P>(sg, buf, j, j, wave);
+    const StageLoad a = stage_load<P>((__attribute__((address_space(3))) unsigned char *)sg.k, buf, j, j, wave);
     issue_load<0>(a, off); issue_load<1>(a, off); issue_load<2>(a, off); issue_load<3>(a, off);
     issue_load<4>(a, off); issue_load<5>(a, off); issue_load<6>(a, off); issue_load<7>(a, off);
-    issue_positions<P>(sg, buf, j, lane);
+    issue_positions<P>((lptr_t)sg.pos, buf, j, lane);
 }
 
 // Every asynchronous load of this wave has landed, then all waves meet: the stages loaded so far are complete.
@@ -182,7 +189,7 @@ struct State {
     floatx16 acc_o[4][2];
     float mref[2], l[2];    // reference (log2 units) and sum of exp2(s*c2 - mref), this lane's half of the keys
     bool seen[2];           // the query has met a visible key, i.e. mref is set
-    bool bad;               // a probability outgrew the fixed reference: this query block is redone by the caller
+    bool all_seen;          // every query of the wave has (the same in all lanes)
 };
 
 __device__ __forceinline__ void load_kf(bf16x8 (&kf)[8], const Stage &sg, const LaneOffsets &off)
@@ -272,6 +279,19 @@ __device__ __forceinline__ void set_reference(State &st, int nt, const floatx16 
     }
 }
 
+// O^T MFMA i of a query tile works on V'^T fragment pv_fragment(i): the four O^T tiles with the first 16 keys, then with
+// the other 16, so that consecutive MFMAs never share an accumulator
+__device__ constexpr int pv_fragment(int i) { return (i & 3) << 1 | i >> 2; }
+
+// What goes out under which of the 32 MFMAs of an iteration (-1: nothing).  The loads and the K' reads take every second
+// slot, so that neither the address unit nor LDS, which four waves share, is asked for one a slot.
+struct Slots {
+    static constexpr int kMeet = 11;                       // the waves meet after this one
+    static constexpr int v_read(int m) { return m < 8 ? m : -1; }
+    static constexpr int load(int m) { return m > kMeet && m < 31 && m % 2 == 1 ? (m - kMeet - 2) / 2 : -1; }    // 8: positions
+    static constexpr int k_read(int m) { return m >= 16 && m % 2 == 0 ? (m - 16) / 2 : -1; }
+};
+
 // One iteration t (t = P mod 4) of the pipeline described at the top of the file.
 // s_cur: scores of sub-tile t (formed by the previous iteration); s_nxt: receives the scores of sub-tile t + 1.
 // kf: K' fragments of sub-tile t + 1 on entry, of sub-tile t + 2 on exit.
@@ -287,11 +307,12 @@ __device__ __forceinline__ void step(State &st, floatx16 (&s_cur)[2], floatx16 (
                                      int wave, int lane)
 {
     bf16x8 vf[8];
-    if (masked || !__all(st.seen[0] && st.seen[1])) {
+    if (__builtin_expect(masked || !st.all_seen, 0)) {
         asm volatile("" ::: "memory");                     // keeps this rare block out of the straight-line code
         if (masked) mask_tile(s_cur, sg_v.pos, room, qpos, lh);
         set_reference(st, 0, s_cur[0], c2);
         set_reference(st, 1, s_cur[1], c2);
+        st.all_seen = __all(st.seen[0] && st.seen[1]);
     }
     __builtin_amdgcn_sched_barrier(0);
     // Softmax of score pair q (query tile q / 8, scores 2 (q % 8) and + 1) in three stages, issued in consecutive
@@ -301,119 +322,67 @@ __device__ __forceinline__ void step(State &st, floatx16 (&s_cur)[2], floatx16 (
     // not overlap with the matrix instructions the way ordinary vector arithmetic does.
     floatx2 rsum[2] = {{0.0f, 0.0f}, {0.0f, 0.0f}};        // per query tile: sums over even and odd scores
     floatx2 pr = {0.0f, 0.0f}, ar = {0.0f, 0.0f};
-#define PBS_SM_FMA(q)                                                                                        \
-    {                                                                                                        \
-        ar[0] = __builtin_fmaf(s_cur[(q) >> 3][2 * ((q) & 7)], c2, -st.mref[(q) >> 3]);                      \
-        ar[1] = __builtin_fmaf(s_cur[(q) >> 3][2 * ((q) & 7) + 1], c2, -st.mref[(q) >> 3]);                  \
-    }
-#define PBS_SM_EXP(q)                                                                                        \
-    {                                                                                                        \
-        pr[0] = __builtin_amdgcn_exp2f(ar[0]);                                                               \
-        pr[1] = __builtin_amdgcn_exp2f(ar[1]);                                                               \
-    }
-#define PBS_SM_PACK(q)                                                                                       \
-    {                                                                                                        \
-        bf16x2 t2 = __builtin_convertvector(pr, bf16x2);                                                     \
-        asm volatile("" : "+v"(t2));                       /* the pack happens here, not where it is consumed */ \
-        rsum[(q) >> 3] += pr;                                                                                \
-        asm volatile("" : "+v"(rsum[(q) >> 3]));                                                             \
-        pf_new[(q) >> 3][((q) & 7) >> 2][2 * ((q) & 3)] = t2[0];                                             \
-        pf_new[(q) >> 3][((q) & 7) >> 2][2 * ((q) & 3) + 1] = t2[1];                                         \
-    }
-    // vector work of MFMA slot m
-#define PBS_SM_SLOT(m)                                                                                       \
-    {                                                                                                        \
-        if (((m) & 1) == 0) {                                                                                \
-            if ((m) > 0) PBS_SM_PACK((((m) >> 1) + 15) & 15)                                                 \
-            PBS_SM_FMA((m) >> 1)                                                                             \
-        } else {                                                                                             \
-            PBS_SM_EXP((m) >> 1)                                                                             \
-        }                                                                                                    \
-        asm volatile("" : "+v"(pr), "+v"(ar));                                                               \
-        __builtin_amdgcn_sched_barrier(0);                                                                   \
-    }
-    // ---- slots 0..15: score MFMAs of sub-tile t + 1 (opaque statements, so the interleaving is written out).
-    // The V'^T fragments are read in slots 0..7.  After slot 11 the waves meet: every wave has those fragments in
-    // registers (stage sg_v is free) and every load issued so far has landed; the refill of sg_v is issued under
-    // slots 12..19.  K' fragment reads of sub-tile t + 2 take slots 16..23.
-#define PBS_S_MFMA(m)                                                                                        \
-    {                                                                                                        \
-        if ((m) == 0) s_mfma_first<0>(s_nxt[0], kf[0], qf[0][0]);                                            \
-        else if ((m) == 1) s_mfma_first<1>(s_nxt[1], kf[0], qf[1][0]);                                       \
-        else if (((m) & 1) == 0) s_mfma_next<0>(s_nxt[0], kf[(m) >> 1], qf[0][(m) >> 1]);                    \
-        else s_mfma_next<1>(s_nxt[1], kf[(m) >> 1], qf[1][(m) >> 1]);                                        \
-        asm volatile("" : "+v"(pr), "+v"(ar));             /* the slot's vector work follows its MFMA */     \
-    }
-#define PBS_VF_SLOT(m)                                                                                       \
-    {                                                                                                        \
-        PBS_S_MFMA(m)                                                                                        \
-        vf[m] = *reinterpret_cast<const bf16x8 *>(sg_v.v + off.vfr[(m) & 1] + ((m) >> 1) * 2048);            \
-        PBS_SM_SLOT(m)                                                                                       \
-    }
-#define PBS_S_SLOT(m)                                                                                        \
-    {                                                                                                        \
-        PBS_S_MFMA(m)                                                                                        \
-        PBS_SM_SLOT(m)                                                                                       \
-    }
-#define PBS_SLD_SLOT(m)                                                                                      \
-    {                                                                                                        \
-        PBS_S_MFMA(m)                                                                                        \
-        issue_load<(m) - 12>(ld, off);                                                                       \
-        PBS_SM_SLOT(m)                                                                                       \
-    }
-    PBS_VF_SLOT(0) PBS_VF_SLOT(1) PBS_VF_SLOT(2) PBS_VF_SLOT(3) PBS_VF_SLOT(4) PBS_VF_SLOT(5) PBS_VF_SLOT(6) PBS_VF_SLOT(7)
-    PBS_S_SLOT(8) PBS_S_SLOT(9) PBS_S_SLOT(10) PBS_S_SLOT(11)
-    sync_older_stages();
-    const StageLoad ld = stage_load<P>(sg_v, buf, jk, jv, wave);
-    PBS_SLD_SLOT(12) PBS_SLD_SLOT(13) PBS_SLD_SLOT(14) PBS_SLD_SLOT(15)
-#undef PBS_SLD_SLOT
-#undef PBS_S_SLOT
-#undef PBS_VF_SLOT
-#undef PBS_S_MFMA
-    // ---- slots 16..31: O^T update with sub-tile t - 1.  MFMA i of a query tile works on fragment PBS_MQ(i): the four
-    // O^T tiles with the first 16 keys, then with the other 16, so that consecutive MFMAs never share an accumulator.
-#define PBS_MQ(i) ((((i) & 3) << 1) | ((i) >> 2))
-#define PBS_PV_MFMA(n)                                                                                       \
-    st.acc_o[PBS_MQ((n) & 7) >> 1][(n) >> 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(                      \
-        vf[PBS_MQ((n) & 7)], pf_prev[(n) >> 3][PBS_MQ((n) & 7) & 1], st.acc_o[PBS_MQ((n) & 7) >> 1][(n) >> 3], 0, 0, 0);
-#define PBS_KF_READ(n) kf[n] = *reinterpret_cast<const bf16x8 *>(sg_k.k + off.kfr[n]);
-#define PBS_PLD_SLOT(n)                                                                                      \
-    {                                                                                                        \
-        PBS_PV_MFMA(n)                                                                                       \
-        issue_load<(n) + 4>(ld, off);                                                                        \
-        PBS_KF_READ(n)                                                                                       \
-        PBS_SM_SLOT(16 + (n))                                                                                \
-    }
-#define PBS_KF_SLOT(n)                                                                                       \
-    {                                                                                                        \
-        PBS_PV_MFMA(n)                                                                                       \
-        PBS_KF_READ(n)                                                                                       \
-        PBS_SM_SLOT(16 + (n))                                                                                \
-    }
-#define PBS_PV_SLOT(n)                                                                                       \
-    {                                                                                                        \
-        PBS_PV_MFMA(n)                                                                                       \
-        PBS_SM_SLOT(16 + (n))                                                                                \
-    }
-    PBS_PLD_SLOT(0) PBS_PLD_SLOT(1) PBS_PLD_SLOT(2) PBS_PLD_SLOT(3)
-    issue_positions<P>(sg_v, buf, jk, lane);
-    PBS_KF_SLOT(4) PBS_KF_SLOT(5) PBS_KF_SLOT(6) PBS_KF_SLOT(7)
-    PBS_PV_SLOT(8) PBS_PV_SLOT(9) PBS_PV_SLOT(10) PBS_PV_SLOT(11) PBS_PV_SLOT(12) PBS_PV_SLOT(13) PBS_PV_SLOT(14)
-    PBS_PV_SLOT(15)
-    PBS_SM_PACK(15)
-#undef PBS_PV_SLOT
-#undef PBS_KF_SLOT
-#undef PBS_PLD_SLOT
-#undef PBS_KF_READ
-#undef PBS_PV_MFMA
-#undef PBS_SM_SLOT
-#undef PBS_SM_PACK
-#undef PBS_SM_EXP
-#undef PBS_SM_FMA
+    // the vector work of MFMA slot m
+    auto softmax_slot = [&](auto mc) __attribute__((always_inline)) {
+        constexpr int m = decltype(mc)::value, q = m >> 1;
+        if constexpr ((m & 1) == 0) {
+            if constexpr (m > 0) {
+                constexpr int z = q - 1, nt = z >> 3;
+                bf16x2 t2 = __builtin_convertvector(pr, bf16x2);
+                asm volatile("" : "+v"(t2));               // the pack happens here, not where it is consumed
+                if constexpr ((z & 7) == 0) rsum[nt] = pr;
+                else rsum[nt] += pr;
+                asm volatile("" : "+v"(rsum[nt]));
+                pf_new[nt][(z & 7) >> 2][2 * (z & 3)] = t2[0];
+                pf_new[nt][(z & 7) >> 2][2 * (z & 3) + 1] = t2[1];
+            }
+            if constexpr (m < 32) {
+                ar[0] = __builtin_fmaf(s_cur[q >> 3][2 * (q & 7)], c2, -st.mref[q >> 3]);
+                ar[1] = __builtin_fmaf(s_cur[q >> 3][2 * (q & 7) + 1], c2, -st.mref[q >> 3]);
+            }
+        } else {
+            pr[0] = __builtin_amdgcn_exp2f(ar[0]);
+            pr[1] = __builtin_amdgcn_exp2f(ar[1]);
+        }
+        if constexpr (m >= 16) asm volatile("" : "+v"(pr), "+v"(ar));
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    StageLoad ld;
+    const auto stage_dst = (__attribute__((address_space(3))) unsigned char *)sg_v.k;
+    const lptr_t pos_dst = (lptr_t)sg_v.pos;
+    auto slot = [&](auto mc) __attribute__((always_inline)) {
+        constexpr int m = decltype(mc)::value;
+        if constexpr (m < 16) {
+            constexpr int x = m >> 1;
+            if constexpr (m == 0) s_mfma_first<0>(s_nxt[0], kf[0], qf[0][0]);
+            else if constexpr (m == 1) s_mfma_first<1>(s_nxt[1], kf[0], qf[1][0]);
+            else if constexpr ((m & 1) == 0) s_mfma_next<0>(s_nxt[0], kf[x], qf[0][x]);
+            else s_mfma_next<1>(s_nxt[1], kf[x], qf[1][x]);
+            __builtin_amdgcn_sched_barrier(0);             // the slot's vector work follows its MFMA
+        } else {
+            constexpr int n = m - 16, f = pv_fragment(n & 7);
+            st.acc_o[f >> 1][n >> 3] =
+                __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[f], pf_prev[n >> 3][f & 1], st.acc_o[f >> 1][n >> 3], 0, 0, 0);
+        }
+        constexpr int v = Slots::v_read(m), k = Slots::k_read(m), l = Slots::load(m);
+        if constexpr (l >= 0 && l < 8) issue_load<l>(ld, off);
+        if constexpr (l == 8) issue_positions<P>(pos_dst, buf, jk, lane);
+        if constexpr (v >= 0) vf[v] = *reinterpret_cast<const bf16x8 *>(sg_v.v + off.vfr[v & 1] + (v >> 1) * 2048);
+        if constexpr (k >= 0) kf[k] = *reinterpret_cast<const bf16x8 *>(sg_k.k + off.kfr[k]);
+        if constexpr (m == Slots::kMeet - 2) {
+            ld = stage_load<P>(stage_dst, buf, jk, jv, wave);
+            asm volatile("" : "+s"(ld.soff));
+        }
+        softmax_slot(mc);
+        if constexpr (m == Slots::kMeet) sync_older_stages();
+    };
+    [&]<int... M>(std::integer_sequence<int, M...>) __attribute__((always_inline)) {
+        (slot(std::integral_constant<int, M>{}), ...);
+    }(std::make_integer_sequence<int, 32>{});
+    softmax_slot(std::integral_constant<int, 32>{});
     const float rs0 = rsum[0][0] + rsum[0][1], rs1 = rsum[1][0] + rsum[1][1];
     st.l[0] += rs0;
     st.l[1] += rs1;
-    st.bad = st.bad || !(rs0 <= kBigRowSum) || !(rs1 <= kBigRowSum);
     __builtin_amdgcn_sched_barrier(0);
 }
 
@@ -427,10 +396,9 @@ __device__ __forceinline__ void drain(State &st, const bf16x8 (&pf)[2][2], const
     for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
         for (int i = 0; i < 8; ++i)
-            st.acc_o[PBS_MQ(i) >> 1][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                vf[PBS_MQ(i)], pf[nt][PBS_MQ(i) & 1], st.acc_o[PBS_MQ(i) >> 1][nt], 0, 0, 0);
+            st.acc_o[pv_fragment(i) >> 1][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                vf[pv_fragment(i)], pf[nt][pv_fragment(i) & 1], st.acc_o[pv_fragment(i) >> 1][nt], 0, 0, 0);
 }
-#undef PBS_MQ
 
 // A row (query block of one head), in LDS; list entries as (block to load | keys that exist << 20 | mask bit).
 struct RowInfo {
@@ -704,7 +672,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         const int len = uniform(info[cur].len);
         const int *list = lists[cur];
         State st;
-        st.bad = false;
+        st.all_seen = false;
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt) {
             st.mref[nt] = 0.0f;
@@ -805,7 +773,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             step<3>(st, sb, sa, kf, qf, pb, pa, sg3, sg1, qpos, room0 - 3 * KS, masked, c2, lh, buf, off, jn, jn, wave, lane);
             jc = jn;
             pk = pn;
-            if (e == event) at_event(e);
+            if (__builtin_expect(e == event, 0)) at_event(e);
         }
         const bool ahead = (pk & kEntryAhead) != 0;        // the ring holds the next row's first block
         drain(st, pa, sg0, off);
@@ -857,7 +825,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                 }
             }
             // each wave's half of the row's flag: some probability outgrew its fixed reference (the caller redoes the row)
-            const bool bad = __any(st.bad);
+            const bool bad = __any(!(st.l[0] <= kBigRowSum) || !(st.l[1] <= kBigRowSum));
             if (lane == 0) {
                 const size_t f = ((size_t)bhq * g.T + i) * 2 + wave;
                 if (tickets) redo[f] = bad ? 1 : 0;
@@ -887,7 +855,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             __builtin_amdgcn_s_barrier();                  // ... and so has the other
             __builtin_amdgcn_sched_barrier(0);
             if (wave == 1) {
-                const StageLoad ld = stage_load<0>(sg0, buf, j1, j1, 1);
+                const StageLoad ld = stage_load<0>((__attribute__((address_space(3))) unsigned char *)sg0.k, buf, j1, j1, 1);
                 issue_load<0>(ld, off); issue_load<1>(ld, off); issue_load<2>(ld, off); issue_load<3>(ld, off);
                 issue_load<4>(ld, off); issue_load<5>(ld, off); issue_load<6>(ld, off); issue_load<7>(ld, off);
             }
