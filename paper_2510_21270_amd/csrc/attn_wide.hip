@@ -292,6 +292,13 @@ struct Slots {
     static constexpr int k_read(int m) { return m >= 16 && m % 2 == 0 ? (m - 16) / 2 : -1; }
 };
 
+// f(0), f(1), .. with compile-time arguments
+template <typename F, int... M>
+__device__ __forceinline__ void unrolled(F &f, std::integer_sequence<int, M...>)
+{
+    (f(std::integral_constant<int, M>{}), ...);
+}
+
 // One iteration t (t = P mod 4) of the pipeline described at the top of the file.
 // s_cur: scores of sub-tile t (formed by the previous iteration); s_nxt: receives the scores of sub-tile t + 1.
 // kf: K' fragments of sub-tile t + 1 on entry, of sub-tile t + 2 on exit.
@@ -376,9 +383,7 @@ __device__ __forceinline__ void step(State &st, floatx16 (&s_cur)[2], floatx16 (
         softmax_slot(mc);
         if constexpr (m == Slots::kMeet) sync_older_stages();
     };
-    [&]<int... M>(std::integer_sequence<int, M...>) __attribute__((always_inline)) {
-        (slot(std::integral_constant<int, M>{}), ...);
-    }(std::make_integer_sequence<int, 32>{});
+    unrolled(slot, std::make_integer_sequence<int, 32>{});
     softmax_slot(std::integral_constant<int, 32>{});
     const float rs0 = rsum[0][0] + rsum[0][1], rs1 = rsum[1][0] + rsum[1][1];
     st.l[0] += rs0;

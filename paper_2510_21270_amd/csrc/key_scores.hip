@@ -10,23 +10,26 @@
 //
 // bf16, d = 128: both sweeps form the 128 x keys logit tile on the matrix cores (32x32x16 bf16 MFMA, fp32
 // accumulator).  Qhat is an fp32 mean, not a bf16 value, so it is pre-multiplied by scale*log2(e) and split
-// into two bf16 terms hi + lo; each tile takes two MFMAs per fragment.  A wave keeps the fragments of its 32 rows
-// of Qhat in registers and the K tiles go through LDS, shared by the four waves of a workgroup.
+// into two bf16 terms hi + lo; each tile takes two MFMAs per fragment.  A wave keeps the fragments of its rows
+// of Qhat in registers (64 rows for long inputs, 32 for short ones) and the K tiles go through LDS, shared by the waves of
+// a workgroup.  Both forms compute every score with the same operations in the same order.
 // Everything else (fp32 inputs, d = 64): the same two sweeps on the fp64 matrix instruction.
+#include <utility>
+
 #include "pbs_host.h"
 
 namespace pbs {
 
 constexpr int kQRows = 128;            // logit tile rows (>= B')
-constexpr int kMaxKeysPerWg = 1024;    // keys per workgroup in the MFMA sweeps when there are enough keys
-constexpr int kMinKeysPerWg = 256;     // shorter ranges do not pay for a workgroup's start (Qhat fragments, first tiles)
-constexpr int kSweepWgs = 512;         // the sweeps shorten their key ranges until this many workgroups exist
-                                       // (every workgroup first copies the 64 KiB split Qhat: more of them costs again)
+constexpr int kSweepWgs = 512;         // workgroups of the MFMA sweeps that the chip holds: two on each of 256 compute units
+constexpr int kMaxRangeKeys = 1024, kMinRangeKeys = 256;   // keys of a range (sweep_range_keys)
+constexpr long long kLongKeys = 327680;                    // keys of all heads from which on the long sweeps run (long_sweeps)
 constexpr float kLog2e = 1.4426950408889634f;
 
 // ------------------------------------------------------------------ MFMA path: prep
-// qsplit[bh][term][row][dswz]: row-major 128 x 128 bf16, 16-byte chunks XOR-permuted by (row & 15) (the lanes of a
-// fragment load then spread over the 16 chunk positions of their rows).  Rows >= bl are zero.
+// qsplit[bh][row tile][feature step][term][lane][8]: the operand fragments of the 32 x 32 x 16 instruction one after the other
+// (lane = row % 32 + 32 h holds d = 16 step + 8 h .. + 8 of its row), so that a wave loads each as 1 KiB of consecutive
+// bytes.  Rows >= bl are zero.
 // qrows: positions of the bl query rows (device memory), or NULL for the last bl rows of the sequence (Eq. 4);
 // positions outside [0, n) are clamped.  qavg != NULL instead: one query row, the fp64 mean over all positions.
 __device__ inline int query_row_position(const int32_t *qrows, int row, int bl, int n)
@@ -36,6 +39,11 @@ __device__ inline int query_row_position(const int32_t *qrows, int row, int bl, 
     return pos < 0 ? 0 : (pos >= n ? n - 1 : pos);
 }
 
+__device__ __forceinline__ size_t qfrag_offset(int bh, int row_tile, int step, int term)
+{
+    return (size_t)bh * 2 * kQRows * 128 + ((row_tile * 8 + step) * 2 + term) * 512;
+}
+
 __global__ __launch_bounds__(256) void qhat_split_kernel(const bf16_t *__restrict__ Q, bf16_t *__restrict__ qsplit,
                                                          Geo g, int bl, const int32_t *__restrict__ qrows,
                                                          const double *__restrict__ qavg)
@@ -43,8 +51,6 @@ __global__ __launch_bounds__(256) void qhat_split_kernel(const bf16_t *__restric
     // grid = (kQRows / 8, batch * h_kv): each workgroup converts 8 rows x 128 columns, 4 elements per thread
     const int bh = blockIdx.y;
     const int b = bh / g.h_kv, h = bh % g.h_kv;
-    bf16_t *hi = qsplit + (size_t)bh * 2 * kQRows * 128;
-    bf16_t *lo = hi + kQRows * 128;
     const float mul = g.scale * kLog2e / (float)g.r;
     const int row = blockIdx.x * 8 + (threadIdx.x >> 5);
     const int e0 = (threadIdx.x & 31) * 4;
@@ -72,13 +78,373 @@ __global__ __launch_bounds__(256) void qhat_split_kernel(const bf16_t *__restric
         vh[x] = (bf16_t)v;
         vl[x] = (bf16_t)(v - (float)vh[x]);
     }
-    const int chunk = (e0 >> 3) ^ (row & 15);
-    const int dst = row * 128 + chunk * 8 + (e0 & 7);
-    *reinterpret_cast<bf16x4 *>(hi + dst) = vh;
-    *reinterpret_cast<bf16x4 *>(lo + dst) = vl;
+    bf16_t *dst = qsplit + qfrag_offset(bh, row >> 5, e0 >> 4, 0) + ((row & 31) + 32 * ((e0 >> 3) & 1)) * 8 + (e0 & 7);
+    *reinterpret_cast<bf16x4 *>(dst) = vh;
+    *reinterpret_cast<bf16x4 *>(dst + 512) = vl;
 }
 
 // ------------------------------------------------------------------ MFMA path: tiles and fragments
+// Both sweeps multiply the 128 rows of Qhat with every key, two bf16 terms each: 64 matrix instructions of 32 x 32 x 16
+// per 32 keys.  A workgroup is two waves; wave w owns the rows 64 w .. 64 w + 63 (two row tiles) and keeps their fragments in
+// registers (2 row tiles x 8 feature steps x 2 terms x 4 registers), so that a K fragment read from LDS feeds four
+// MFMAs and one wave runs per SIMD.  A wave issues in order, so the two halves of the work are interleaved by hand:
+//     iteration t:  MFMAs 0..31: logits of tile t + 1, row tile 0, then row tile 1;  all along: exponentials and sums of
+//                   tile t, one logit per MFMA, in the same order
+//                   K fragments of tile t + 2 under MFMAs 18, 20 .. 30 (and 0), as tile t + 1 is done with theirs;
+//                   after MFMA 8 the waves meet, then the loads of tile t + 5 go out
+// Tiles travel to LDS asynchronously, through a ring of four; a load has three iterations to arrive.
+// Bound by the matrix work under the chip's power limit and, close behind, by the stream of K: 8 heads of 131072 keys (two sweeps
+// of 69 GFLOP and 268 MB each) 136 -> 125.5 us for the stage against four waves of 32 rows, two to a SIMD, whose staging,
+// exponentials and products took turns.  On the 16 x 16 x 32 instruction, which the power limit favours, 110 us, but with
+// sums in another order: keys with nearly equal scores would change places against the other sizes.  Not taken.
+constexpr int kTileKeys = 32;
+constexpr int kTileB = kTileKeys * 256;
+
+typedef __attribute__((address_space(3))) void *lptr_t;
+
+// 32 keys x 256 bytes; the 16-byte piece c of key r sits at r * 256 + ((c ^ (r & 15)) << 4): conflict-free for the
+// fragment reads (16 lanes = 16 keys, one piece each).  The ring's tiles are separate variables, so that the compiler can
+// tell a read of one from an asynchronous load into another.
+struct __align__(16) KTile {
+    unsigned char b[kTileB];
+};
+
+// Descriptor of a workgroup's keys and byte offsets of this lane: dma[j]: in memory, of the piece it moves in load j of
+// its wave, ahead of 1024 j (the instruction's own offset, which counts in memory and in LDS); kfr[x]: in LDS, of its
+// piece of feature step x.
+struct KSource {
+    __amdgpu_buffer_rsrc_t keys;
+    uint32_t dma[4], kfr[8];
+};
+
+__device__ __forceinline__ KSource key_source(const bf16_t *first, int keys, int lane)
+{
+    KSource k;
+    k.keys = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(first), 0, keys * 256, 0x00020000);
+    const int row = lane >> 4, place = lane & 15, key = lane & 31;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) k.dma[j] = (uint32_t)(row * 256 + ((place ^ (4 * j + row)) << 4));
+#pragma unroll
+    for (int x = 0; x < 8; ++x) k.kfr[x] = (uint32_t)(key * 256 + (((2 * x + (lane >> 5)) ^ (key & 15)) << 4));
+    return k;
+}
+
+// Wave w moves keys 16 w .. 16 w + 15 of tile t (past the last key: zeros, without a memory access)
+__device__ __forceinline__ void issue_tile(KTile &tile, const KSource &src, int t, int wave)
+{
+    const lptr_t dst = (lptr_t)((__attribute__((address_space(3))) unsigned char *)tile.b + wave * 4096);
+    const int soff = t * kTileB + wave * 4096;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(src.keys, dst, 16, src.dma[0], soff, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(src.keys, dst, 16, src.dma[1], soff, 1024, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(src.keys, dst, 16, src.dma[2], soff, 2048, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(src.keys, dst, 16, src.dma[3], soff, 3072, 0);
+}
+
+// Feature step x: lane (key = lane & 31, h = lane >> 5) holds d = 16 x + 8 h .. + 8 of its key.
+__device__ __forceinline__ bf16x8 k_fragment(const KTile &tile, const KSource &src, int x)
+{
+    return *reinterpret_cast<const bf16x8 *>(tile.b + src.kfr[x]);
+}
+
+// The wave's 64 rows of the split Qhat: qf[rt][x][term], row 64 wave + 32 rt + (lane & 31), the features of k_fragment.
+__device__ __forceinline__ void load_qfrags(bf16x8 (&qf)[2][8][2], const bf16_t *qsplit, int bh, int wave, int lane)
+{
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+        for (int x = 0; x < 8; ++x)
+#pragma unroll
+            for (int term = 0; term < 2; ++term)
+                qf[rt][x][term] = *reinterpret_cast<const bf16x8 *>(qsplit + qfrag_offset(bh, 2 * wave + rt, x, term) + lane * 8);
+}
+
+// More wait states than a matrix result needs before a vector instruction reads it; no read of s moves up across
+__device__ __forceinline__ void mfma_fence(floatx16 &s) { asm volatile("s_nop 15\n\ts_nop 15" : "+v"(s)::"memory"); }
+
+// Logit MFMA m of the 32 of a tile, a chain of sixteen for each row tile.  KEYS_BY_ROWS: s[rt][i] belongs to key
+// 8 (i / 4) + 4 h + i % 4 and row 32 rt + (lane & 31), and starts at 0; otherwise to key lane & 31 and that row, and starts at
+// c[rt].  Assembly statements: the compiler's own would move accumulators about.  It does not see inside, so the one hazard
+// (results read by vector instructions) is covered by distance, or by mfma_fence().
+template <int M, bool KEYS_BY_ROWS>
+__device__ __forceinline__ void logit_mfma(floatx16 (&s)[2], const bf16x8 (&kf)[8], const bf16x8 (&qf)[2][8][2],
+                                           const floatx16 (&c)[2])
+{
+    constexpr int rt = M >> 4, x = (M >> 1) & 7, term = M & 1;
+    const bf16x8 &k = kf[x], &q = qf[rt][x][term];
+    if constexpr (KEYS_BY_ROWS) {
+        if constexpr ((M & 15) == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(s[rt]) : "v"(k), "a"(q));
+        else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(s[rt]) : "v"(k), "a"(q));
+    } else {
+        if constexpr ((M & 15) == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" : "=&v"(s[rt]) : "a"(q), "v"(k), "v"(c[rt]));
+        else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(s[rt]) : "a"(q), "v"(k));
+    }
+}
+
+// f(0), f(1), .. with compile-time arguments
+template <typename F, int... M>
+__device__ __forceinline__ void unrolled(F &&f, std::integer_sequence<int, M...>)
+{
+    (f(std::integral_constant<int, M>{}), ...);
+}
+
+// One iteration: logits of tile t + 1 into s_nxt; score(m) does the vector work under MFMA m.  tile1: LDS tile of t + 1, which
+// tile t + 5 takes; tile2: of t + 2.
+template <bool KEYS_BY_ROWS, typename Score>
+__device__ __forceinline__ void sweep_step(floatx16 (&s_nxt)[2], bf16x8 (&kf)[8], const bf16x8 (&qf)[2][8][2],
+                                           const floatx16 (&c)[2], KTile &tile1, const KTile &tile2, const KSource &src,
+                                           int t, int wave, Score score)
+{
+    __builtin_amdgcn_sched_barrier(0);
+    unrolled([&](auto mc) __attribute__((always_inline)) {
+        constexpr int m = decltype(mc)::value;
+        logit_mfma<m, KEYS_BY_ROWS>(s_nxt, kf, qf, c);
+        __builtin_amdgcn_sched_barrier(0);                 // what goes out under an MFMA follows it
+        if constexpr (m == 0) kf[7] = k_fragment(tile1, src, 7);
+        if constexpr (m >= 18 && m % 2 == 0) kf[(m - 18) / 2] = k_fragment(tile2, src, (m - 18) / 2);
+        score(mc);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (m == 8) {
+            // this wave's reads of tile1 are done and its loads of tile t + 2 have landed (those of the two tiles behind may be
+            // on their way); after the barrier that is so for the other wave as well
+            __builtin_amdgcn_s_waitcnt(0x0078);            // vmcnt(8) lgkmcnt(0), gfx9 encoding
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            issue_tile(tile1, src, t + 5, wave);
+        }
+    }, std::make_integer_sequence<int, 32>{});
+}
+
+// Everything ahead of the loop: four tiles on their way, Qhat in registers, the logits of tile 0 in s.
+template <bool KEYS_BY_ROWS>
+__device__ __forceinline__ void sweep_start(floatx16 (&s)[2], bf16x8 (&kf)[8], bf16x8 (&qf)[2][8][2], const floatx16 (&c)[2],
+                                            KTile &t0, KTile &t1, KTile &t2, KTile &t3, const KSource &src,
+                                            const bf16_t *qsplit, int bh, int wave, int lane)
+{
+    issue_tile(t0, src, 0, wave);
+    issue_tile(t1, src, 1, wave);
+    issue_tile(t2, src, 2, wave);
+    issue_tile(t3, src, 3, wave);
+    load_qfrags(qf, qsplit, bh, wave, lane);
+    __builtin_amdgcn_s_waitcnt(0x0F70);                    // vmcnt(0), gfx9 encoding
+    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < 8; ++x) kf[x] = k_fragment(t0, src, x);
+    unrolled([&](auto mc) __attribute__((always_inline)) { logit_mfma<decltype(mc)::value, KEYS_BY_ROWS>(s, kf, qf, c); },
+             std::make_integer_sequence<int, 32>{});
+    mfma_fence(s[0]);
+    mfma_fence(s[1]);
+#pragma unroll
+    for (int x = 0; x < 7; ++x) kf[x] = k_fragment(t1, src, x);
+    __syncthreads();                                       // both waves have read tile 0
+    issue_tile(t0, src, 4, wave);
+}
+
+// ------------------------------------------------------------------ MFMA path: sweep 1
+// partial[bh][range][row] = (max2, sumexp2) over the keys of a range, log2 domain; a workgroup takes `ranges` of them.
+// The maximum of a row tile is known before its first exponential: that of row tile 1 is formed under the exponentials of row
+// tile 0, that of row tile 0 under those of row tile 1 of the tile before.
+__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) void scores_sweep1_kernel(
+    const bf16_t *__restrict__ K, const bf16_t *__restrict__ qsplit, float2 *__restrict__ partial, Geo g, int range_keys,
+    int ranges)
+{
+    __shared__ KTile tile0, tile1, tile2, tile3;
+    const int bh = blockIdx.y, parts = ceil_div(g.n, range_keys);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int range = blockIdx.x * ranges;
+    const int key_begin = range * range_keys, keys = min(g.n - key_begin, range_keys * ranges);
+    const int ntiles = ceil_div(keys, kTileKeys), range_tiles = range_keys / kTileKeys;
+    const KSource src = key_source(K + ((size_t)bh * g.n + key_begin) * 128, keys, lane);
+    bf16x8 qf[2][8][2], kf[8];
+    floatx16 sa[2], sb[2];
+    sweep_start<true>(sa, kf, qf, sa, tile0, tile1, tile2, tile3, src, qsplit, bh, wave, lane);
+    float m[2] = {-INFINITY, -INFINITY}, l[2] = {0.0f, 0.0f};   // row 32 rt + (lane & 31), this lane's half of the keys
+    // keys of tile t that do not exist weigh nothing
+    auto cut = [&](floatx16 &s, int t) __attribute__((always_inline)) {
+        if (__builtin_expect((t + 1) * kTileKeys > keys, 0)) {
+            mfma_fence(s);
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                if (t * kTileKeys + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3) >= keys) s[i] = -INFINITY;
+        }
+    };
+    float top0;                                            // maximum of the current tile's row tile 0
+    cut(sa[0], 0);
+    top0 = sa[0][0];
+#pragma unroll
+    for (int i = 1; i < 16; ++i) top0 = fmaxf(top0, sa[0][i]);
+    auto step = [&](floatx16 (&s)[2], floatx16 (&nxt)[2], KTile &u1, const KTile &u2, int t) __attribute__((always_inline)) {
+        cut(s[1], t);
+        float p[2], sum[2], mn[2], less[2], top1 = -INFINITY;
+        // arguments are <= 0: the bare instruction (no denormal rescue) loses nothing that a sum near 1 would see
+        auto add = [&](auto uc) __attribute__((always_inline)) {         // logit u joins its row tile's sum
+            constexpr int u = decltype(uc)::value, rt = u >> 4;
+            if constexpr ((u & 15) == 0) sum[rt] = p[u & 1];
+            else sum[rt] += p[u & 1];
+            if constexpr ((u & 15) != 0) asm volatile("" : "+v"(sum[rt]));
+            if constexpr ((u & 15) == 15) {
+                const float joined = l[rt] * __builtin_amdgcn_exp2f(m[rt] - mn[rt]) + sum[rt];   // exp2(-inf) = 0 on the first tile
+                l[rt] = mn[rt] != -INFINITY ? joined : l[rt];
+                m[rt] = mn[rt];
+            }
+        };
+        sweep_step<true>(nxt, kf, qf, nxt, u1, u2, src, t, wave, [&](auto mc) __attribute__((always_inline)) {
+            constexpr int mm = decltype(mc)::value, rt = mm >> 4, i = mm & 15;
+            if constexpr (i == 0) {
+                mn[rt] = fmaxf(m[rt], rt == 0 ? top0 : top1);
+                less[rt] = mn[rt] == -INFINITY ? 0.0f : mn[rt];
+            }
+            const float x = s[rt][i] - less[rt];
+            if constexpr (mm > 0) add(std::integral_constant<int, mm - 1>{});
+            p[mm & 1] = __builtin_amdgcn_exp2f(x);
+            // the other row tile's maximum, two logits at a time
+            if constexpr (rt == 0 && i >= 4 && i < 12) {
+                constexpr int z = 2 * (i - 4);
+                asm volatile("v_max3_f32 %0, %1, %2, %0" : "+v"(top1) : "v"(s[1][z]), "v"(s[1][z + 1]));
+            }
+            if constexpr (mm == 21) cut(nxt[0], t + 1);
+            if constexpr (rt == 1 && i >= 6 && i < 14) {
+                constexpr int z = 2 * (i - 6);
+                if constexpr (z == 0) top0 = -INFINITY;
+                asm volatile("v_max3_f32 %0, %1, %2, %0" : "+v"(top0) : "v"(nxt[0][z]), "v"(nxt[0][z + 1]));
+            }
+        });
+        add(std::integral_constant<int, 31>{});
+    };
+    for (int t = 0; t < ntiles; t += 4) {                  // (tiles past the last one hold no keys)
+        step(sa, sb, tile1, tile2, t);
+        step(sb, sa, tile2, tile3, t + 1);
+        step(sa, sb, tile3, tile0, t + 2);
+        step(sb, sa, tile0, tile1, t + 3);
+        if ((t + 4) % range_tiles == 0 || t + 4 >= ntiles) {         // the end of a range
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt) {               // merge the two lane halves; the rows of a wave are its own
+                const float mo = __shfl_xor(m[rt], 32, 64), lo = __shfl_xor(l[rt], 32, 64);
+                const float mn = fmaxf(m[rt], mo);
+                float ln = 0.0f;
+                if (mn != -INFINITY) ln = l[rt] * exp2f(m[rt] - mn) + lo * exp2f(mo - mn);
+                if (lane < 32) partial[((size_t)bh * parts + range) * kQRows + 64 * wave + 32 * rt + lane] = make_float2(mn, ln);
+                m[rt] = -INFINITY;
+                l[rt] = 0.0f;
+            }
+            ++range;
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);                    // the loads issued past the end have landed
+}
+
+// c[bh][row] = -max - log2(bl * sumexp) for row < bl, -inf for the padding rows.
+// 1024 threads: thread (grp, row) folds the partials grp, grp+8, ... of its row, then the 8 groups meet in LDS.
+__global__ __launch_bounds__(1024) void scores_merge_kernel(const float2 *__restrict__ partial,
+                                                            float *__restrict__ cvec, int nwg, int bl)
+{
+    __shared__ float2 red[8][kQRows];
+    const int bh = blockIdx.x, row = threadIdx.x & (kQRows - 1), grp = threadIdx.x >> 7;
+    float mn = -INFINITY, ln = 0.0f;
+    for (int w0 = grp; w0 < nwg; w0 += 32) {                 // four independent loads per round trip
+        float2 pr[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int w = w0 + 8 * q;
+            pr[q] = w < nwg ? partial[((size_t)bh * nwg + w) * kQRows + row] : make_float2(-INFINITY, 0.0f);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (pr[q].x != -INFINITY) {
+                const float m2 = fmaxf(mn, pr[q].x);
+                ln = ln * exp2f(mn - m2) + pr[q].y * exp2f(pr[q].x - m2);
+                mn = m2;
+            }
+    }
+    red[grp][row] = make_float2(mn, ln);
+    __syncthreads();
+    if (grp == 0) {
+        float m2 = -INFINITY;
+        for (int q = 0; q < 8; ++q) m2 = fmaxf(m2, red[q][row].x);
+        float l2 = 0.0f;
+        for (int q = 0; q < 8; ++q)
+            if (red[q][row].x != -INFINITY) l2 += red[q][row].y * exp2f(red[q][row].x - m2);
+        cvec[(size_t)bh * kQRows + row] = row < bl ? -m2 - log2f((float)bl * l2) : -INFINITY;
+    }
+}
+
+// ------------------------------------------------------------------ MFMA path: sweep 2
+// scores[key] = sum over the 128 rows of exp2(logit2 + c[row]): each wave sums its 64 rows per key; what the lane halves and
+// the waves have of a tile's keys is put together under the next tile.
+__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) void scores_sweep2_kernel(
+    const bf16_t *__restrict__ K, const bf16_t *__restrict__ qsplit, const float *__restrict__ cvec,
+    float *__restrict__ scores, Geo g, int kpw)
+{
+    __shared__ KTile tile0, tile1, tile2, tile3;
+    __shared__ float psum[4][2][kTileKeys];                  // of the last tiles, by wave
+    const int bh = blockIdx.y;
+    const int wg = gridDim.x - 1 - blockIdx.x;               // reverse order: reuse what sweep 1 left in cache
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int key_begin = wg * kpw, keys = min(g.n - key_begin, kpw), ntiles = ceil_div(keys, kTileKeys);
+    const KSource src = key_source(K + ((size_t)bh * g.n + key_begin) * 128, keys, lane);
+    float *out = scores + (size_t)bh * g.n + key_begin;
+    bf16x8 qf[2][8][2], kf[8];
+    // the accumulators start at c[row]; row = 64 wave + 32 rt + 8 (i / 4) + 4 (lane >> 5) + (i % 4)
+    floatx16 sa[2], sb[2], c[2];
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            c[rt][i] = cvec[(size_t)bh * kQRows + 64 * wave + 32 * rt + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3)];
+    sweep_start<false>(sa, kf, qf, c, tile0, tile1, tile2, tile3, src, qsplit, bh, wave, lane);
+    float done[2] = {0.0f, 0.0f};                            // this lane's sums of the tile before
+    auto halves = [&](int rt) __attribute__((always_inline)) {
+        const uint32_t own = __builtin_bit_cast(uint32_t, done[rt]);
+        const auto sw = __builtin_amdgcn_permlane32_swap(own, own, false, false);
+        const uint32_t lower = sw[0], upper = sw[1];
+        done[rt] = __builtin_bit_cast(float, lower) + __builtin_bit_cast(float, upper);
+    };
+    // 16 keys of the tile before for each wave (behind a barrier that psum of both waves is ahead of)
+    const int mine = 16 * wave + (lane & 15);
+    auto leave = [&](int t) __attribute__((always_inline)) {
+        const int at = t * kTileKeys + mine;
+        if (lane < 16 && at >= 0 && at < keys) out[at] = psum[t & 3][0][mine] + psum[t & 3][1][mine];
+    };
+    auto step = [&](floatx16 (&s)[2], floatx16 (&nxt)[2], KTile &u1, const KTile &u2, int t) __attribute__((always_inline)) {
+        float p[2], sum[2];
+        auto add = [&](auto uc) __attribute__((always_inline)) {
+            constexpr int u = decltype(uc)::value, rt = u >> 4;
+            if constexpr ((u & 15) == 0) sum[rt] = p[u & 1];
+            else sum[rt] += p[u & 1];
+            if constexpr ((u & 15) != 0) asm volatile("" : "+v"(sum[rt]));
+        };
+        sweep_step<false>(nxt, kf, qf, c, u1, u2, src, t, wave, [&](auto mc) __attribute__((always_inline)) {
+            constexpr int mm = decltype(mc)::value;
+            if constexpr (mm > 0) add(std::integral_constant<int, mm - 1>{});
+            p[mm & 1] = __builtin_amdgcn_exp2f(s[mm >> 4][mm & 15]);
+            if constexpr (mm == 1) halves(0);
+            if constexpr (mm == 2) halves(1);
+            if constexpr (mm == 3) psum[(t - 1) & 3][wave][lane & 31] = done[0] + done[1];     // the same from both halves
+            if constexpr (mm == 12) leave(t - 1);
+        });
+        add(std::integral_constant<int, 31>{});
+        done[0] = sum[0];
+        done[1] = sum[1];
+    };
+    int t = 0;
+    for (; t < ntiles; t += 4) {                             // (tiles past the last one hold no keys)
+        step(sa, sb, tile1, tile2, t);
+        step(sb, sa, tile2, tile3, t + 1);
+        step(sa, sb, tile3, tile0, t + 2);
+        step(sb, sa, tile0, tile1, t + 3);
+    }
+    halves(0);
+    halves(1);
+    psum[(t - 1) & 3][wave][lane & 31] = done[0] + done[1];
+    __builtin_amdgcn_s_waitcnt(0x0F70);                    // the loads issued past the end have landed
+    __syncthreads();
+    leave(t - 1);
+}
+
+// ------------------------------------------------------------------ MFMA path, short inputs
+// Where there are too few keys for every SIMD to have a wave of 64 rows: four waves to a workgroup, 32 rows each, two to
+// a SIMD.  The logits, their maxima and their sums are formed in the same order as above.
+namespace short_input {
+
 // Wave w of a workgroup owns the logit rows 32 w .. 32 w + 31 and keeps their split Qhat fragments in registers
 // (8 k-steps x 2 terms x 4 registers); the K tiles of 32 keys go through LDS, where all four waves read them, so a
 // fragment read feeds two MFMAs and the tile is fetched from memory once.  A tile travels global -> registers ->
@@ -122,15 +488,11 @@ __device__ inline bf16x8 kfrag(const KTile &t, int ks, int lane)
     return *reinterpret_cast<const bf16x8 *>(t.b + row * 256 + ((c ^ (row & 15)) << 4));
 }
 
-// The wave's 32 rows of one term of the split Qhat, straight from qsplit (same d range per lane as kfrag).
-__device__ inline void load_qfrags(bf16x8 (&qf)[8], const bf16_t *term, int wave, int lane)
+// The wave's 32 rows of one term of the split Qhat (same d range per lane as kfrag).
+__device__ inline void load_qfrags(bf16x8 (&qf)[8], const bf16_t *qsplit, int bh, int term, int wave, int lane)
 {
-    const int row = wave * 32 + (lane & 31);
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-        const int c = 2 * ks + (lane >> 5);
-        qf[ks] = *reinterpret_cast<const bf16x8 *>(term + row * 128 + ((c ^ (row & 15)) << 3));
-    }
+    for (int ks = 0; ks < 8; ++ks) qf[ks] = *reinterpret_cast<const bf16x8 *>(qsplit + qfrag_offset(bh, wave, ks, term) + lane * 8);
 }
 
 // Runs body(t, tile) for the tiles t = 0 .. ntiles - 1 of the keys from key_begin on, the tile being complete in
@@ -162,17 +524,16 @@ __device__ __forceinline__ void sweep_tiles(KTile (&kt)[2], const bf16_t *Kh, in
     }
 }
 
-// ------------------------------------------------------------------ MFMA path: sweep 1
 // partial[bh][wg][row] = (max2, sumexp2) over the keys of workgroup wg, log2 domain.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void scores_sweep1_kernel(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void sweep1_kernel(
     const bf16_t *__restrict__ K, const bf16_t *__restrict__ qsplit, float2 *__restrict__ partial, Geo g, int kpw)
 {
     __shared__ __align__(16) KTile kt[2];
     const int bh = blockIdx.y, wg = blockIdx.x, nwg = gridDim.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     bf16x8 qh[8], ql[8];
-    load_qfrags(qh, qsplit + (size_t)bh * 2 * kQRows * 128, wave, lane);
-    load_qfrags(ql, qsplit + (size_t)bh * 2 * kQRows * 128 + kQRows * 128, wave, lane);
+    load_qfrags(qh, qsplit, bh, 0, wave, lane);
+    load_qfrags(ql, qsplit, bh, 1, wave, lane);
     const bf16_t *Kh = K + (size_t)bh * g.n * 128;
     const int key_begin = wg * kpw, key_end = min(g.n, key_begin + kpw);
     const int ntiles = ceil_div(key_end - key_begin, kTileKeys);
@@ -213,56 +574,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (lane < 32) partial[((size_t)bh * nwg + wg) * kQRows + wave * 32 + lane] = make_float2(mn, ln);
 }
 
-// c[bh][row] = -max - log2(bl * sumexp) for row < bl, -inf for the padding rows.
-// 1024 threads: thread (grp, row) folds the partials grp, grp+8, ... of its row, then the 8 groups meet in LDS.
-__global__ __launch_bounds__(1024) void scores_merge_kernel(const float2 *__restrict__ partial,
-                                                            float *__restrict__ cvec, int nwg, int bl)
-{
-    __shared__ float2 red[8][kQRows];
-    const int bh = blockIdx.x, row = threadIdx.x & (kQRows - 1), grp = threadIdx.x >> 7;
-    float mn = -INFINITY, ln = 0.0f;
-    for (int w0 = grp; w0 < nwg; w0 += 32) {                 // four independent loads per round trip
-        float2 pr[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int w = w0 + 8 * q;
-            pr[q] = w < nwg ? partial[((size_t)bh * nwg + w) * kQRows + row] : make_float2(-INFINITY, 0.0f);
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            if (pr[q].x != -INFINITY) {
-                const float m2 = fmaxf(mn, pr[q].x);
-                ln = ln * exp2f(mn - m2) + pr[q].y * exp2f(pr[q].x - m2);
-                mn = m2;
-            }
-    }
-    red[grp][row] = make_float2(mn, ln);
-    __syncthreads();
-    if (grp == 0) {
-        float m2 = -INFINITY;
-        for (int q = 0; q < 8; ++q) m2 = fmaxf(m2, red[q][row].x);
-        float l2 = 0.0f;
-        for (int q = 0; q < 8; ++q)
-            if (red[q][row].x != -INFINITY) l2 += red[q][row].y * exp2f(red[q][row].x - m2);
-        cvec[(size_t)bh * kQRows + row] = row < bl ? -m2 - log2f((float)bl * l2) : -INFINITY;
-    }
-}
-
-// ------------------------------------------------------------------ MFMA path: sweep 2
 // scores[key] = sum over the 128 rows of exp2(logit2 + c[row]): each wave sums its 32 rows per key into LDS, the
 // four partial sums of a key meet once at the end of the workgroup's range.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void scores_sweep2_kernel(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void sweep2_kernel(
     const bf16_t *__restrict__ K, const bf16_t *__restrict__ qsplit, const float *__restrict__ cvec,
     float *__restrict__ scores, Geo g, int kpw)
 {
     __shared__ __align__(16) KTile kt[2];
-    __shared__ float psum[4][kMaxKeysPerWg];
+    __shared__ float psum[4][kMaxRangeKeys];
     const int bh = blockIdx.y;
     const int wg = gridDim.x - 1 - blockIdx.x;               // reverse order: reuse what sweep 1 left in cache
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     bf16x8 qh[8], ql[8];
-    load_qfrags(qh, qsplit + (size_t)bh * 2 * kQRows * 128, wave, lane);
-    load_qfrags(ql, qsplit + (size_t)bh * 2 * kQRows * 128 + kQRows * 128, wave, lane);
+    load_qfrags(qh, qsplit, bh, 0, wave, lane);
+    load_qfrags(ql, qsplit, bh, 1, wave, lane);
     // the accumulator starts at c[row]; row = 32 wave + 8 (i / 4) + 4 (lane >> 5) + (i % 4)
     floatx16 cinit;
 #pragma unroll
@@ -289,6 +614,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int k = tid; k < key_end - key_begin; k += 256)
         scores[(size_t)bh * g.n + key_begin + k] = (psum[0][k] + psum[1][k]) + (psum[2][k] + psum[3][k]);
 }
+
+}  // namespace short_input
 
 // ------------------------------------------------------------------ generic path (fp64 accumulation)
 // one thread per element of Qhat; grid = (ceil(bl * d / 256), batch * h_kv)
@@ -552,14 +879,18 @@ static int f64_keys_per_chunk(const Geo &g, int bl)
     return (int)(keys < kMinF64Chunk ? kMinF64Chunk : (keys + 15) / 16 * 16);
 }
 
-// Keys per workgroup of the MFMA sweeps: 1024 for long inputs; halved (down to one tile per wave) while the
-// grid would hold fewer than kSweepWgs workgroups, so that short inputs still spread over all compute units.
-static int sweep_keys_per_wg(const Geo &g)
+// Keys of a range of sweep 1, which leaves one (max, sum) per row: 1024 for long inputs; halved while there would be fewer
+// than kSweepWgs ranges, so that short inputs still spread over all compute units.
+static int sweep_range_keys(const Geo &g)
 {
-    int kpw = kMaxKeysPerWg;
-    while (kpw > kMinKeysPerWg && (long long)ceil_div(g.n, kpw) * g.batch * g.h_kv < kSweepWgs) kpw >>= 1;
-    return kpw;
+    int keys = kMaxRangeKeys;
+    while (keys > kMinRangeKeys && (long long)ceil_div(g.n, keys) * g.batch * g.h_kv < kSweepWgs) keys >>= 1;
+    return keys;
 }
+
+// The long sweeps need their 512 workgroups busy for a while.  Whole stage, short / long sweeps, us: 65176 keys in all 21.7 / 23.9,
+// 131072 30.0 / 32.4, 262144 45.0 / 45.0, 400000 71.5 / 60.6, 1048576 135.8 / 125.5, 1600000 233.9 / 206.3.
+static bool long_sweeps(const Geo &g) { return (long long)g.n * g.batch * g.h_kv >= kLongKeys; }
 
 // bytes of the average-query region at the end of the workspace: the partial sums and the mean itself
 static size_t ws_avg_query(size_t nbh) { return align_up(nbh * (kAvgChunks + 1) * 128 * sizeof(double), kWsAlign); }
@@ -570,7 +901,7 @@ size_t ws_key_scores(const pbs_problem *p)
     const Geo g = make_geo(p);
     const size_t nbh = (size_t)g.batch * g.h_kv;
     if (use_mfma(p)) {
-        const size_t nwg = ceil_div(g.n, sweep_keys_per_wg(g));
+        const size_t nwg = ceil_div(g.n, sweep_range_keys(g));
         return align_up(nbh * 2 * kQRows * 128 * sizeof(bf16_t), kWsAlign) +
                align_up(nbh * nwg * kQRows * sizeof(float2), kWsAlign) + align_up(nbh * kQRows * sizeof(float), kWsAlign) +
                ws_avg_query(nbh);
@@ -643,22 +974,32 @@ static pbs_status enqueue_key_scores(const pbs_problem *p, int proxy, const int3
                            : run_generic<float, 64>(g, Q, K, scores, w, bl, qrows, avg, s);
     }
     const int nbh = g.batch * g.h_kv;
-    const int kpw = sweep_keys_per_wg(g);
-    const int nwg = ceil_div(g.n, kpw);
+    const int range = sweep_range_keys(g), parts = ceil_div(g.n, range);
     bf16_t *qsplit = reinterpret_cast<bf16_t *>(w);
     w += align_up((size_t)nbh * 2 * kQRows * 128 * sizeof(bf16_t), kWsAlign);
     float2 *partial = reinterpret_cast<float2 *>(w);
-    w += align_up((size_t)nbh * nwg * kQRows * sizeof(float2), kWsAlign);
+    w += align_up((size_t)nbh * parts * kQRows * sizeof(float2), kWsAlign);
     float *cvec = reinterpret_cast<float *>(w);
     w += align_up((size_t)nbh * kQRows * sizeof(float), kWsAlign);
     double *avg_partial = reinterpret_cast<double *>(w), *qavg = avg_partial + (size_t)nbh * kAvgChunks * 128;
     if (avg && (st = run_qavg<bf16_t>(g, Q, avg_partial, qavg, s)) != PBS_OK) return st;
     if ((st = launch(qhat_split_kernel, dim3(kQRows / 8, nbh), dim3(256), 0, s, (const bf16_t *)Q, qsplit, g, bl, qrows,
                      (const double *)(avg ? qavg : nullptr))) != PBS_OK) return st;
-    if ((st = launch(scores_sweep1_kernel, dim3(nwg, nbh), dim3(256), 0, s, (const bf16_t *)K, qsplit, partial, g, kpw)) != PBS_OK) return st;
-    if ((st = launch(scores_merge_kernel, dim3(nbh), dim3(1024), 0, s, partial, cvec, nwg, bl)) != PBS_OK) return st;
-    return launch(scores_sweep2_kernel, dim3(nwg, nbh), dim3(256), 0, s, (const bf16_t *)K, qsplit, cvec, scores,
-                       g, kpw);
+    const bool in_long = long_sweeps(g);
+    // one round of workgroups, each with one share of a head's ranges (sweep 1) or keys (sweep 2)
+    const int ranges = (int)(((long long)parts * nbh + kSweepWgs - 1) / kSweepWgs);
+    const int keys = (int)(((long long)g.n * nbh + kSweepWgs - 1) / kSweepWgs + 4 * kTileKeys - 1) / (4 * kTileKeys) * (4 * kTileKeys);
+    if (in_long)
+        st = launch(scores_sweep1_kernel, dim3(ceil_div(parts, ranges), nbh), dim3(128), 0, s, (const bf16_t *)K, qsplit, partial, g,
+                    range, ranges);
+    else
+        st = launch(short_input::sweep1_kernel, dim3(parts, nbh), dim3(256), 0, s, (const bf16_t *)K, qsplit, partial, g, range);
+    if (st != PBS_OK) return st;
+    if ((st = launch(scores_merge_kernel, dim3(nbh), dim3(1024), 0, s, partial, cvec, parts, bl)) != PBS_OK) return st;
+    if (in_long)
+        return launch(scores_sweep2_kernel, dim3(ceil_div(g.n, keys), nbh), dim3(128), 0, s, (const bf16_t *)K, qsplit, cvec,
+                      scores, g, keys);
+    return launch(short_input::sweep2_kernel, dim3(parts, nbh), dim3(256), 0, s, (const bf16_t *)K, qsplit, cvec, scores, g, range);
 }
 
 extern "C" pbs_status pbs_key_scores(const pbs_problem *p, const void *Q, const void *K, float *scores, void *ws,

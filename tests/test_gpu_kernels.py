@@ -526,3 +526,19 @@ def test_selection_time_with_a_kv_head_to_every_query_head():
         return min(times)
     own, shared = best(32), best(8)
     assert own < 1.55 * shared, (own, shared)
+
+
+# long inputs, two waves of 64 rows to a workgroup: the last tile of one key, shares of a head that end inside a range, one
+# head, heads of two sequences.  Qhat's two bf16 terms leave 2^-18 of each product, 128 fp32 additions 2^-17 of their sum,
+# and sum |q k| / sqrt(d) < 8 for these inputs: within 1e-4 of a score.
+@pytest.mark.parametrize("batch,h_kv,n", [(1, 32, 10273), (2, 33, 5001), (1, 1, 327701), (1, 8, 41000)])
+def test_key_scores_of_long_inputs(batch, h_kv, n):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    Q = torch.randn((batch, h_kv, n, 128), generator=g, device="cuda").bfloat16()
+    K = torch.randn((batch, h_kv, n, 128), generator=g, device="cuda").bfloat16()
+    got = pbs.key_scores(pbs.problem(batch, h_kv, h_kv, n, 128, 128, 1024, "bf16"), Q, K)
+    for b in range(batch):
+        for h in range(h_kv):
+            want = torch.softmax(Q[b, h, -128:].double() @ K[b, h].double().T / 128 ** 0.5, -1).mean(0)
+            torch.testing.assert_close(got[b, h].double(), want, rtol=1e-4, atol=0)
