@@ -49,7 +49,8 @@ constexpr int KS = 32;                                     // keys per sub-tile
 constexpr int kStageB = 8192;                              // K' sub-tile: 32 rows x 256 B; V'^T sub-tile: 128 rows x 64 B
 constexpr int kLoadsPerWave = 8;                           // 16-byte-per-lane loads a wave issues per stage
 constexpr int kList = 1024;                                // listed blocks staged in LDS at a time
-constexpr int kXcds = 8, kCohortLog2 = 6;
+constexpr int kXcds = 8;
+constexpr int kCohortLog2 = 6, kOwnCohortLog2 = 3;         // rows from queues, every row with a workgroup of its own
 constexpr int kResident = 512;                             // workgroups the chip holds: two on each of 256 compute units
 constexpr int kTicketStride = 32;                          // queue heads lie 128 bytes apart
 constexpr int kQueueRows = 8 * kResident;                  // rows from which on workgroups take them from queues
@@ -893,19 +894,23 @@ pbs_status launch_attn_wide(const Geo &g, const void *Qp, const void *Kp, const 
                             void *redo, int tok_delta, hipStream_t s)
 {
     const long long units = (long long)g.batch * g.h_kv, rows = (long long)g.r * g.T;
-    int cohort_log2 = wide::kCohortLog2;
+    const bool queues = wide_rows_from_queues(g);
+    const int cohort_log2 = queues ? wide::kCohortLog2 : wide::kOwnCohortLog2;
     unsigned wgs = wide::kResident;
     unsigned long long key = 0;
-    if (wide_rows_from_queues(g)) {
+    if (queues) {
         static std::atomic<unsigned long long> calls{0};
         key = calls.fetch_add(1, std::memory_order_relaxed) + 1;
         const pbs_status st = launch(wide::take_queues_kernel, dim3(1), dim3(64), 0, s, key);
         if (st != PBS_OK) return st;
     } else {
-        // every row has a workgroup of its own; cohorts narrower while some XCD would get none
-        auto cohorts = [&]() { return units * ((rows + (1 << cohort_log2) - 1) >> cohort_log2); };
-        while (cohort_log2 > 3 && cohorts() < wide::kXcds) --cohort_log2;
-        wgs = (unsigned)(((cohorts() + wide::kXcds - 1) / wide::kXcds * wide::kXcds) << cohort_log2);
+        // Every row has a workgroup of its own, and nothing evens out what the XCDs get: with fewer kv heads than XCDs the
+        // ones that start with the longer cohorts keep them throughout.  Cohorts of 64 rows against 8, causal lists, whole
+        // call: 4 / 2 heads x 20000 515 -> 417 us, 8 / 2 x 30000 1714 -> 1465 us, 16 / 4 x 12288 587 -> 532 us, 28 / 4 x 16384
+        // 1631 -> 1548 us; a fifth of the blocks 4 / 2 x 20000 153 -> 140 us, 28 / 4 x 9000 196 -> 180 us; with a kv head to
+        // every XCD (32 / 8 x 2048 .. 8147) the same.
+        const long long cohorts = units * ((rows + (1 << cohort_log2) - 1) >> cohort_log2);
+        wgs = (unsigned)(((cohorts + wide::kXcds - 1) / wide::kXcds * wide::kXcds) << cohort_log2);
     }
     return launch(wide::attn_wide_kernel, dim3(wgs), dim3(128), 0, s, (const bf16_t *)Qp, (const bf16_t *)Kp,
                   (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse, (int8_t *)redo, g, tok_delta,
