@@ -52,6 +52,7 @@ constexpr int kList = 1024;                                // listed blocks stag
 constexpr int kXcds = 8;
 constexpr int kCohortLog2 = 6, kOwnCohortLog2 = 3;         // rows from queues, every row with a workgroup of its own
 constexpr int kResident = 512;                             // workgroups the chip holds: two on each of 256 compute units
+constexpr int kSplitRows = 256;                            // rows up to which each has four waves
 constexpr int kTicketStride = 32;                          // queue heads lie 128 bytes apart
 constexpr int kQueueRows = 8 * kResident;                  // rows from which on workgroups take them from queues
 constexpr float kLog2eF = 1.4426950408889634f;
@@ -79,9 +80,11 @@ struct __align__(16) Stage {
 
 __device__ __forceinline__ int swap23(int m) { return (m & ~12) | ((m & 4) << 1) | ((m & 8) >> 1); }
 
-// Descriptors of one kv head: what this wave loads (wave 0: K', wave 1: V'^T) and the key positions.
+// Descriptors of one kv head: what this wave loads (wave 0: K', wave 1: V'^T) and the key positions; ring: byte offset
+// of this wave's stages behind those of the first half of a split row.
 struct TileBuffers {
     __amdgpu_buffer_rsrc_t tile, pos;
+    int ring;
 };
 
 // A stage is 16 chunks of 1 KiB, one load instruction each (64 lanes x 16 bytes, consecutive in LDS).  Both waves
@@ -106,7 +109,8 @@ __device__ __forceinline__ uint32_t v_lane_offset(int chunk, int lane)
     return (uint32_t)(row * (KS * 2) + ((place ^ ((row >> 2) & 3)) << 4));
 }
 
-__device__ __forceinline__ LaneOffsets lane_offsets(int wave, int lane)
+// half: which of the two rings of a split row (see attn_wide_kernel) this wave reads
+__device__ __forceinline__ LaneOffsets lane_offsets(int half, int wave, int lane)
 {
     LaneOffsets r;
     const int ln = lane & 31, lh = lane >> 5;
@@ -114,9 +118,9 @@ __device__ __forceinline__ LaneOffsets lane_offsets(int wave, int lane)
     for (int c = 0; c < kLoadsPerWave; ++c) r.dma[c] = wave == 0 ? k_lane_offset(c, lane) : v_lane_offset(c, lane);
     // K' fragment x: logical piece 2 x + h of row n;  V'^T fragment (dt, k2): logical piece 2 k2 + h of row 32 dt + n
 #pragma unroll
-    for (int x = 0; x < 8; ++x) r.kfr[x] = (uint32_t)(ln * 256 + (((2 * x + lh) ^ (ln & 15)) << 4));
+    for (int x = 0; x < 8; ++x) r.kfr[x] = (uint32_t)(half * sizeof(Stage) + ln * 256 + (((2 * x + lh) ^ (ln & 15)) << 4));
 #pragma unroll
-    for (int k2 = 0; k2 < 2; ++k2) r.vfr[k2] = (uint32_t)(ln * 64 + (((2 * k2 + lh) ^ ((ln >> 2) & 3)) << 4));
+    for (int k2 = 0; k2 < 2; ++k2) r.vfr[k2] = (uint32_t)(half * sizeof(Stage) + ln * 64 + (((2 * k2 + lh) ^ ((ln >> 2) & 3)) << 4));
     return r;
 }
 
@@ -135,9 +139,9 @@ __device__ __forceinline__ StageLoad stage_load(__attribute__((address_space(3))
     static_assert(BLOCK * 256 == D * BLOCK * 2 && KS * 256 == D * KS * 2, "blocks and sub-tiles of K' and Vt are equally large");
     a.rsrc = buf.tile;
     a.soff = (wave == 0 ? jk : jv) * (BLOCK * 256) + (wave == 0 ? P : (P + 3) & 3) * (KS * 256);
-    int half = wave * kStageB;                             // sg.k for wave 0, sg.v behind it for wave 1
-    asm volatile("" : "+s"(half));     // formed here: 32 loop-invariant addresses would not fit the scalar registers
-    a.dst = dst + half;
+    int own = buf.ring + wave * kStageB;                   // sg.k for wave 0, sg.v behind it for wave 1
+    asm volatile("" : "+s"(own));      // formed here: 32 loop-invariant addresses would not fit the scalar registers
+    a.dst = dst + own;
     return a;
 }
 
@@ -152,19 +156,21 @@ __device__ __forceinline__ void issue_load(const StageLoad &a, const LaneOffsets
 // token-level mask read them, but the load is issued for every sub-tile, by all lanes of both waves (four bytes per
 // lane, the same 256 bytes from each wave): one more instruction in the stream costs less than a branch around it.
 template <int P>
-__device__ __forceinline__ void issue_positions(lptr_t dst, const TileBuffers &buf, int j, int lane)
+__device__ __forceinline__ void issue_positions(__attribute__((address_space(3))) unsigned char *dst, const TileBuffers &buf,
+                                                int j, int lane)
 {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(buf.pos, dst, 4, lane * 4, (j * BLOCK + P * KS) * 4, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(buf.pos, (lptr_t)(dst + buf.ring), 4, lane * 4, (j * BLOCK + P * KS) * 4, 0, 0);
 }
 
+// K' part P of block j and the V'^T part (P + 3) % 4 of block jv
 template <int P>
-__device__ __forceinline__ void issue_stage(Stage &sg, const TileBuffers &buf, const LaneOffsets &off, int j, int wave,
+__device__ __forceinline__ void issue_stage(Stage &sg, const TileBuffers &buf, const LaneOffsets &off, int j, int jv, int wave,
                                             int lane)
 {
-    const StageLoad a = stage_load<P>((__attribute__((address_space(3))) unsigned char *)sg.k, buf, j, j, wave);
+    const StageLoad a = stage_load<P>((__attribute__((address_space(3))) unsigned char *)sg.k, buf, j, jv, wave);
     issue_load<0>(a, off); issue_load<1>(a, off); issue_load<2>(a, off); issue_load<3>(a, off);
     issue_load<4>(a, off); issue_load<5>(a, off); issue_load<6>(a, off); issue_load<7>(a, off);
-    issue_positions<P>((lptr_t)sg.pos, buf, j, lane);
+    issue_positions<P>((__attribute__((address_space(3))) unsigned char *)sg.pos, buf, j, lane);
 }
 
 // Every asynchronous load of this wave has landed, then all waves meet: the stages loaded so far are complete.
@@ -317,7 +323,7 @@ __device__ __forceinline__ void step(State &st, floatx16 (&s_cur)[2], floatx16 (
     bf16x8 vf[8];
     if (__builtin_expect(masked || !st.all_seen, 0)) {
         asm volatile("" ::: "memory");                     // keeps this rare block out of the straight-line code
-        if (masked) mask_tile(s_cur, sg_v.pos, room, qpos, lh);
+        if (masked) mask_tile(s_cur, sg_v.pos + buf.ring / 4, room, qpos, lh);
         set_reference(st, 0, s_cur[0], c2);
         set_reference(st, 1, s_cur[1], c2);
         st.all_seen = __all(st.seen[0] && st.seen[1]);
@@ -357,7 +363,7 @@ __device__ __forceinline__ void step(State &st, floatx16 (&s_cur)[2], floatx16 (
     };
     StageLoad ld;
     const auto stage_dst = (__attribute__((address_space(3))) unsigned char *)sg_v.k;
-    const lptr_t pos_dst = (lptr_t)sg_v.pos;
+    const auto pos_dst = (__attribute__((address_space(3))) unsigned char *)sg_v.pos;
     auto slot = [&](auto mc) __attribute__((always_inline)) {
         constexpr int m = decltype(mc)::value;
         if constexpr (m < 16) {
@@ -479,23 +485,32 @@ __global__ __launch_bounds__(64) void take_queues_kernel(unsigned long long key)
 // block would issue past its end are then those of the next row's first block, and the next Q' fragments travel under
 // the epilogue.  (A workgroup per row spent 9-10 us outside its loop and 1-6 us between two workgroups, against 3.3 us per
 // block; and the XCDs, which run at clocks up to 8 % apart, waited for the slowest.)
-__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) void attn_wide_kernel(
+//
+// HALVES == 2 (key == 0, lists of one chunk): a row has four waves, two to each half of its list, one workgroup to a
+// compute unit.  Each half is the pipeline as it stands, on a ring of its own; at the end the halves exchange O^T of
+// one query tile each through LDS, bring both to the larger reference and store a tile each.
+template <int HALVES>
+__global__ __launch_bounds__(128 * HALVES) __attribute__((amdgpu_waves_per_eu(1, 1))) void attn_wide_kernel(
     const bf16_t *__restrict__ Qp, const bf16_t *__restrict__ Kp, const bf16_t *__restrict__ Vt,
     const int32_t *__restrict__ qidx, const int32_t *__restrict__ kidx, const int32_t *__restrict__ row_cnt,
     const int32_t *__restrict__ col_idx, bf16_t *__restrict__ Op, float *__restrict__ lse,
     int8_t *__restrict__ redo, Geo g, int tok_delta, unsigned long long key, int cohort_log2)
 {
-    __shared__ Stage sg0, sg1, sg2, sg3;                   // 4 x 16 KiB
+    __shared__ Stage rg0[HALVES], rg1[HALVES], rg2[HALVES], rg3[HALVES];         // 4 x 16 KiB
+    Stage &sg0 = rg0[0], &sg1 = rg1[0], &sg2 = rg2[0], &sg3 = rg3[0];            // buf.ring and off lead to the own ones
+    __shared__ floatx4 sums[HALVES == 2 ? 256 : 1];        // row sums and references of a split row's halves
     __shared__ int lists[2][kList];                        // block lists (a chunk of each) of this row and the next
     __shared__ int tails[64];                              // the end of a list that is longer than a chunk
     __shared__ int next_cnt[64], sink[64];
     __shared__ RowInfo info[2];
 
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(HALVES == 2 ? threadIdx.x >> 6 & 1 : threadIdx.x >> 6);
+    const int half = HALVES == 2 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 7) : 0;
+    const bool keeper = wave == 0 && half == 0;            // the wave that keeps the lists
     const int ln = lane & 31, lh = lane >> 5;
     const float c2 = g.scale * kLog2eF;
-    const LaneOffsets off = lane_offsets(wave, lane);
+    const LaneOffsets off = lane_offsets(half, wave, lane);
     constexpr int kRawDword = 0x00020000;                  // gfx9 descriptor word 3: raw 32-bit data format
 
     auto decode = [&](int unit, int mrow, int &bhq, int &i) {
@@ -569,6 +584,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         }
     };
     TileBuffers buf;
+    buf.ring = half * (int)sizeof(Stage);
     auto open_buffers = [&](int unit) {
         // tok_delta > 0: a token-order copy of K', Vt and kidx lies tok_delta = batch * h_kv * T blocks behind the
         // permuted one, so block j of this head in token order is block tok_delta + j of the same descriptors
@@ -579,11 +595,13 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                                                                  (tok_delta + g.T) * (D * BLOCK * 2), kRawDword);
         buf.pos = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(kidx + bhk * (size_t)g.n), 0, reach * 4, kRawDword);
     };
-    auto issue_block = [&](int j) {
-        issue_stage<0>(sg0, buf, off, j, wave, lane);
-        issue_stage<1>(sg1, buf, off, j, wave, lane);
-        issue_stage<2>(sg2, buf, off, j, wave, lane);
-        issue_stage<3>(sg3, buf, off, j, wave, lane);
+    // jv0: the first iteration of a row multiplies V'^T part 3 of this block by zero probabilities; that is a block of the
+    // row's list, the same one for both halves, so that infinite values meet no more zeros than they would in one piece
+    auto issue_block = [&](int j, int jv0) {
+        issue_stage<0>(sg0, buf, off, j, jv0, wave, lane);
+        issue_stage<1>(sg1, buf, off, j, j, wave, lane);
+        issue_stage<2>(sg2, buf, off, j, j, wave, lane);
+        issue_stage<3>(sg3, buf, off, j, j, wave, lane);
     };
     auto query_buffer = [&](int bhq) {
         return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(Qp + (size_t)bhq * g.n * D), 0, g.n * 256, kRawDword);
@@ -607,7 +625,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 
     const int home = blockIdx.x % kXcds;
     int32_t *tickets = nullptr;
-    if (key) {
+    if (HALVES == 1 && key) {
         const uint64_t mine = __ballot(__hip_atomic_load(&queue_owner[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == key);
         if (!mine) {                                       // no set was free: every row is flagged
             for (long long f = 128LL * blockIdx.x + threadIdx.x; f < 2LL * g.batch * g.h_q * g.T; f += 128LL * gridDim.x) redo[f] = 1;
@@ -630,7 +648,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     int unit, bhq, i;                                      // of the current row
     {
         int mrow;
-        if (!tickets) {
+        if (HALVES == 2 || !tickets) {
             if (!ticket_row(g, cohort_log2, home, blockIdx.x / kXcds, unit, mrow) || unit < 0) return;
         } else {
             // the first row is drawn too, not tied to the workgroup's id: a workgroup that another kernel's work keeps off
@@ -648,35 +666,46 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         }
         decode(unit, mrow, bhq, i);
         const size_t at = (size_t)bhq * g.T + i;
-        if (wave == 0) load_list(bhq, i, lists[0], 0);
+        if (keeper) load_list(bhq, i, lists[0], 0);
         load_queries(bhq, i);
         open_buffers(unit);
         const int raw0 = uniform(col_idx[at * g.T]);       // read beside the count
         const int cnt = max(0, min(uniform(row_cnt[at]), g.T));
-        if (wave == 0) load_tail(bhq, i, cnt);
+        if (keeper) load_tail(bhq, i, cnt);
         const bool early = cnt > own_blocks(i);            // the first entry cannot be one that token order replaces
         int j0 = raw0 >= 0 && raw0 < allowed_cols(i, g) ? raw0 : 0;
         if (!early) {
             sync_stages();
-            if (wave == 0) close_list(info[0], i, cnt, lists[0]);
+            if (keeper) close_list(info[0], i, cnt, lists[0]);
             __syncthreads();
             j0 = uniform(lists[0][0]) & kEntryBlock;
         }
-        issue_block(j0);
-        if (early && wave == 0) {
+        if (half == 0) issue_block(j0, j0);
+        if (early && keeper) {
             __builtin_amdgcn_s_waitcnt(0x8F74);            // vmcnt(36): what was issued before the tiles has landed
             asm volatile("" ::: "memory");
             close_list(info[0], i, cnt, lists[0]);
         }
-        if (threadIdx.x == 0) open_next(info[1], tickets ? atomicAdd(tickets + home * kTicketStride, 1) : -1);
+        if constexpr (HALVES == 2) {
+            __builtin_amdgcn_s_waitcnt(0xC07F);            // lgkmcnt(0): the list is in LDS; the tiles may still travel
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            if (half == 1) issue_block(uniform(lists[0][(uniform(info[0].len) + 1) >> 1]) & kEntryBlock, j0);
+        } else if (threadIdx.x == 0) {
+            open_next(info[1], tickets ? atomicAdd(tickets + home * kTicketStride, 1) : -1);
+        }
         sync_stages();
     }
 
     for (int cur = 0;; cur ^= 1) {
         // here: the first block's tiles (its four K' parts and V'^T parts) are in the ring, Q' in registers, the row's
         // info and list (first chunk) in info[cur], lists[cur]
-        const int len = uniform(info[cur].len);
-        const int *list = lists[cur];
+        // a split row: the halves' blocks differ by one at most
+        const int whole = uniform(info[cur].len), upper = (whole + 1) >> 1;
+        const int len = HALVES == 1 ? whole : half == 0 ? upper : whole - upper;
+        const int skip = HALVES == 1 ? 0 : half * upper;   // entries of the list in front of this half's
+        const int *list = lists[cur] + skip;
         State st;
         st.all_seen = false;
 #pragma unroll
@@ -765,7 +794,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         int jc = pk & kEntryBlock;
         for (int e = 0; e < len; ++e) {
             const int pn = uniform(later);                 // past the end: the next row's first block or any (unused)
-            later = list[(e + 2) & (kList - 1)];
+            later = HALVES == 1 ? list[(e + 2) & (kList - 1)] : lists[cur][(skip + e + 2) & (kList - 1)];
             const int jn = pn & kEntryBlock;
             const bool masked = (pk & kEntryMask) != 0;
             const int room0 = (pk >> kEntryRoomShift) & 255;             // keys of the block that exist
@@ -779,8 +808,11 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             step<3>(st, sb, sa, kf, qf, pb, pa, sg3, sg1, qpos, room0 - 3 * KS, masked, c2, lh, buf, off, jn, jn, wave, lane);
             jc = jn;
             pk = pn;
-            if (__builtin_expect(e == event, 0)) at_event(e);
+            if constexpr (HALVES == 1)
+                if (__builtin_expect(e == event, 0)) at_event(e);
         }
+        if (HALVES == 2 && len < upper)                    // the other half's last block: its meeting points
+            for (int p = 0; p < BLOCK / KS; ++p) __builtin_amdgcn_s_barrier();
         const bool ahead = (pk & kEntryAhead) != 0;        // the ring holds the next row's first block
         drain(st, pa, sg0, off);
 
@@ -788,56 +820,123 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         // The two lanes of a query exchange pieces so that each stores 8 consecutive features.
         uintx4 out[2][4][2];
         float lt[2];
-        auto finish = [&]() {
+        auto finish_tile = [&](auto tile) __attribute__((always_inline)) {
+            constexpr int nt = decltype(tile)::value;
+            lt[nt] = st.l[nt] + __shfl_xor(st.l[nt], 32, 64);
+            const float inv = lt[nt] > 0.0f ? 1.0f / lt[nt] : 0.0f;
 #pragma unroll
-            for (int nt = 0; nt < 2; ++nt) {
-                lt[nt] = st.l[nt] + __shfl_xor(st.l[nt], 32, 64);
-                const float inv = lt[nt] > 0.0f ? 1.0f / lt[nt] : 0.0f;
+            for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+                for (int a = 0; a < 2; ++a) {
+                    uint32_t piece[2][2];                  // [features 8 (2 a + y)][pair]
+#pragma unroll
+                    for (int y = 0; y < 2; ++y)
+#pragma unroll
+                        for (int z = 0; z < 2; ++z) {
+                            const int x = 4 * (2 * a + y) + 2 * z;
+                            const floatx2 o = {st.acc_o[dt][nt][x] * inv, st.acc_o[dt][nt][x + 1] * inv};
+                            piece[y][z] = __builtin_bit_cast(uint32_t, __builtin_convertvector(o, bf16x2));
+                        }
+#pragma unroll
+                    for (int z = 0; z < 2; ++z) {
+                        // lower half: (own, other's) of piece 0; upper half: (other's, own) of piece 1
+                        const auto sw = __builtin_amdgcn_permlane32_swap(piece[0][z], piece[1][z], false, false);
+                        out[nt][dt][a][z] = sw[0];
+                        out[nt][dt][a][2 + z] = sw[1];
+                    }
+                }
+        };
+        auto store_tile = [&](auto tile) __attribute__((always_inline)) {
+            constexpr int nt = decltype(tile)::value;
+            const int qs = i * BLOCK + wave * 64 + 32 * nt + ln;
+            if (qs < g.n) {
+                bf16_t *dst = Op + ((size_t)bhq * g.n + qs) * D + 8 * lh;
 #pragma unroll
                 for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-                    for (int a = 0; a < 2; ++a) {
-                        uint32_t piece[2][2];              // [features 8 (2 a + y)][pair]
-#pragma unroll
-                        for (int y = 0; y < 2; ++y)
-#pragma unroll
-                            for (int z = 0; z < 2; ++z) {
-                                const int x = 4 * (2 * a + y) + 2 * z;
-                                const floatx2 o = {st.acc_o[dt][nt][x] * inv, st.acc_o[dt][nt][x + 1] * inv};
-                                piece[y][z] = __builtin_bit_cast(uint32_t, __builtin_convertvector(o, bf16x2));
-                            }
-#pragma unroll
-                        for (int z = 0; z < 2; ++z) {
-                            // lower half: (own, other's) of piece 0; upper half: (other's, own) of piece 1
-                            const auto sw = __builtin_amdgcn_permlane32_swap(piece[0][z], piece[1][z], false, false);
-                            out[nt][dt][a][z] = sw[0];
-                            out[nt][dt][a][2 + z] = sw[1];
-                        }
-                    }
+                    for (int a = 0; a < 2; ++a) *reinterpret_cast<uintx4 *>(dst + 32 * dt + 16 * a) = out[nt][dt][a];
+                if (lse && lh == 0)
+                    lse[(size_t)bhq * g.n + qs] = lt[nt] > 0.0f ? (st.mref[nt] + log2f(lt[nt])) * kLn2F : -INFINITY;
             }
         };
-        auto store = [&]() {
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt) {
-                const int qs = i * BLOCK + wave * 64 + 32 * nt + ln;
-                if (qs < g.n) {
-                    bf16_t *dst = Op + ((size_t)bhq * g.n + qs) * D + 8 * lh;
-#pragma unroll
-                    for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-                        for (int a = 0; a < 2; ++a) *reinterpret_cast<uintx4 *>(dst + 32 * dt + 16 * a) = out[nt][dt][a];
-                    if (lse && lh == 0)
-                        lse[(size_t)bhq * g.n + qs] = lt[nt] > 0.0f ? (st.mref[nt] + log2f(lt[nt])) * kLn2F : -INFINITY;
-                }
-            }
-            // each wave's half of the row's flag: some probability outgrew its fixed reference (the caller redoes the row)
-            const bool bad = __any(!(st.l[0] <= kBigRowSum) || !(st.l[1] <= kBigRowSum));
+        constexpr auto tile0 = std::integral_constant<int, 0>{};
+        constexpr auto tile1 = std::integral_constant<int, 1>{};
+        auto finish = [&]() {
+            finish_tile(tile0);
+            finish_tile(tile1);
+        };
+        // each wave's half of the row's flag: some probability outgrew its fixed reference (the caller redoes the row)
+        auto outgrown = [](float l) { return !(l <= kBigRowSum); };
+        auto flag_row = [&](bool lane_bad) {
+            const bool bad = __any(lane_bad);
             if (lane == 0) {
                 const size_t f = ((size_t)bhq * g.T + i) * 2 + wave;
-                if (tickets) redo[f] = bad ? 1 : 0;
+                if (HALVES == 1 && tickets) redo[f] = bad ? 1 : 0;
                 else reinterpret_cast<int16_t *>(redo)[f] = bad ? 1 : 0;
             }
         };
+        auto store = [&]() {
+            store_tile(tile0);
+            store_tile(tile1);
+            flag_row(outgrown(st.l[0]) || outgrown(st.l[1]));
+        };
+        if constexpr (HALVES == 2) {
+            // Half h keeps query tile h: it leaves O^T of the other one in its own ring, where stage dt takes
+            // [wave][4 registers][lane] of feature tile dt, and adds what the other half has left.
+            sync_stages();                                 // every load has landed, every fragment has been read
+            auto ring_tile = [&](int dt, int of) {
+                Stage &sg = dt == 0 ? rg0[of] : dt == 1 ? rg1[of] : dt == 2 ? rg2[of] : rg3[of];
+                static_assert(sizeof(floatx4) * 2 * 4 * 64 == kStageB, "a feature tile of both waves fits the K' part of a stage");
+                return reinterpret_cast<floatx4 *>(sg.k) + wave * 256 + lane;
+            };
+            auto leave_tile = [&](auto tile) __attribute__((always_inline)) {
+                constexpr int nt = decltype(tile)::value;
+#pragma unroll
+                for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+                    for (int x = 0; x < 4; ++x)
+                        ring_tile(dt, half)[64 * x] = floatx4{st.acc_o[dt][nt][4 * x], st.acc_o[dt][nt][4 * x + 1],
+                                                              st.acc_o[dt][nt][4 * x + 2], st.acc_o[dt][nt][4 * x + 3]};
+            };
+            if (half == 0) leave_tile(tile1);
+            else leave_tile(tile0);
+            // a query that has met no key has no reference: the other half's is taken
+            sums[threadIdx.x] = floatx4{st.l[0], st.l[1], st.seen[0] ? st.mref[0] : -INFINITY, st.seen[1] ? st.mref[1] : -INFINITY};
+            __syncthreads();
+            const floatx4 other = sums[threadIdx.x ^ 128];
+            // (first half) the sums of the whole row against its first reference, as an undivided row has them: the same rows
+            // are redone
+            bool bad = outgrown(other[0]) || outgrown(other[1]);
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt)
+                bad = bad || outgrown(st.l[nt] + (st.seen[nt] ? other[nt] * __builtin_amdgcn_exp2f(other[2 + nt] - st.mref[nt]) : 0.0f));
+            auto merge_tile = [&](auto tile) __attribute__((always_inline)) {
+                constexpr int nt = decltype(tile)::value;
+                const float ra = st.seen[nt] ? st.mref[nt] : -INFINITY, rb = other[2 + nt], ref = fmaxf(ra, rb);
+                const float wa = ra == ref ? 1.0f : __builtin_amdgcn_exp2f(ra - ref);
+                const float wb = rb == ref ? 1.0f : __builtin_amdgcn_exp2f(rb - ref);
+                st.mref[nt] = ref;
+                st.l[nt] = st.l[nt] * wa + other[nt] * wb;
+#pragma unroll
+                for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) {
+                        const floatx4 o = ring_tile(dt, half ^ 1)[64 * x];
+#pragma unroll
+                        for (int y = 0; y < 4; ++y)
+                            st.acc_o[dt][nt][4 * x + y] = st.acc_o[dt][nt][4 * x + y] * wa + o[y] * wb;
+                    }
+                finish_tile(tile);
+                store_tile(tile);
+            };
+            if (half == 0) {
+                merge_tile(tile0);
+                flag_row(bad);
+            } else {
+                merge_tile(tile1);
+            }
+            return;
+        }
         if (!ahead) {
             if (wave == 0)
                 while (step_no < 3) {                      // a list too short to prepare the next row under it
@@ -867,7 +966,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             }
         } else {
             open_buffers(unit1);
-            issue_block(j1);
+            issue_block(j1, j1);
         }
         __builtin_amdgcn_sched_barrier(0);
         finish();
@@ -896,6 +995,13 @@ pbs_status launch_attn_wide(const Geo &g, const void *Qp, const void *Kp, const 
     const long long units = (long long)g.batch * g.h_kv, rows = (long long)g.r * g.T;
     const bool queues = wide_rows_from_queues(g);
     const int cohort_log2 = queues ? wide::kCohortLog2 : wide::kOwnCohortLog2;
+    // With one row to a compute unit the longest row is what a call waits for, and half of the chip is idle: its list is cut
+    // in two.  One piece against two, whole call on causal lists: 4 / 2 heads x 1024 29.9 -> 22.7 us, 32 / 8 x 1024 (256
+    // rows) 32.2 -> 25.7 us, 4 / 2 x 4096 77.7 -> 49.5 us.  A second row after the first pays its start and end again, which
+    // the lists have to be long for: 8 / 2 x 8192 (512 rows) 168 -> 136 us, but with a twentieth of the blocks 38.5 ->
+    // 43.0 us; the lengths are not known here.  (A list of such a call fits one chunk.)
+    const bool split = units * rows <= wide::kSplitRows;
+    static_assert(wide::kSplitRows < wide::kList, "a split row's list lies in LDS whole, with an entry behind it");
     unsigned wgs = wide::kResident;
     unsigned long long key = 0;
     if (queues) {
@@ -912,9 +1018,9 @@ pbs_status launch_attn_wide(const Geo &g, const void *Qp, const void *Kp, const 
         const long long cohorts = units * ((rows + (1 << cohort_log2) - 1) >> cohort_log2);
         wgs = (unsigned)(((cohorts + wide::kXcds - 1) / wide::kXcds * wide::kXcds) << cohort_log2);
     }
-    return launch(wide::attn_wide_kernel, dim3(wgs), dim3(128), 0, s, (const bf16_t *)Qp, (const bf16_t *)Kp,
-                  (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse, (int8_t *)redo, g, tok_delta,
-                  key, cohort_log2);
+    return launch(split ? wide::attn_wide_kernel<2> : wide::attn_wide_kernel<1>, dim3(wgs), dim3(split ? 256 : 128), 0, s,
+                  (const bf16_t *)Qp, (const bf16_t *)Kp, (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse,
+                  (int8_t *)redo, g, tok_delta, key, cohort_log2);
 }
 
 }  // namespace pbs

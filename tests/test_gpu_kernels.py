@@ -155,6 +155,53 @@ def test_rows_from_queues_and_lists_of_every_length(oracle):
             check_close(got[0, h, lo:hi], want[k][:hi - lo], "bf16", "row %d of head %d" % (i, h))
 
 
+@pytest.mark.parametrize("token_copy", [False, True])
+@pytest.mark.parametrize("Hq,Hkv,T,tail", [(2, 1, 1, 77), (4, 4, 2, 0), (2, 2, 9, 127), (4, 2, 41, 1)])
+def test_rows_in_two_halves(oracle, Hq, Hkv, T, tail, token_copy):
+    # calls with few rows give each half of a list two waves of its own: lists of 0, 1, 2, 3 .. entries, halves that differ
+    # by a block, halves without a key some queries may see, and references that rise along the list by up to 25 nats
+    # (no probability outgrows the first one's reference by 2^64) and fall by as much in every other head
+    block, d, seg = 128, 128, 256
+    n, R = T * block - tail, seg // block
+    g = torch.Generator(device="cuda")
+    g.manual_seed(31 + T)
+    Q, K, V = (torch.randn((1, h, n, d), generator=g, device="cuda") for h in (Hq, Hkv, Hkv))
+    u = torch.nn.functional.normalize(torch.randn(d, generator=g, device="cuda"), dim=0)
+    rise = torch.linspace(0.0, 1.0, n, device="cuda")
+    Q += 8.0 * u
+    for h in range(Hkv):
+        K[0, h] += 25.0 * d ** 0.5 / 8.0 * (rise if h % 2 == 0 else 1.0 - rise)[:, None] * u
+    Q, K, V = (x.to(torch.bfloat16) for x in (Q, K, V))
+    p = pbs.problem(1, Hq, Hkv, n, d, block, seg, "bf16", flags=pbs.FLAG_TOKEN_ORDER_COPY if token_copy else 0)
+    scores = torch.softmax(torch.randn((1, Hkv, n), generator=g, device="cuda"), dim=-1)
+    kidx, Kp, Vt = pbs.segment_permute(p, scores, K, V)
+    rng = np.random.default_rng(T)
+    cnt = np.zeros((1, Hq, T), dtype=np.int32)
+    cols = np.full((1, Hq, T, T), -1, dtype=np.int32)
+    for h in range(Hq):
+        for i in range(T):
+            seg_lo, full = i // R * R, (i // R + 1) * seg <= n
+            own = list(range(seg_lo, seg_lo + R)) if full else [i]
+            below = seg_lo if full else i
+            lst = [] if (i + h) % 7 == 3 else sorted(rng.choice(below, min(below, (3 * i + h) % (T + 1)), replace=False).tolist()) + own
+            if i % 5 == 4:
+                lst = lst[::-1]
+            cnt[0, h, i] = len(lst)
+            cols[0, h, i, :len(lst)] = lst
+    got, lse = pbs.attn_fwd(p, Q, Kp, Vt, None, kidx, i32_dev(cnt), i32_dev(cols), want_lse=True)
+    torch.cuda.synchronize()
+    host = [x.float().cpu().numpy() for x in (Q, K, V)]
+    kg = kidx.cpu().numpy()
+    want, want_lse = oracle.attn_fwd(host[0], oracle.gather_rows(host[1], kg), oracle.gather_rows(host[2], kg), None, kg, cnt,
+                                     cols, block, want_lse=True)
+    got, lse = to_host(got), lse.cpu().numpy()
+    empty = np.repeat(cnt == 0, block, axis=-1)[..., :n]
+    assert (got[empty] == 0).all() and np.isneginf(lse[empty]).all()
+    check_close(got, np.where(empty[..., None], 0.0, want), "bf16", "rows in two halves")
+    # fp32 logits of up to 40 and sums of a thousand terms: 2^-24 * 40 * log2(1000) is 2.4e-5; bf16 products are exact
+    np.testing.assert_allclose(lse[~empty], want_lse[~empty], atol=1e-4)
+
+
 def test_flagged_rows_from_queues_go_to_the_second_pass(oracle):
     # 4096 rows, the fewest that come from queues: their flags share the workspace with the queue heads.  Logits rise by
     # 60 nats along a sequence in the first head of each group only, so that it alone is flagged.
