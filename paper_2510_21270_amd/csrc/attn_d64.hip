@@ -466,8 +466,7 @@ pbs_status launch_attn_d64(const Geo &g, const void *Qp, const void *Kp, const v
                            hipStream_t s)
 {
     const long long rows = (long long)g.r * ceil_div(g.n, d64::kQ), units = (long long)g.batch * g.h_kv;
-    int cohort = 64;                                       // narrower while some XCD would get no workgroup
-    while (cohort > 8 && units * ((rows + cohort - 1) / cohort) < d64::kXcds) cohort >>= 1;
+    const int cohort = cohort_rows(g);
     const long long ncoh = units * ((rows + cohort - 1) / cohort);
     const long long wgs = (ncoh + d64::kXcds - 1) / d64::kXcds * d64::kXcds * cohort;
     constexpr long long kMaxX = 1 << 20;

@@ -268,10 +268,8 @@ static pbs_status launch_waves(const Geo &g, const void *Qp, const void *Kp, con
                                const int32_t *kidx, const int32_t *row_cnt, const int32_t *col_idx, void *Op, float *lse,
                                hipStream_t s)
 {
-    // cohorts as wide as the workgroups one XCD holds at a time, narrower while some XCD would get none
     const long long rows = (long long)g.r * ceil_div(g.n, kQ), units = (long long)g.batch * g.h_kv;
-    int cohort = 64;
-    while (cohort > 8 && units * ((rows + cohort - 1) / cohort) < kXcds) cohort >>= 1;
+    const int cohort = cohort_rows(g);
     const long long ncoh = units * ((rows + cohort - 1) / cohort);
     const long long wgs = (ncoh + kXcds - 1) / kXcds * kXcds * cohort;
     constexpr long long kMaxX = 1 << 20;

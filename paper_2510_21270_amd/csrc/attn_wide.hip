@@ -49,8 +49,7 @@ constexpr int KS = 32;                                     // keys per sub-tile
 constexpr int kStageB = 8192;                              // K' sub-tile: 32 rows x 256 B; V'^T sub-tile: 128 rows x 64 B
 constexpr int kLoadsPerWave = 8;                           // 16-byte-per-lane loads a wave issues per stage
 constexpr int kList = 1024;                                // listed blocks staged in LDS at a time
-constexpr int kXcds = 8;
-constexpr int kCohortLog2 = 6, kOwnCohortLog2 = 3;         // rows from queues, every row with a workgroup of its own
+constexpr int kXcds = 8, kCohortLog2 = 6;
 constexpr int kResident = 512;                             // workgroups the chip holds: two on each of 256 compute units
 constexpr int kSplitRows = 256;                            // rows up to which each has four waves
 constexpr int kTicketStride = 32;                          // queue heads lie 128 bytes apart
@@ -994,7 +993,7 @@ pbs_status launch_attn_wide(const Geo &g, const void *Qp, const void *Kp, const 
 {
     const long long units = (long long)g.batch * g.h_kv, rows = (long long)g.r * g.T;
     const bool queues = wide_rows_from_queues(g);
-    const int cohort_log2 = queues ? wide::kCohortLog2 : wide::kOwnCohortLog2;
+    const int cohort_log2 = queues ? wide::kCohortLog2 : __builtin_ctz(cohort_rows(g));
     // With one row to a compute unit the longest row is what a call waits for, and half of the chip is idle: its list is cut
     // in two.  One piece against two, whole call on causal lists: 4 / 2 heads x 1024 29.9 -> 22.7 us, 32 / 8 x 1024 (256
     // rows) 32.2 -> 25.7 us, 4 / 2 x 4096 77.7 -> 49.5 us.  A second row after the first pays its start and end again, which
@@ -1010,11 +1009,6 @@ pbs_status launch_attn_wide(const Geo &g, const void *Qp, const void *Kp, const 
         const pbs_status st = launch(wide::take_queues_kernel, dim3(1), dim3(64), 0, s, key);
         if (st != PBS_OK) return st;
     } else {
-        // Every row has a workgroup of its own, and nothing evens out what the XCDs get: with fewer kv heads than XCDs the
-        // ones that start with the longer cohorts keep them throughout.  Cohorts of 64 rows against 8, causal lists, whole
-        // call: 4 / 2 heads x 20000 515 -> 417 us, 8 / 2 x 30000 1714 -> 1465 us, 16 / 4 x 12288 587 -> 532 us, 28 / 4 x 16384
-        // 1631 -> 1548 us; a fifth of the blocks 4 / 2 x 20000 153 -> 140 us, 28 / 4 x 9000 196 -> 180 us; with a kv head to
-        // every XCD (32 / 8 x 2048 .. 8147) the same.
         const long long cohorts = units * ((rows + (1 << cohort_log2) - 1) >> cohort_log2);
         wgs = (unsigned)(((cohorts + wide::kXcds - 1) / wide::kXcds * wide::kXcds) << cohort_log2);
     }

@@ -49,6 +49,15 @@ inline Geo make_geo(const pbs_problem *p)
     return g;
 }
 
+// Rows of one kv head that an XCD is handed at a time, longest lists first, where a workgroup per row is launched and
+// nothing evens out what the XCDs get.  A kv head (unit) to every XCD: 64, which is what an XCD holds, so that all of them
+// share tiles in its L2.  Fewer units: the XCDs that start with the longer cohorts would keep them throughout, and 8 rows
+// spread them evenly.  64 rows against 8, causal lists, us: wide kernel 4 / 2 heads x 20000 515 / 417, 28 / 4 x 9000 541 /
+// 494, 16 / 4 x 12288 587 / 532; block 64 4 / 2 x 32768 1248 / 1118, 16 / 4 x 3000 89 / 76, 28 / 4 x 32700 7725 / 7510 and, a
+// quarter of the blocks, 2618 / 2575; d = 64 4 / 2 x 12000 233 / 175, 16 / 4 x 12301 678 / 638; float32 2 / 2 x 4096 231 / 147,
+// 8 / 2 x 4096 608 / 537.  With 8 units both give the same order.
+inline int cohort_rows(const Geo &g) { return (long long)g.batch * g.h_kv < 8 ? 8 : 64; }
+
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 inline bool aligned16(const void *ptr) { return (reinterpret_cast<uintptr_t>(ptr) & 15u) == 0; }
