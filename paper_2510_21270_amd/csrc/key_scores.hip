@@ -109,18 +109,40 @@ struct __align__(16) KTile {
     unsigned char b[kTileB];
 };
 
-// Descriptor of a workgroup's keys and byte offsets of this lane: dma[j]: in memory, of the piece it moves in load j of
-// its wave, ahead of 1024 j (the instruction's own offset, which counts in memory and in LDS); kfr[x]: in LDS, of its
-// piece of feature step x.
+// Descriptor of a workgroup's keys (bytes of them) and byte offsets of this lane: dma[j]: in memory, of the piece it moves in
+// load j of its wave, ahead of 1024 j (the instruction's own offset, which counts in memory and in LDS); kfr[x]: in LDS, of
+// its piece of feature step x.
 struct KSource {
     __amdgpu_buffer_rsrc_t keys;
+    int bytes;
     uint32_t dma[4], kfr[8];
 };
+
+// Scalar offset of what wave w moves of tile t.  The hardware compares a lane's own offset with the descriptor's size less the
+// scalar offset, a difference that must not fall below zero: a tile past the last key starts at the end, where every lane
+// is out of range.
+__host__ __device__ constexpr int tile_offset(int t, int wave, int bytes)
+{
+    const int first = t * kTileB + wave * (kTileB / 2);
+    return first < bytes ? first : bytes;
+}
+constexpr bool tile_offsets_hold()
+{
+    for (int keys = 1; keys <= 3 * kTileKeys; ++keys)
+        for (int t = 0; t <= 3 + 8; ++t)                   // the loop runs in steps of four tiles and loads five ahead
+            for (int wave = 0; wave < 2; ++wave) {
+                const int at = tile_offset(t, wave, keys * 256);
+                if (at > keys * 256 || (t * kTileKeys + wave * 16 < keys && at != (t * kTileKeys + wave * 16) * 256)) return false;
+            }
+    return true;
+}
+static_assert(tile_offsets_hold(), "no load starts behind the descriptor's end, and every key is loaded from its place");
 
 __device__ __forceinline__ KSource key_source(const bf16_t *first, int keys, int lane)
 {
     KSource k;
-    k.keys = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(first), 0, keys * 256, 0x00020000);
+    k.bytes = keys * 256;
+    k.keys = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(first), 0, k.bytes, 0x00020000);
     const int row = lane >> 4, place = lane & 15, key = lane & 31;
 #pragma unroll
     for (int j = 0; j < 4; ++j) k.dma[j] = (uint32_t)(row * 256 + ((place ^ (4 * j + row)) << 4));
@@ -133,7 +155,7 @@ __device__ __forceinline__ KSource key_source(const bf16_t *first, int keys, int
 __device__ __forceinline__ void issue_tile(KTile &tile, const KSource &src, int t, int wave)
 {
     const lptr_t dst = (lptr_t)((__attribute__((address_space(3))) unsigned char *)tile.b + wave * 4096);
-    const int soff = t * kTileB + wave * 4096;
+    const int soff = tile_offset(t, wave, src.bytes);
     __builtin_amdgcn_raw_ptr_buffer_load_lds(src.keys, dst, 16, src.dma[0], soff, 0, 0);
     __builtin_amdgcn_raw_ptr_buffer_load_lds(src.keys, dst, 16, src.dma[1], soff, 1024, 0);
     __builtin_amdgcn_raw_ptr_buffer_load_lds(src.keys, dst, 16, src.dma[2], soff, 2048, 0);
