@@ -12,7 +12,8 @@
 // accumulator).  Qhat is an fp32 mean, not a bf16 value, so it is pre-multiplied by scale*log2(e) and split
 // into two bf16 terms hi + lo; each tile takes two MFMAs per fragment.  A wave keeps the fragments of its rows
 // of Qhat in registers (64 rows for long inputs, 32 for short ones) and the K tiles go through LDS, shared by the waves of
-// a workgroup.  Both forms compute every score with the same operations in the same order.
+// a workgroup.  Both forms compute a logit with the same operations in the same order; a row's sum of exponentials adds the
+// keys in an order that depends on the size.
 // Everything else (fp32 inputs, d = 64): the same two sweeps on the fp64 matrix instruction.
 #include <utility>
 
@@ -95,8 +96,8 @@ __global__ __launch_bounds__(256) void qhat_split_kernel(const bf16_t *__restric
 // Tiles travel to LDS asynchronously, through a ring of four; a load has three iterations to arrive.
 // Bound by the matrix work under the chip's power limit and, close behind, by the stream of K: 8 heads of 131072 keys (two sweeps
 // of 69 GFLOP and 268 MB each) 136 -> 125.5 us for the stage against four waves of 32 rows, two to a SIMD, whose staging,
-// exponentials and products took turns.  On the 16 x 16 x 32 instruction, which the power limit favours, 110 us, but with
-// sums in another order: keys with nearly equal scores would change places against the other sizes.  Not taken.
+// exponentials and products took turns.  (The 16 x 16 x 32 instruction, which the power limit favours, was seen at 110 us in
+// a form of these sweeps that adds a logit's products in another order; the short form would have to change with it.)
 constexpr int kTileKeys = 32;
 constexpr int kTileB = kTileKeys * 256;
 
@@ -162,6 +163,47 @@ __device__ __forceinline__ void issue_tile(KTile &tile, const KSource &src, int 
     __builtin_amdgcn_raw_ptr_buffer_load_lds(src.keys, dst, 16, src.dma[3], soff, 3072, 0);
 }
 
+// The order in which a workgroup goes through its tiles: each starts elsewhere in its share.  All of them move at one pace, and
+// where shares begin at multiples of a power of two (8 heads of 65536, 131072, 262144 keys) workgroups in step were slow to get
+// keys that are not in the caches.  Stage, us, behind a kernel that has written 1 GiB, all from their first tile on / each from
+// another: 65536 keys 101 / 95, 131072 175 / 165, 262144 329 / 299, 66000 114 / 100 (on one machine of four 91 / 90, 163 / 160,
+// 282 / 291, 112 / 99); with the keys in the caches 131072 takes 127 either way, 66000 1 more.
+// Tiles come in groups of four and groups in ranges (a power of two of them): the ranges are taken in turn, the groups of a range
+// in turn and the tiles of a group in turn, each from another one on.  A share that ends inside a range keeps its order.
+struct TileOrder {
+    int in[4];             // tile of a group at each of its four steps
+    int groups;            // of the share
+    int log2_groups;       // of a range
+    int first, turn;       // range and group of a range that the share starts with
+    __device__ __forceinline__ int range(int g) const
+    {
+        const int r = (g >> log2_groups) + first, ranges = groups >> log2_groups;
+        return r >= ranges ? r - ranges : r;
+    }
+    // first tile of the group at place g; behind the last one: past the share's end
+    __device__ __forceinline__ int group(int g) const
+    {
+        if (g >= groups) return 4 * g;
+        return 4 * ((range(g) << log2_groups) | ((g + turn) & ((1 << log2_groups) - 1)));
+    }
+};
+
+// range_keys: a power of two, from a group on
+__device__ __forceinline__ TileOrder tile_order(int keys, int range_keys)
+{
+    const bool whole = (keys & (range_keys - 1)) == 0;
+    const uint32_t place = (blockIdx.y * gridDim.x + blockIdx.x) * 0x9E3779B1u;           // 2^32 / golden ratio: evenly spread
+    const int phase = whole ? place >> 11 & 31 : 0;
+    TileOrder o;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o.in[i] = (i + phase) & 3;
+    o.groups = (keys + 4 * kTileKeys - 1) / (4 * kTileKeys);
+    o.log2_groups = whole ? 31 - __builtin_clz(range_keys / (4 * kTileKeys)) : 0;
+    o.turn = phase >> 2;
+    o.first = whole ? (int)((place >> 16) * (uint32_t)(o.groups >> o.log2_groups) >> 16) : 0;
+    return o;
+}
+
 // Feature step x: lane (key = lane & 31, h = lane >> 5) holds d = 16 x + 8 h .. + 8 of its key.
 __device__ __forceinline__ bf16x8 k_fragment(const KTile &tile, const KSource &src, int x)
 {
@@ -210,11 +252,11 @@ __device__ __forceinline__ void unrolled(F &&f, std::integer_sequence<int, M...>
 }
 
 // One iteration: logits of tile t + 1 into s_nxt; score(m) does the vector work under MFMA m.  tile1: LDS tile of t + 1, which
-// tile t + 5 takes; tile2: of t + 2.
+// tile t + 5 takes, number `later` of the share; tile2: of t + 2.
 template <bool KEYS_BY_ROWS, typename Score>
 __device__ __forceinline__ void sweep_step(floatx16 (&s_nxt)[2], bf16x8 (&kf)[8], const bf16x8 (&qf)[2][8][2],
                                            const floatx16 (&c)[2], KTile &tile1, const KTile &tile2, const KSource &src,
-                                           int t, int wave, Score score)
+                                           int later, int wave, Score score)
 {
     __builtin_amdgcn_sched_barrier(0);
     unrolled([&](auto mc) __attribute__((always_inline)) {
@@ -231,7 +273,7 @@ __device__ __forceinline__ void sweep_step(floatx16 (&s_nxt)[2], bf16x8 (&kf)[8]
             __builtin_amdgcn_s_waitcnt(0x0078);            // vmcnt(8) lgkmcnt(0), gfx9 encoding
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_sched_barrier(0);
-            issue_tile(tile1, src, t + 5, wave);
+            issue_tile(tile1, src, later, wave);
         }
     }, std::make_integer_sequence<int, 32>{});
 }
@@ -240,12 +282,13 @@ __device__ __forceinline__ void sweep_step(floatx16 (&s_nxt)[2], bf16x8 (&kf)[8]
 template <bool KEYS_BY_ROWS>
 __device__ __forceinline__ void sweep_start(floatx16 (&s)[2], bf16x8 (&kf)[8], bf16x8 (&qf)[2][8][2], const floatx16 (&c)[2],
                                             KTile &t0, KTile &t1, KTile &t2, KTile &t3, const KSource &src,
-                                            const bf16_t *qsplit, int bh, int wave, int lane)
+                                            const TileOrder &order, const bf16_t *qsplit, int bh, int wave, int lane)
 {
-    issue_tile(t0, src, 0, wave);
-    issue_tile(t1, src, 1, wave);
-    issue_tile(t2, src, 2, wave);
-    issue_tile(t3, src, 3, wave);
+    const int g0 = order.group(0);
+    issue_tile(t0, src, g0 + order.in[0], wave);
+    issue_tile(t1, src, g0 + order.in[1], wave);
+    issue_tile(t2, src, g0 + order.in[2], wave);
+    issue_tile(t3, src, g0 + order.in[3], wave);
     load_qfrags(qf, qsplit, bh, wave, lane);
     __builtin_amdgcn_s_waitcnt(0x0F70);                    // vmcnt(0), gfx9 encoding
     __syncthreads();
@@ -258,7 +301,7 @@ __device__ __forceinline__ void sweep_start(floatx16 (&s)[2], bf16x8 (&kf)[8], b
 #pragma unroll
     for (int x = 0; x < 7; ++x) kf[x] = k_fragment(t1, src, x);
     __syncthreads();                                       // both waves have read tile 0
-    issue_tile(t0, src, 4, wave);
+    issue_tile(t0, src, order.group(1) + order.in[0], wave);
 }
 
 // ------------------------------------------------------------------ MFMA path: sweep 1
@@ -272,13 +315,14 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     __shared__ KTile tile0, tile1, tile2, tile3;
     const int bh = blockIdx.y, parts = ceil_div(g.n, range_keys);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int range = blockIdx.x * ranges;
-    const int key_begin = range * range_keys, keys = min(g.n - key_begin, range_keys * ranges);
+    const int first_range = blockIdx.x * ranges;
+    const int key_begin = first_range * range_keys, keys = min(g.n - key_begin, range_keys * ranges);
     const int ntiles = ceil_div(keys, kTileKeys), range_tiles = range_keys / kTileKeys;
     const KSource src = key_source(K + ((size_t)bh * g.n + key_begin) * 128, keys, lane);
+    const TileOrder order = tile_order(keys, range_keys);
     bf16x8 qf[2][8][2], kf[8];
     floatx16 sa[2], sb[2];
-    sweep_start<true>(sa, kf, qf, sa, tile0, tile1, tile2, tile3, src, qsplit, bh, wave, lane);
+    sweep_start<true>(sa, kf, qf, sa, tile0, tile1, tile2, tile3, src, order, qsplit, bh, wave, lane);
     float m[2] = {-INFINITY, -INFINITY}, l[2] = {0.0f, 0.0f};   // row 32 rt + (lane & 31), this lane's half of the keys
     // keys of tile t that do not exist weigh nothing
     auto cut = [&](floatx16 &s, int t) __attribute__((always_inline)) {
@@ -294,7 +338,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     top0 = sa[0][0];
 #pragma unroll
     for (int i = 1; i < 16; ++i) top0 = fmaxf(top0, sa[0][i]);
-    auto step = [&](floatx16 (&s)[2], floatx16 (&nxt)[2], KTile &u1, const KTile &u2, int t) __attribute__((always_inline)) {
+    auto step = [&](floatx16 (&s)[2], floatx16 (&nxt)[2], KTile &u1, const KTile &u2, int t, int later) __attribute__((always_inline)) {
         cut(s[1], t);
         float p[2], sum[2], mn[2], less[2], top1 = -INFINITY;
         // arguments are <= 0: the bare instruction (no denormal rescue) loses nothing that a sum near 1 would see
@@ -309,7 +353,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                 m[rt] = mn[rt];
             }
         };
-        sweep_step<true>(nxt, kf, qf, nxt, u1, u2, src, t, wave, [&](auto mc) __attribute__((always_inline)) {
+        sweep_step<true>(nxt, kf, qf, nxt, u1, u2, src, later, wave, [&](auto mc) __attribute__((always_inline)) {
             constexpr int mm = decltype(mc)::value, rt = mm >> 4, i = mm & 15;
             if constexpr (i == 0) {
                 mn[rt] = fmaxf(m[rt], rt == 0 ? top0 : top1);
@@ -332,12 +376,16 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         });
         add(std::integral_constant<int, 31>{});
     };
+    int g1 = order.group(1);                               // the next group and the one after it
     for (int t = 0; t < ntiles; t += 4) {                  // (tiles past the last one hold no keys)
-        step(sa, sb, tile1, tile2, t);
-        step(sb, sa, tile2, tile3, t + 1);
-        step(sa, sb, tile3, tile0, t + 2);
-        step(sb, sa, tile0, tile1, t + 3);
+        const int g2 = order.group((t >> 2) + 2);
+        step(sa, sb, tile1, tile2, t, g1 + order.in[1]);
+        step(sb, sa, tile2, tile3, t + 1, g1 + order.in[2]);
+        step(sa, sb, tile3, tile0, t + 2, g1 + order.in[3]);
+        step(sb, sa, tile0, tile1, t + 3, g2 + order.in[0]);
+        g1 = g2;
         if ((t + 4) % range_tiles == 0 || t + 4 >= ntiles) {         // the end of a range
+            const int range = first_range + (order.log2_groups ? order.range(t >> 2) : t / range_tiles);
 #pragma unroll
             for (int rt = 0; rt < 2; ++rt) {               // merge the two lane halves; the rows of a wave are its own
                 const float mo = __shfl_xor(m[rt], 32, 64), lo = __shfl_xor(l[rt], 32, 64);
@@ -348,7 +396,6 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                 m[rt] = -INFINITY;
                 l[rt] = 0.0f;
             }
-            ++range;
         }
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);                    // the loads issued past the end have landed
@@ -403,6 +450,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int key_begin = wg * kpw, keys = min(g.n - key_begin, kpw), ntiles = ceil_div(keys, kTileKeys);
     const KSource src = key_source(K + ((size_t)bh * g.n + key_begin) * 128, keys, lane);
+    const TileOrder order = tile_order(keys, 4 * kTileKeys);
     float *out = scores + (size_t)bh * g.n + key_begin;
     bf16x8 qf[2][8][2], kf[8];
     // the accumulators start at c[row]; row = 64 wave + 32 rt + 8 (i / 4) + 4 (lane >> 5) + (i % 4)
@@ -412,7 +460,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
         for (int i = 0; i < 16; ++i)
             c[rt][i] = cvec[(size_t)bh * kQRows + 64 * wave + 32 * rt + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3)];
-    sweep_start<false>(sa, kf, qf, c, tile0, tile1, tile2, tile3, src, qsplit, bh, wave, lane);
+    sweep_start<false>(sa, kf, qf, c, tile0, tile1, tile2, tile3, src, order, qsplit, bh, wave, lane);
     float done[2] = {0.0f, 0.0f};                            // this lane's sums of the tile before
     auto halves = [&](int rt) __attribute__((always_inline)) {
         const uint32_t own = __builtin_bit_cast(uint32_t, done[rt]);
@@ -422,11 +470,12 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     };
     // 16 keys of the tile before for each wave (behind a barrier that psum of both waves is ahead of)
     const int mine = 16 * wave + (lane & 15);
-    auto leave = [&](int t) __attribute__((always_inline)) {
-        const int at = t * kTileKeys + mine;
+    auto leave = [&](int t, int number) __attribute__((always_inline)) {
+        const int at = number * kTileKeys + mine;
         if (lane < 16 && at >= 0 && at < keys) out[at] = psum[t & 3][0][mine] + psum[t & 3][1][mine];
     };
-    auto step = [&](floatx16 (&s)[2], floatx16 (&nxt)[2], KTile &u1, const KTile &u2, int t) __attribute__((always_inline)) {
+    auto step = [&](floatx16 (&s)[2], floatx16 (&nxt)[2], KTile &u1, const KTile &u2, int t, int before, int later)
+                    __attribute__((always_inline)) {
         float p[2], sum[2];
         auto add = [&](auto uc) __attribute__((always_inline)) {
             constexpr int u = decltype(uc)::value, rt = u >> 4;
@@ -434,32 +483,37 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             else sum[rt] += p[u & 1];
             if constexpr ((u & 15) != 0) asm volatile("" : "+v"(sum[rt]));
         };
-        sweep_step<false>(nxt, kf, qf, c, u1, u2, src, t, wave, [&](auto mc) __attribute__((always_inline)) {
+        sweep_step<false>(nxt, kf, qf, c, u1, u2, src, later, wave, [&](auto mc) __attribute__((always_inline)) {
             constexpr int mm = decltype(mc)::value;
             if constexpr (mm > 0) add(std::integral_constant<int, mm - 1>{});
             p[mm & 1] = __builtin_amdgcn_exp2f(s[mm >> 4][mm & 15]);
             if constexpr (mm == 1) halves(0);
             if constexpr (mm == 2) halves(1);
             if constexpr (mm == 3) psum[(t - 1) & 3][wave][lane & 31] = done[0] + done[1];     // the same from both halves
-            if constexpr (mm == 12) leave(t - 1);
+            if constexpr (mm == 12) leave(t - 1, before);
         });
         add(std::integral_constant<int, 31>{});
         done[0] = sum[0];
         done[1] = sum[1];
     };
-    int t = 0;
+    int t = 0, before = -1;                                  // number of tile t - 1
+    int g0 = order.group(0), g1 = order.group(1);            // the group of tile t and the next one
     for (; t < ntiles; t += 4) {                             // (tiles past the last one hold no keys)
-        step(sa, sb, tile1, tile2, t);
-        step(sb, sa, tile2, tile3, t + 1);
-        step(sa, sb, tile3, tile0, t + 2);
-        step(sb, sa, tile0, tile1, t + 3);
+        const int g2 = order.group((t >> 2) + 2);
+        step(sa, sb, tile1, tile2, t, before, g1 + order.in[1]);
+        step(sb, sa, tile2, tile3, t + 1, g0 + order.in[0], g1 + order.in[2]);
+        step(sa, sb, tile3, tile0, t + 2, g0 + order.in[1], g1 + order.in[3]);
+        step(sb, sa, tile0, tile1, t + 3, g0 + order.in[2], g2 + order.in[0]);
+        before = g0 + order.in[3];
+        g0 = g1;
+        g1 = g2;
     }
     halves(0);
     halves(1);
     psum[(t - 1) & 3][wave][lane & 31] = done[0] + done[1];
     __builtin_amdgcn_s_waitcnt(0x0F70);                    // the loads issued past the end have landed
     __syncthreads();
-    leave(t - 1);
+    leave(t - 1, before);
 }
 
 // ------------------------------------------------------------------ MFMA path, short inputs

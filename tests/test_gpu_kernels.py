@@ -576,9 +576,10 @@ def test_selection_time_with_a_kv_head_to_every_query_head():
 
 
 # long inputs, two waves of 64 rows to a workgroup: the last tile of one key, shares of a head that end inside a range, one
-# head, heads of two sequences.  Qhat's two bf16 terms leave 2^-18 of each product, 128 fp32 additions 2^-17 of their sum,
+# head, heads of two sequences; whole shares of one and of three ranges, which the workgroups start at different tiles.  Qhat's two bf16 terms leave 2^-18 of each product, 128 fp32 additions 2^-17 of their sum,
 # and sum |q k| / sqrt(d) < 8 for these inputs: within 1e-4 of a score.
-@pytest.mark.parametrize("batch,h_kv,n", [(1, 32, 10273), (2, 33, 5001), (1, 1, 327701), (1, 8, 41000)])
+@pytest.mark.parametrize("batch,h_kv,n", [(1, 32, 10273), (2, 33, 5001), (1, 1, 327701), (1, 8, 41000),
+                                          (1, 8, 65536), (1, 3, 524288)])
 def test_key_scores_of_long_inputs(batch, h_kv, n):
     g = torch.Generator(device="cuda")
     g.manual_seed(n)
