@@ -12,8 +12,8 @@
 // accumulator).  Qhat is an fp32 mean, not a bf16 value, so it is pre-multiplied by scale*log2(e) and split
 // into two bf16 terms hi + lo; each tile takes two MFMAs per fragment.  A wave keeps the fragments of its rows
 // of Qhat in registers (64 rows for long inputs, 32 for short ones) and the K tiles go through LDS, shared by the waves of
-// a workgroup.  Both forms compute a logit with the same operations in the same order; a row's sum of exponentials adds the
-// keys in an order that depends on the size.
+// a workgroup.  Both forms compute a logit, and the sums of a range of keys, with the same operations in the same order; how
+// long the ranges are depends on the keys of all heads (sweep_range_keys).
 // Everything else (fp32 inputs, d = 64): the same two sweeps on the fp64 matrix instruction.
 #include <utility>
 
@@ -130,7 +130,7 @@ __host__ __device__ constexpr int tile_offset(int t, int wave, int bytes)
 constexpr bool tile_offsets_hold()
 {
     for (int keys = 1; keys <= 3 * kTileKeys; ++keys)
-        for (int t = 0; t <= 3 + 8; ++t)                   // the loop runs in steps of four tiles and loads five ahead
+        for (int t = 0; t <= 3 + 32; ++t)                  // what is loaded past the end starts up to a range of tiles behind it
             for (int wave = 0; wave < 2; ++wave) {
                 const int at = tile_offset(t, wave, keys * 256);
                 if (at > keys * 256 || (t * kTileKeys + wave * 16 < keys && at != (t * kTileKeys + wave * 16) * 256)) return false;
@@ -165,44 +165,84 @@ __device__ __forceinline__ void issue_tile(KTile &tile, const KSource &src, int 
 
 // The order in which a workgroup goes through its tiles: each starts elsewhere in its share.  All of them move at one pace, and
 // where shares begin at multiples of a power of two (8 heads of 65536, 131072, 262144 keys) workgroups in step were slow to get
-// keys that are not in the caches.  Stage, us, behind a kernel that has written 1 GiB, all from their first tile on / each from
-// another: 65536 keys 101 / 95, 131072 175 / 165, 262144 329 / 299, 66000 114 / 100 (on one machine of four 91 / 90, 163 / 160,
-// 282 / 291, 112 / 99); with the keys in the caches 131072 takes 127 either way, 66000 1 more.
-// Tiles come in groups of four and groups in ranges (a power of two of them): the ranges are taken in turn, the groups of a range
-// in turn and the tiles of a group in turn, each from another one on.  A share that ends inside a range keeps its order.
-struct TileOrder {
-    int in[4];             // tile of a group at each of its four steps
-    int groups;            // of the share
-    int log2_groups;       // of a range
-    int first, turn;       // range and group of a range that the share starts with
-    __device__ __forceinline__ int range(int g) const
+// keys that are not in the caches.  Stage, us, behind a kernel that has written 1 GiB, on five machines, all from their first
+// tile on / each from another: 65536 keys 91 .. 109 / 90 .. 97, 131072 163 .. 188 / 160 .. 172, 262144 282 .. 337 / 291 .. 304,
+// 66000 112 .. 115 / 99 .. 100; with the keys in the caches 131072 takes 125.9 / 125.7, 262144 272 / 266, 66000 82.5 / 83.2.
+// Sweep 1 walks a range from the tile on that only the range's place in its head decides, so that a row's sums, which a range
+// adds up, do not depend on the other heads of a call (and from its first tile on where a call of fewer heads takes the short
+// form, with ranges of the same length); it takes the ranges of its share in turn from any one on.  Sweep 2 walks its whole
+// share from any tile on.  Tiles go in groups of four, as the loops do: the groups in turn and the tiles of a group in turn.
+// A range, and a share of sweep 2, that is not full keeps its order.  Past the end both go on behind the last key.
+__device__ __forceinline__ uint32_t spread32(uint32_t i) { return i * 0x9E3779B1u; }       // 2^32 / golden ratio
+
+// a place in 0 .. count - 1 for this workgroup
+__device__ __forceinline__ int own_place(int count)
+{
+    return (int)((spread32(blockIdx.y * gridDim.x + blockIdx.x) >> 16) * (uint32_t)count >> 16);
+}
+
+struct RangeWalk {
+    int tiles;             // of a range, a power of two
+    int ranges, turned;    // of the share; those that do not start with their first tile
+    int first, place;      // the range it starts with; number in its head of the share's range 0
+    int begun;             // ranges begun
+    int base, at, left;    // range's first tile, group's first tile in it, groups of it that are left
+    int in[4];             // tile of a group at each step
+
+    // the share's keys from range first_range of a head of n keys on
+    __device__ __forceinline__ RangeWalk(int first_range, int keys, int range_keys, int n)
     {
-        const int r = (g >> log2_groups) + first, ranges = groups >> log2_groups;
-        return r >= ranges ? r - ranges : r;
+        const int full = keys >> (31 - __builtin_clz(range_keys));
+        tiles = range_keys / kTileKeys;
+        // 2048 keys in ranges of 1024: at least 349525 keys in all, so that no call with such heads takes the short form
+        static_assert(kLongKeys <= kSweepWgs * (long long)kMaxRangeKeys * 2 / 3, "3 ranges at most for each 2 that are full");
+        turned = range_keys == kMaxRangeKeys && n >= 2 * kMaxRangeKeys ? full : 0;
+        ranges = (keys & (range_keys - 1)) == 0 ? full : full + 1;
+        first = full == ranges ? own_place(ranges) : 0;
+        place = first_range;
+        begun = 0;
+        open();
     }
-    // first tile of the group at place g; behind the last one: past the share's end
-    __device__ __forceinline__ int group(int g) const
+    // the range that is the k-th to be taken
+    __device__ __forceinline__ int range(int k) const { return k + first >= ranges && k < ranges ? k + first - ranges : k + first; }
+    __device__ __forceinline__ void open()
     {
-        if (g >= groups) return 4 * g;
-        return 4 * ((range(g) << log2_groups) | ((g + turn) & ((1 << log2_groups) - 1)));
+        const int r = range(begun), phase = r < turned ? (int)(spread32(place + r) >> 27) : 0;       // 0 .. 31
+        static_assert(kMaxRangeKeys / kTileKeys == 32, "a phase is a tile of a range");
+        base = r * tiles;
+        at = phase & ~3;
+        left = tiles / 4;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) in[i] = (i + phase) & 3;
+        ++begun;
     }
+    __device__ __forceinline__ void next_group()
+    {
+        at = (at + 4) & (tiles - 1);
+        if (__builtin_expect(--left == 0, 0)) open();
+    }
+    __device__ __forceinline__ int tile(int i) const { return base + at + in[i]; }
 };
 
-// range_keys: a power of two, from a group on
-__device__ __forceinline__ TileOrder tile_order(int keys, int range_keys)
-{
-    const bool whole = (keys & (range_keys - 1)) == 0;
-    const uint32_t place = (blockIdx.y * gridDim.x + blockIdx.x) * 0x9E3779B1u;           // 2^32 / golden ratio: evenly spread
-    const int phase = whole ? place >> 11 & 31 : 0;
-    TileOrder o;
+struct ShareWalk {
+    int groups, group, left, in[4];
+
+    __device__ __forceinline__ explicit ShareWalk(int keys)
+    {
+        const bool full = keys % (4 * kTileKeys) == 0;
+        groups = (keys + 4 * kTileKeys - 1) / (4 * kTileKeys);
+        group = full ? own_place(groups) : 0;
+        left = groups;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) o.in[i] = (i + phase) & 3;
-    o.groups = (keys + 4 * kTileKeys - 1) / (4 * kTileKeys);
-    o.log2_groups = whole ? 31 - __builtin_clz(range_keys / (4 * kTileKeys)) : 0;
-    o.turn = phase >> 2;
-    o.first = whole ? (int)((place >> 16) * (uint32_t)(o.groups >> o.log2_groups) >> 16) : 0;
-    return o;
-}
+        for (int i = 0; i < 4; ++i) in[i] = (i + (full ? (int)blockIdx.x : 0)) & 3;
+    }
+    __device__ __forceinline__ void next_group()
+    {
+        group = group + 1 == groups ? 0 : group + 1;
+        if (--left == 0) group = groups;
+    }
+    __device__ __forceinline__ int tile(int i) const { return 4 * group + in[i]; }
+};
 
 // Feature step x: lane (key = lane & 31, h = lane >> 5) holds d = 16 x + 8 h .. + 8 of its key.
 __device__ __forceinline__ bf16x8 k_fragment(const KTile &tile, const KSource &src, int x)
@@ -279,16 +319,16 @@ __device__ __forceinline__ void sweep_step(floatx16 (&s_nxt)[2], bf16x8 (&kf)[8]
 }
 
 // Everything ahead of the loop: four tiles on their way, Qhat in registers, the logits of tile 0 in s.
-template <bool KEYS_BY_ROWS>
+template <bool KEYS_BY_ROWS, typename Walk>
 __device__ __forceinline__ void sweep_start(floatx16 (&s)[2], bf16x8 (&kf)[8], bf16x8 (&qf)[2][8][2], const floatx16 (&c)[2],
                                             KTile &t0, KTile &t1, KTile &t2, KTile &t3, const KSource &src,
-                                            const TileOrder &order, const bf16_t *qsplit, int bh, int wave, int lane)
+                                            Walk &walk, const bf16_t *qsplit, int bh, int wave, int lane)
 {
-    const int g0 = order.group(0);
-    issue_tile(t0, src, g0 + order.in[0], wave);
-    issue_tile(t1, src, g0 + order.in[1], wave);
-    issue_tile(t2, src, g0 + order.in[2], wave);
-    issue_tile(t3, src, g0 + order.in[3], wave);
+    issue_tile(t0, src, walk.tile(0), wave);
+    issue_tile(t1, src, walk.tile(1), wave);
+    issue_tile(t2, src, walk.tile(2), wave);
+    issue_tile(t3, src, walk.tile(3), wave);
+    walk.next_group();
     load_qfrags(qf, qsplit, bh, wave, lane);
     __builtin_amdgcn_s_waitcnt(0x0F70);                    // vmcnt(0), gfx9 encoding
     __syncthreads();
@@ -301,7 +341,7 @@ __device__ __forceinline__ void sweep_start(floatx16 (&s)[2], bf16x8 (&kf)[8], b
 #pragma unroll
     for (int x = 0; x < 7; ++x) kf[x] = k_fragment(t1, src, x);
     __syncthreads();                                       // both waves have read tile 0
-    issue_tile(t0, src, order.group(1) + order.in[0], wave);
+    issue_tile(t0, src, walk.tile(0), wave);
 }
 
 // ------------------------------------------------------------------ MFMA path: sweep 1
@@ -319,10 +359,10 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const int key_begin = first_range * range_keys, keys = min(g.n - key_begin, range_keys * ranges);
     const int ntiles = ceil_div(keys, kTileKeys), range_tiles = range_keys / kTileKeys;
     const KSource src = key_source(K + ((size_t)bh * g.n + key_begin) * 128, keys, lane);
-    const TileOrder order = tile_order(keys, range_keys);
+    RangeWalk walk(first_range, keys, range_keys, g.n);         // tiles to load
     bf16x8 qf[2][8][2], kf[8];
     floatx16 sa[2], sb[2];
-    sweep_start<true>(sa, kf, qf, sa, tile0, tile1, tile2, tile3, src, order, qsplit, bh, wave, lane);
+    sweep_start<true>(sa, kf, qf, sa, tile0, tile1, tile2, tile3, src, walk, qsplit, bh, wave, lane);
     float m[2] = {-INFINITY, -INFINITY}, l[2] = {0.0f, 0.0f};   // row 32 rt + (lane & 31), this lane's half of the keys
     // keys of tile t that do not exist weigh nothing
     auto cut = [&](floatx16 &s, int t) __attribute__((always_inline)) {
@@ -376,16 +416,15 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         });
         add(std::integral_constant<int, 31>{});
     };
-    int g1 = order.group(1);                               // the next group and the one after it
+    int done = 0;                                          // ranges
     for (int t = 0; t < ntiles; t += 4) {                  // (tiles past the last one hold no keys)
-        const int g2 = order.group((t >> 2) + 2);
-        step(sa, sb, tile1, tile2, t, g1 + order.in[1]);
-        step(sb, sa, tile2, tile3, t + 1, g1 + order.in[2]);
-        step(sa, sb, tile3, tile0, t + 2, g1 + order.in[3]);
-        step(sb, sa, tile0, tile1, t + 3, g2 + order.in[0]);
-        g1 = g2;
+        step(sa, sb, tile1, tile2, t, walk.tile(1));
+        step(sb, sa, tile2, tile3, t + 1, walk.tile(2));
+        step(sa, sb, tile3, tile0, t + 2, walk.tile(3));
+        walk.next_group();
+        step(sb, sa, tile0, tile1, t + 3, walk.tile(0));
         if ((t + 4) % range_tiles == 0 || t + 4 >= ntiles) {         // the end of a range
-            const int range = first_range + (order.log2_groups ? order.range(t >> 2) : t / range_tiles);
+            const int range = first_range + walk.range(done++);
 #pragma unroll
             for (int rt = 0; rt < 2; ++rt) {               // merge the two lane halves; the rows of a wave are its own
                 const float mo = __shfl_xor(m[rt], 32, 64), lo = __shfl_xor(l[rt], 32, 64);
@@ -450,7 +489,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int key_begin = wg * kpw, keys = min(g.n - key_begin, kpw), ntiles = ceil_div(keys, kTileKeys);
     const KSource src = key_source(K + ((size_t)bh * g.n + key_begin) * 128, keys, lane);
-    const TileOrder order = tile_order(keys, 4 * kTileKeys);
+    ShareWalk walk(keys);                                    // tiles to load
     float *out = scores + (size_t)bh * g.n + key_begin;
     bf16x8 qf[2][8][2], kf[8];
     // the accumulators start at c[row]; row = 64 wave + 32 rt + 8 (i / 4) + 4 (lane >> 5) + (i % 4)
@@ -460,7 +499,8 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
         for (int i = 0; i < 16; ++i)
             c[rt][i] = cvec[(size_t)bh * kQRows + 64 * wave + 32 * rt + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3)];
-    sweep_start<false>(sa, kf, qf, c, tile0, tile1, tile2, tile3, src, order, qsplit, bh, wave, lane);
+    const int group0 = walk.group;
+    sweep_start<false>(sa, kf, qf, c, tile0, tile1, tile2, tile3, src, walk, qsplit, bh, wave, lane);
     float done[2] = {0.0f, 0.0f};                            // this lane's sums of the tile before
     auto halves = [&](int rt) __attribute__((always_inline)) {
         const uint32_t own = __builtin_bit_cast(uint32_t, done[rt]);
@@ -497,16 +537,16 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         done[1] = sum[1];
     };
     int t = 0, before = -1;                                  // number of tile t - 1
-    int g0 = order.group(0), g1 = order.group(1);            // the group of tile t and the next one
+    int own = 4 * group0;                                    // first tile of its group
     for (; t < ntiles; t += 4) {                             // (tiles past the last one hold no keys)
-        const int g2 = order.group((t >> 2) + 2);
-        step(sa, sb, tile1, tile2, t, before, g1 + order.in[1]);
-        step(sb, sa, tile2, tile3, t + 1, g0 + order.in[0], g1 + order.in[2]);
-        step(sa, sb, tile3, tile0, t + 2, g0 + order.in[1], g1 + order.in[3]);
-        step(sb, sa, tile0, tile1, t + 3, g0 + order.in[2], g2 + order.in[0]);
-        before = g0 + order.in[3];
-        g0 = g1;
-        g1 = g2;
+        const int later = 4 * walk.group;
+        step(sa, sb, tile1, tile2, t, before, walk.tile(1));
+        step(sb, sa, tile2, tile3, t + 1, own + walk.in[0], walk.tile(2));
+        step(sa, sb, tile3, tile0, t + 2, own + walk.in[1], walk.tile(3));
+        walk.next_group();
+        step(sb, sa, tile0, tile1, t + 3, own + walk.in[2], walk.tile(0));
+        before = own + walk.in[3];
+        own = later;
     }
     halves(0);
     halves(1);

@@ -590,3 +590,16 @@ def test_key_scores_of_long_inputs(batch, h_kv, n):
         for h in range(h_kv):
             want = torch.softmax(Q[b, h, -128:].double() @ K[b, h].double().T / 128 ** 0.5, -1).mean(0)
             torch.testing.assert_close(got[b, h].double(), want, rtol=1e-4, atol=0)
+
+
+# five heads take the long form, four of them the short one, with ranges of 512 keys both; eight heads and seven of them both
+# the long form, with shares of three and two ranges: a head's scores do not depend on the others
+@pytest.mark.parametrize("h_kv,fewer,n", [(5, 4, 65536), (5, 4, 65555), (8, 7, 140000), (8, 7, 147456)])
+def test_key_scores_of_a_head_do_not_depend_on_the_others(h_kv, fewer, n):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    Q = torch.randn((1, h_kv, n, 128), generator=g, device="cuda", dtype=torch.bfloat16)
+    K = torch.randn((1, h_kv, n, 128), generator=g, device="cuda", dtype=torch.bfloat16)
+    got = [pbs.key_scores(pbs.problem(1, h, h, n, 128, 128, 1024, "bf16"), Q[:, :h].contiguous(), K[:, :h].contiguous())
+           for h in (h_kv, fewer)]
+    assert torch.equal(got[0][:, :fewer], got[1])
