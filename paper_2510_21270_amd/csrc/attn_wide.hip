@@ -323,9 +323,11 @@ __device__ __forceinline__ void step(State &st, floatx16 (&s_cur)[2], floatx16 (
     if (__builtin_expect(masked || !st.all_seen, 0)) {
         asm volatile("" ::: "memory");                     // keeps this rare block out of the straight-line code
         if (masked) mask_tile(s_cur, sg_v.pos + buf.ring / 4, room, qpos, lh);
-        set_reference(st, 0, s_cur[0], c2);
-        set_reference(st, 1, s_cur[1], c2);
-        st.all_seen = __all(st.seen[0] && st.seen[1]);
+        if (!st.all_seen) {
+            set_reference(st, 0, s_cur[0], c2);
+            set_reference(st, 1, s_cur[1], c2);
+            st.all_seen = __all(st.seen[0] && st.seen[1]);
+        }
     }
     __builtin_amdgcn_sched_barrier(0);
     // Softmax of score pair q (query tile q / 8, scores 2 (q % 8) and + 1) in three stages, issued in consecutive
@@ -475,8 +477,34 @@ __global__ __launch_bounds__(64) void take_queues_kernel(unsigned long long key)
     if (set >= 0 && lane == kXcds) queue_heads[set][kLeft] = 0;
 }
 
-// key == 0: one workgroup per row, which it finds from its id.  Otherwise the grid is what the chip holds at a time and
-// every workgroup takes rows from the queues of that key until none is left.
+struct Args {
+    const bf16_t *Qp, *Kp, *Vt;
+    const int32_t *qidx, *kidx, *row_cnt, *col_idx;
+    bf16_t *Op;
+    float *lse;
+    int8_t *redo;
+    Geo g;
+    int tok_delta;
+    unsigned long long key;
+    int cohort_log2;
+};
+
+// The kernel's arguments, read again where they are used: what only a row's start and end need would otherwise hold scalar
+// registers throughout the loop.
+__device__ __forceinline__ const Args &args_again()
+{
+    typedef const __attribute__((address_space(4))) Args *args_t;
+    args_t a = (args_t)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(a));
+    return *(const Args *)a;
+}
+
+// !QUEUES (key == 0): one workgroup per row, which it finds from its id.  QUEUES: the grid is what the chip holds at a time
+// and every workgroup takes rows from the queues of `key` until none is left.  Two kernels, since the loop has no scalar
+// registers to spare: as one, with arguments that stayed in registers, 162 of them lay in lanes of vector registers, and a masked
+// sub-tile fetched 24 .. 28 back among its 120 instructions.  Without that, and with references that are not looked for
+// again once all queries have theirs, attention over 32 / 8 heads x 1152, a twentieth of the blocks, takes 22.1 instead of 25.8 us,
+// x 2048 with nothing but masked blocks 81.1 instead of 89.8, x 16384 (queues) over a fiftieth 163.7 instead of 169 .. 174.
 //
 // Between two rows a wave that has its SIMD to itself has nothing to overlap with, so the next row is prepared under
 // the current one: near the end of the current row wave 0 loads its list into LDS (asynchronously) and, a block later,
@@ -485,59 +513,60 @@ __global__ __launch_bounds__(64) void take_queues_kernel(unsigned long long key)
 // the epilogue.  (A workgroup per row spent 9-10 us outside its loop and 1-6 us between two workgroups, against 3.3 us per
 // block; and the XCDs, which run at clocks up to 8 % apart, waited for the slowest.)
 //
-// HALVES == 2 (key == 0, lists of one chunk): a row has four waves, two to each half of its list, one workgroup to a
+// HALVES == 2 (!QUEUES, lists of one chunk): a row has four waves, two to each half of its list, one workgroup to a
 // compute unit.  Each half is the pipeline as it stands, on a ring of its own; at the end the halves exchange O^T of
 // one query tile each through LDS, bring both to the larger reference and store a tile each.
-template <int HALVES>
-__global__ __launch_bounds__(128 * HALVES) __attribute__((amdgpu_waves_per_eu(1, 1))) void attn_wide_kernel(
-    const bf16_t *__restrict__ Qp, const bf16_t *__restrict__ Kp, const bf16_t *__restrict__ Vt,
-    const int32_t *__restrict__ qidx, const int32_t *__restrict__ kidx, const int32_t *__restrict__ row_cnt,
-    const int32_t *__restrict__ col_idx, bf16_t *__restrict__ Op, float *__restrict__ lse,
-    int8_t *__restrict__ redo, Geo g, int tok_delta, unsigned long long key, int cohort_log2)
+template <int HALVES, bool QUEUES>
+__global__ __launch_bounds__(128 * HALVES) __attribute__((amdgpu_waves_per_eu(1, 1))) void attn_wide_kernel(Args args)
 {
     __shared__ Stage rg0[HALVES], rg1[HALVES], rg2[HALVES], rg3[HALVES];         // 4 x 16 KiB
     Stage &sg0 = rg0[0], &sg1 = rg1[0], &sg2 = rg2[0], &sg3 = rg3[0];            // buf.ring and off lead to the own ones
     __shared__ floatx4 sums[HALVES == 2 ? 256 : 1];        // row sums and references of a split row's halves
-    __shared__ int lists[2][kList];                        // block lists (a chunk of each) of this row and the next
+    __shared__ int lists[QUEUES ? 2 : 1][kList];           // block lists (a chunk of each) of this row and the next
     __shared__ int tails[64];                              // the end of a list that is longer than a chunk
     __shared__ int next_cnt[64], sink[64];
-    __shared__ RowInfo info[2];
+    __shared__ RowInfo info[QUEUES ? 2 : 1];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(HALVES == 2 ? threadIdx.x >> 6 & 1 : threadIdx.x >> 6);
     const int half = HALVES == 2 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 7) : 0;
     const bool keeper = wave == 0 && half == 0;            // the wave that keeps the lists
     const int ln = lane & 31, lh = lane >> 5;
-    const float c2 = g.scale * kLog2eF;
+    const float c2 = args.g.scale * kLog2eF;
     const LaneOffsets off = lane_offsets(half, wave, lane);
     constexpr int kRawDword = 0x00020000;                  // gfx9 descriptor word 3: raw 32-bit data format
 
-    auto decode = [&](int unit, int mrow, int &bhq, int &i) {
+    auto decode = [&](const Args &a, int unit, int mrow, int &bhq, int &i) {
+        const Geo &g = a.g;
         const int later = mrow / g.r, kv = unit / g.h_kv;
         i = g.T - 1 - later;
         bhq = kv * g.h_q + (unit - kv * g.h_kv) * g.r + mrow - later * g.r;
     };
     auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
     // the raw list entries [base, base + kList) of a row, up to T (wave 0)
-    auto load_list = [&](int bhq, int i, int *list, int base) {
+    auto load_list = [&](const Args &a, int bhq, int i, int *list, int base) {
+        const Geo &g = a.g;
         const int m = max(0, min(g.T - base, kList));
         const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<int32_t *>(col_idx + ((size_t)bhq * g.T + i) * g.T + base), 0, m * 4, kRawDword);
+            const_cast<int32_t *>(a.col_idx + ((size_t)bhq * g.T + i) * g.T + base), 0, m * 4, kRawDword);
         for (int k = 0; k < m; k += 64)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)(list + k), 4, lane * 4, k * 4, 0, 0);
     };
     // blocks of a row's own segment that token order may replace, 0: none
-    auto own_blocks = [&](int i) { return tok_delta > 0 && i / g.R < g.G ? allowed_cols(i, g) - first_masked_col(i, g) : 0; };
+    auto own_blocks = [&](const Args &a, int i) {
+        return a.tok_delta > 0 && i / a.g.R < a.g.G ? allowed_cols(i, a.g) - first_masked_col(i, a.g) : 0;
+    };
     // Raw entries [base, base + kList) -> the form the loop reads (wave 0).  An entry that the causal structure does not
     // admit becomes block 0 with no existing key under the mask: a sub-tile that contributes nothing.
     // Behind the last entry stands a copy of it: the loop reads one entry ahead.
-    auto pack_list = [&](int i, int first, int len, int *list, int base) {
+    auto pack_list = [&](const Args &a, int i, int first, int len, int *list, int base) {
+        const Geo &g = a.g;
         const int ni = allowed_cols(i, g), jmask = first_masked_col(i, g);
         auto packed = [&](int e, int raw) {
             int j = raw, to = raw;
             if (e >= first) {                              // token order: keys of the diagonal block need the mask
                 j = jmask + e - first;
-                to = tok_delta + j;
+                to = a.tok_delta + j;
             } else if (j < 0 || j >= ni) {
                 return (int)kEntryMask;
             }
@@ -553,8 +582,8 @@ __global__ __launch_bounds__(128 * HALVES) __attribute__((amdgpu_waves_per_eu(1,
     // segment, ascending, these entries stand for the blocks jmask .. i of the token-order copies.  Keys of a segment are
     // the same set in either order, so the visible keys are the same; in token order the blocks before the diagonal
     // need no mask and those after it hold no visible key.
-    auto close_list = [&](RowInfo &w, int i, int cnt, int *list) {
-        const int own = own_blocks(i), jmask = first_masked_col(i, g);
+    auto close_list = [&](const Args &a, RowInfo &w, int i, int cnt, int *list) {
+        const int own = own_blocks(a, i), jmask = first_masked_col(i, a.g);
         int first = INT_MAX, len = cnt;
         if (own > 0 && cnt >= own) {
             const int t = cnt <= kList ? list[min(cnt - own + lane, kList - 1)] : tails[lane];
@@ -567,32 +596,34 @@ __global__ __launch_bounds__(128 * HALVES) __attribute__((amdgpu_waves_per_eu(1,
             len = 1;
             if (lane == 0) list[0] = -1;
         }
-        pack_list(i, first, len, list, 0);
+        pack_list(a, i, first, len, list, 0);
         if (lane == 0) {
             w.cnt = cnt;
             w.first = first;
             w.len = len;
         }
     };
-    auto load_tail = [&](int bhq, int i, int cnt) {
-        const int own = own_blocks(i);
+    auto load_tail = [&](const Args &a, int bhq, int i, int cnt) {
+        const Geo &g = a.g;
+        const int own = own_blocks(a, i);
         if (own > 0 && cnt > kList) {
             const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
-                const_cast<int32_t *>(col_idx + ((size_t)bhq * g.T + i) * g.T + cnt - own), 0, own * 4, kRawDword);
+                const_cast<int32_t *>(a.col_idx + ((size_t)bhq * g.T + i) * g.T + cnt - own), 0, own * 4, kRawDword);
             __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)tails, 4, lane * 4, 0, 0, 0);
         }
     };
     TileBuffers buf;
     buf.ring = half * (int)sizeof(Stage);
-    auto open_buffers = [&](int unit) {
+    auto open_buffers = [&](const Args &a, int unit) {
+        const Geo &g = a.g;
         // tok_delta > 0: a token-order copy of K', Vt and kidx lies tok_delta = batch * h_kv * T blocks behind the
         // permuted one, so block j of this head in token order is block tok_delta + j of the same descriptors
         const size_t bhk = unit;
-        const int reach = tok_delta * BLOCK + g.n;         // rows within reach of this head's descriptors
-        buf.tile = wave == 0 ? __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(Kp + bhk * (size_t)g.n * D), 0, reach * 256, kRawDword)
-                             : __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(Vt + bhk * (size_t)g.T * D * BLOCK), 0,
-                                                                 (tok_delta + g.T) * (D * BLOCK * 2), kRawDword);
-        buf.pos = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(kidx + bhk * (size_t)g.n), 0, reach * 4, kRawDword);
+        const int reach = a.tok_delta * BLOCK + g.n;       // rows within reach of this head's descriptors
+        buf.tile = wave == 0 ? __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(a.Kp + bhk * (size_t)g.n * D), 0, reach * 256, kRawDword)
+                             : __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(a.Vt + bhk * (size_t)g.T * D * BLOCK), 0,
+                                                                 (a.tok_delta + g.T) * (D * BLOCK * 2), kRawDword);
+        buf.pos = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(a.kidx + bhk * (size_t)g.n), 0, reach * 4, kRawDword);
     };
     // jv0: the first iteration of a row multiplies V'^T part 3 of this block by zero probabilities; that is a block of the
     // row's list, the same one for both halves, so that infinite values meet no more zeros than they would in one piece
@@ -602,58 +633,61 @@ __global__ __launch_bounds__(128 * HALVES) __attribute__((amdgpu_waves_per_eu(1,
         issue_stage<2>(sg2, buf, off, j, j, wave, lane);
         issue_stage<3>(sg3, buf, off, j, j, wave, lane);
     };
-    auto query_buffer = [&](int bhq) {
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(Qp + (size_t)bhq * g.n * D), 0, g.n * 256, kRawDword);
+    auto query_buffer = [&](const Args &a, int bhq) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(a.Qp + (size_t)bhq * a.g.n * D), 0, a.g.n * 256, kRawDword);
     };
     // Q' fragments: lane (n, h) holds Q'[q0 + 32 nt + n][16 ks + 8 h .. +8]
     // (buffer loads: the compiler moves plain loads of read-only memory down to their use, behind the waits; rows past
     // the end of the head read as zeros)
     bf16x8 qf[2][8];
     int qpos[2];
-    auto load_queries = [&](int bhq, int i) {
-        const __amdgpu_buffer_rsrc_t r = query_buffer(bhq);
+    auto load_queries = [&](const Args &a, int bhq, int i) {
+        const __amdgpu_buffer_rsrc_t r = query_buffer(a, bhq);
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt) {
             const int qs = i * BLOCK + wave * 64 + 32 * nt + ln;
 #pragma unroll
             for (int k = 0; k < 8; ++k)
                 qf[nt][k] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, qs * 256 + 16 * lh, 32 * k, 0));
-            qpos[nt] = qs < g.n ? (qidx ? qidx[(size_t)bhq * g.n + qs] : qs) : -1;
+            qpos[nt] = qs < a.g.n ? (a.qidx ? a.qidx[(size_t)bhq * a.g.n + qs] : qs) : -1;
         }
     };
 
     const int home = blockIdx.x % kXcds;
     int32_t *tickets = nullptr;
-    if (HALVES == 1 && key) {
-        const uint64_t mine = __ballot(__hip_atomic_load(&queue_owner[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == key);
+    if constexpr (QUEUES) {
+        const uint64_t mine = __ballot(__hip_atomic_load(&queue_owner[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == args.key);
         if (!mine) {                                       // no set was free: every row is flagged
-            for (long long f = 128LL * blockIdx.x + threadIdx.x; f < 2LL * g.batch * g.h_q * g.T; f += 128LL * gridDim.x) redo[f] = 1;
+            for (long long f = 128LL * blockIdx.x + threadIdx.x; f < 2LL * args.g.batch * args.g.h_q * args.g.T; f += 128LL * gridDim.x)
+                args.redo[f] = 1;
             return;
         }
         tickets = queue_heads[__builtin_ctzll(mine)];
     }
     auto leave = [&]() {                                   // no ticket is drawn after this (one lane)
-        if (tickets && atomicAdd(tickets + kLeft, 1) == (int)gridDim.x - 1)
+        if (atomicAdd(tickets + kLeft, 1) == (int)gridDim.x - 1)
             atomicExch(&queue_owner[(tickets - queue_heads[0]) / (kXcds * kTicketStride)], 0ull);
     };
     // the row of a ticket as the next one (one lane); ticket < 0: there is none
-    auto open_next = [&](RowInfo &w, int ticket) {
+    auto open_next = [&](const Args &a, RowInfo &w, int ticket) {
         int unit = -1, mrow = 0;
-        if (ticket >= 0) claim_row(g, cohort_log2, tickets, home, ticket, unit, mrow);
+        if (ticket >= 0) claim_row(a.g, a.cohort_log2, tickets, home, ticket, unit, mrow);
         w.unit = unit;
         w.len = 0;
-        if (unit >= 0) decode(unit, mrow, w.bhq, w.i);
+        if (unit >= 0) decode(a, unit, mrow, w.bhq, w.i);
     };
     int unit, bhq, i;                                      // of the current row
     {
+        const Args &a = args;
+        const Geo &g = a.g;
         int mrow;
-        if (HALVES == 2 || !tickets) {
-            if (!ticket_row(g, cohort_log2, home, blockIdx.x / kXcds, unit, mrow) || unit < 0) return;
+        if constexpr (!QUEUES) {
+            if (!ticket_row(g, a.cohort_log2, home, blockIdx.x / kXcds, unit, mrow) || unit < 0) return;
         } else {
             // the first row is drawn too, not tied to the workgroup's id: a workgroup that another kernel's work keeps off
             // the chip then holds no row back
             if (threadIdx.x == 0)
-                claim_row(g, cohort_log2, tickets, home, atomicAdd(tickets + home * kTicketStride, 1), next_cnt[0], next_cnt[1]);
+                claim_row(g, a.cohort_log2, tickets, home, atomicAdd(tickets + home * kTicketStride, 1), next_cnt[0], next_cnt[1]);
             __syncthreads();
             unit = uniform(next_cnt[0]);
             mrow = uniform(next_cnt[1]);
@@ -663,19 +697,19 @@ __global__ __launch_bounds__(128 * HALVES) __attribute__((amdgpu_waves_per_eu(1,
             }
             __syncthreads();                               // (next_cnt is loaded into later)
         }
-        decode(unit, mrow, bhq, i);
+        decode(a, unit, mrow, bhq, i);
         const size_t at = (size_t)bhq * g.T + i;
-        if (keeper) load_list(bhq, i, lists[0], 0);
-        load_queries(bhq, i);
-        open_buffers(unit);
-        const int raw0 = uniform(col_idx[at * g.T]);       // read beside the count
-        const int cnt = max(0, min(uniform(row_cnt[at]), g.T));
-        if (keeper) load_tail(bhq, i, cnt);
-        const bool early = cnt > own_blocks(i);            // the first entry cannot be one that token order replaces
+        if (keeper) load_list(a, bhq, i, lists[0], 0);
+        load_queries(a, bhq, i);
+        open_buffers(a, unit);
+        const int raw0 = uniform(a.col_idx[at * g.T]);     // read beside the count
+        const int cnt = max(0, min(uniform(a.row_cnt[at]), g.T));
+        if (keeper) load_tail(a, bhq, i, cnt);
+        const bool early = cnt > own_blocks(a, i);            // the first entry cannot be one that token order replaces
         int j0 = raw0 >= 0 && raw0 < allowed_cols(i, g) ? raw0 : 0;
         if (!early) {
             sync_stages();
-            if (keeper) close_list(info[0], i, cnt, lists[0]);
+            if (keeper) close_list(a, info[0], i, cnt, lists[0]);
             __syncthreads();
             j0 = uniform(lists[0][0]) & kEntryBlock;
         }
@@ -683,7 +717,7 @@ __global__ __launch_bounds__(128 * HALVES) __attribute__((amdgpu_waves_per_eu(1,
         if (early && keeper) {
             __builtin_amdgcn_s_waitcnt(0x8F74);            // vmcnt(36): what was issued before the tiles has landed
             asm volatile("" ::: "memory");
-            close_list(info[0], i, cnt, lists[0]);
+            close_list(a, info[0], i, cnt, lists[0]);
         }
         if constexpr (HALVES == 2) {
             __builtin_amdgcn_s_waitcnt(0xC07F);            // lgkmcnt(0): the list is in LDS; the tiles may still travel
@@ -691,8 +725,8 @@ __global__ __launch_bounds__(128 * HALVES) __attribute__((amdgpu_waves_per_eu(1,
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
             if (half == 1) issue_block(uniform(lists[0][(uniform(info[0].len) + 1) >> 1]) & kEntryBlock, j0);
-        } else if (threadIdx.x == 0) {
-            open_next(info[1], tickets ? atomicAdd(tickets + home * kTicketStride, 1) : -1);
+        } else if (QUEUES && threadIdx.x == 0) {
+            open_next(a, info[1], atomicAdd(tickets + home * kTicketStride, 1));
         }
         sync_stages();
     }
@@ -743,49 +777,52 @@ __global__ __launch_bounds__(128 * HALVES) __attribute__((amdgpu_waves_per_eu(1,
                 step_no = 3;
                 return;
             }
+            const Args &a = args_again();
             const int nb = uniform(w.bhq), nq = uniform(w.i);
             if (step_no == 0) {
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                    __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(row_cnt + (size_t)nb * g.T + nq), 0, 4, kRawDword),
+                    __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(a.row_cnt + (size_t)nb * a.g.T + nq), 0, 4, kRawDword),
                     (lptr_t)next_cnt, 4, lane * 4, 0, 0, 0);
-                load_list(nb, nq, lists[cur ^ 1], 0);
+                load_list(a, nb, nq, lists[cur ^ 1], 0);
                 // one word of every line of the row's Q' block, so that its fragments come from the cache
-                const __amdgpu_buffer_rsrc_t r = query_buffer(nb);
+                const __amdgpu_buffer_rsrc_t r = query_buffer(a, nb);
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
                     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)sink, 4, lane * 128, nq * (BLOCK * 256) + k * 8192, 0, 0);
                 step_no = 1;
                 return;
             }
-            const int cnt = max(0, min(uniform(next_cnt[0]), g.T));
+            const int cnt = max(0, min(uniform(next_cnt[0]), a.g.T));
             if (step_no == 1 && cnt > kList) {
-                load_tail(nb, nq, cnt);
+                load_tail(a, nb, nq, cnt);
                 step_no = 2;
                 return;
             }
-            close_list(w, nq, cnt, lists[cur ^ 1]);
+            close_list(a, w, nq, cnt, lists[cur ^ 1]);
             if (lane == 0 && w.unit == unit) lists[cur][len & (kList - 1)] = lists[cur ^ 1][0] | kEntryAhead;
             if (lane == 0) ticket = atomicAdd(tickets + home * kTicketStride, 1);        // of the row after that, used in the epilogue
             step_no = 3;
         };
         // rare work at the end of block e: the next chunk of a list of more than kList entries, preparation steps
         const int chunk_end = len >= kList ? kList - 3 : INT_MAX;
-        int event = wave == 0 ? min(chunk_end, max(0, len - kPrepare)) : chunk_end;
+        int event = QUEUES && wave == 0 ? min(chunk_end, max(0, len - kPrepare)) : chunk_end;
         auto at_event = [&](int e) {
             asm volatile("" ::: "memory");
             if (((e + 3) & (kList - 1)) == 0 && e + 3 <= len) {
                 __syncthreads();
                 if (wave == 0) {
-                    load_list(bhq, i, lists[cur], e + 3);
+                    const Args &a = args_again();
+                    load_list(a, bhq, i, lists[cur], e + 3);
                     __builtin_amdgcn_s_waitcnt(0x0F70);
                     asm volatile("" ::: "memory");
-                    pack_list(i, uniform(info[cur].first), len, lists[cur], e + 3);
+                    pack_list(a, i, uniform(info[cur].first), len, lists[cur], e + 3);
                 }
                 sync_stages();
             }
-            if (wave == 0 && e >= len - kPrepare && e <= len - 4 && step_no < 3) prepare();
+            if constexpr (QUEUES)
+                if (wave == 0 && e >= len - kPrepare && e <= len - 4 && step_no < 3) prepare();
             const int chunk = e + 3 + kList <= len ? ((e + 3) & -kList) + kList - 3 : INT_MAX;
-            event = wave == 0 ? min(chunk, e < len - kPrepare ? len - kPrepare : e + 1) : chunk;
+            event = QUEUES && wave == 0 ? min(chunk, e < len - kPrepare ? len - kPrepare : e + 1) : chunk;
         };
 
         int pk = uniform(list[0]);
@@ -814,6 +851,7 @@ __global__ __launch_bounds__(128 * HALVES) __attribute__((amdgpu_waves_per_eu(1,
             for (int p = 0; p < BLOCK / KS; ++p) __builtin_amdgcn_s_barrier();
         const bool ahead = (pk & kEntryAhead) != 0;        // the ring holds the next row's first block
         drain(st, pa, sg0, off);
+        const Args &a = args_again();
 
         // ---- O' = diag(l)^-1 O; acc_o[dt][nt][x]: d = 32 dt + 8 (x / 4) + 4 h + (x % 4), query = q0 + 32 nt + n.
         // The two lanes of a query exchange pieces so that each stores 8 consecutive features.
@@ -826,13 +864,13 @@ __global__ __launch_bounds__(128 * HALVES) __attribute__((amdgpu_waves_per_eu(1,
 #pragma unroll
             for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-                for (int a = 0; a < 2; ++a) {
-                    uint32_t piece[2][2];                  // [features 8 (2 a + y)][pair]
+                for (int half8 = 0; half8 < 2; ++half8) {
+                    uint32_t piece[2][2];                  // [features 8 (2 half8 + y)][pair]
 #pragma unroll
                     for (int y = 0; y < 2; ++y)
 #pragma unroll
                         for (int z = 0; z < 2; ++z) {
-                            const int x = 4 * (2 * a + y) + 2 * z;
+                            const int x = 4 * (2 * half8 + y) + 2 * z;
                             const floatx2 o = {st.acc_o[dt][nt][x] * inv, st.acc_o[dt][nt][x + 1] * inv};
                             piece[y][z] = __builtin_bit_cast(uint32_t, __builtin_convertvector(o, bf16x2));
                         }
@@ -840,22 +878,22 @@ __global__ __launch_bounds__(128 * HALVES) __attribute__((amdgpu_waves_per_eu(1,
                     for (int z = 0; z < 2; ++z) {
                         // lower half: (own, other's) of piece 0; upper half: (other's, own) of piece 1
                         const auto sw = __builtin_amdgcn_permlane32_swap(piece[0][z], piece[1][z], false, false);
-                        out[nt][dt][a][z] = sw[0];
-                        out[nt][dt][a][2 + z] = sw[1];
+                        out[nt][dt][half8][z] = sw[0];
+                        out[nt][dt][half8][2 + z] = sw[1];
                     }
                 }
         };
         auto store_tile = [&](auto tile) __attribute__((always_inline)) {
             constexpr int nt = decltype(tile)::value;
             const int qs = i * BLOCK + wave * 64 + 32 * nt + ln;
-            if (qs < g.n) {
-                bf16_t *dst = Op + ((size_t)bhq * g.n + qs) * D + 8 * lh;
+            if (qs < a.g.n) {
+                bf16_t *dst = a.Op + ((size_t)bhq * a.g.n + qs) * D + 8 * lh;
 #pragma unroll
                 for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-                    for (int a = 0; a < 2; ++a) *reinterpret_cast<uintx4 *>(dst + 32 * dt + 16 * a) = out[nt][dt][a];
-                if (lse && lh == 0)
-                    lse[(size_t)bhq * g.n + qs] = lt[nt] > 0.0f ? (st.mref[nt] + log2f(lt[nt])) * kLn2F : -INFINITY;
+                    for (int y = 0; y < 2; ++y) *reinterpret_cast<uintx4 *>(dst + 32 * dt + 16 * y) = out[nt][dt][y];
+                if (a.lse && lh == 0)
+                    a.lse[(size_t)bhq * a.g.n + qs] = lt[nt] > 0.0f ? (st.mref[nt] + log2f(lt[nt])) * kLn2F : -INFINITY;
             }
         };
         constexpr auto tile0 = std::integral_constant<int, 0>{};
@@ -869,9 +907,9 @@ __global__ __launch_bounds__(128 * HALVES) __attribute__((amdgpu_waves_per_eu(1,
         auto flag_row = [&](bool lane_bad) {
             const bool bad = __any(lane_bad);
             if (lane == 0) {
-                const size_t f = ((size_t)bhq * g.T + i) * 2 + wave;
-                if (HALVES == 1 && tickets) redo[f] = bad ? 1 : 0;
-                else reinterpret_cast<int16_t *>(redo)[f] = bad ? 1 : 0;
+                const size_t f = ((size_t)bhq * a.g.T + i) * 2 + wave;
+                if (QUEUES) a.redo[f] = bad ? 1 : 0;
+                else reinterpret_cast<int16_t *>(a.redo)[f] = bad ? 1 : 0;
             }
         };
         auto store = [&]() {
@@ -936,6 +974,11 @@ __global__ __launch_bounds__(128 * HALVES) __attribute__((amdgpu_waves_per_eu(1,
             }
             return;
         }
+        if constexpr (!QUEUES) {
+            finish();
+            store();
+            break;
+        }
         if (!ahead) {
             if (wave == 0)
                 while (step_no < 3) {                      // a list too short to prepare the next row under it
@@ -953,7 +996,7 @@ __global__ __launch_bounds__(128 * HALVES) __attribute__((amdgpu_waves_per_eu(1,
         }
         const int bhq1 = uniform(info[cur ^ 1].bhq), i1 = uniform(info[cur ^ 1].i);
         const int j1 = uniform(lists[cur ^ 1][0]) & kEntryBlock;
-        load_queries(bhq1, i1);
+        load_queries(a, bhq1, i1);
         if (ahead) {                                       // V'^T part 3 of the first block is all that is missing
             __builtin_amdgcn_s_waitcnt(0xC07F);            // lgkmcnt(0): this wave has read sg0.v ...
             __builtin_amdgcn_s_barrier();                  // ... and so has the other
@@ -964,13 +1007,13 @@ __global__ __launch_bounds__(128 * HALVES) __attribute__((amdgpu_waves_per_eu(1,
                 issue_load<4>(ld, off); issue_load<5>(ld, off); issue_load<6>(ld, off); issue_load<7>(ld, off);
             }
         } else {
-            open_buffers(unit1);
+            open_buffers(a, unit1);
             issue_block(j1, j1);
         }
         __builtin_amdgcn_sched_barrier(0);
         finish();
         __builtin_amdgcn_sched_barrier(0);
-        if (threadIdx.x == 0) open_next(info[cur], ticket);              // in the place of this row's
+        if (threadIdx.x == 0) open_next(a, info[cur], ticket);              // in the place of this row's
         sync_stages();                                     // Q' and the first block are here
         store();
         unit = unit1;
@@ -1012,9 +1055,10 @@ pbs_status launch_attn_wide(const Geo &g, const void *Qp, const void *Kp, const 
         const long long cohorts = units * ((rows + (1 << cohort_log2) - 1) >> cohort_log2);
         wgs = (unsigned)(((cohorts + wide::kXcds - 1) / wide::kXcds * wide::kXcds) << cohort_log2);
     }
-    return launch(split ? wide::attn_wide_kernel<2> : wide::attn_wide_kernel<1>, dim3(wgs), dim3(split ? 256 : 128), 0, s,
-                  (const bf16_t *)Qp, (const bf16_t *)Kp, (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse,
-                  (int8_t *)redo, g, tok_delta, key, cohort_log2);
+    return launch(queues ? wide::attn_wide_kernel<1, true> : split ? wide::attn_wide_kernel<2, false> : wide::attn_wide_kernel<1, false>,
+                  dim3(wgs), dim3(split ? 256 : 128), 0, s,
+                  wide::Args{(const bf16_t *)Qp, (const bf16_t *)Kp, (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op,
+                             lse, (int8_t *)redo, g, tok_delta, key, cohort_log2});
 }
 
 }  // namespace pbs
