@@ -40,7 +40,7 @@ __device__ inline int swap23(int m) { return (m & ~12) | ((m & 4) << 1) | ((m & 
 // ---------------------------------------------------------------------------------------------
 constexpr int kListChunk = 256;                            // listed blocks staged in LDS at a time
 constexpr int kXcds = 8;                                   // accelerator dies, each with a private L2
-constexpr int kCohort = 64;                                // rows of a cohort in the second pass: what an XCD holds (32 CUs x 2)
+constexpr int kCohortLog2 = 6;                             // rows of a cohort in the second pass: what an XCD holds (32 CUs x 2)
 constexpr float kBigRowSum = 65536.0f;                     // lazy-reference overflow guard
 
 typedef __attribute__((address_space(3))) void *lptr_t;
@@ -482,25 +482,24 @@ __device__ __forceinline__ void attn_row(
 
 // Workgroup id -> kv head, query head, query block.  Workgroups are handed to the 8 XCDs round-robin by linear id and
 // every XCD has its own L2, so the id is decoded as (xcd, slot): workgroups that are resident on one XCD at a time form
-// cohorts of `cohort` rows of ONE kv head with nearly equal list lengths (consecutive query blocks
+// cohorts of 2^cohort_log2 rows of ONE kv head with nearly equal list lengths (consecutive query blocks
 // x the r query heads of the group, longest first).  A cohort walks its ascending lists in near lock-step, so a
 // K'/V' sub-tile is fetched into that L2 once and hit by the other members.  false: there is no such row.
 struct Place {
     int unit, bhq, i;
 };
-__host__ __device__ inline int place_cohorts(const Geo &g, int cohort)
+__host__ __device__ inline int place_cohorts(const Geo &g, int cohort_log2)
 {
-    return g.batch * g.h_kv * ceil_div(g.r * g.T, cohort);
+    return g.batch * g.h_kv * ((g.r * g.T + (1 << cohort_log2) - 1) >> cohort_log2);
 }
-__device__ __forceinline__ bool place_of(const Geo &g, int cohort, int id, Place &at)
+__device__ __forceinline__ bool place_of(const Geo &g, int cohort_log2, int id, Place &at)
 {
     const int nbk = g.batch * g.h_kv;
     const int rows_per_unit = g.r * g.T;
     const int xcd = id % kXcds, slot = id / kXcds;
-    const int coh = (slot / cohort) * kXcds + xcd;
-    if (coh >= place_cohorts(g, cohort)) return false;
-    at.unit = coh % nbk;
-    const int mrow = (coh / nbk) * cohort + slot % cohort;
+    const int coh = (slot >> cohort_log2) * kXcds + xcd, index = coh / nbk;
+    at.unit = coh - index * nbk;
+    const int mrow = (index << cohort_log2) + (slot & ((1 << cohort_log2) - 1));   // past the last cohort: past the last row
     if (mrow >= rows_per_unit) return false;
     at.i = g.T - 1 - mrow / g.r;
     at.bhq = at.unit / g.h_kv * g.h_q + (at.unit % g.h_kv) * g.r + mrow % g.r;
@@ -511,10 +510,10 @@ template <int BLOCK, int WAVES, int KT, bool REMAP = false>
 __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_mfma_kernel(
     const bf16_t *__restrict__ Qp, const bf16_t *__restrict__ Kp, const bf16_t *__restrict__ Vt,
     const int32_t *__restrict__ qidx, const int32_t *__restrict__ kidx, const int32_t *__restrict__ row_cnt,
-    const int32_t *__restrict__ col_idx, bf16_t *__restrict__ Op, float *__restrict__ lse, Geo g, int cohort)
+    const int32_t *__restrict__ col_idx, bf16_t *__restrict__ Op, float *__restrict__ lse, int cohort_log2, Geo g)
 {
     Place at;
-    if (!place_of(g, cohort, blockIdx.x, at)) return;
+    if (!place_of(g, cohort_log2, blockIdx.x, at)) return;
     attn_row<BLOCK, WAVES, KT, REMAP>(Qp, Kp, Vt, qidx, kidx, row_cnt, col_idx, Op, lse, g, at.bhq, at.unit, at.i, threadIdx.x);
 }
 
@@ -548,13 +547,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         if (!__syncthreads_or(last || (any[0] | any[1] | any[2] | any[3]) != 0)) return;
     }
     __shared__ uint64_t masks[kRedoIds / 64];
-    const int ids = (place_cohorts(g, kCohort) + kXcds - 1) / kXcds * kXcds * kCohort;
+    const int ids = ((place_cohorts(g, kCohortLog2) + kXcds - 1) / kXcds * kXcds) << kCohortLog2;
     int turn = blockIdx.x;                                 // flagged rows from here on until it is this workgroup's turn
     for (int base = 0; base < ids; base += kRedoIds) {
 #pragma unroll 4
         for (int k = threadIdx.x; k < kRedoIds; k += 256) {
             Place at;
-            const uint64_t m = __ballot(base + k < ids && place_of(g, kCohort, base + k, at) && flagged(at.bhq * g.T + at.i));
+            const uint64_t m = __ballot(base + k < ids && place_of(g, kCohortLog2, base + k, at) && flagged(at.bhq * g.T + at.i));
             if ((threadIdx.x & 63) == 0) masks[k >> 6] = m;
         }
         __syncthreads();
@@ -575,7 +574,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             uint64_t m = masks[word];
             for (int skip = turn - (__builtin_amdgcn_readlane(upto, word) - __popcll(m)); skip > 0; --skip) m &= m - 1;
             Place at;
-            place_of(g, kCohort, __builtin_amdgcn_readfirstlane(base + 64 * word + __builtin_ctzll(m)), at);
+            place_of(g, kCohortLog2, __builtin_amdgcn_readfirstlane(base + 64 * word + __builtin_ctzll(m)), at);
             int tid = threadIdx.x;
             asm volatile("" : "+v"(tid));                  // per-lane offsets are formed per row, not kept across rows
             attn_row<128, 4, 64, false>(Qp, Kp, Vt, qidx, kidx, row_cnt, col_idx, Op, lse, g, at.bhq, at.unit, at.i, tid);
@@ -631,16 +630,16 @@ extern "C" pbs_status pbs_attn_fwd(const pbs_problem *p, const void *Qp, const v
     const Geo g = make_geo(p);
     hipStream_t s = (hipStream_t)stream;
     if (p->dtype == PBS_BF16 && p->d == 128 && (p->block == 128 || p->block == 64)) {
-        const int cohort = cohort_rows(g);
-        const dim3 mgrid((unsigned)((place_cohorts(g, cohort) + kXcds - 1) / kXcds * cohort * kXcds));
+        const int cohort_log2 = __builtin_ctz(cohort_rows(g));
+        const dim3 mgrid((unsigned)(((place_cohorts(g, cohort_log2) + kXcds - 1) / kXcds * kXcds) << cohort_log2));
         const bool remap = (p->flags & PBS_FLAG_INDEX_REMAP) != 0;     // Kp is the caller's K
         const bool narrow_only = (p->flags & PBS_FLAG_RUNNING_MAX_ONLY) != 0 || remap;
         if (remap) {
             if (p->block == 128)
                 return launch((attn_mfma_kernel<128, 4, 64, true>), mgrid, dim3(256), 0, s, (const bf16_t *)Qp,
-                              (const bf16_t *)Kp, (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse, g, cohort);
+                              (const bf16_t *)Kp, (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse, cohort_log2, g);
             return launch((attn_mfma_kernel<64, 2, 32, true>), mgrid, dim3(128), 0, s, (const bf16_t *)Qp,
-                          (const bf16_t *)Kp, (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse, g, cohort);
+                          (const bf16_t *)Kp, (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse, cohort_log2, g);
         }
         if (p->block == 128) {
             // first pass: every query block with a fixed softmax reference; second pass: the flagged blocks (none
@@ -663,10 +662,10 @@ extern "C" pbs_status pbs_attn_fwd(const pbs_problem *p, const void *Qp, const v
                             (bf16_t *)Op, lse, (const void *)redo, wide_rows_from_queues(g) ? 1 : 0, g);
             else
                 st = launch((attn_mfma_kernel<128, 4, 64>), mgrid, dim3(256), 0, s, (const bf16_t *)Qp,
-                            (const bf16_t *)Kp, (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse, g, cohort);
+                            (const bf16_t *)Kp, (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse, cohort_log2, g);
         } else {
             st = launch((attn_mfma_kernel<64, 2, 32>), mgrid, dim3(128), 0, s, (const bf16_t *)Qp,
-                               (const bf16_t *)Kp, (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse, g, cohort);
+                               (const bf16_t *)Kp, (const bf16_t *)Vt, qidx, kidx, row_cnt, col_idx, (bf16_t *)Op, lse, cohort_log2, g);
         }
         return st;
     }
