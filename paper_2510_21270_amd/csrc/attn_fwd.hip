@@ -630,7 +630,7 @@ extern "C" pbs_status pbs_attn_fwd(const pbs_problem *p, const void *Qp, const v
     const Geo g = make_geo(p);
     hipStream_t s = (hipStream_t)stream;
     if (p->dtype == PBS_BF16 && p->d == 128 && (p->block == 128 || p->block == 64)) {
-        const int cohort_log2 = __builtin_ctz(cohort_rows(g));
+        const int cohort_log2 = __builtin_ctz(cohort_rows(g, true));
         const dim3 mgrid((unsigned)(((place_cohorts(g, cohort_log2) + kXcds - 1) / kXcds * kXcds) << cohort_log2));
         const bool remap = (p->flags & PBS_FLAG_INDEX_REMAP) != 0;     // Kp is the caller's K
         const bool narrow_only = (p->flags & PBS_FLAG_RUNNING_MAX_ONLY) != 0 || remap;

@@ -56,7 +56,16 @@ inline Geo make_geo(const pbs_problem *p)
 // 494, 16 / 4 x 12288 587 / 532; block 64 4 / 2 x 32768 1248 / 1118, 16 / 4 x 3000 89 / 76, 28 / 4 x 32700 7725 / 7510 and, a
 // quarter of the blocks, 2618 / 2575; d = 64 4 / 2 x 12000 233 / 175, 16 / 4 x 12301 678 / 638; float32 2 / 2 x 4096 231 / 147,
 // 8 / 2 x 4096 608 / 537.  With 8 units both give the same order.
-inline int cohort_rows(const Geo &g) { return (long long)g.batch * g.h_kv < 8 ? 8 : 64; }
+// 1, 2 and 4 units leave each XCD with one unit also in cohorts of 8; with 3, 5, 6 and 7 an XCD gets rows of 3 to 7 units in
+// turn, whose tiles push each other out of its L2.  A kernel whose tiles serve 64 queries only (alone) loses more by that
+// than it gains: block 64, an eighth of the blocks, 5 / 5 x 40000 386 / 498, 3 / 3 x 40000 250 / 273, a quarter, 7 / 7 x 20000
+// 245 / 318, 28 / 7 x 9000 206 / 241 (causal lists 682 / 685, 5 / 5 x 9000 222 / 203); the wide kernel gains all the same,
+// a twentieth to a third of the blocks 5 / 5 x 40000 156 .. 682 / 151 .. 615, 7 / 7 x 16000 causal 418 / 392.
+inline int cohort_rows(const Geo &g, bool alone = false)
+{
+    const long long units = (long long)g.batch * g.h_kv;
+    return units < 8 && (!alone || 8 % units == 0) ? 8 : 64;
+}
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 

@@ -603,3 +603,32 @@ def test_key_scores_of_a_head_do_not_depend_on_the_others(h_kv, fewer, n):
     got = [pbs.key_scores(pbs.problem(1, h, h, n, 128, 128, 1024, "bf16"), Q[:, :h].contiguous(), K[:, :h].contiguous())
            for h in (h_kv, fewer)]
     assert torch.equal(got[0][:, :fewer], got[1])
+
+
+def test_block_64_attention_time_with_five_kv_heads():
+    # sparse lists share tiles in an XCD's L2, which rows of all five heads on every XCD would crowd (5 / 5 heads x 40000, an
+    # eighth of the blocks: 386 us against 498; a head's time 1.11 .. 1.18 and 1.41 .. 1.44 of that with four heads, two XCDs
+    # to each)
+    n, block, rho = 40000, 64, 0.12
+    T = -(-n // block)
+
+    def best(heads):
+        g = torch.Generator(device="cuda")
+        g.manual_seed(heads)
+        Q, K, V = (torch.randn((1, heads, n, 128), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+        on = torch.tril(torch.rand((1, heads, T, T), generator=g, device="cuda") < rho, -1) | torch.eye(T, dtype=torch.bool, device="cuda")
+        cnt = on.sum(-1, dtype=torch.int32)
+        cols = torch.argsort(on.to(torch.uint8), dim=-1, descending=True, stable=True).to(torch.int32)
+        p = pbs.problem(1, heads, heads, n, 128, block, 1024, "bf16")
+        kidx, kp, vt = pbs.segment_permute(p, None, K, V)
+        O, times = torch.empty_like(Q), []
+        for _ in range(9):
+            start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            pbs.attn_fwd(p, Q, kp, vt, None, kidx, cnt, cols, O)
+            stop.record()
+            torch.cuda.synchronize()
+            times.append(start.elapsed_time(stop))
+        return min(times) / heads
+    four, five = best(4), best(5)
+    assert five < 1.3 * four, (four, five)
