@@ -1036,7 +1036,6 @@ pbs_status launch_attn_wide(const Geo &g, const void *Qp, const void *Kp, const 
 {
     const long long units = (long long)g.batch * g.h_kv, rows = (long long)g.r * g.T;
     const bool queues = wide_rows_from_queues(g);
-    const int cohort_log2 = queues ? wide::kCohortLog2 : __builtin_ctz(cohort_rows(g));
     // With one row to a compute unit the longest row is what a call waits for, and half of the chip is idle: its list is cut
     // in two.  One piece against two, whole call on causal lists: 4 / 2 heads x 1024 29.9 -> 22.7 us, 32 / 8 x 1024 (256
     // rows) 32.2 -> 25.7 us, 4 / 2 x 4096 77.7 -> 49.5 us.  A second row after the first pays its start and end again, which
@@ -1044,6 +1043,11 @@ pbs_status launch_attn_wide(const Geo &g, const void *Qp, const void *Kp, const 
     // 43.0 us; the lengths are not known here.  (A list of such a call fits one chunk.)
     const bool split = units * rows <= wide::kSplitRows;
     static_assert(wide::kSplitRows < wide::kList, "a split row's list lies in LDS whole, with an entry behind it");
+    // A split row has a compute unit to itself: the XCDs take turns row by row, so that none has more rows than compute units,
+    // and no workgroup is there for the unused end of a cohort.  In cohorts of 64 with 8 or more kv heads, of 8 with fewer,
+    // against that, lists of a tenth of the blocks, us: 250 heads x 128 79.4 / 17.1, 64 x 512 29.6 / 17.4, 40 x 700 33.0 / 20.1, 12 x
+    // 2600 33.8 / 22.2, 7 x 4600 32.6 / 25.4, 32 / 8 x 1024 20.1 / 20.1, 2 / 1 x 16000 35.6 / 35.1.
+    const int cohort_log2 = queues ? wide::kCohortLog2 : split ? 0 : __builtin_ctz(cohort_rows(g));
     unsigned wgs = wide::kResident;
     unsigned long long key = 0;
     if (queues) {

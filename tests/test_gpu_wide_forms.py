@@ -177,3 +177,28 @@ def test_lists_longer_than_a_staged_chunk_with_a_workgroup_per_row(oracle):
     for k, (_, h, i) in enumerate(rows):
         lo, hi = i * BLOCK, min(n, (i + 1) * BLOCK)
         check_close(got[0, h, lo:hi], want[k][:hi - lo], "bf16", "%d entries" % lens[k])
+
+
+def test_time_of_one_row_to_a_head_is_that_of_eight_rows_to_a_head():
+    # 256 rows of a block each: 17 and 18 us; 81 where workgroups without a row wait for a compute unit between those that
+    # have one
+    def best(Hq, Hkv, T):
+        n = T * BLOCK
+        Q, K, V = _qkv(1, 1, Hq, Hkv, n)
+        p = pbs.problem(1, Hq, Hkv, n, D, BLOCK, BLOCK, "bf16")
+        kidx, kp, vt = pbs.segment_permute(p, None, K, V)
+        cnt = torch.ones((1, Hq, T), dtype=torch.int32, device="cuda")
+        cols = torch.arange(T, dtype=torch.int32, device="cuda").view(1, 1, T, 1).expand(1, Hq, T, T).contiguous()
+        O, ws, times = torch.empty_like(Q), pbs.alloc_workspace(p, pbs.STAGE_ATTN_FWD), []
+        for _ in range(7):
+            start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            torch.cuda.synchronize()
+            start.record()
+            for _ in range(20):
+                pbs.attn_fwd(p, Q, kp, vt, None, kidx, cnt, cols, O, ws=ws)
+            stop.record()
+            torch.cuda.synchronize()
+            times.append(start.elapsed_time(stop))
+        return min(times)
+    many, few = best(256, 256, 1), best(32, 8, 8)
+    assert many < 1.5 * few, (many, few)
