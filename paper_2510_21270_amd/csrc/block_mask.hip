@@ -470,7 +470,7 @@ static pbs_status launch_select(const E *Qp, const double *KbarT, uint64_t *mask
 
 // Block means of K' into KbarT ([kv head][feature][kbar_stride(T)] fp64); also called by pbs_segment_permute for the
 // shapes its gather kernel does not pool on the way.
-pbs_status launch_pool_keys(const pbs_problem *p, const Geo &g, const void *Kp, double *KbarT, hipStream_t s)
+static pbs_status launch_pool_keys(const pbs_problem *p, const Geo &g, const void *Kp, double *KbarT, hipStream_t s)
 {
     const int nk = g.batch * g.h_kv;
     if (p->dtype == PBS_BF16)

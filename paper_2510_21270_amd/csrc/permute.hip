@@ -510,19 +510,113 @@ __global__ __launch_bounds__(256) void gather_vt_kernel(const E *__restrict__ V,
 // 8 x 131072 keys with the token-order copies (7 TB/s), 6.4 + 5.9 -> 7.9 us at 8 x 2048.
 // LDS (dynamic): what either of the two needs.
 template <bool TWICE>
-__global__ __launch_bounds__(256) void gather_both_kernel(const uintx4 *__restrict__ K, const uint16_t *__restrict__ V,
-                                                          const int32_t *__restrict__ kidx, uintx4 *__restrict__ Kp,
+__global__ __launch_bounds__(256) void gather_both_kernel(const uint16_t *__restrict__ K, const uint16_t *__restrict__ V,
+                                                          const int32_t *__restrict__ kidx, uint16_t *__restrict__ Kp,
                                                           uint16_t *__restrict__ Vt, int n, int d, int cpr_log2,
                                                           size_t kcopy, size_t vcopy, double *__restrict__ kbarT,
                                                           int block, int T, int Ts, uint32_t kwgs)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     if (blockIdx.x < kwgs)
-        gather_pool<TWICE>(K, kidx, Kp, n, cpr_log2, kcopy, kbarT, block, Ts, blockIdx.x, kwgs,
+        gather_pool<TWICE>(reinterpret_cast<const uintx4 *>(K), kidx, reinterpret_cast<uintx4 *>(Kp), n, cpr_log2, kcopy, kbarT, block, Ts, blockIdx.x, kwgs,
                            reinterpret_cast<double *>(smem_raw));
     else
         gather_vt<uint16_t, TWICE>(V, kidx, Vt, n, d, block, T, vcopy, blockIdx.x - kwgs,
                                    reinterpret_cast<uint32_t *>(smem_raw));
+}
+
+// The rows of one key block of K and their mean, for storage and blocks that gather_pool does not take (float; 2-byte blocks of
+// fewer than 1024 chunks): the workgroup owns the block whole.  bf16 values are summed on the way, as there; float rows
+// are kept in LDS and added in ascending order, column by column.  Odd workgroups write the token-order copy, as everywhere.
+template <typename E, bool TWICE>
+__device__ __forceinline__ void gather_block(const uintx4 *__restrict__ src, const int32_t *__restrict__ idx,
+                                             uintx4 *__restrict__ dst, int n, int cpr_log2, size_t copy_stride,
+                                             double *__restrict__ kbarT, int block, int Ts, uint32_t bx, unsigned char *lds)
+{
+    constexpr int U = 4;
+    constexpr bool wide = sizeof(E) == 4;
+    const bool plain = copy_stride != 0 && (bx & 1);
+    const int j = (int)(copy_stride ? bx >> 1 : bx), row0 = j * block, rows = min(block, n - row0);
+    const int cpr = 1 << cpr_log2, total = rows << cpr_log2, d = cpr * (16 / (int)sizeof(E));
+    const size_t head = (size_t)blockIdx.y * n;
+    const uintx4 *hsrc = src + (head << cpr_log2);
+    uintx4 *hdst = dst + ((head + row0) << cpr_log2) + (plain ? copy_stride : 0);
+    const int32_t *hidx = plain ? nullptr : idx + head + row0;
+    uintx4 *tile = reinterpret_cast<uintx4 *>(lds);        // float: the block's rows
+    double acc[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};            // bf16: this thread's column group
+    for (int c0 = threadIdx.x; c0 < total; c0 += U * 256) {
+        int32_t from[U];
+        uintx4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int row = (c0 + u * 256) >> cpr_log2;
+            from[u] = row < rows ? (hidx ? hidx[row] : row0 + row) : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            v[u] = uintx4{0u, 0u, 0u, 0u};
+            if (from[u] >= 0 && from[u] < n)
+                v[u] = load_once_or_twice<TWICE>(hsrc + ((size_t)from[u] << cpr_log2) + ((c0 + u * 256) & (cpr - 1)));
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (c0 + u * 256 < total) {
+                __builtin_nontemporal_store(v[u], hdst + c0 + u * 256);
+                if (wide && !plain) tile[c0 + u * 256] = v[u];
+            }
+        if (!wide && !plain) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)                    // rows past the end were loaded as zeros
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    acc[2 * x] += (double)__uint_as_float(v[u][x] << 16);
+                    acc[2 * x + 1] += (double)__uint_as_float(v[u][x] & 0xffff0000u);
+                }
+        }
+    }
+    if (plain) return;
+    double *red = reinterpret_cast<double *>(lds);         // 256 * 8
+    if (!wide) {
+#pragma unroll
+        for (int x = 0; x < 8; ++x) red[threadIdx.x * 8 + x] = acc[x];
+    }
+    __syncthreads();
+    const int e = threadIdx.x;
+    if (e >= d) return;
+    double s = 0.0;
+    if (wide) {
+        const float *column = reinterpret_cast<const float *>(lds) + e;
+        int r = 0;
+        for (; r + 16 <= rows; r += 16) {                  // the reads of sixteen rows go out ahead of their additions
+            float v[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) v[u] = column[(r + u) * d];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) s += (double)v[u];
+        }
+        for (; r < rows; ++r) s += (double)column[r * d];
+    } else {
+        for (int q = 0; q < 256 / cpr; ++q) s += red[(q * cpr + (e >> 3)) * 8 + (e & 7)];
+    }
+    kbarT[((size_t)blockIdx.y * d + e) * Ts + j] = s / (double)rows;
+}
+
+// gather_both_kernel for the blocks of gather_block.  One launch in the place of three (rows, means, V'), each of which was mostly
+// its own start and end: float, 2 heads x 2048 x 64 3.1 + 3.2 + 4.3 -> 5.2 us, the layer 81.6 -> 74.9; bf16, 4 heads x 12301 x 64
+// 5.4 + 5.2 + 5.2 -> 7.8 us, the layer 664 -> 658.
+template <typename E, bool TWICE>
+__global__ __launch_bounds__(256) void gather_blocks_kernel(const E *__restrict__ K, const E *__restrict__ V,
+                                                            const int32_t *__restrict__ kidx, E *__restrict__ Kp,
+                                                            E *__restrict__ Vt, int n, int d, int cpr_log2, size_t kcopy,
+                                                            size_t vcopy, double *__restrict__ kbarT, int block, int T, int Ts,
+                                                            uint32_t kwgs)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    if (blockIdx.x < kwgs)
+        gather_block<E, TWICE>(reinterpret_cast<const uintx4 *>(K), kidx, reinterpret_cast<uintx4 *>(Kp), n, cpr_log2, kcopy,
+                               kbarT, block, Ts, blockIdx.x, smem_raw);
+    else
+        gather_vt<E, TWICE>(V, kidx, Vt, n, d, block, T, vcopy, blockIdx.x - kwgs, reinterpret_cast<uint32_t *>(smem_raw));
 }
 
 static int ilog2(int v) { int l = 0; while ((1 << l) < v) ++l; return l; }
@@ -555,7 +649,6 @@ pbs_status launch_segment_sort_by_int_key(const Geo &g, int heads, const int32_t
 }
 
 size_t ws_block_mask(const pbs_problem *p);
-pbs_status launch_pool_keys(const pbs_problem *p, const Geo &g, const void *Kp, double *KbarT, hipStream_t s);
 
 }  // namespace pbs
 
@@ -598,8 +691,8 @@ extern "C" pbs_status pbs_segment_permute(const pbs_problem *p, const float *sco
     const int cpr = (int)(g.d * es / 16);
     const size_t vt_half = (size_t)nbh * g.T * g.d * g.block;           // elements
 
-    // with a workspace, the block means of K' are left there for pbs_block_mask: by the gather itself where a key
-    // block is a whole number of its 1024-chunk batches (2-byte storage), by the pooling kernel otherwise
+    // with a workspace, the block means of K' are left there for pbs_block_mask by the gather itself: gather_pool where a key
+    // block is a whole number of its 1024-chunk batches (2-byte storage), gather_block otherwise
     double *kbarT = reinterpret_cast<double *>(ws);
     const bool pool_on_the_way = kbarT && p->dtype == PBS_BF16 && (g.block * cpr) % 1024 == 0;
     dim3 mg = pool_on_the_way ? move_grid(g.n, cpr, nbh, (size_t)g.block * cpr) : move_grid(g.n, cpr, nbh);
@@ -612,24 +705,32 @@ extern "C" pbs_status pbs_segment_permute(const pbs_problem *p, const float *sco
     const size_t vlds = p->dtype == PBS_BF16                              // tile + skew
                             ? (size_t)g.block * g.d * 2 + (size_t)(g.block / 8) * (64 / (vt_group(g.block) / 8)) * 4
                             : (size_t)g.block * g.d * 4 + (size_t)(g.block / 4) * (64 / (vt_group(g.block) / 4)) * 4;
-    if (pool_on_the_way) {
-        const size_t pool_lds = 256 * 8 * sizeof(double), lds = vlds > pool_lds ? vlds : pool_lds;
-        auto gather = [&](unsigned kwgs, unsigned vwgs) {
-            const dim3 grid(kwgs + vwgs, nbh);
-            return token_copy ? launch(gather_both_kernel<true>, grid, dim3(256), lds, s, (const uintx4 *)K, (const uint16_t *)V,
-                                       (const int32_t *)kidx, (uintx4 *)kdst, (uint16_t *)Vt, g.n, g.d, cl, kcopy, vcopy, kbarT,
-                                       g.block, g.T, Tsk, kwgs)
-                              : launch(gather_both_kernel<false>, grid, dim3(256), lds, s, (const uintx4 *)K, (const uint16_t *)V,
-                                       (const int32_t *)kidx, (uintx4 *)kdst, (uint16_t *)Vt, g.n, g.d, cl, kcopy, vcopy, kbarT,
-                                       g.block, g.T, Tsk, kwgs);
-        };
+    if (kbarT) {
         // V' may take the place of K, which nothing needs once K' is gathered: then one after the other
         const uintptr_t k0 = reinterpret_cast<uintptr_t>(K), v0 = reinterpret_cast<uintptr_t>(Vt);
-        if (v0 < k0 + (size_t)nbh * g.n * g.d * es && k0 < v0 + pbs_vt_bytes(p)) {
-            st = gather(mg.x, 0);
-            return st == PBS_OK ? gather(0, vg.x) : st;
-        }
-        return gather(mg.x, vg.x);
+        const bool in_place = v0 < k0 + (size_t)nbh * g.n * g.d * es && k0 < v0 + pbs_vt_bytes(p);
+        const unsigned kwgs = pool_on_the_way ? mg.x : vg.x;                // by blocks: as many workgroups as V' takes
+        const size_t klds = p->dtype == PBS_BF16 ? 256 * 8 * sizeof(double) : (size_t)g.block * g.d * 4;
+        const size_t lds = vlds > klds ? vlds : klds;
+        auto gather = [&](auto kernel, auto *element, unsigned kw, unsigned vw) {
+            typedef std::remove_pointer_t<decltype(element)> E;
+            return launch(kernel, dim3(kw + vw, nbh), dim3(256), lds, s, (const E *)K, (const E *)V, (const int32_t *)kidx, (E *)kdst,
+                          (E *)Vt, g.n, g.d, cl, kcopy, vcopy, kbarT, g.block, g.T, Tsk, kw);
+        };
+        auto part = [&](unsigned kw, unsigned vw) {
+            uint16_t *two = nullptr;
+            uint32_t *four = nullptr;
+            if (p->dtype != PBS_BF16)
+                return token_copy ? gather(gather_blocks_kernel<uint32_t, true>, four, kw, vw)
+                                  : gather(gather_blocks_kernel<uint32_t, false>, four, kw, vw);
+            if (pool_on_the_way)
+                return token_copy ? gather(gather_both_kernel<true>, two, kw, vw) : gather(gather_both_kernel<false>, two, kw, vw);
+            return token_copy ? gather(gather_blocks_kernel<uint16_t, true>, two, kw, vw)
+                              : gather(gather_blocks_kernel<uint16_t, false>, two, kw, vw);
+        };
+        if (!in_place) return part(kwgs, vg.x);
+        st = part(kwgs, 0);
+        return st == PBS_OK ? part(0, vg.x) : st;
     }
     if (kdst)
         st = token_copy ? launch((move_rows_kernel<false, true>), mg, dim3(256), 0, s, (const uintx4 *)K,
@@ -637,7 +738,6 @@ extern "C" pbs_status pbs_segment_permute(const pbs_problem *p, const float *sco
                         : launch((move_rows_kernel<false, false>), mg, dim3(256), 0, s, (const uintx4 *)K,
                                  (const int32_t *)kidx, (uintx4 *)kdst, g.n, cl, kcopy);
     if (st != PBS_OK) return st;
-    if (kbarT && (st = launch_pool_keys(p, g, Kp, kbarT, s)) != PBS_OK) return st;
     if (p->dtype == PBS_BF16)
         st = token_copy ? launch((gather_vt_kernel<uint16_t, true>), vg, dim3(256), vlds, s, (const uint16_t *)V,
                                  (const int32_t *)kidx, (uint16_t *)Vt, g.n, g.d, g.block, g.T, vcopy)

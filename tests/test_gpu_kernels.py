@@ -632,3 +632,33 @@ def test_block_64_attention_time_with_five_kv_heads():
         return min(times) / heads
     four, five = best(4), best(5)
     assert five < 1.3 * four, (four, five)
+
+
+# K', V' and the block means of K' out of one launch (float32 storage; bf16 blocks of fewer than 1024 pieces of 16 bytes), against
+# the launches that a call without a workspace and pbs_block_mask make: the same bytes.  One key, ragged blocks, whole ones.
+@pytest.mark.parametrize("copy", [False, True])
+@pytest.mark.parametrize("dtype,d,block", [("f32", 64, 16), ("f32", 64, 64), ("f32", 128, 128), ("bf16", 64, 16),
+                                           ("bf16", 64, 64), ("bf16", 128, 32)])
+def test_gather_with_means_in_one_launch(dtype, d, block, copy):
+    for n in (1, block + 1, 5 * block - 3, 6 * block):
+        flags = pbs.FLAG_TOKEN_ORDER_COPY if copy else 0
+        p = pbs.problem(2, 3, 3, n, d, block, 2 * block, dtype, flags=flags)
+        rng = np.random.default_rng(n)
+        K, V = (to_dev(rng.standard_normal((2, 3, n, d)) * 2.0 ** rng.integers(-12, 13, (2, 3, n, 1)), dtype) for _ in range(2))
+        scores = torch.from_numpy(rng.random((2, 3, n)).astype(np.float32)).cuda()
+        ws = pbs.alloc_workspace(p, pbs.STAGE_BLOCK_MASK)
+        kidx, Kp, Vt = pbs.segment_permute(p, scores, K, V, ws=ws)
+        kidx0, Kp0, Vt0 = pbs.segment_permute(p, scores, K, V)
+        assert torch.equal(kidx, kidx0) and torch.equal(Kp, Kp0) and torch.equal(Vt, Vt0)
+        if copy:
+            for x, x0, e in ((kidx, kidx0, 1), (Kp, Kp0, d), (Vt, Vt0, d)):
+                assert torch.equal(pbs.token_copy(p, x, e), pbs.token_copy(p, x0, e))
+        ws0 = pbs.alloc_workspace(p, pbs.STAGE_BLOCK_MASK)
+        pbs.block_mask(p, K, Kp0, ws=ws0)
+        T = pbs.T_of(p)
+        stride = -(-T // 4) * 4
+        means, means0 = (w[:6 * d * stride * 8].view(torch.float64).view(6, d, stride)[..., :T] for w in (ws, ws0))
+        assert torch.equal(means, means0)
+        if n % block == 0 and not copy:                    # V' in the place of K
+            pbs.segment_permute(p, scores, K, V, kidx, Kp, K.view(Vt.shape), ws=ws)
+            assert torch.equal(Kp, Kp0) and torch.equal(K.view(Vt.shape), Vt0)
