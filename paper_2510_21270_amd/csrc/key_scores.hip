@@ -820,12 +820,36 @@ struct F64Logits {
     int row[2];                        // those rows' indices
     int tiles;                         // row tiles of this wave
 
-    __device__ __forceinline__ void load_rows(const double *qhat, int bl, int wr, int rw, int lane)
+    // qhat: what qhat_f64_kernel has left, or NULL: formed here from Q in the same way, for one or two query heads, by which a
+    // division is a multiplication
+    __device__ __forceinline__ void load_rows(const double *qhat, const E *Q, const int32_t *qrows, const Geo &g, int bh, int bl,
+                                              int wr, int rw, int lane)
     {
         tiles = wr * 16 >= bl ? 0 : ((wr + rw) * 16 >= bl ? 1 : 2);
+        const int b = bh / g.h_kv, h = bh % g.h_kv;
+        if (qhat) qhat += (size_t)bh * bl * D;
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
             row[t] = 16 * (wr + rw * t) + (lane & 15);
+            if (!qhat) {
+                if (t >= tiles) continue;
+                const int pos = query_row_position(qrows, min(row[t], bl - 1), bl, g.n);
+                const E *from = Q + (((size_t)b * g.h_q + h * g.r) * g.n + pos) * (size_t)D + 4 * (lane >> 4);
+#pragma unroll
+                for (int e = 0; e < D / 4; ++e) q[t][e] = 0.0;
+#pragma unroll 1
+                for (int head = 0; head < g.r; ++head) {
+                    floatx4 v[D / 16];
+#pragma unroll
+                    for (int u = 0; u < D / 16; ++u) v[u] = load4(from + (size_t)head * g.n * D + 16 * u);
+#pragma unroll
+                    for (int e = 0; e < D / 4; ++e) q[t][e] += (double)v[e >> 2][e & 3];
+                }
+                const double mean = 1.0 / (double)g.r;
+#pragma unroll
+                for (int e = 0; e < D / 4; ++e) q[t][e] *= mean;
+                continue;
+            }
             const double *src = qhat + (size_t)min(row[t], bl - 1) * D + 4 * (lane >> 4);
             if (t < tiles)
 #pragma unroll
@@ -853,7 +877,8 @@ struct F64Logits {
 // partial[bh][row][part], part = chunk * kg + key share.
 template <typename E, int D>
 __global__ __launch_bounds__(256) void scores_stats_f64_kernel(const E *__restrict__ K,
-                                                               const double *__restrict__ qhat,
+                                                               const double *__restrict__ qhat, const E *__restrict__ Q,
+                                                               const int32_t *__restrict__ qrows,
                                                                double2 *__restrict__ partial, Geo g, int bl,
                                                                int keys_per_chunk)
 {
@@ -862,7 +887,7 @@ __global__ __launch_bounds__(256) void scores_stats_f64_kernel(const E *__restri
     const WaveShare ws = wave_share(bl);
     const int wr = wave % ws.rw, wk = wave / ws.rw;
     F64Logits<E, D> logits;
-    logits.load_rows(qhat + (size_t)bh * bl * D, bl, wr, ws.rw, lane);
+    logits.load_rows(qhat, Q, qrows, g, bh, bl, wr, ws.rw, lane);
     const E *Kh = K + (size_t)bh * g.n * D;
     const int end = min(g.n, (chunk + 1) * keys_per_chunk);
     double m[2] = {-INFINITY, -INFINITY}, l[2] = {0.0, 0.0};
@@ -930,7 +955,8 @@ constexpr int kF64Keys = 256;
 
 template <typename E, int D>
 __global__ __launch_bounds__(256) void scores_final_f64_kernel(const E *__restrict__ K,
-                                                               const double *__restrict__ qhat,
+                                                               const double *__restrict__ qhat, const E *__restrict__ Q,
+                                                               const int32_t *__restrict__ qrows,
                                                                const double2 *__restrict__ stats,
                                                                float *__restrict__ scores, Geo g, int bl, int keys)
 {
@@ -940,7 +966,7 @@ __global__ __launch_bounds__(256) void scores_final_f64_kernel(const E *__restri
     const WaveShare ws = wave_share(bl);
     const int wr = wave % ws.rw, wk = wave / ws.rw;
     F64Logits<E, D> logits;
-    logits.load_rows(qhat + (size_t)bh * bl * D, bl, wr, ws.rw, lane);
+    logits.load_rows(qhat, Q, qrows, g, bh, bl, wr, ws.rw, lane);
     double mrow[2], inv[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -982,6 +1008,11 @@ static bool use_mfma(const pbs_problem *p) { return p->dtype == PBS_BF16 && p->d
 // partial sums of that region are dead once Qhat is formed, so sweep 1 may use both.
 constexpr int kGenericKeysPerChunk = 4096;
 constexpr int kMinF64Chunk = 64;       // keys a sweep-1 workgroup takes at least
+// Query heads of a kv head up to which both sweeps form Qhat from Q instead of reading what qhat_f64_kernel has left: a launch less,
+// but every workgroup reads Q's last block once per head.  Stage, own launch / formed, us: one head, float32 2 x 2048 x 64 21.1 / 18.5,
+// 2 x 4096 x 128 42.7 / 36.3, bf16 8 x 12288 x 64 104 / 97.7; two, float32 4/2 x 2048 x 64 21.2 / 19.5, x 128 42.7 / 39.6, bf16 4/2 x
+// 4000 x 64 21.2 / 19.1; four, float32 8/2 x 2048 x 64 21.3 / 21.1, x 128 42.8 / 46.5, bf16 16/4 x 12301 x 64 46.0 / 50.0.
+constexpr int kFormF64Heads = 2;
 
 static size_t ws_avg_query(size_t nbh);
 
@@ -1055,18 +1086,21 @@ static pbs_status run_generic(const Geo &g, const void *Q, const void *K, float 
     double *avg_partial = reinterpret_cast<double *>(ws), *qavg = avg_partial + (size_t)nbh * kAvgChunks * 128;
     pbs_status st;
     if (avg && (st = run_qavg<E>(g, Q, avg_partial, qavg, s)) != PBS_OK) return st;
-    if ((st = launch(qhat_f64_kernel<E>, dim3(ceil_div(bl * g.d, 256), nbh), dim3(256), 0, s, (const E *)Q, qhat, g, bl,
-                     qrows, (const double *)(avg ? qavg : nullptr))) != PBS_OK) return st;
-    if ((st = launch((scores_stats_f64_kernel<E, D>), dim3(chunks, nbh), dim3(256), 0, s, (const E *)K, qhat, partial, g,
-                     bl, kpc)) != PBS_OK) return st;
+    static_assert(kFormF64Heads <= 2, "a division by the number of heads has to be exact as a multiplication");
+    const bool form = !avg && g.r <= kFormF64Heads;
+    const double *given = form ? nullptr : qhat;
+    if (!form && (st = launch(qhat_f64_kernel<E>, dim3(ceil_div(bl * g.d, 256), nbh), dim3(256), 0, s, (const E *)Q, qhat, g, bl,
+                              qrows, (const double *)(avg ? qavg : nullptr))) != PBS_OK) return st;
+    if ((st = launch((scores_stats_f64_kernel<E, D>), dim3(chunks, nbh), dim3(256), 0, s, (const E *)K, given, (const E *)Q, qrows,
+                     partial, g, bl, kpc)) != PBS_OK) return st;
     if ((st = launch(scores_merge_f64_kernel, dim3(ceil_div(bl, 4), nbh), dim3(256), 0, s, partial, stats, bl,
                      chunks * wave_share(bl).kg)) != PBS_OK) return st;
     // Short ranges until there are workgroups enough for eight per compute unit.  Measured, 256 keys / 64, us: d = 64, 4096 keys in
     // all 23.2 / 7.7, 49204 23.5 / 19.3, 98304 37.9 / 31.4, 131072 40.3 / 41.8, 196608 55.0 / 60.2; d = 128, 32768 keys 38.0 / 19.9,
     // 98304 58.8 / 57.9, 131072 61.2 / 74.9, 262144 116 / 147 (a workgroup reads Qhat, 128 KiB, before its first key).
     const int keys = (long long)g.n * nbh >= 256LL * 8 * 64 ? kF64Keys : 64;
-    return launch((scores_final_f64_kernel<E, D>), dim3(ceil_div(g.n, keys), nbh), dim3(256), 0, s, (const E *)K, qhat,
-                  stats, scores, g, bl, keys);
+    return launch((scores_final_f64_kernel<E, D>), dim3(ceil_div(g.n, keys), nbh), dim3(256), 0, s, (const E *)K, given,
+                  (const E *)Q, qrows, (const double2 *)stats, scores, g, bl, keys);
 }
 
 }  // namespace pbs

@@ -662,3 +662,15 @@ def test_gather_with_means_in_one_launch(dtype, d, block, copy):
         if n % block == 0 and not copy:                    # V' in the place of K
             pbs.segment_permute(p, scores, K, V, kidx, Kp, K.view(Vt.shape), ws=ws)
             assert torch.equal(Kp, Kp0) and torch.equal(K.view(Vt.shape), Vt0)
+
+
+# Qhat formed by the sweeps themselves (one or two query heads) and by a launch of its own, against the oracle: fp64 sums, a float
+# result (2^-24), exponentials good to an ulp of fp64
+@pytest.mark.parametrize("r", [1, 2, 3, 8])
+@pytest.mark.parametrize("dtype,d,block,n", [("f32", 64, 64, 700), ("f32", 128, 128, 130), ("bf16", 64, 16, 9), ("f32", 64, 32, 1)])
+def test_fp64_key_scores_of_query_groups(oracle, dtype, d, block, n, r):
+    Q, K, _ = _qkv(r + n, 2 * r, 2, n, d, dtype)
+    p = pbs.problem(1, 2 * r, 2, n, d, block, 2 * block, dtype)
+    got = pbs.key_scores(p, to_dev(Q, dtype), to_dev(K, dtype))
+    want = oracle.key_scores(Q, K, block)
+    np.testing.assert_allclose(got.cpu().numpy(), want, rtol=1e-6, atol=0)
