@@ -23,7 +23,7 @@ namespace pbs {
 
 constexpr int kQRows = 128;            // logit tile rows (>= B')
 constexpr int kSweepWgs = 512;         // workgroups of the MFMA sweeps that the chip holds: two on each of 256 compute units
-constexpr int kMaxRangeKeys = 1024, kMinRangeKeys = 256;   // keys of a range (sweep_range_keys)
+constexpr int kMaxRangeKeys = 1024, kMinRangeKeys = 64;    // keys of a range (sweep_range_keys)
 constexpr long long kLongKeys = 327680;                    // keys of all heads from which on the long sweeps run (long_sweeps)
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -1027,11 +1027,18 @@ static int f64_keys_per_chunk(const Geo &g, int bl)
 }
 
 // Keys of a range of sweep 1, which leaves one (max, sum) per row: 1024 for long inputs; halved while there would be fewer
-// than kSweepWgs ranges, so that short inputs still spread over all compute units.
+// than kSweepWgs ranges, so that short inputs still spread over all compute units; below 256 keys, where a workgroup's start
+// weighs more, only while all ranges have a compute unit each.  256 keys at least / this, whole stage, us: 8 heads x 1024
+// 18.7 / 13.8, x 2048 19.4 / 14.2, x 4096 20.2 / 18.0, 2 x 8192 19.1 / 15.6, 4 x 4000 19.4 / 14.6; with 512 ranges of 128 keys 8 x 8147
+// 21.4 -> 22.2, with 1000 of 64 4 x 16000 22.3 -> 31.1.  (Up to 16 heads: ws_key_scores has room for kSmallRanges ranges there, whatever
+// n is, and pbs_key_scores_static takes what it took.)
+constexpr int kSmallRanges = 256, kSmallHeads = 16;
 static int sweep_range_keys(const Geo &g)
 {
+    const long long nbh = (long long)g.batch * g.h_kv;
     int keys = kMaxRangeKeys;
-    while (keys > kMinRangeKeys && (long long)ceil_div(g.n, keys) * g.batch * g.h_kv < kSweepWgs) keys >>= 1;
+    while (keys > 256 && ceil_div(g.n, keys) * nbh < kSweepWgs) keys >>= 1;
+    while (keys <= 256 && keys > kMinRangeKeys && nbh <= kSmallHeads && ceil_div(g.n, keys / 2) * nbh <= kSmallRanges) keys >>= 1;
     return keys;
 }
 
@@ -1048,9 +1055,10 @@ size_t ws_key_scores(const pbs_problem *p)
     const Geo g = make_geo(p);
     const size_t nbh = (size_t)g.batch * g.h_kv;
     if (use_mfma(p)) {
-        const size_t nwg = ceil_div(g.n, sweep_range_keys(g));
+        size_t ranges = nbh * ceil_div(g.n, sweep_range_keys(g));
+        if (nbh <= kSmallHeads && ranges < kSmallRanges) ranges = kSmallRanges;   // room for every shorter input as well
         return align_up(nbh * 2 * kQRows * 128 * sizeof(bf16_t), kWsAlign) +
-               align_up(nbh * nwg * kQRows * sizeof(float2), kWsAlign) + align_up(nbh * kQRows * sizeof(float), kWsAlign) +
+               align_up(ranges * kQRows * sizeof(float2), kWsAlign) + align_up(nbh * kQRows * sizeof(float), kWsAlign) +
                ws_avg_query(nbh);
     }
     const size_t chunks = ceil_div(g.n, kGenericKeysPerChunk);

@@ -674,3 +674,12 @@ def test_fp64_key_scores_of_query_groups(oracle, dtype, d, block, n, r):
     got = pbs.key_scores(p, to_dev(Q, dtype), to_dev(K, dtype))
     want = oracle.key_scores(Q, K, block)
     np.testing.assert_allclose(got.cpu().numpy(), want, rtol=1e-6, atol=0)
+
+
+# Ranges of 64, 128 and 256 keys, whole and ragged ones, up to 16 kv heads and beyond: 16 bits of Qhat in two terms, sums in fp32
+@pytest.mark.parametrize("Hq,Hkv,n", [(2, 2, 1), (2, 1, 63), (4, 2, 129), (8, 8, 2050), (4, 2, 8193), (16, 16, 1100), (17, 17, 1100)])
+def test_key_scores_in_short_ranges(oracle, Hq, Hkv, n):
+    Q, K, _ = _qkv(n, Hq, Hkv, n, 128, "bf16")
+    p = pbs.problem(1, Hq, Hkv, n, 128, 128, 1024, "bf16")
+    got = pbs.key_scores(p, to_dev(Q, "bf16"), to_dev(K, "bf16"))
+    np.testing.assert_allclose(got.cpu().numpy(), oracle.key_scores(Q, K, 128), rtol=1e-4, atol=0)
