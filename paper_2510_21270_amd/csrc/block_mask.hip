@@ -179,10 +179,12 @@ __device__ __forceinline__ MassCount mass_at_least(RowProbs<NC> &row, double v)
 // Query blocks are taken from the last one down: the long rows start first, the short ones fill the tail.
 // The registers of a row of at most 512 columns (NC = 8) leave room for eight waves per SIMD, of 1024 for six, of 2048 for
 // four, of 4096 for two; the more there are, the more they hide of each other's phases.
-constexpr int select_waves(int nc) { return nc == 8 ? 8 : nc == 16 ? 6 : nc == 32 ? 4 : 2; }
+// FEW (at most 512 columns, bf16 blocks of 128 x 128): no more workgroups than compute units, so that no other wave hides a phase's
+// latencies; with registers for two waves per SIMD a whole query block and twice the pooled keys are on their way at a time.
+constexpr int select_waves(int nc, bool few) { return few ? 2 : nc == 8 ? 8 : nc == 16 ? 6 : nc == 32 ? 4 : 2; }
 
-template <int RB, int QB, int NC, typename E>
-__global__ __launch_bounds__(64 * RB * QB) __attribute__((amdgpu_waves_per_eu(select_waves(NC), select_waves(NC))))
+template <int RB, int QB, int NC, bool FEW, typename E>
+__global__ __launch_bounds__(64 * RB * QB) __attribute__((amdgpu_waves_per_eu(select_waves(NC, FEW), select_waves(NC, FEW))))
 void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
                    const double *__restrict__ KbarT,   // [bhkv][d][Ts]
                    uint64_t *__restrict__ mask_bits, int32_t *__restrict__ row_cnt, int32_t *__restrict__ col_idx,
@@ -190,7 +192,7 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
 {
     constexpr int RT = RB * QB;                                      // rows (= waves) of the workgroup
     constexpr int NG = (RT + 3) / 4;                                 // groups of four rows
-    constexpr int FS = 4;                                            // steps of four features per register buffer
+    constexpr int FS = FEW ? 8 : 4;                                  // steps of four features per register buffer
     extern __shared__ __align__(16) unsigned char smem_raw[];
     double *prob = reinterpret_cast<double *>(smem_raw);             // [RT][kPanel, or Tpad if less]
     __shared__ __align__(16) double qs[128][RT];                     // block means of the RT query rows, feature-major
@@ -234,7 +236,7 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
             // A register is requested again as soon as it is added up, so that the additions (a conversion and an fp64
             // addition per value) run under the loads of the others.  Buffer loads: rows past the block lie past
             // the descriptor's end and read as zeros, without a branch per load.
-            constexpr int U = 4, kNonTemporal = 2;
+            constexpr int U = FEW ? 32 : 4, kNonTemporal = 2;        // FEW: blocks of 32 pieces
             const int row_bytes = g.d * (int)sizeof(E);
             const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
                 const_cast<E *>(Qp + ((size_t)(bhq0 + wh) * g.n + lo) * g.d), 0, (hi - lo) * row_bytes, 0x00020000);
@@ -246,15 +248,23 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
             for (int q = 0; q < U; ++q)
                 v[q] = __builtin_bit_cast(vec_t, __builtin_amdgcn_raw_buffer_load_b128(r, voff, q * 1024, kNonTemporal));
             __builtin_amdgcn_sched_barrier(0);
-            for (int q0 = 0; q0 < pieces; q0 += U)
+            auto add = [&](int q) __attribute__((always_inline)) {
 #pragma unroll
-                for (int q = 0; q < U; ++q) {
+                for (int u = 0; u < VEC; ++u) acc[u] += (double)ElemTraits<E>::to_float(v[q][u]);
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            if constexpr (FEW) {
 #pragma unroll
-                    for (int u = 0; u < VEC; ++u) acc[u] += (double)ElemTraits<E>::to_float(v[q][u]);
-                    __builtin_amdgcn_sched_barrier(0);
-                    v[q] = __builtin_bit_cast(vec_t, __builtin_amdgcn_raw_buffer_load_b128(r, voff, (q0 + U + q) * 1024, kNonTemporal));
-                    __builtin_amdgcn_sched_barrier(0);
-                }
+                for (int q = 0; q < U; ++q) add(q);
+            } else {
+                for (int q0 = 0; q0 < pieces; q0 += U)
+#pragma unroll
+                    for (int q = 0; q < U; ++q) {
+                        add(q);
+                        v[q] = __builtin_bit_cast(vec_t, __builtin_amdgcn_raw_buffer_load_b128(r, voff, (q0 + U + q) * 1024, kNonTemporal));
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+            }
         }
         for (int o = cpr; o < 64; o <<= 1)
 #pragma unroll
@@ -424,14 +434,14 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
     if (lane == 0) row_cnt[orow] = base;
 }
 
-template <int RB, int QB, int NC, typename E>
+template <int RB, int QB, int NC, bool FEW, typename E>
 static pbs_status launch_select_nc(const E *Qp, const double *KbarT, uint64_t *mask_bits, int32_t *row_cnt,
                                    int32_t *col_idx, const Geo &g, hipStream_t s)
 {
     const int chunks = (g.r + RB - 1) / RB;
     const int Tpad = (g.T + 63) & ~63;
     const size_t lds = (size_t)RB * QB * (Tpad > kPanel ? kPanel : Tpad) * sizeof(double);           // at most 32 KiB
-    return launch((select_kernel<RB, QB, NC, E>), dim3((g.T + QB - 1) / QB, g.batch * g.h_kv * chunks), dim3(64 * RB * QB),
+    return launch((select_kernel<RB, QB, NC, FEW, E>), dim3((g.T + QB - 1) / QB, g.batch * g.h_kv * chunks), dim3(64 * RB * QB),
                   lds, s, Qp, KbarT, mask_bits, row_cnt, col_idx, g, chunks, Tpad, kbar_stride(g.T));
 }
 
@@ -439,15 +449,23 @@ static pbs_status launch_select_nc(const E *Qp, const double *KbarT, uint64_t *m
 // 8 / 4 x 131072 1.57 ms, block 128: 32 / 8 x 139264 499 us.  With the rows in LDS, one query block to a workgroup and
 // the logits on v_fma_f64 that took 433 us, 2.73 ms and 513 us; with the rows in LDS and the logits on the matrix instruction
 // 504 us, 3.82 ms and 562 us.
+constexpr int kFewWgs = 256;
 template <int RB, int QB, typename E>
 static pbs_status launch_select_qb(const E *Qp, const double *KbarT, uint64_t *mask_bits, int32_t *row_cnt,
                                    int32_t *col_idx, const Geo &g, hipStream_t s)
 {
     static_assert(kMaxT <= 4096, "columns of a row");
-    if (g.T <= 512) return launch_select_nc<RB, QB, 8>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
-    if (g.T <= 1024) return launch_select_nc<RB, QB, 16>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
-    if (g.T <= 2048) return launch_select_nc<RB, QB, 32>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
-    return launch_select_nc<RB, QB, 64>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
+    // Whole query blocks on their way at a time, where no workgroup shares a compute unit.  Stage, four pieces / a block of 32, us: 32 / 8
+    // heads x 1024 14.4 / 12.5, x 2048 16.1 / 14.1, x 8147 20.0 / 18.8, 4 / 2 x 8192 13.1 / 11.2, 28 / 4 x 4000 16.7 / 14.9; blocks of fewer
+    // pieces, whose other loads are idle: 16 / 4 x 3000 x 64, block 64 11.5 / 12.9, 8 / 8 x 2000 x 64, block 128 8.9 / 9.4, 8 / 8 x 3000
+    // x 128, block 64 10.4 / 10.5.
+    if (sizeof(E) == 2 && g.T <= 512 && g.block * g.d == 128 * 128 &&
+        (long long)ceil_div(g.T, QB) * g.batch * g.h_kv * ceil_div(g.r, RB) <= kFewWgs)
+        return launch_select_nc<RB, QB, 8, sizeof(E) == 2>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
+    if (g.T <= 512) return launch_select_nc<RB, QB, 8, false>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
+    if (g.T <= 1024) return launch_select_nc<RB, QB, 16, false>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
+    if (g.T <= 2048) return launch_select_nc<RB, QB, 32, false>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
+    return launch_select_nc<RB, QB, 64, false>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
 }
 
 // A matrix instruction takes four rows: with one query head to a kv head two query blocks leave half of it empty, so four come to

@@ -683,3 +683,16 @@ def test_key_scores_in_short_ranges(oracle, Hq, Hkv, n):
     p = pbs.problem(1, Hq, Hkv, n, 128, 128, 1024, "bf16")
     got = pbs.key_scores(p, to_dev(Q, "bf16"), to_dev(K, "bf16"))
     np.testing.assert_allclose(got.cpu().numpy(), oracle.key_scores(Q, K, 128), rtol=1e-4, atol=0)
+
+
+# Selection with a compute unit to every workgroup (whole query blocks loaded at a time) and with more workgroups than that, ragged
+# last blocks, 3 and 4 query heads in a chunk: the masks of the oracle, bit for bit
+@pytest.mark.parametrize("Hq,Hkv,n,segment", [(4, 4, 5, 256), (3, 1, 130, 256), (7, 1, 2000, 512), (2, 1, 8200, 1024),
+                                               (8, 2, 8191, 1024), (8, 2, 33000, 1024)])
+def test_selection_with_few_workgroups(oracle, Hq, Hkv, n, segment):
+    Q, K, _ = _qkv(n, Hq, Hkv, n, 128, "bf16")
+    p = pbs.problem(1, Hq, Hkv, n, 128, 128, segment, "bf16", tau=0.9)
+    bits, cnt, _ = pbs.block_mask(p, to_dev(Q, "bf16"), to_dev(K, "bf16"))
+    want = oracle.block_mask(Q, K, 128, segment, float(np.float32(0.9)))[0]
+    mask = mask_from_bits(bits, pbs.T_of(p))
+    assert np.array_equal(mask, want) and np.array_equal(cnt.cpu().numpy(), want.sum(-1))
