@@ -120,7 +120,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
             const int j = __builtin_amdgcn_readfirstlane(cols[u_next >> subs_log2]);
             const int sub = u_next & ((1 << subs_log2) - 1);
             u_next += WAVES;
-            if (j >= 0 && j < ni) return j * g.block + sub * KS;
+            const int first = listed_slot(j, sub, KS, g.block, ni, g.n);
+            if (first >= 0) return first;
         }
         return -1;
     };
@@ -145,7 +146,9 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
     unsigned char *const own = ring[wave];
     // Vt keeps a block as groups of KT slots, each [D][KT]: a sub-tile is one group or one of its halves
     auto values_at = [&](int s0) __attribute__((always_inline)) { return (s0 & -KT) * D + (s0 & (KT - 1)); };
-    auto load_tile = [&](int s0) __attribute__((always_inline)) {            // reads past the end give zeros; masked below
+    // Keys past the end give zeros and are masked below.  s0 is one of the n keys, so that no load starts behind the end of its
+    // descriptor: the hardware compares a lane's offset with the size less the scalar offset, which must not fall below zero.
+    auto load_tile = [&](int s0) __attribute__((always_inline)) {
 #pragma unroll
         for (int c = 0; c < kLoads; ++c) load_to_lds(rk, own + 1024 * c, koff[c], s0 * kKeyB);
 #pragma unroll

@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include "../../include/pbs.h"
+#include "load_places.h"
 
 namespace pbs {
 
