@@ -228,8 +228,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
             for (int x = 0; x < 16; ++x) st.acc[dt][nt][x] = 0.0f;
     }
 
-    // Loads: a sub-tile of K' or Vt is 4 instructions of 1 KiB.  Reads past the end of K' give zeros (such slots are masked);
-    // Vt is zero-filled to whole blocks.
+    // Loads: a sub-tile of K' or Vt is 4 instructions of 1 KiB.  Reads past the end of K' give zeros (such slots are masked) and
+    // start at the end at the latest (scalar_offset); Vt is zero-filled to whole blocks; a pair's positions start with one of the n keys.
     constexpr int kRawDword = 0x00020000;                  // gfx9 descriptor word 3: raw 32-bit data format
     const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(w.k), 0, g.n * (D * 2), kRawDword);
     const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(w.vt), 0, g.T * g.block * (D * 2), kRawDword);
@@ -248,7 +248,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
     // load C of the K' rows or the Vt group of the 32 slots from slot0 on
     auto load_k = [&](auto cc, Tile &to, int slot0) __attribute__((always_inline)) {
         constexpr int c = decltype(cc)::value;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (lptr_t)(to.b + c * 1024), 16, koff[c & 1], (slot0 + (c >> 1) * 16) * (D * 2), 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (lptr_t)(to.b + c * 1024), 16, koff[c & 1],
+                                                 scalar_offset((slot0 + (c >> 1) * 16) * (D * 2), g.n * (D * 2)), 0, 0);
     };
     auto load_v = [&](auto cc, Tile &to, int slot0) __attribute__((always_inline)) {
         constexpr int c = decltype(cc)::value;
@@ -272,7 +273,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
             const int j = __builtin_amdgcn_readfirstlane(w.cols[u_next >> halves_log2]);
             const int part = u_next & halves_log2;
             u_next += WAVES;
-            if (j >= 0 && j < w.ni) return j * g.block + 64 * part;
+            const int first = listed_slot(j, part, 64, g.block, w.ni, g.n);
+            if (first >= 0) return first;
         }
         return -1;
     };
@@ -290,9 +292,10 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
     };
     auto load_kf = [&](bf16x8 (&kf)[4], int slot0) __attribute__((always_inline)) {           // from memory
         const int id = fresh_lane(), at = swap23(id & 31) * (D * 2) + (id >> 5) * 16;
+        const int from = scalar_offset(slot0 * (D * 2), g.n * (D * 2));
 #pragma unroll
         for (int x = 0; x < 4; ++x)
-            kf[x] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rk, at, slot0 * (D * 2) + 32 * x, 0));
+            kf[x] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rk, at + 32 * x, from, 0));
     };
     auto far_scores = [&](int nt, int slot0, floatx16 &s) __attribute__((always_inline)) {
         bf16x8 kf[4];

@@ -16,6 +16,13 @@ SCALAR_OFFSET = {"__builtin_amdgcn_raw_ptr_buffer_load_lds": 4, "__builtin_amdgc
 
 # scalar offsets by which no load starts behind its descriptor, and why
 WITHIN = {
+    "attn_d64.hip": {
+        "scalar_offset((slot0 + (c >> 1) * 16) * (D * 2), g.n * (D * 2))": "stops at the end",
+        "from": "the same: load_kf forms it so",
+        "slot0 * (D * 2) + c * 1024": "Vt holds whole blocks",
+        "slot0 * (D * 2)": "Vt",
+        "slot0 * 4": "the first slot of a pair comes from listed_slot: one of the n keys",
+    },
     "attn_fp32.hip": {
         "at": "load_to_lds passes on what its callers give",
         "s0 * kKeyB": "s0 comes from listed_slot: one of the n keys",
@@ -53,7 +60,9 @@ def test_no_load_starts_behind_its_descriptor(name):
         found += 1
         assert offset == "0" or offset in WITHIN[name], (name, offset)
     assert found
-    if name in ("attn_fp32.hip",):                          # slots to load come from nowhere else
+    if name == "attn_d64.hip":
+        assert "const int from = scalar_offset(slot0 * (D * 2), g.n * (D * 2));" in text
+    if name in ("attn_fp32.hip", "attn_d64.hip"):           # slots to load come from nowhere else
         slots = re.search(r"auto next_slot = .*?\n    };", text, re.S).group(0)
         assert set(re.findall(r"return ([^;]*);", slots)) == {"first", "-1"} and "first = listed_slot(" in slots
 
@@ -81,6 +90,9 @@ int main()
                         if (keys != want) return 2;
                     }
             }
+    for (int bytes = 0; bytes <= 4096; bytes += 128)
+        for (int at = 0; at <= 8192; at += 128)
+            if (pbs::scalar_offset(at, bytes) > bytes || (at <= bytes && pbs::scalar_offset(at, bytes) != at)) return 3;
     std::puts("all places hold");
 }
 """
