@@ -235,7 +235,8 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
         if (active) {
             // A register is requested again as soon as it is added up, so that the additions (a conversion and an fp64
             // addition per value) run under the loads of the others.  Buffer loads: rows past the block lie past
-            // the descriptor's end and read as zeros, without a branch per load.
+            // the descriptor's end and read as zeros, without a branch per load.  The way into the block is part of the lane's offset:
+            // a scalar offset may not lie behind the descriptor's end (see scalar_offset).
             constexpr int U = FEW ? 32 : 4, kNonTemporal = 2;        // FEW: blocks of 32 pieces
             const int row_bytes = g.d * (int)sizeof(E);
             const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
@@ -246,7 +247,7 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
             vec_t v[U];
 #pragma unroll
             for (int q = 0; q < U; ++q)
-                v[q] = __builtin_bit_cast(vec_t, __builtin_amdgcn_raw_buffer_load_b128(r, voff, q * 1024, kNonTemporal));
+                v[q] = __builtin_bit_cast(vec_t, __builtin_amdgcn_raw_buffer_load_b128(r, voff + q * 1024, 0, kNonTemporal));
             __builtin_amdgcn_sched_barrier(0);
             auto add = [&](int q) __attribute__((always_inline)) {
 #pragma unroll
@@ -261,7 +262,7 @@ void select_kernel(const E *__restrict__ Qp,           // [bhq][n][d]
 #pragma unroll
                     for (int q = 0; q < U; ++q) {
                         add(q);
-                        v[q] = __builtin_bit_cast(vec_t, __builtin_amdgcn_raw_buffer_load_b128(r, voff, (q0 + U + q) * 1024, kNonTemporal));
+                        v[q] = __builtin_bit_cast(vec_t, __builtin_amdgcn_raw_buffer_load_b128(r, voff + (q0 + U + q) * 1024, 0, kNonTemporal));
                         __builtin_amdgcn_sched_barrier(0);
                     }
             }

@@ -29,6 +29,7 @@ WITHIN = {
         "s0 * 4": "the same",
         "values_at(s0) * kB": "Vt holds whole blocks",
     },
+    "block_mask.hip": {},
 }
 
 
