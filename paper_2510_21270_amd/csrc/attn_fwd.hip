@@ -47,9 +47,11 @@ typedef __attribute__((address_space(3))) void *lptr_t;
 
 // Buffer descriptors (base, size in bytes) of one kv head's K', V'^T and key positions.  A load is
 // "descriptor base + scalar tile offset + per-lane offset": no 64-bit vector arithmetic, and anything past the end
-// of K' or of the positions reads as zero (such key slots are rejected by index in the exact softmax path).
+// of K' or of the positions reads as zero (such key slots are rejected by index in the exact softmax path); a sub-tile behind
+// the n-th key starts at the end (scalar_offset).
 struct TileBuffers {
     __amdgpu_buffer_rsrc_t k, v, pos;
+    int n;
 };
 
 template <int BLOCK>
@@ -60,6 +62,7 @@ __device__ inline TileBuffers tile_buffers(const bf16_t *Kh, const bf16_t *Vh, c
     b.k = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(Kh), 0, n * 256, kRawDword);
     b.v = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(Vh), 0, T * 128 * BLOCK * 2, kRawDword);
     b.pos = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(kih), 0, n * 4, kRawDword);
+    b.n = n;
     return b;
 }
 
@@ -122,7 +125,7 @@ template <int BLOCK, int WAVES, int KT>
 __device__ inline void fetch_key_rows(KeyRows<WAVES, KT> &kr, const TileBuffers &buf, const LaneOffsets<WAVES, KT> &off,
                                       int j, int half)
 {
-    const int slot0 = j * BLOCK + half * KT;
+    const int slot0 = scalar_offset(j * BLOCK + half * KT, buf.n);
 #pragma unroll
     for (int y = 0; y < (SubTile<KT>::kKLoads + WAVES - 1) / WAVES; ++y)
         kr.row[y] = __builtin_amdgcn_raw_buffer_load_b32(buf.pos, (off.k[y] >> 8) * 4, slot0 * 4, 0);
@@ -134,7 +137,7 @@ __device__ inline void issue_subtile(unsigned char *kbuf, unsigned char *vbuf, i
                                      bool masked, int wave, int lane)
 {
     constexpr int kKLoads = SubTile<KT>::kKLoads, kVLoads = SubTile<KT>::kVLoads;
-    const int slot0 = j * BLOCK + half * KT;               // uniform
+    const int slot0 = scalar_offset(j * BLOCK + half * KT, buf.n);         // uniform
     // full rounds are unconditional; only the last, partial round of chunks tests the wave index
 #pragma unroll
     for (int y = 0; y < (kKLoads + WAVES - 1) / WAVES; ++y)

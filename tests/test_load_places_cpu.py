@@ -29,6 +29,11 @@ WITHIN = {
         "s0 * 4": "the same",
         "values_at(s0) * kB": "Vt holds whole blocks",
     },
+    "attn_fwd.hip": {
+        "slot0 * 4": "slot0 stops at the n-th key",
+        "slot0 * 256": "the same",
+        "j * (128 * BLOCK * 2) + half * (128 * KT * 2)": "Vt holds whole blocks",
+    },
     "block_mask.hip": {},
 }
 
@@ -61,6 +66,8 @@ def test_no_load_starts_behind_its_descriptor(name):
         found += 1
         assert offset == "0" or offset in WITHIN[name], (name, offset)
     assert found
+    if name == "attn_fwd.hip":
+        assert set(re.findall(r"int slot0 = ([^;]*);", text)) == {"scalar_offset(j * BLOCK + half * KT, buf.n)"}
     if name == "attn_d64.hip":
         assert "const int from = scalar_offset(slot0 * (D * 2), g.n * (D * 2));" in text
     if name in ("attn_fp32.hip", "attn_d64.hip"):           # slots to load come from nowhere else
