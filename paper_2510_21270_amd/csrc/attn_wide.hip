@@ -79,10 +79,12 @@ struct __align__(16) Stage {
 
 __device__ __forceinline__ int swap23(int m) { return (m & ~12) | ((m & 4) << 1) | ((m & 8) >> 1); }
 
-// Descriptors of one kv head: what this wave loads (wave 0: K', wave 1: V'^T) and the key positions; ring: byte offset
-// of this wave's stages behind those of the first half of a split row.
+// Descriptors of one kv head: what this wave loads (wave 0: K', wave 1: V'^T) and the key positions, and their sizes (a sub-tile
+// behind the n-th key starts at the end, see scalar_offset); ring: byte offset of this wave's stages behind those of the
+// first half of a split row.
 struct TileBuffers {
     __amdgpu_buffer_rsrc_t tile, pos;
+    int tile_bytes, pos_bytes;
     int ring;
 };
 
@@ -137,7 +139,7 @@ __device__ __forceinline__ StageLoad stage_load(__attribute__((address_space(3))
     StageLoad a;
     static_assert(BLOCK * 256 == D * BLOCK * 2 && KS * 256 == D * KS * 2, "blocks and sub-tiles of K' and Vt are equally large");
     a.rsrc = buf.tile;
-    a.soff = (wave == 0 ? jk : jv) * (BLOCK * 256) + (wave == 0 ? P : (P + 3) & 3) * (KS * 256);
+    a.soff = scalar_offset((wave == 0 ? jk : jv) * (BLOCK * 256) + (wave == 0 ? P : (P + 3) & 3) * (KS * 256), buf.tile_bytes);
     int own = buf.ring + wave * kStageB;                   // sg.k for wave 0, sg.v behind it for wave 1
     asm volatile("" : "+s"(own));      // formed here: 32 loop-invariant addresses would not fit the scalar registers
     a.dst = dst + own;
@@ -158,7 +160,8 @@ template <int P>
 __device__ __forceinline__ void issue_positions(__attribute__((address_space(3))) unsigned char *dst, const TileBuffers &buf,
                                                 int j, int lane)
 {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(buf.pos, (lptr_t)(dst + buf.ring), 4, lane * 4, (j * BLOCK + P * KS) * 4, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(buf.pos, (lptr_t)(dst + buf.ring), 4, lane * 4,
+                                             scalar_offset((j * BLOCK + P * KS) * 4, buf.pos_bytes), 0, 0);
 }
 
 // K' part P of block j and the V'^T part (P + 3) % 4 of block jv
@@ -620,10 +623,12 @@ __global__ __launch_bounds__(128 * HALVES) __attribute__((amdgpu_waves_per_eu(1,
         // permuted one, so block j of this head in token order is block tok_delta + j of the same descriptors
         const size_t bhk = unit;
         const int reach = a.tok_delta * BLOCK + g.n;       // rows within reach of this head's descriptors
-        buf.tile = wave == 0 ? __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(a.Kp + bhk * (size_t)g.n * D), 0, reach * 256, kRawDword)
-                             : __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(a.Vt + bhk * (size_t)g.T * D * BLOCK), 0,
-                                                                 (a.tok_delta + g.T) * (D * BLOCK * 2), kRawDword);
-        buf.pos = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(a.kidx + bhk * (size_t)g.n), 0, reach * 4, kRawDword);
+        buf.tile_bytes = wave == 0 ? reach * 256 : (a.tok_delta + g.T) * (D * BLOCK * 2);
+        buf.pos_bytes = reach * 4;
+        buf.tile = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(wave == 0 ? a.Kp + bhk * (size_t)g.n * D
+                                                                                    : a.Vt + bhk * (size_t)g.T * D * BLOCK),
+                                                     0, buf.tile_bytes, kRawDword);
+        buf.pos = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(a.kidx + bhk * (size_t)g.n), 0, buf.pos_bytes, kRawDword);
     };
     // jv0: the first iteration of a row multiplies V'^T part 3 of this block by zero probabilities; that is a block of the
     // row's list, the same one for both halves, so that infinite values meet no more zeros than they would in one piece
@@ -788,7 +793,8 @@ __global__ __launch_bounds__(128 * HALVES) __attribute__((amdgpu_waves_per_eu(1,
                 const __amdgpu_buffer_rsrc_t r = query_buffer(a, nb);
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
-                    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)sink, 4, lane * 128, nq * (BLOCK * 256) + k * 8192, 0, 0);
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)sink, 4, lane * 128,
+                                                             scalar_offset(nq * (BLOCK * 256) + k * 8192, a.g.n * 256), 0, 0);
                 step_no = 1;
                 return;
             }
