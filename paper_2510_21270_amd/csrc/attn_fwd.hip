@@ -137,7 +137,8 @@ __device__ inline void issue_subtile(unsigned char *kbuf, unsigned char *vbuf, i
                                      bool masked, int wave, int lane)
 {
     constexpr int kKLoads = SubTile<KT>::kKLoads, kVLoads = SubTile<KT>::kVLoads;
-    const int slot0 = scalar_offset(j * BLOCK + half * KT, buf.n);         // uniform
+    static_assert(BLOCK * 256 == 128 * BLOCK * 2 && KT * 256 == 128 * KT * 2, "blocks and sub-tiles of K' and Vt are equally large");
+    const int from = j * (BLOCK * 256) + half * (KT * 256);                // uniform
     // full rounds are unconditional; only the last, partial round of chunks tests the wave index
 #pragma unroll
     for (int y = 0; y < (kKLoads + WAVES - 1) / WAVES; ++y)
@@ -147,15 +148,16 @@ __device__ inline void issue_subtile(unsigned char *kbuf, unsigned char *vbuf, i
                                                          (uint32_t)kr.row[y] * 256u + (off.k[y] & 255u), 0, 0, 0);
             else
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(buf.k, (lptr_t)(kbuf + (wave + WAVES * y) * 1024), 16, off.k[y],
-                                                         slot0 * 256, 0, 0);
+                                                         scalar_offset(from, buf.n * 256), 0, 0);
         }
 #pragma unroll
     for (int y = 0; y < (kVLoads + WAVES - 1) / WAVES; ++y)
         if (y < kVLoads / WAVES || wave < kVLoads % WAVES)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(buf.v, (lptr_t)(vbuf + (wave + WAVES * y) * 1024), 16, off.v[y],
-                                                     j * (128 * BLOCK * 2) + half * (128 * KT * 2), 0, 0);
+                                                     from, 0, 0);
     if (masked && wave == WAVES - 1)                       // original positions of 64 keys from the sub-tile's first on
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(buf.pos, (lptr_t)kpos, 4, lane * 4, slot0 * 4, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(buf.pos, (lptr_t)kpos, 4, lane * 4,
+                                                 scalar_offset(j * BLOCK + half * KT, buf.n) * 4, 0, 0);
 }
 
 // Barrier that also publishes the asynchronous LDS loads of every wave: the loads of a wave are only counted by

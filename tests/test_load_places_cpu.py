@@ -31,8 +31,9 @@ WITHIN = {
     },
     "attn_fwd.hip": {
         "slot0 * 4": "slot0 stops at the n-th key",
-        "slot0 * 256": "the same",
-        "j * (128 * BLOCK * 2) + half * (128 * KT * 2)": "Vt holds whole blocks",
+        "scalar_offset(from, buf.n * 256)": "stops at the end",
+        "scalar_offset(j * BLOCK + half * KT, buf.n) * 4": "the same",
+        "from": "Vt holds whole blocks",
     },
     "attn_wide.hip": {
         "a.soff": "stage_load stops it at the end",
