@@ -12,8 +12,9 @@
 // accumulator).  Qhat is an fp32 mean, not a bf16 value, so it is pre-multiplied by scale*log2(e) and split
 // into two bf16 terms hi + lo; each tile takes two MFMAs per fragment.  A wave keeps the fragments of its rows
 // of Qhat in registers (64 rows for long inputs, 32 for short ones) and the K tiles go through LDS, shared by the waves of
-// a workgroup.  Both forms compute a logit, and the sums of a range of keys, with the same operations in the same order; how
-// long the ranges are depends on the keys of all heads (sweep_range_keys).
+// a workgroup.  Both forms compute a logit, and the sums of a range of keys, with the same operations in the same order.  How
+// long the ranges are is a matter of a head's length up to 262144 keys in all, and of the keys of all heads from there on
+// (sweep_range_keys).
 // Everything else (fp32 inputs, d = 64): the same two sweeps on the fp64 matrix instruction.
 #include <utility>
 
@@ -23,7 +24,7 @@ namespace pbs {
 
 constexpr int kQRows = 128;            // logit tile rows (>= B')
 constexpr int kSweepWgs = 512;         // workgroups of the MFMA sweeps that the chip holds: two on each of 256 compute units
-constexpr int kMaxRangeKeys = 1024, kMinRangeKeys = 64;    // keys of a range (sweep_range_keys)
+constexpr int kMaxRangeKeys = 1024;                        // keys of a range at most (sweep_range_keys)
 constexpr long long kLongKeys = 327680;                    // keys of all heads from which on the long sweeps run (long_sweeps)
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -640,12 +641,13 @@ __device__ __forceinline__ void sweep_tiles(KTile (&kt)[2], const bf16_t *Kh, in
     }
 }
 
-// partial[bh][wg][row] = (max2, sumexp2) over the keys of workgroup wg, log2 domain.
+// partial[bh][range][row] = (max2, sumexp2) over the keys of a range, log2 domain; a workgroup takes kpw keys, a whole number of
+// ranges of range_keys (a multiple of a tile).
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void sweep1_kernel(
-    const bf16_t *__restrict__ K, const bf16_t *__restrict__ qsplit, float2 *__restrict__ partial, Geo g, int kpw)
+    const bf16_t *__restrict__ K, const bf16_t *__restrict__ qsplit, float2 *__restrict__ partial, Geo g, int kpw, int range_keys)
 {
     __shared__ __align__(16) KTile kt[2];
-    const int bh = blockIdx.y, wg = blockIdx.x, nwg = gridDim.x;
+    const int bh = blockIdx.y, wg = blockIdx.x, parts = ceil_div(g.n, range_keys);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     bf16x8 qh[8], ql[8];
     load_qfrags(qh, qsplit, bh, 0, wave, lane);
@@ -653,6 +655,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const bf16_t *Kh = K + (size_t)bh * g.n * 128;
     const int key_begin = wg * kpw, key_end = min(g.n, key_begin + kpw);
     const int ntiles = ceil_div(key_end - key_begin, kTileKeys);
+    float2 *first = partial + ((size_t)bh * parts + key_begin / range_keys) * kQRows + wave * 32 + lane;
     float m = -INFINITY, l = 0.0f;                           // row 32 wave + (lane & 31), this lane's half of the keys
     sweep_tiles(kt, Kh, key_begin, ntiles, g.n, tid, [&](int t, const KTile &tile) {
         floatx16 acc = {0};
@@ -681,13 +684,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             l = l * __builtin_amdgcn_exp2f(m - mn) + sum;    // exp2(-inf) = 0 on the first tile
             m = mn;
         }
+        if (((t + 1) * kTileKeys & (range_keys - 1)) != 0 && t + 1 < ntiles) return;
+        // the end of a range: merge the two lane halves; the rows of a wave are its own.  (Without LDS and without a rescue of
+        // denormals, which next to the half that holds the maximum count for nothing: a range may end every other tile.)
+        const uint32_t mb = __builtin_bit_cast(uint32_t, m), lb = __builtin_bit_cast(uint32_t, l);
+        const auto ms = __builtin_amdgcn_permlane32_swap(mb, mb, false, false), ls = __builtin_amdgcn_permlane32_swap(lb, lb, false, false);
+        const uint32_t ml = ms[0], mh = ms[1], ll = ls[0], lh = ls[1];       // of the lower and of the upper half
+        const float m0 = __builtin_bit_cast(float, ml), m1 = __builtin_bit_cast(float, mh), both = fmaxf(m0, m1);
+        float ln = 0.0f;
+        if (both != -INFINITY)
+            ln = __builtin_bit_cast(float, ll) * __builtin_amdgcn_exp2f(m0 - both) + __builtin_bit_cast(float, lh) * __builtin_amdgcn_exp2f(m1 - both);
+        if (lane < 32) first[(size_t)(t * kTileKeys / range_keys) * kQRows] = make_float2(both, ln);
+        m = -INFINITY;
+        l = 0.0f;
     });
-    // merge the two lane halves; the rows of a wave are its own
-    const float mo = __shfl_xor(m, 32, 64), lo = __shfl_xor(l, 32, 64);
-    const float mn = fmaxf(m, mo);
-    float ln = 0.0f;
-    if (mn != -INFINITY) ln = l * exp2f(m - mn) + lo * exp2f(mo - mn);
-    if (lane < 32) partial[((size_t)bh * nwg + wg) * kQRows + wave * 32 + lane] = make_float2(mn, ln);
 }
 
 // scores[key] = sum over the 128 rows of exp2(logit2 + c[row]): each wave sums its 32 rows per key into LDS, the
@@ -1037,18 +1047,30 @@ static int f64_keys_per_chunk(const Geo &g, int bl)
 }
 
 // Keys of a range of sweep 1, which leaves one (max, sum) per row: 1024 for long inputs; halved while there would be fewer
-// than kSweepWgs ranges, so that short inputs still spread over all compute units; below 256 keys, where a workgroup's start
-// weighs more, only while all ranges have a compute unit each.  256 keys at least / this, whole stage, us: 8 heads x 1024
-// 18.7 / 13.8, x 2048 19.4 / 14.2, x 4096 20.2 / 18.0, 2 x 8192 19.1 / 15.6, 4 x 4000 19.4 / 14.6; with 512 ranges of 128 keys 8 x 8147
-// 21.4 -> 22.2, with 1000 of 64 4 x 16000 22.3 -> 31.1.  (Up to 16 heads: ws_key_scores has room for kSmallRanges ranges there, whatever
-// n is, and pbs_key_scores_static takes what it took.)
-constexpr int kSmallRanges = 256, kSmallHeads = 16;
+// than kSweepWgs ranges, so that short inputs still spread over all compute units.  From 256 keys down a range's length depends on
+// its head's length alone, so that a head's sums do not depend on the other heads of a call.  Ranges of 256 keys / this, whole
+// stage, us: 8 heads x 1024 18.7 / 15.5, x 2048 19.4 / 14.7, x 4096 20.4 / 16.9, x 8147 21.4 / 22.4, 2 x 8192 18.9 / 15.7, 4 x 8000
+// 20.1 / 17.4, 32 x 2048 24.4 / 25.6 (four ranges to a workgroup), 32 x 4096 28.6 / 29.2; with 64 keys up to 4096 8 x 4096 17.5,
+// with 128 up to 16384 2 x 16384 20.5 -> 17.7, but 4 x 16000 22.7 -> 24.4 and 8 x 16384 26.7 -> 28.5.
+constexpr int kShortHead = 8192;       // keys of a head up to which its ranges are shorter than 256
+static int long_range_keys(const Geo &g)
+{
+    int keys = kMaxRangeKeys;
+    while (keys > 256 && (long long)ceil_div(g.n, keys) * g.batch * g.h_kv < kSweepWgs) keys >>= 1;
+    return keys;
+}
 static int sweep_range_keys(const Geo &g)
 {
-    const long long nbh = (long long)g.batch * g.h_kv;
-    int keys = kMaxRangeKeys;
-    while (keys > 256 && ceil_div(g.n, keys) * nbh < kSweepWgs) keys >>= 1;
-    while (keys <= 256 && keys > kMinRangeKeys && nbh <= kSmallHeads && ceil_div(g.n, keys / 2) * nbh <= kSmallRanges) keys >>= 1;
+    const int keys = long_range_keys(g);
+    return keys > 256 || g.n > kShortHead ? keys : g.n > kShortHead / 4 ? 128 : 64;
+}
+
+// Keys of a workgroup of the short sweeps: 256 at least, where a workgroup's start weighs little, and fewer, down to one range, while
+// every workgroup has a compute unit.
+static int short_sweep_keys(const Geo &g, int range_keys)
+{
+    int keys = range_keys < 256 ? 256 : range_keys;
+    while (keys > range_keys && (long long)ceil_div(g.n, keys / 2) * g.batch * g.h_kv <= 256) keys >>= 1;
     return keys;
 }
 
@@ -1059,17 +1081,22 @@ static bool long_sweeps(const Geo &g) { return (long long)g.n * g.batch * g.h_kv
 // bytes of the average-query region at the end of the workspace: the partial sums and the mean itself
 static size_t ws_avg_query(size_t nbh) { return align_up(nbh * (kAvgChunks + 1) * 128 * sizeof(double), kWsAlign); }
 
+// bytes set aside for the partial results of ranges of 256 keys and more; shorter ones run on into the average-query region
+// behind it, whose contents are dead once Qhat is split: a head of up to kShortHead keys has room there
+static size_t partial_room(const Geo &g)
+{
+    static_assert(kShortHead / 128 * kQRows * sizeof(float2) <= kAvgChunks * 128 * sizeof(double), "partial results of a head");
+    return align_up((size_t)g.batch * g.h_kv * ceil_div(g.n, long_range_keys(g)) * kQRows * sizeof(float2), kWsAlign);
+}
+
 // The generic path sizes its workspace for up to kQRows query rows (the block size may be smaller).
 size_t ws_key_scores(const pbs_problem *p)
 {
     const Geo g = make_geo(p);
     const size_t nbh = (size_t)g.batch * g.h_kv;
     if (use_mfma(p)) {
-        size_t ranges = nbh * ceil_div(g.n, sweep_range_keys(g));
-        if (nbh <= kSmallHeads && ranges < kSmallRanges) ranges = kSmallRanges;   // room for every shorter input as well
-        return align_up(nbh * 2 * kQRows * 128 * sizeof(bf16_t), kWsAlign) +
-               align_up(ranges * kQRows * sizeof(float2), kWsAlign) + align_up(nbh * kQRows * sizeof(float), kWsAlign) +
-               ws_avg_query(nbh);
+        return align_up(nbh * 2 * kQRows * 128 * sizeof(bf16_t), kWsAlign) + align_up(nbh * kQRows * sizeof(float), kWsAlign) +
+               partial_room(g) + ws_avg_query(nbh);
     }
     const size_t chunks = ceil_div(g.n, kGenericKeysPerChunk);
     const size_t rows = kQRows;
@@ -1142,13 +1169,13 @@ static pbs_status enqueue_key_scores(const pbs_problem *p, int proxy, const int3
                            : run_generic<float, 64>(g, Q, K, scores, w, bl, qrows, avg, s);
     }
     const int nbh = g.batch * g.h_kv;
-    const int range = sweep_range_keys(g), parts = ceil_div(g.n, range);
+    const int range = sweep_range_keys(g), parts = ceil_div(g.n, range), short_keys = short_sweep_keys(g, range);
     bf16_t *qsplit = reinterpret_cast<bf16_t *>(w);
     w += align_up((size_t)nbh * 2 * kQRows * 128 * sizeof(bf16_t), kWsAlign);
-    float2 *partial = reinterpret_cast<float2 *>(w);
-    w += align_up((size_t)nbh * parts * kQRows * sizeof(float2), kWsAlign);
     float *cvec = reinterpret_cast<float *>(w);
     w += align_up((size_t)nbh * kQRows * sizeof(float), kWsAlign);
+    float2 *partial = reinterpret_cast<float2 *>(w);       // may run on into the average-query region (partial_room)
+    w += partial_room(g);
     double *avg_partial = reinterpret_cast<double *>(w), *qavg = avg_partial + (size_t)nbh * kAvgChunks * 128;
     if (avg && (st = run_qavg<bf16_t>(g, Q, avg_partial, qavg, s)) != PBS_OK) return st;
     if ((st = launch(qhat_split_kernel, dim3(kQRows / 8, nbh), dim3(256), 0, s, (const bf16_t *)Q, qsplit, g, bl, qrows,
@@ -1161,13 +1188,15 @@ static pbs_status enqueue_key_scores(const pbs_problem *p, int proxy, const int3
         st = launch(scores_sweep1_kernel, dim3(ceil_div(parts, ranges), nbh), dim3(128), 0, s, (const bf16_t *)K, qsplit, partial, g,
                     range, ranges);
     else
-        st = launch(short_input::sweep1_kernel, dim3(parts, nbh), dim3(256), 0, s, (const bf16_t *)K, qsplit, partial, g, range);
+        st = launch(short_input::sweep1_kernel, dim3(ceil_div(g.n, short_keys), nbh), dim3(256), 0, s, (const bf16_t *)K, qsplit, partial,
+                    g, short_keys, range);
     if (st != PBS_OK) return st;
     if ((st = launch(scores_merge_kernel, dim3(nbh), dim3(1024), 0, s, partial, cvec, parts, bl)) != PBS_OK) return st;
     if (in_long)
         return launch(scores_sweep2_kernel, dim3(ceil_div(g.n, keys), nbh), dim3(128), 0, s, (const bf16_t *)K, qsplit, cvec,
                       scores, g, keys);
-    return launch(short_input::sweep2_kernel, dim3(parts, nbh), dim3(256), 0, s, (const bf16_t *)K, qsplit, cvec, scores, g, range);
+    return launch(short_input::sweep2_kernel, dim3(ceil_div(g.n, short_keys), nbh), dim3(256), 0, s, (const bf16_t *)K, qsplit, cvec,
+                  scores, g, short_keys);
 }
 
 extern "C" pbs_status pbs_key_scores(const pbs_problem *p, const void *Q, const void *K, float *scores, void *ws,

@@ -134,3 +134,17 @@ def test_bench_refuses_more_than_one_gpu():
                          timeout=120)
     assert res.returncode != 0
     assert "one GPU" in (res.stderr + res.stdout)
+
+
+def test_key_score_workspace_is_that_of_ranges_of_256_keys_and_more(lib):
+    # shorter ranges find their room in the part for the average query
+    def up(v):
+        return -(-v // 256) * 256
+    for heads in (1, 2, 8, 16, 17, 64, 300):
+        for n in (1, 64, 1100, 2048, 2049, 4096, 8147, 8192, 8193, 20000, 32320, 131072):
+            keys = 1024
+            while keys > 256 and -(-n // keys) * heads < 512:
+                keys //= 2
+            want = up(heads * 65536) + up(heads * 512) + up(heads * -(-n // keys) * 1024) + up(heads * 129 * 1024)
+            p = b.problem(1, heads, heads, n, 128, 128, 1024, "bf16")
+            assert lib.pbs_workspace_bytes(ctypes.byref(p), b.STAGE_KEY_SCORES) == want, (heads, n)

@@ -594,7 +594,9 @@ def test_key_scores_of_long_inputs(batch, h_kv, n):
 
 # five heads take the long form, four of them the short one, with ranges of 512 keys both; eight heads and seven of them both
 # the long form, with shares of three and two ranges: a head's scores do not depend on the others
-@pytest.mark.parametrize("h_kv,fewer,n", [(5, 4, 65536), (5, 4, 65555), (8, 7, 140000), (8, 7, 147456)])
+# short inputs: ranges of 64, 128 and 256 keys, of which a workgroup takes one, two or four
+@pytest.mark.parametrize("h_kv,fewer,n", [(5, 4, 65536), (5, 4, 65555), (8, 7, 140000), (8, 7, 147456), (40, 1, 40), (17, 16, 1100),
+                                          (100, 3, 2048), (17, 8, 2050), (40, 7, 4100), (16, 5, 8192), (17, 4, 8193), (9, 2, 20001)])
 def test_key_scores_of_a_head_do_not_depend_on_the_others(h_kv, fewer, n):
     g = torch.Generator(device="cuda")
     g.manual_seed(n)
