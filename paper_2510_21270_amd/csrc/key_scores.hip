@@ -1027,11 +1027,14 @@ static size_t ws_avg_query(size_t nbh);
 
 // Keys that a workgroup of either sweep takes at least: 64, and fewer where every workgroup has a compute unit then.  Stage, 64 keys /
 // 32 / 16, us: float32 2 heads x 2048 x 64 18.6 / 13.7 / 12.7, 8/2 x 2048 x 128 42.6 / 30.2 / 27.0, 2 x 4096 x 128 36.3 / 30.4 / 31.7
-// (256 workgroups of 32), bf16 4/2 x 4000 x 64 19.2 / 15.1 / 15.3, 8 x 4000 x 64 (500 of 64) 41.0 / 42.3 / 45.5.
-static int min_f64_keys(const Geo &g)
+// (256 workgroups of 32), bf16 4/2 x 4000 x 64 19.2 / 15.1 / 15.3, 8 x 4000 x 64 (500 of 64) 41.0 / 42.3 / 45.5.  Every share of the keys
+// gets a tile of 16 (few query rows: wave_share): without that, with 16 rows, float32 2 x 2048 x 64 14.3 / 12.5, x 128 16.1 /
+// 13.9, bf16 4/2 x 2048 x 64 15.1 / 12.7 with 64 keys to a workgroup.
+static int min_f64_keys(const Geo &g, int bl)
 {
+    const int least = 16 * wave_share(bl).kg;
     int keys = 64;
-    while (keys > 16 && (long long)ceil_div(g.n, keys / 2) * g.batch * g.h_kv <= 256) keys >>= 1;
+    while (keys > least && (long long)ceil_div(g.n, keys / 2) * g.batch * g.h_kv <= 256) keys >>= 1;
     return keys;
 }
 
@@ -1042,7 +1045,7 @@ static int f64_keys_per_chunk(const Geo &g, int bl)
     const size_t room = nbh * kQRows * ceil_div(g.n, kGenericKeysPerChunk) * sizeof(double2) + ws_avg_query(nbh);
     const size_t parts = room / (nbh * bl * sizeof(double2)) / wave_share(bl).kg;
     const size_t keys = (g.n + parts - 1) / parts;
-    const size_t least = min_f64_keys(g);
+    const size_t least = min_f64_keys(g, bl);
     return (int)(keys < least ? least : (keys + 15) / 16 * 16);
 }
 
@@ -1143,7 +1146,7 @@ static pbs_status run_generic(const Geo &g, const void *Q, const void *K, float 
     // Short ranges until there are workgroups enough for eight per compute unit.  Measured, 256 keys / 64, us: d = 64, 4096 keys in
     // all 23.2 / 7.7, 49204 23.5 / 19.3, 98304 37.9 / 31.4, 131072 40.3 / 41.8, 196608 55.0 / 60.2; d = 128, 32768 keys 38.0 / 19.9,
     // 98304 58.8 / 57.9, 131072 61.2 / 74.9, 262144 116 / 147 (a workgroup reads Qhat, 128 KiB, before its first key).
-    const int keys = (long long)g.n * nbh >= 256LL * 8 * 64 ? kF64Keys : min_f64_keys(g);
+    const int keys = (long long)g.n * nbh >= 256LL * 8 * 64 ? kF64Keys : min_f64_keys(g, bl);
     return launch((scores_final_f64_kernel<E, D>), dim3(ceil_div(g.n, keys), nbh), dim3(256), 0, s, (const E *)K, given,
                   (const E *)Q, qrows, (const double2 *)stats, scores, g, bl, keys);
 }
