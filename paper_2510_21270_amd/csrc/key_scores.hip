@@ -883,61 +883,63 @@ struct F64Logits {
     }
 };
 
-// Sweep 1.  grid = (chunks, nbh): (max, sum of exp) of every query row over one chunk of keys and one key share;
-// partial[bh][row][part], part = chunk * kg + key share.
+// Sweep 1.  grid = (ceil(chunks / per), nbh): (max, sum of exp) of every query row over a chunk of keys and one key share, for `per`
+// chunks one after the other; partial[bh][row][part], part = chunk * kg + key share.
 template <typename E, int D>
 __global__ __launch_bounds__(256) void scores_stats_f64_kernel(const E *__restrict__ K,
                                                                const double *__restrict__ qhat, const E *__restrict__ Q,
                                                                const int32_t *__restrict__ qrows,
                                                                double2 *__restrict__ partial, Geo g, int bl,
-                                                               int keys_per_chunk)
+                                                               int keys_per_chunk, int per)
 {
-    const int chunk = blockIdx.x, bh = blockIdx.y;
+    const int bh = blockIdx.y, chunks = ceil_div(g.n, keys_per_chunk);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const WaveShare ws = wave_share(bl);
     const int wr = wave % ws.rw, wk = wave / ws.rw;
     F64Logits<E, D> logits;
     logits.load_rows(qhat, Q, qrows, g, bh, bl, wr, ws.rw, lane);
     const E *Kh = K + (size_t)bh * g.n * D;
-    const int end = min(g.n, (chunk + 1) * keys_per_chunk);
-    double m[2] = {-INFINITY, -INFINITY}, l[2] = {0.0, 0.0};
-    for (int key0 = chunk * keys_per_chunk + 16 * wk; key0 < end; key0 += 16 * ws.kg) {
-        floatx4 k[D / 16];
-        logits.load_keys(k, Kh, key0, g.n, lane);
+    const int parts = chunks * ws.kg;
+    for (int chunk = blockIdx.x * per; chunk < min(chunks, ((int)blockIdx.x + 1) * per); ++chunk) {
+        const int end = min(g.n, (chunk + 1) * keys_per_chunk);
+        double m[2] = {-INFINITY, -INFINITY}, l[2] = {0.0, 0.0};
+        for (int key0 = chunk * keys_per_chunk + 16 * wk; key0 < end; key0 += 16 * ws.kg) {
+            floatx4 k[D / 16];
+            logits.load_keys(k, Kh, key0, g.n, lane);
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                if (t >= logits.tiles) break;
+                doublex4 v = logits(k, t);
+                double top = -INFINITY;
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    v[x] = key0 + (lane >> 4) + 4 * x < end ? v[x] * g.scale64 : -INFINITY;
+                    top = fmax(top, v[x]);
+                }
+                if (__any(top > m[t])) {                       // rare after the first tiles
+                    const double mn = fmax(m[t], top);
+                    if (mn != -INFINITY) l[t] *= exp(m[t] - mn);
+                    m[t] = mn;
+                }
+#pragma unroll
+                for (int x = 0; x < 4; ++x)                    // (a logit that is not a number counts, whatever m is)
+                    if (v[x] != -INFINITY) l[t] += exp(v[x] - m[t]);
+            }
+        }
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
             if (t >= logits.tiles) break;
-            doublex4 v = logits(k, t);
-            double top = -INFINITY;
+            // the four lane groups hold different keys of the same row
 #pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                v[x] = key0 + (lane >> 4) + 4 * x < end ? v[x] * g.scale64 : -INFINITY;
-                top = fmax(top, v[x]);
-            }
-            if (__any(top > m[t])) {                       // rare after the first tiles
-                const double mn = fmax(m[t], top);
-                if (mn != -INFINITY) l[t] *= exp(m[t] - mn);
+            for (int o = 16; o < 64; o <<= 1) {
+                const double mo = __shfl_xor(m[t], o, 64), lo = __shfl_xor(l[t], o, 64);
+                const double mn = fmax(m[t], mo);
+                l[t] = mn == -INFINITY ? l[t] + lo : l[t] * exp(m[t] - mn) + lo * exp(mo - mn);
                 m[t] = mn;
             }
-#pragma unroll
-            for (int x = 0; x < 4; ++x)                    // (a logit that is not a number counts, whatever m is)
-                if (v[x] != -INFINITY) l[t] += exp(v[x] - m[t]);
+            if (lane < 16 && logits.row[t] < bl)
+                partial[((size_t)bh * bl + logits.row[t]) * parts + chunk * ws.kg + wk] = make_double2(m[t], l[t]);
         }
-    }
-    const int parts = gridDim.x * ws.kg;
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        if (t >= logits.tiles) break;
-        // the four lane groups hold different keys of the same row
-#pragma unroll
-        for (int o = 16; o < 64; o <<= 1) {
-            const double mo = __shfl_xor(m[t], o, 64), lo = __shfl_xor(l[t], o, 64);
-            const double mn = fmax(m[t], mo);
-            l[t] = mn == -INFINITY ? l[t] + lo : l[t] * exp(m[t] - mn) + lo * exp(mo - mn);
-            m[t] = mn;
-        }
-        if (lane < 16 && logits.row[t] < bl)
-            partial[((size_t)bh * bl + logits.row[t]) * parts + chunk * ws.kg + wk] = make_double2(m[t], l[t]);
     }
 }
 
@@ -1025,11 +1027,11 @@ constexpr int kFormF64Heads = 2;
 
 static size_t ws_avg_query(size_t nbh);
 
-// Keys that a workgroup of either sweep takes at least: 64, and fewer where every workgroup has a compute unit then.  Stage, 64 keys /
-// 32 / 16, us: float32 2 heads x 2048 x 64 18.6 / 13.7 / 12.7, 8/2 x 2048 x 128 42.6 / 30.2 / 27.0, 2 x 4096 x 128 36.3 / 30.4 / 31.7
-// (256 workgroups of 32), bf16 4/2 x 4000 x 64 19.2 / 15.1 / 15.3, 8 x 4000 x 64 (500 of 64) 41.0 / 42.3 / 45.5.  Every share of the keys
-// gets a tile of 16 (few query rows: wave_share): without that, with 16 rows, float32 2 x 2048 x 64 14.3 / 12.5, x 128 16.1 /
-// 13.9, bf16 4/2 x 2048 x 64 15.1 / 12.7 with 64 keys to a workgroup.
+// Keys that a workgroup of either sweep takes at least (sweep 1: in chunks of their own): 64, and fewer where every workgroup has a
+// compute unit then.  Stage, 64 keys / 32 / 16, us: float32 2 heads x 2048 x 64 18.6 / 13.7 / 12.7, 8/2 x 2048 x 128 42.6 / 30.2 /
+// 27.0, 2 x 4096 x 128 36.3 / 30.4 / 31.7 (256 workgroups of 32), bf16 4/2 x 4000 x 64 19.2 / 15.1 / 15.3, 8 x 4000 x 64 (500 of 64)
+// 41.0 / 42.3 / 45.5.  Every share of the keys gets a tile of 16 (few query rows: wave_share): without that, with 16 rows, float32
+// 2 x 2048 x 64 14.3 / 12.5, x 128 16.1 / 13.9, bf16 4/2 x 2048 x 64 15.1 / 12.7 with 64 keys to a workgroup.
 static int min_f64_keys(const Geo &g, int bl)
 {
     const int least = 16 * wave_share(bl).kg;
@@ -1038,14 +1040,18 @@ static int min_f64_keys(const Geo &g, int bl)
     return keys;
 }
 
-// keys per chunk of sweep 1: as many chunks as the workspace has room for, of at least min_f64_keys keys
+// Keys per chunk of sweep 1: as many chunks as the workspace has room for, of at least 16, 32 or 64 keys.  That is a matter of a head's
+// length and the query rows alone, so that a head's sums do not depend on the other heads of a call; where a workgroup is to
+// take more keys it takes several chunks.  By the heads of a call / this, stage, us: float32 2 x 2048 x 64 12.3 / 12.4, 8 x 2048 18.6 /
+// 19.2, 32 x 1024 26.3 / 28.5, 32 x 2048 43.1 / 44.5, 8/2 x 1024 x 128 23.8 / 23.6 (26.5 with 32 keys), 16 x 2048 x 128 60.8 / 62.0.
 static int f64_keys_per_chunk(const Geo &g, int bl)
 {
     const size_t nbh = (size_t)g.batch * g.h_kv;
     const size_t room = nbh * kQRows * ceil_div(g.n, kGenericKeysPerChunk) * sizeof(double2) + ws_avg_query(nbh);
     const size_t parts = room / (nbh * bl * sizeof(double2)) / wave_share(bl).kg;
     const size_t keys = (g.n + parts - 1) / parts;
-    const size_t least = min_f64_keys(g, bl);
+    const int shortest = g.n <= 1024 ? 16 : g.n <= 4096 ? 32 : 64, tiles = 16 * wave_share(bl).kg;
+    const size_t least = shortest > tiles ? shortest : tiles;
     return (int)(keys < least ? least : (keys + 15) / 16 * 16);
 }
 
@@ -1139,14 +1145,16 @@ static pbs_status run_generic(const Geo &g, const void *Q, const void *K, float 
     const double *given = form ? nullptr : qhat;
     if (!form && (st = launch(qhat_f64_kernel<E>, dim3(ceil_div(bl * g.d, 256), nbh), dim3(256), 0, s, (const E *)Q, qhat, g, bl,
                               qrows, (const double *)(avg ? qavg : nullptr))) != PBS_OK) return st;
-    if ((st = launch((scores_stats_f64_kernel<E, D>), dim3(chunks, nbh), dim3(256), 0, s, (const E *)K, given, (const E *)Q, qrows,
-                     partial, g, bl, kpc)) != PBS_OK) return st;
+    // chunks to a workgroup of sweep 1
+    const int least = min_f64_keys(g, bl), per = kpc < least ? least / kpc : 1;
+    if ((st = launch((scores_stats_f64_kernel<E, D>), dim3(ceil_div(chunks, per), nbh), dim3(256), 0, s, (const E *)K, given,
+                     (const E *)Q, qrows, partial, g, bl, kpc, per)) != PBS_OK) return st;
     if ((st = launch(scores_merge_f64_kernel, dim3(ceil_div(bl, 4), nbh), dim3(256), 0, s, partial, stats, bl,
                      chunks * wave_share(bl).kg)) != PBS_OK) return st;
     // Short ranges until there are workgroups enough for eight per compute unit.  Measured, 256 keys / 64, us: d = 64, 4096 keys in
     // all 23.2 / 7.7, 49204 23.5 / 19.3, 98304 37.9 / 31.4, 131072 40.3 / 41.8, 196608 55.0 / 60.2; d = 128, 32768 keys 38.0 / 19.9,
     // 98304 58.8 / 57.9, 131072 61.2 / 74.9, 262144 116 / 147 (a workgroup reads Qhat, 128 KiB, before its first key).
-    const int keys = (long long)g.n * nbh >= 256LL * 8 * 64 ? kF64Keys : min_f64_keys(g, bl);
+    const int keys = (long long)g.n * nbh >= 256LL * 8 * 64 ? kF64Keys : least;
     return launch((scores_final_f64_kernel<E, D>), dim3(ceil_div(g.n, keys), nbh), dim3(256), 0, s, (const E *)K, given,
                   (const E *)Q, qrows, (const double2 *)stats, scores, g, bl, keys);
 }

@@ -607,6 +607,28 @@ def test_key_scores_of_a_head_do_not_depend_on_the_others(h_kv, fewer, n):
     assert torch.equal(got[0][:, :fewer], got[1])
 
 
+# the fp64 sweeps: chunks of 16, 32 and 64 keys, of which a workgroup takes one to four.  Another order of sums shows in few results
+# after their rounding to float32, so the rows' maxima and sums are compared too, which a call leaves in its workspace behind Qhat
+@pytest.mark.parametrize("dtype,d,block,heads,fewer,n", [("f32", 64, 64, 40, 2, 1024), ("f32", 64, 64, 33, 2, 4096), ("bf16", 64, 128, 12, 1, 2048),
+                                                         ("f32", 128, 16, 70, 3, 700), ("f32", 64, 32, 24, 4, 4097)])
+def test_fp64_key_scores_of_a_head_do_not_depend_on_the_others(dtype, d, block, heads, fewer, n):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    kind = torch.float32 if dtype == "f32" else torch.bfloat16
+    Q, K = (torch.randn((1, heads, n, d), generator=g, device="cuda").to(kind) for _ in range(2))
+
+    def run(lo, hi):
+        p = pbs.problem(1, hi - lo, hi - lo, n, d, block, 128, dtype)
+        ws = pbs.alloc_workspace(p, pbs.STAGE_KEY_SCORES)
+        scores = pbs.key_scores(p, Q[:, lo:hi].contiguous(), K[:, lo:hi].contiguous(), ws=ws)
+        stats = ws[(hi - lo) * 128 * d * 8:].view(torch.int64)[:(hi - lo) * block * 2].clone()
+        return scores, stats.view(hi - lo, block, 2)
+    scores, stats = run(0, heads)
+    for lo in range(0, heads - fewer + 1, fewer):
+        one, own = run(lo, lo + fewer)
+        assert torch.equal(scores[:, lo:lo + fewer], one) and torch.equal(stats[lo:lo + fewer], own)
+
+
 def test_block_64_attention_time_with_five_kv_heads():
     # sparse lists share tiles in an XCD's L2, which rows of all five heads on every XCD would crowd (5 / 5 heads x 40000, an
     # eighth of the blocks: 386 us against 498; a head's time 1.11 .. 1.18 and 1.41 .. 1.44 of that with four heads, two XCDs
