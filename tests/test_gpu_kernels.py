@@ -64,10 +64,11 @@ def test_d64_attention_over_given_lists(oracle, block, Hq, Hkv, n, rho):
     np.testing.assert_allclose(lse[fin], want_lse[fin], atol=1e-4, rtol=0)
 
 
-@pytest.mark.parametrize("dtype,d,block", [("f32", 64, 64), ("f32", 128, 16), ("bf16", 64, 32), ("bf16", 64, 64),
-                                           ("bf16", 64, 128)])
-def test_values_that_are_not_finite_reach_only_the_queries_that_see_them(oracle, dtype, d, block):
-    n, at = 3 * block - 5, block + block // 2
+# (float32, d = 128, blocks of 32 and more: sub-tiles are halves of a group of 32 keys; later: the key in the second half)
+@pytest.mark.parametrize("dtype,d,block,later", [("f32", 64, 64, 0), ("f32", 128, 16, 0), ("bf16", 64, 32, 0), ("bf16", 64, 64, 0),
+                                                 ("bf16", 64, 128, 0), ("f32", 128, 32, 3), ("f32", 128, 128, 19)])
+def test_values_that_are_not_finite_reach_only_the_queries_that_see_them(oracle, dtype, d, block, later):
+    n, at = 3 * block - 5, block + block // 2 + later
     Q, K, V = _qkv(7, 2, 1, n, d, dtype)
     kidx = np.arange(n, dtype=np.int32).reshape(1, 1, n)
     p = pbs.problem(1, 2, 1, n, d, block, block, dtype)
@@ -88,7 +89,7 @@ def test_values_that_are_not_finite_reach_only_the_queries_that_see_them(oracle,
     np.testing.assert_allclose(got, want, rtol=2.0 ** -7, atol=2.0 ** -15, equal_nan=True)
 
 
-# key tiles of 16, chunks of at least 64 keys, one to eight row tiles shared by four waves; 140001 keys: long ranges in
+# key tiles of 16, chunks of at least 16, 32 and 64 keys, one to eight row tiles shared by four waves; 140001 keys: long ranges in
 # both sweeps, the statistics running on into the average-query region of the workspace
 @pytest.mark.parametrize("n", [1, 15, 63, 65, 1000, 140001])
 @pytest.mark.parametrize("dtype,d,block", [("f32", 64, 64), ("f32", 128, 128), ("bf16", 64, 64), ("bf16", 64, 128)])
@@ -274,12 +275,13 @@ def test_segment_argsort_by_counting(oracle, heads, segment, segments):
 # A value that is not finite in a block that every later query sees in full, the later blocks' own values finite: what
 # p * v gives must come out, also where p enters the product as several terms of either sign.  The long case has more than 4096
 # query tiles: there a wave has its list to itself.
-@pytest.mark.parametrize("dtype,d,block,Hq,Hkv,n", [("bf16", 64, 64, 4, 2, 500), ("bf16", 64, 128, 2, 1, 700),
-                                                    ("bf16", 64, 64, 64, 2, 16410), ("bf16", 64, 32, 2, 1, 300),
-                                                    ("f32", 64, 64, 2, 1, 300)])
-def test_values_of_an_earlier_segment_that_are_not_finite(dtype, d, block, Hq, Hkv, n):
+@pytest.mark.parametrize("dtype,d,block,Hq,Hkv,n,later", [("bf16", 64, 64, 4, 2, 500, 0), ("bf16", 64, 128, 2, 1, 700, 0),
+                                                          ("bf16", 64, 64, 64, 2, 16410, 0), ("bf16", 64, 32, 2, 1, 300, 0),
+                                                          ("f32", 64, 64, 2, 1, 300, 0), ("f32", 128, 32, 2, 1, 300, 3),
+                                                          ("f32", 128, 128, 2, 1, 700, 19)])
+def test_values_of_an_earlier_segment_that_are_not_finite(dtype, d, block, Hq, Hkv, n, later):
     Q, K, V = (to_dev(x, dtype) for x in _qkv(9, Hq, Hkv, n, d, dtype))
-    T, at = -(-n // block), block // 2
+    T, at = -(-n // block), block // 2 + later
     p = pbs.problem(1, Hq, Hkv, n, d, block, block, dtype)
     i = torch.arange(T, dtype=torch.int32, device="cuda")
     cnt = torch.clamp(i + 1, max=2).repeat(1, Hq, 1).contiguous()
@@ -697,7 +699,7 @@ def test_fp64_key_scores_of_query_groups(oracle, dtype, d, block, n, r):
     p = pbs.problem(1, 2 * r, 2, n, d, block, 2 * block, dtype)
     got = pbs.key_scores(p, to_dev(Q, dtype), to_dev(K, dtype))
     want = oracle.key_scores(Q, K, block)
-    np.testing.assert_allclose(got.cpu().numpy(), want, rtol=1e-6, atol=0)
+    np.testing.assert_allclose(got.cpu().numpy(), want, rtol=2.0 ** -23, atol=1e-37)       # as in test_fp64_key_scores
 
 
 # Ranges of 64, 128 and 256 keys, whole and ragged ones, up to 16 kv heads and beyond: 16 bits of Qhat in two terms, sums in fp32
@@ -710,13 +712,56 @@ def test_key_scores_in_short_ranges(oracle, Hq, Hkv, n):
 
 
 # Selection with a compute unit to every workgroup (whole query blocks loaded at a time) and with more workgroups than that, ragged
-# last blocks, 3 and 4 query heads in a chunk: the masks of the oracle, bit for bit
+# last blocks, 3 and 4 query heads in a chunk; four query blocks to a workgroup with one query head to a kv head (more than 64
+# blocks) and with two (256 workgroups): the masks and lists of the oracle, bit for bit
 @pytest.mark.parametrize("Hq,Hkv,n,segment", [(4, 4, 5, 256), (3, 1, 130, 256), (7, 1, 2000, 512), (2, 1, 8200, 1024),
-                                               (8, 2, 8191, 1024), (8, 2, 33000, 1024)])
+                                               (8, 2, 8191, 1024), (8, 2, 33000, 1024), (2, 2, 8200, 1024), (1, 1, 16389, 1024),
+                                               (16, 8, 16300, 1024), (16, 8, 16400, 1024)])
 def test_selection_with_few_workgroups(oracle, Hq, Hkv, n, segment):
     Q, K, _ = _qkv(n, Hq, Hkv, n, 128, "bf16")
     p = pbs.problem(1, Hq, Hkv, n, 128, 128, segment, "bf16", tau=0.9)
-    bits, cnt, _ = pbs.block_mask(p, to_dev(Q, "bf16"), to_dev(K, "bf16"))
-    want = oracle.block_mask(Q, K, 128, segment, float(np.float32(0.9)))[0]
+    bits, cnt, cols = pbs.block_mask(p, to_dev(Q, "bf16"), to_dev(K, "bf16"))
+    want, want_cnt, want_cols = oracle.block_mask(Q, K, 128, segment, float(np.float32(0.9)))
     mask = mask_from_bits(bits, pbs.T_of(p))
     assert np.array_equal(mask, want) and np.array_equal(cnt.cpu().numpy(), want.sum(-1))
+    listed = np.arange(pbs.T_of(p)) < want_cnt[..., None]
+    assert np.array_equal(cols.cpu().numpy()[listed], want_cols[listed])
+
+
+# d = 64: a row of probabilities that outgrows its reference in a sub-tile under the token-level mask, whose queries have met keys
+# before: its scores are formed again from memory and masked again.  In either sub-tile of a pair and for either query tile a
+# visible key stands 30 nats above all others, and a hidden one 45.  Four waves to a list, and one (4096 query tiles).
+@pytest.mark.parametrize("heads", [3, 512])
+@pytest.mark.parametrize("block", [64, 128])
+@pytest.mark.parametrize("part", [0, 1])
+@pytest.mark.parametrize("tile", [0, 1])
+def test_d64_probabilities_that_outgrow_their_reference_under_the_mask(tile, part, block, heads):
+    n, d, seg = 8 * block if block == 64 else 6 * block, 64, 2 * block
+    g = torch.Generator(device="cuda")
+    g.manual_seed(block + 2 * part + tile)
+    Q, K, V = (torch.randn((1, heads, n, d), generator=g, device="cuda") for _ in range(3))
+    Q[..., 0] = 0.0
+    K[..., 0] = 0.0
+    kidx = torch.arange(n, dtype=torch.int32, device="cuda")
+    first = n - seg                                        # the last segment: keys of its own slots are masked
+    seen, hidden = first + block + 32 * part + 5, first + block + 32 * part + 9      # slots, both in one sub-tile
+    for slot, pos in ((seen, first), (hidden, n - 1)):     # exchanged: the segment's first key and its last one
+        other = int((kidx == pos).nonzero())
+        kidx[other], kidx[slot] = kidx[slot].clone(), pos
+    queries = first + block + 32 * tile                    # of the segment's second block
+    Q[0, :, queries:queries + 32, 0] = 8.0
+    K[0, :, seen, 0], K[0, :, hidden, 0] = 30.0, 45.0      # (K as permuted: row = slot)
+    Q, K, V = (x.to(torch.bfloat16) for x in (Q, K, V))
+    p = pbs.problem(1, heads, heads, n, d, block, seg, "bf16")
+    cnt, cols = pbs.admitted_lists(p)
+    _, _, vt = pbs.segment_permute(p, None, K, V)
+    got, lse = pbs.attn_fwd(p, Q, K, vt, None, kidx.repeat(1, heads, 1).contiguous(), cnt, cols, want_lse=True)
+    see = kidx[None].long() <= torch.arange(n, device="cuda")[:, None]
+    for h in range(0, heads, 64):
+        at = slice(h, min(heads, h + 64))
+        s = (Q[0, at].double() @ K[0, at].double().transpose(1, 2).contiguous() / 8.0).masked_fill(~see, -np.inf)
+        torch.testing.assert_close(lse[0, at].double(), torch.logsumexp(s, -1), rtol=0, atol=1e-4)
+        err = (got[0, at].double() - torch.softmax(s, -1) @ V[0, at].double()).abs()
+        assert err.max() <= 2e-2 and err.mean() <= 2e-3
+    top = see[queries:queries + 32, seen].all() and not see[queries:queries + 31, hidden].any()
+    assert bool(top)
