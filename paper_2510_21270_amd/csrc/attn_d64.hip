@@ -84,8 +84,8 @@ struct Split {
 
 // Score pairs of a query tile on their way to terms: the upper halves of two numbers are a pair of terms, and what is left of a
 // number is an exact difference of 16, then of 8 bits.  Masks, differences and byte moves run under matrix instructions; the
-// bf16 dot product that would form a difference in one instruction does not: two beside a matrix instruction make 53 clocks
-// of its 32, four times as many masks and differences 38.
+// bf16 dot product that would form a difference in one instruction does not: two beside a matrix instruction make 54 clocks
+// of its 32, four masks or differences 34, eight of them 44.
 struct Softmax {
     uint32_t upper;                                        // 0xffff0000, in a scalar register
     floatx2 p, r;
@@ -466,10 +466,10 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
     }
 
     // A value that is not finite does not come through these products: 0 * inf of a hidden key is NaN, and so is
-    // the sum over the terms of a visible one whenever a term is zero or negative.  A wave that finds NaN in its O^T forms it again,
+    // the sum over the terms of a visible one whenever a term is zero.  A wave that finds NaN in its O^T forms it again,
     // relative to the references it has ended with: such values leave the products and are added one key at a time, with the
     // undivided probability, for the queries that see the key.  Nothing is prefetched here; with one infinite value that every
-    // query of the call sees, 16 / 4 heads x 12301 tokens take 1.26 ms instead of 0.62.
+    // query of the call sees, 16 / 4 heads x 12301 tokens take 1.24 ms instead of 0.61.
     bool odd = false;
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt)

@@ -14,13 +14,15 @@
 // and the S^T accumulator (query = lane % 16, keys 4 g + r) is already the B operand of the second product.  The contraction
 // order over features is permuted the same way in K' and Q', which changes nothing but the order of an fp32 sum.
 // Neighbouring lanes want different rows, so these operands as loads from memory would be an access of 16 bytes per lane
-// (58 cache accesses to an instruction, the address units busy throughout): a wave's sub-tile goes through its own LDS instead,
-// by asynchronous loads of consecutive memory; no wave wants another's, so nothing waits at a barrier.
+// (59 cache accesses to an instruction; 18 now, and the address units busy 19 % of a launch of 2 heads x 2048 instead of 34 %): a
+// wave's sub-tile goes through its own LDS instead, by asynchronous loads of consecutive memory; no wave wants another's, so
+// nothing waits at a barrier.
 //
 // Bound: the fp32 matrix rate (64 operations per clock and SIMD): 64 instructions of 32 clocks per 32 keys and 16
 // queries at d = 64; at the small sizes the longest list.  Measured, operands from memory / through LDS, us, every admitted block
 // of float32: d = 64, 2 heads x 2048 33.9 / 22.8, 8 / 2 x 4096 248 / 163; d = 128, 2 x 2048 65.6 / 38.5, 8 / 2 x 4096 494 / 295
-// (116 TFLOP/s); bf16 8 / 2 x 2048 x 128 in blocks of 32 142 / 99.
+// (116 TFLOP/s); bf16 8 / 2 x 2048 x 128 in blocks of 32 142 / 100, of 16 127 / 100, 4 / 2 x 2048 x 64 in blocks of 16 38.9 / 33.0, 32 / 8
+// x 4096 x 128 in blocks of 16 1618 / 1294 and, a twentieth of the blocks, 196 / 157.
 #include "pbs_host.h"
 
 namespace pbs {

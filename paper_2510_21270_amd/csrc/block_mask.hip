@@ -459,7 +459,10 @@ static pbs_status launch_select_qb(const E *Qp, const double *KbarT, uint64_t *m
     // Whole query blocks on their way at a time, where no workgroup shares a compute unit.  Stage, four pieces / a block of 32, us: 32 / 8
     // heads x 1024 14.4 / 12.5, x 2048 16.1 / 14.1, x 8147 20.0 / 18.8, 4 / 2 x 8192 13.1 / 11.2, 28 / 4 x 4000 16.7 / 14.9; blocks of fewer
     // pieces, whose other loads are idle: 16 / 4 x 3000 x 64, block 64 11.5 / 12.9, 8 / 8 x 2000 x 64, block 128 8.9 / 9.4, 8 / 8 x 3000
-    // x 128, block 64 10.4 / 10.5.
+    // x 128, block 64 10.4 / 10.5.  Where the line lies, the same two: workgroups of eight waves (three heads and more to a kv head), 256
+    // of them 17.9 / 19.0 and 19.9 / 21.1, 288 29.8 / 26.0, 316 32.0 / 29.1, 512 39.0 / 33.5.  Those of four waves (one or two heads) share
+    // a compute unit before its registers are full and gain somewhat further, 256 14.0 / 15.2, 320 18.6 / 19.0, 384 17.3 / 17.5, 512
+    // 27.8 / 28.4, 768 47.7 / 38.7; the line is the same for them.
     if (sizeof(E) == 2 && g.T <= 512 && g.block * g.d == 128 * 128 &&
         (long long)ceil_div(g.T, QB) * g.batch * g.h_kv * ceil_div(g.r, RB) <= kFewWgs)
         return launch_select_nc<RB, QB, 8, sizeof(E) == 2>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
@@ -487,8 +490,7 @@ static pbs_status launch_select(const E *Qp, const double *KbarT, uint64_t *mask
                     : launch_select_qb<1, 2>(Qp, KbarT, mask_bits, row_cnt, col_idx, g, s);
 }
 
-// Block means of K' into KbarT ([kv head][feature][kbar_stride(T)] fp64); also called by pbs_segment_permute for the
-// shapes its gather kernel does not pool on the way.
+// Block means of K' into KbarT ([kv head][feature][kbar_stride(T)] fp64).
 static pbs_status launch_pool_keys(const pbs_problem *p, const Geo &g, const void *Kp, double *KbarT, hipStream_t s)
 {
     const int nk = g.batch * g.h_kv;

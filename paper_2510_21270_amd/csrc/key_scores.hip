@@ -813,8 +813,8 @@ __global__ __launch_bounds__(128) void qavg_final_kernel(const double *__restric
 // The four waves of a workgroup divide the 16-row tiles of Qhat among them (at most two each) and, where there are
 // fewer than three, the key tiles as well.
 // Bound: the exponentials (one fp64 exp per logit and sweep, about 30 fp64 instructions) and the latency of a few short
-// launches.  Measured, stage: float32, 2 heads x 2048 keys 541 -> 28 us; bf16 d = 64, 4 kv heads x 12301 keys 757 -> 52 us
-// against one thread per key (or per key and row) walking its K row alone.
+// launches.  Measured, stage: float32, 2 heads x 2048 keys x 64 12.4 us, bf16 d = 64, 4 kv heads x 12301 keys 46 us (541 and 757 us with
+// one thread per key, or per key and row, walking its K row alone).
 struct WaveShare {
     int rw, kg;                        // waves that share the rows, waves that share the keys; rw * kg = 4
 };
@@ -1151,8 +1151,8 @@ static pbs_status run_generic(const Geo &g, const void *Q, const void *K, float 
                      (const E *)Q, qrows, partial, g, bl, kpc, per)) != PBS_OK) return st;
     if ((st = launch(scores_merge_f64_kernel, dim3(ceil_div(bl, 4), nbh), dim3(256), 0, s, partial, stats, bl,
                      chunks * wave_share(bl).kg)) != PBS_OK) return st;
-    // Short ranges until there are workgroups enough for eight per compute unit.  Measured, 256 keys / 64, us: d = 64, 4096 keys in
-    // all 23.2 / 7.7, 49204 23.5 / 19.3, 98304 37.9 / 31.4, 131072 40.3 / 41.8, 196608 55.0 / 60.2; d = 128, 32768 keys 38.0 / 19.9,
+    // Short ranges until there are workgroups enough for eight per compute unit.  Measured, 256 keys / 64, us: d = 64, 49204 keys in
+    // all 23.5 / 19.3, 98304 37.9 / 31.4, 131072 40.3 / 41.8, 196608 55.0 / 60.2; d = 128, 32768 keys 38.0 / 19.9,
     // 98304 58.8 / 57.9, 131072 61.2 / 74.9, 262144 116 / 147 (a workgroup reads Qhat, 128 KiB, before its first key).
     const int keys = (long long)g.n * nbh >= 256LL * 8 * 64 ? kF64Keys : least;
     return launch((scores_final_f64_kernel<E, D>), dim3(ceil_div(g.n, keys), nbh), dim3(256), 0, s, (const E *)K, given,

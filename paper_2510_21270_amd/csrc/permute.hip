@@ -601,9 +601,11 @@ __device__ __forceinline__ void gather_block(const uintx4 *__restrict__ src, con
     kbarT[((size_t)blockIdx.y * d + e) * Ts + j] = s / (double)rows;
 }
 
-// gather_both_kernel for the blocks of gather_block.  One launch in the place of three (rows, means, V'), each of which was mostly
-// its own start and end: float, 2 heads x 2048 x 64 3.1 + 3.2 + 4.3 -> 5.2 us, the layer 81.6 -> 74.9; bf16, 4 heads x 12301 x 64
-// 5.4 + 5.2 + 5.2 -> 7.8 us, the layer 664 -> 658.
+// gather_both_kernel for the blocks of gather_block.  One launch in the place of three (rows, means, V'): short ones were mostly their
+// own start and end, and long ones read K' once more for its means.  Whole stage, three launches / this, us: float, 2 heads x 2048
+// x 64 14.3 / 10.0, 8 x 131072 x 64 244 / 190, 8 x 131072 x 128, block 128 (64 KiB of LDS) 517 / 425, with the token-order copies 788 /
+// 694, 8 x 65536 x 128, block 16 274 / 209; bf16, 4 x 12288 x 64, block 64 20.4 / 13.6, 8 x 131072 141 / 109, with copies 205 / 178,
+// 8 x 65536 x 64, block 16 (a workgroup of 2 KiB) 119 / 109, block 32 92 / 71.
 template <typename E, bool TWICE>
 __global__ __launch_bounds__(256) void gather_blocks_kernel(const E *__restrict__ K, const E *__restrict__ V,
                                                             const int32_t *__restrict__ kidx, E *__restrict__ Kp,
