@@ -79,12 +79,12 @@ struct __align__(16) Stage {
 
 __device__ __forceinline__ int swap23(int m) { return (m & ~12) | ((m & 4) << 1) | ((m & 8) >> 1); }
 
-// Descriptors of one kv head: what this wave loads (wave 0: K', wave 1: V'^T) and the key positions, and their sizes (a sub-tile
-// behind the n-th key starts at the end, see scalar_offset); ring: byte offset of this wave's stages behind those of the
-// first half of a split row.
+// Descriptors of one kv head: what this wave loads (wave 0: K', wave 1: V'^T), with its size (a sub-tile behind the n-th key starts
+// at the end, see scalar_offset), and the key positions; ring: byte offset of this wave's stages behind those of the first
+// half of a split row.
 struct TileBuffers {
     __amdgpu_buffer_rsrc_t tile, pos;
-    int tile_bytes, pos_bytes;
+    int tile_bytes;
     int ring;
 };
 
@@ -155,13 +155,15 @@ __device__ __forceinline__ void issue_load(const StageLoad &a, const LaneOffsets
 
 // Original positions of the 32 keys of part P of block j, next to their K' rows.  Only sub-tiles under the
 // token-level mask read them, but the load is issued for every sub-tile, by all lanes of both waves (four bytes per
-// lane, the same 256 bytes from each wave): one more instruction in the stream costs less than a branch around it.
+// lane, the same 256 bytes from each wave): one more instruction in the stream costs less than a branch around it.  The way to the
+// part is the instruction's own offset, which counts in memory and in LDS and belongs to what the hardware checks against the
+// descriptor's size; the scalar one, to the block, lies within it, since a block has at least one key.
 template <int P>
 __device__ __forceinline__ void issue_positions(__attribute__((address_space(3))) unsigned char *dst, const TileBuffers &buf,
                                                 int j, int lane)
 {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(buf.pos, (lptr_t)(dst + buf.ring), 4, lane * 4,
-                                             scalar_offset((j * BLOCK + P * KS) * 4, buf.pos_bytes), 0, 0);
+    constexpr int part = P * KS * 4;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(buf.pos, (lptr_t)(dst + buf.ring - part), 4, lane * 4, j * (BLOCK * 4), part, 0);
 }
 
 // K' part P of block j and the V'^T part (P + 3) % 4 of block jv
@@ -624,11 +626,10 @@ __global__ __launch_bounds__(128 * HALVES) __attribute__((amdgpu_waves_per_eu(1,
         const size_t bhk = unit;
         const int reach = a.tok_delta * BLOCK + g.n;       // rows within reach of this head's descriptors
         buf.tile_bytes = wave == 0 ? reach * 256 : (a.tok_delta + g.T) * (D * BLOCK * 2);
-        buf.pos_bytes = reach * 4;
         buf.tile = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(wave == 0 ? a.Kp + bhk * (size_t)g.n * D
                                                                                     : a.Vt + bhk * (size_t)g.T * D * BLOCK),
                                                      0, buf.tile_bytes, kRawDword);
-        buf.pos = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(a.kidx + bhk * (size_t)g.n), 0, buf.pos_bytes, kRawDword);
+        buf.pos = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(a.kidx + bhk * (size_t)g.n), 0, reach * 4, kRawDword);
     };
     // jv0: the first iteration of a row multiplies V'^T part 3 of this block by zero probabilities; that is a block of the
     // row's list, the same one for both halves, so that infinite values meet no more zeros than they would in one piece

@@ -37,7 +37,7 @@ WITHIN = {
     },
     "attn_wide.hip": {
         "a.soff": "stage_load stops it at the end",
-        "scalar_offset((j * BLOCK + P * KS) * 4, buf.pos_bytes)": "stops at the end",
+        "j * (BLOCK * 4)": "a block that is listed has at least one key",
         "k * 4": "a list's pieces of 64 entries, of which the first exists",
         "32 * k": "less than a row of Q'",
         "scalar_offset(nq * (BLOCK * 256) + k * 8192, a.g.n * 256)": "stops at the end",
