@@ -10,9 +10,9 @@ constexpr int listed_slot(int j, int part, int step, int block, int ni, int n)
     return j >= 0 && j < ni && j * block + part * step < n ? j * block + part * step : -1;
 }
 
-// Scalar offset of a raw buffer load that would start at `at` of a descriptor of `size` bytes (or rows): it stops at the end, where every lane
-// is out of range and reads zeros.  The hardware compares a lane's own offset with the size less the scalar offset, a difference
-// that must not fall below zero.
+// Scalar offset of a raw buffer load that would start at `at` of a descriptor of `size` bytes (or rows): it stops at the end,
+// where every lane is out of range and reads zeros.  The hardware compares a lane's own offset with the size less the
+// scalar offset, a difference that must not fall below zero.
 constexpr int scalar_offset(int at, int size) { return at < size ? at : size; }
 
 }  // namespace pbs
